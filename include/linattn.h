@@ -184,8 +184,10 @@ size_t linattn_noalloc_scratch_bytes(void);
  * FLASH, Sec. 5 "Settings"); LINATTN_ERR_UNSUPPORTED otherwise, and for fp32 rows
  * of 128 elements in groups of 256.  bf16 rows run on the matrix cores (groups of
  * 256 keep their running state in the workspace, which they need for every L > 0);
- * fp32 rows on a plain fp32 kernel that is exact to fp32 rounding but not built
- * for speed (one workgroup per (b, h), no workspace). */
+ * fp32 rows in exact fp32 products: groups of 64 on the fp32 matrix instructions,
+ * groups of 256 on the vector ALUs.  For fp32 rows (here and in linattn_prefill) a
+ * missing or short workspace is no error: the sequence is then not split over
+ * workgroups. */
 linattn_status linattn_prefill_grouped(const linattn_desc *desc, int32_t L, float alpha,
                                        const void *q, const void *k, const void *v,
                                        const float *conv_w,

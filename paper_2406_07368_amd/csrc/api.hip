@@ -82,15 +82,16 @@ linattn_status check_desc(const linattn_desc* d, bool chunk, bool strides, int m
 }
 
 struct PrefillPlan {
-  bool mfma;
+  bool mfma;                // bf16 rows
+  bool direct;              // fp32 rows: see F32Plan
   int nseg, seg_len;
   size_t ws_bytes;
 };
 
-// How a prefill call is laid out on the chip.  fp32 inputs go to the vector-ALU
-// kernel (exact fp32 products).  bf16 inputs go to the matrix-core kernel; when
-// B*H alone cannot fill the 256 compute units the sequence axis is cut into
-// segments whose start states come from a first pass over K, V and a scan.
+// How a prefill call is laid out on the chip.  fp32 inputs go to the kernel on the fp32
+// matrix instructions (exact fp32 products), bf16 inputs to the bf16 one; when B*H alone
+// cannot fill the 256 compute units the sequence axis is cut into segments whose start
+// states come from a first pass over K, V and a scan.
 PrefillPlan plan_prefill(const linattn_desc* d, int32_t L, bool grouped = false) {
   PrefillPlan p{};
   p.mfma = d->io_dtype == LINATTN_BF16;
@@ -98,14 +99,21 @@ PrefillPlan plan_prefill(const linattn_desc* d, int32_t L, bool grouped = false)
   p.nseg = 1;
   p.seg_len = L;
   const int heads = d->B * d->H * value_blocks(d);      // what the kernels see as heads: one per value block
-  if (p.mfma && L > 0) {
+  if (!p.mfma) {
+    if (L <= 0 || (grouped && d->chunk == 256)) return p;   // (groups of 256: one workgroup per head)
+    const F32Plan f = prefill_f32_plan(heads, L, d->d, grouped);
+    p.nseg = f.nseg; p.seg_len = f.seg_len; p.direct = f.direct;
+    p.ws_bytes = prefill_f32_workspace_bytes(heads, d->d, f);
+    return p;
+  }
+  if (L > 0) {
     p.nseg = g256 ? prefill_grouped256_pick_segments(heads, L) : prefill_mfma_pick_segments(heads, L, d->chunk, d->d);
     const int chunks = (L + d->chunk - 1) / d->chunk;
     const int cps = (chunks + p.nseg - 1) / p.nseg;
     p.seg_len = cps * d->chunk;
     p.nseg = (L + p.seg_len - 1) / p.seg_len;
   }
-  p.ws_bytes = !p.mfma ? 0 : g256 ? prefill_grouped256_workspace_bytes(heads, d->d, p.nseg)
+  p.ws_bytes = g256 ? prefill_grouped256_workspace_bytes(heads, d->d, p.nseg)
                                   : prefill_mfma_workspace_bytes(heads, d->d, p.nseg);
   return p;
 }
@@ -175,7 +183,9 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
   if (grouped) {
     if (!(alpha == alpha) || alpha - alpha != 0.f) return LINATTN_ERR_SHAPE;   // NaN, infinity
     // the groups are part of the result here: 64 tokens (the paper's size for LLaMA) or 256 (its size for FLASH)
-    if (!prefill_grouped_simt_available(desc->io_dtype == LINATTN_BF16, desc->d, desc->chunk)) return LINATTN_ERR_UNSUPPORTED;
+    // (fp32 rows of 128 in groups of 256: no kernel)
+    if (desc->chunk != 64 && desc->chunk != 256) return LINATTN_ERR_UNSUPPORTED;
+    if (desc->io_dtype == LINATTN_F32 && desc->chunk == 256 && desc->d == 128) return LINATTN_ERR_UNSUPPORTED;
   }
   if (!conv_w) return LINATTN_ERR_NULL;
   if (L > 0 && (!q || !k || !v || !out)) return LINATTN_ERR_NULL;
@@ -190,8 +200,13 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
   if ((double)desc->stride_b * desc->B + (double)desc->stride_h * desc->H + (double)desc->stride_t * L > 9.0e18 ||
       (double)desc->stride_b_v * desc->B + (double)desc->stride_h_v * desc->H + (double)desc->stride_t_v * L > 9.0e18)
     return LINATTN_ERR_SHAPE;
-  const PrefillPlan plan = plan_prefill(desc, L, grouped);
-  if (plan.ws_bytes > 0 && (!workspace || workspace_bytes < plan.ws_bytes)) return LINATTN_ERR_WORKSPACE;
+  PrefillPlan plan = plan_prefill(desc, L, grouped);
+  const bool no_ws = plan.ws_bytes > 0 && (!workspace || workspace_bytes < plan.ws_bytes);
+  if (no_ws && plan.mfma) return LINATTN_ERR_WORKSPACE;
+  // fp32 rows: a workspace buys segments, nothing else; and in the quadratic kernel every workgroup reads
+  // the incoming state, so none of the outputs may be it
+  const bool in_place = (S_in && S_in == S_out) || (z_in && z_in == z_out) || (hist_in && hist_in == hist_out);
+  if (no_ws || (plan.direct && in_place)) { plan.nseg = 1; plan.seg_len = L; plan.direct = false; }
 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   PrefillArgs a{};
@@ -210,7 +225,7 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
   a.sb_v = m > 1 ? desc->stride_b_v : desc->stride_b;
   a.sh_v = m > 1 ? desc->stride_h_v : desc->stride_h;
   a.st_v = m > 1 ? desc->stride_t_v : desc->stride_t;
-  a.nseg = plan.nseg; a.seg_len = plan.seg_len;
+  a.nseg = plan.nseg; a.seg_len = plan.seg_len; a.direct = plan.direct; a.f32 = !plan.mfma;
   a.alpha = alpha;
   a.wait_spins = g_wait_spins.load(std::memory_order_relaxed);
   hipError_t e;
@@ -234,9 +249,10 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
     if (e == hipSuccess) e = launch_prefill_grouped256(a, desc->d, stream);
     return e == hipSuccess ? LINATTN_OK : LINATTN_ERR_HIP;
   }
-  if (plan.mfma && L > 0) e = launch_prefill_mfma(a, desc->d, desc->chunk, grouped, stream);
-  else if (grouped && L > 0) e = launch_prefill_grouped_simt(a, bf16, desc->d, stream);   // fp32 rows; groups of 256
-  else e = launch_prefill_simt(a, bf16, desc->d, stream);                                 // L = 0: the state is handed through
+  if (L == 0) e = launch_state_through(a, desc->d, bf16 ? 2 : 4, stream);
+  else if (bf16) e = launch_prefill_mfma(a, desc->d, desc->chunk, grouped, stream);
+  else if (grouped && desc->chunk == 256) e = launch_prefill_grouped_simt(a, desc->d, stream);
+  else e = launch_prefill_f32(a, desc->d, grouped, stream);
   if (e == hipSuccess && long_conv) {
     ConvLongArgs c{};
     c.v = v; c.conv_w = conv_w; c.hist_in = hist_in; c.out = out; c.hist_out = hist_out;
@@ -275,7 +291,7 @@ size_t linattn_workspace_bytes(const linattn_desc* desc, int32_t L) {
   if (check_desc(desc, true, true, LINATTN_MAX_CONV_K_PREFILL) != LINATTN_OK || L < 0) return 0;
   // the descriptor does not say which prefill form will be called: enough for either
   const size_t a = plan_prefill(desc, L, false).ws_bytes;
-  const size_t b = desc->chunk == 256 && value_blocks(desc) == 1 ? plan_prefill(desc, L, true).ws_bytes : 0;
+  const size_t b = (desc->chunk == 256 || desc->io_dtype == LINATTN_F32) && value_blocks(desc) == 1 ? plan_prefill(desc, L, true).ws_bytes : 0;
   return a > b ? a : b;
 }
 

@@ -98,6 +98,8 @@ struct PrefillArgs {
   int nseg;                 // workgroups along the sequence axis per (b, h)
   int seg_len;              // tokens per segment (multiple of the chunk size)
   int wait_spins;           // polls before a wait between the waves of a workgroup gives up; < 0: give up at once
+  int direct;               // fp32 rows: the quadratic kernel, see F32Plan
+  int f32;                  // fp32 rows (the history rows staged by the prefix sum are floats)
   int no_conv;              // the taps are taken as zero: a convolution with more than 8 taps runs as a pass of its own
   int group;                // three-branch form: tokens per group (64 or 256)
   // Value rows wider than key rows: d_v = m d.  The kernels then see B*H*m heads of d value channels each, head
@@ -181,11 +183,20 @@ hipError_t launch_verify_tree(const VerifyTreeArgs& a, int d, hipStream_t st);
 // verify_tree_simt.hip : the same for fp32 candidates, exact fp32 multiply-adds on the vector ALUs
 hipError_t launch_verify_tree_simt(const VerifyTreeArgs& a, int d, hipStream_t st);
 
-// prefill_simt.hip : fp32 arithmetic on the vector ALUs, one workgroup per (b, h)
-hipError_t launch_prefill_simt(const PrefillArgs& a, bool bf16, int d, hipStream_t st);
-// ... and the three-branch form (a.group tokens per group, a.alpha): fp32 rows, and any rows in groups of 256
-bool prefill_grouped_simt_available(bool bf16, int d, int group);
-hipError_t launch_prefill_grouped_simt(const PrefillArgs& a, bool bf16, int d, hipStream_t st);
+// prefill_f32.hip : fp32 rows on the fp32 matrix instructions, token-level and three-branch form (groups of 64)
+struct F32Plan {
+  int nseg, seg_len;        // workgroups along the sequence axis, tokens of each
+  bool direct;              // the quadratic kernel: one launch, no workspace
+};
+F32Plan prefill_f32_plan(int heads, int L, int d, bool grouped);
+size_t prefill_f32_workspace_bytes(int heads, int d, const F32Plan& p);
+hipError_t launch_prefill_f32(const PrefillArgs& a, int d, bool grouped, hipStream_t st);
+
+// prefill_simt.hip : the three-branch form for fp32 rows of 64 in groups of 256, on the vector ALUs
+hipError_t launch_prefill_grouped_simt(const PrefillArgs& a, int d, hipStream_t st);
+
+// prefill_mfma.hip : no tokens: the state is handed through
+hipError_t launch_state_through(const PrefillArgs& a, int d, int elem_bytes, hipStream_t st);
 
 // conv_long.hip : out += causal depthwise conv with 9..63 taps, and the history that goes with it
 hipError_t launch_conv_long(const ConvLongArgs& a, bool bf16, int d, hipStream_t st);

@@ -45,11 +45,34 @@ __global__ __launch_bounds__(256) void segment_scan_kernel(PrefillArgs a) {
     }
   }
   if (a.hist_in && e < HALO * D) {
-    uint16_t* staged = reinterpret_cast<uint16_t*>(a.ws + (size_t)a.B * a.H * a.m * a.nseg * SLOT) + (size_t)hx.bhs * HALO * D;
+    float* staged = a.ws + (size_t)a.B * a.H * a.m * a.nseg * SLOT;
+    const size_t se = (size_t)hx.bhs * HALO * D + e;
     const int r = e / D, cc = e % D;           // staged row r holds token r - HALO
     const int hr = (a.Kc - 1) - HALO + r;      // row of the incoming history
-    staged[e] = hr >= 0 ? static_cast<const uint16_t*>(a.hist_in)[((size_t)bh * (a.Kc - 1) + hr) * hx.dvt + hx.blk * D + cc] : (uint16_t)0;
+    const size_t he = hr >= 0 ? ((size_t)bh * (a.Kc - 1) + hr) * hx.dvt + hx.blk * D + cc : 0;
+    if (a.f32) staged[se] = hr >= 0 ? static_cast<const float*>(a.hist_in)[he] : 0.f;
+    else reinterpret_cast<uint16_t*>(staged)[se] = hr >= 0 ? static_cast<const uint16_t*>(a.hist_in)[he] : (uint16_t)0;
   }
+}
+
+// No tokens: S, z and the history as they came (zeros for a new sequence).  Plain copies, element by element, so that an
+// output may be its input.
+__global__ __launch_bounds__(256) void state_through_kernel(PrefillArgs a, size_t n_S, size_t n_z, size_t n_hist) {
+  const size_t step = (size_t)gridDim.x * 256;
+  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n_S || e < n_z || e < n_hist; e += step) {
+    if (a.S_out && e < n_S) a.S_out[e] = a.S_in ? a.S_in[e] : 0.f;
+    if (a.z_out && e < n_z) a.z_out[e] = a.z_in ? a.z_in[e] : 0.f;
+    if (a.hist_out && e < n_hist) static_cast<uint16_t*>(a.hist_out)[e] = a.hist_in ? static_cast<const uint16_t*>(a.hist_in)[e] : (uint16_t)0;
+  }
+}
+
+hipError_t launch_state_through(const PrefillArgs& a, int d, int elem_bytes, hipStream_t st) {
+  const size_t BH = (size_t)a.B * a.H, n_S = BH * d * d * a.m, n_z = BH * d;
+  const size_t n_hist = BH * (a.Kc - 1) * d * a.m * (elem_bytes / 2);      // in units of two bytes
+  const size_t most = n_S > n_hist ? n_S : n_hist;
+  const unsigned grid = (unsigned)((most + 255) / 256 < 2048 ? (most + 255) / 256 : 2048);
+  hipLaunchKernelGGL(state_through_kernel, dim3(grid), dim3(256), 0, st, a, n_S, n_z, n_hist);
+  return hipGetLastError();
 }
 
 // Segments per (b, h): as many as keep all workgroups of the second pass resident at once (at d = 128 one per compute

@@ -272,3 +272,30 @@ def test_a_wait_that_gives_up_shows_as_nan(grouped, L):
     torch.cuda.synchronize()
     want = oracle.prefill_grouped(q, k, v, w, 64, alpha=alpha) if grouped else oracle.prefill_recurrent(q, k, v, w)
     compare((host(out), host(S), host(z), host(h)), want, "bf16", "default limit")
+
+
+@pytest.mark.parametrize("grouped", [False, True])
+@pytest.mark.parametrize("B,H,L,d,Kc,with_state", [
+    (1, 2, 31, 64, 3, True), (1, 4, 33, 128, 8, False), (1, 4, 512, 64, 5, True),      # quadratic kernel, edges of its tiles
+    (1, 4, 545, 64, 3, True), (2, 8, 289, 128, 4, True), (1, 40, 257, 64, 8, True),    # segmented walk, ragged last segments
+    (8, 40, 97, 64, 3, False), (3, 100, 65, 128, 1, True)])                            # one workgroup per head
+def test_fp32_rows_on_either_side_of_the_dispatch(grouped, B, H, L, d, Kc, with_state):
+    """The fp32 kernels (quadratic, segmented, whole heads) against the oracle; S and z updated in place take the walk."""
+    q, k, v, w, state = small_case(6200 + L + d, B, H, L, d, Kc, "f32", with_state)
+    args = {} if state is None else dict(S0=state[0], z0=state[1], hist0=state[2])
+    want = oracle.prefill_grouped(q, k, v, w, 64, alpha=0.7, eps=1e-2, **args) if grouped else oracle.prefill_recurrent(q, k, v, w, eps=1e-2, **args)
+    gq, gk, gv, gw = dev(q), dev(k), dev(v), dev(w)
+    desc = binding.make_desc(B, H, d, Kc, 64, torch.float32, 1e-2, L=L)
+    need = binding.linattn_workspace_bytes(desc, L)
+    ws = torch.full((max(need, 16) // 4,), float("nan"), device="cuda")
+    for in_place in (False, True) if with_state else (False,):
+        st = (None, None, None) if state is None else tuple(dev(x) for x in state)
+        res = st if in_place else (torch.full((B, H, d, d), float("nan"), device="cuda"), torch.full((B, H, d), float("nan"), device="cuda"),
+                                   torch.full((B, H, Kc - 1, d), float("nan"), device="cuda"))
+        out = torch.full_like(gq, float("nan"))
+        if grouped:
+            binding.linattn_prefill_grouped(desc, L, 0.7, gq, gk, gv, gw, *st, out, *res, ws, need)
+        else:
+            binding.linattn_prefill(desc, L, gq, gk, gv, gw, *st, out, *res, ws, need)
+        torch.cuda.synchronize()
+        compare((host(out), *(host(x) for x in res)), want, "f32", f"grouped={grouped} L={L} d={d} in place={in_place}")
