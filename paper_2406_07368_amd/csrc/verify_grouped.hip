@@ -11,7 +11,7 @@
 // Memory-bound on the read of S (64 KB per head at d = 128); S is only written when the kept drafts
 // complete the group (once in 64 tokens), so a step moves about half the bytes of the token-level form.
 //
-// One workgroup of 256 threads per (b, h), fp32 arithmetic on the vector ALUs throughout:
+// One workgroup of 256 threads per (b, h), fp32 arithmetic throughout, on the vector ALUs up to step 5:
 //   1. logits: one wave per row of (window ++ drafts), lanes over features, wave reduction;
 //   2. per draft: softmax over its rows, the linear normaliser, one weight per row in LDS;
 //   3. the state streams through registers once (16-byte nontemporal loads, a few row passes in
@@ -36,17 +36,14 @@ struct VgScore {
   float red[KP][D];           // phi(q_j)^T S
   float loc[KP][D];           // sum_r W[j][r] v_r
 };
-template <int D>
-struct VgStage {              // completion of a group: 16 rows of phi(k) and of v at a time
-  float k[16][D];
-  float v[16][D];
+template <typename Elem, int D>
+struct VgStage {              // completion of a group: its raw rows
+  Elem k[GC][D + 16 / sizeof(Elem)];
+  Elem v[GC][D + 16 / sizeof(Elem)];
 };
 template <int D, int KP>
-struct VgSmem {
-  union {                     // the completion runs when the outputs are done
-    VgScore<D, KP> sc;
-    VgStage<D> st;
-  };
+struct VgStep {
+  VgScore<D, KP> sc;
   float W[KP][GROWS];         // first the logits, then the weight of value row r in the output of draft j
   float lin[KP][GC];          // phi(q_j).phi(k_r) for the rows of the group being completed
   float vv[KP][D];            // v_j (conv)
@@ -54,6 +51,11 @@ struct VgSmem {
   float zz[D];
   float wt[8][D];             // conv taps, tap-major (taps >= Kc are 0)
   float hh[8][D];             // hh[t]: the value row t+1 positions before the first draft
+};
+template <typename Elem, int D, int KP>
+union VgSmem {                // the completion runs when the outputs are stored
+  VgStep<D, KP> step;
+  VgStage<Elem, D> st;
 };
 
 // x[l] + x[l ^ 8] (rotation by 8 inside a row of 16)
@@ -94,8 +96,8 @@ __global__ __launch_bounds__(256, (sizeof(typename Io::elem) != 2 ? 2 : KP <= 8 
   constexpr int CG = D / 4;          // float4 column groups per state row
   constexpr int RPP = 256 / CG;      // state rows per pass
   constexpr int NPASS = D / RPP;
-  constexpr int EPL = D / 64;        // features per lane where a wave walks a feature vector
-  __shared__ VgSmem<D, KP> sm;
+  __shared__ VgSmem<typename Io::elem, D, KP> smem;
+  VgStep<D, KP>& sm = smem.step;
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int bh = blockIdx.x;
@@ -432,43 +434,65 @@ __global__ __launch_bounds__(256, (sizeof(typename Io::elem) != 2 ? 2 : KP <= 8 
     }
     return;
   }
-  // the group is complete: rows 0..63 of (window ++ drafts) enter S and z, 16 rows at a time through LDS.
-  // Once in 64 tokens: the state slice is walked once per 16 rows (through the cache) rather than held in
-  // registers, which would cost the common path its occupancy.
-  float* Sw = a.S + (size_t)bh * D * D + 4 * cg;
-  float zsum = tid < D ? sm.zz[tid] : 0.f;
-  for (int rb = 0; rb < GC; rb += 16) {
-    __syncthreads();                                                // the previous 16 rows have been used (first turn: the outputs are done)
-    for (int e = tid; e < 16 * D; e += 256) {
-      const int r = rb + e / D, i = e % D;
-      int64_t ik, iv;
-      const void* ksrc = row_of(a.kwin, a.k, win0, tok0, D, n, r, &ik);
-      const void* vsrc = row_of(a.vwin, a.v, win0, tok0, D, n, r, &iv);
-      sm.st.k[e / D][i] = phi_any(Io::load1(ksrc, ik + i), a.relu);
-      sm.st.v[e / D][i] = Io::load1(vsrc, iv + i);
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int p = 0; p < NPASS; ++p) {
-      const int i = p * RPP + r0;
-      f32x4 cur = *reinterpret_cast<const f32x4*>(Sw + (size_t)i * D);
+  // The group is complete: its 64 rows of (window ++ drafts) enter S and z, S += phi(K)^T V on the fp32 matrix
+  // instructions (exact fp32 products, as everywhere in this kernel), the 32 x 32 tiles of S dealt out over the waves.
+  // Only the heads whose group fills up come here, a few of a launch at a time, so it is their latency that counts:
+  // every request -- rows and tiles -- leaves at once.  (Sixteen rows at a time with the state slice read, added to
+  // and written back per sixteen rows on the vector ALUs took up to 70 us: a step of 1024 heads whose batch rows stand at
+  // different counts had almost always one of them to wait for: 46 us a step of 1024 heads at D = 128, now 22.)
+  constexpr int TPW = D * D / (32 * 32) / 4;                        // tiles per wave: one column of tiles (D = 64: half of one)
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int cb = TPW == 1 ? (wv & 1) : wv, ib0 = TPW == 1 ? (wv >> 1) : 0;
+  constexpr int CRT = GC / NPART;
+  typename Io::raw8 ck[CRT], cv[CRT];
+#pragma unroll
+  for (int t = 0; t < CRT; ++t) {
+    int64_t ik, iv;
+    const void* ksrc = row_of(a.kwin, a.k, win0, tok0, D, n, part + NPART * t, &ik);
+    const void* vsrc = row_of(a.vwin, a.v, win0, tok0, D, n, part + NPART * t, &iv);
+    ck[t] = Io::load_raw8(ksrc, ik + 8 * c8);
+    cv[t] = Io::load_raw8(vsrc, iv + 8 * c8);
+  }
+  // tile register r: feature 8(r/4) + 4hi + r%4, channel l32 (descriptor, lane offset and a constant: no address registers)
+  const __amdgpu_buffer_rsrc_t Srs = __builtin_amdgcn_make_buffer_rsrc(a.S + (size_t)bh * D * D, 0, D * D * 4, 0x00020000);
+  const int so = ((32 * ib0 + 4 * hi) * D + 32 * cb + l32) * 4;
+  f32x16 S[TPW];
+#pragma unroll
+  for (int i = 0; i < TPW; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      S[i][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(Srs, so, (32 * i + 8 * (r >> 2) + (r & 3)) * (D * 4), 0));
+  const bool z_mine = TPW > 1 || cb == 0;                           // D = 64: two waves see the same features
+  const int z_f = 32 * (TPW > 1 ? wv : ib0) + l32;
+  const float z_old = sm.zz[z_f];
+  __syncthreads();                                                  // outputs and history are done with LDS
+#pragma unroll
+  for (int t = 0; t < CRT; ++t) {
+    *reinterpret_cast<typename Io::raw8*>(&smem.st.k[part + NPART * t][8 * c8]) = ck[t];
+    *reinterpret_cast<typename Io::raw8*>(&smem.st.v[part + NPART * t][8 * c8]) = cv[t];
+  }
+  __syncthreads();
+  float zsum = 0.f;
 #pragma unroll 4
-      for (int r = 0; r < 16; ++r) {
-        const f32x4 v4 = *reinterpret_cast<const f32x4*>(&sm.st.v[r][4 * cg]);
-        const float kf = sm.st.k[r][i];
+  for (int j = 0; j < GC / 2; ++j) {                                // two rows per instruction, four apart (banks)
+    const int r = 8 * (j >> 2) + 4 * hi + (j & 3);
+    const float x = Io::load1(&smem.st.v[r][0], 32 * cb + l32);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) cur[e] = fmaf(kf, v4[e], cur[e]);
-      }
-      *reinterpret_cast<f32x4*>(Sw + (size_t)i * D) = cur;
-    }
-    if (tid < D) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) zsum += sm.st.k[r][tid];
+    for (int i = 0; i < TPW; ++i) {
+      const float y = phi_any(Io::load1(&smem.st.k[r][0], 32 * (ib0 + i) + l32), a.relu);
+      S[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(y, x, S[i], 0, 0, 0);
+      if (ib0 + i == z_f / 32) zsum += y;                           // uniform
     }
   }
-  if (tid < D) a.z[(size_t)bh * D + tid] = zsum;
-  __syncthreads();                                                  // every read of the old window rows is done
+#pragma unroll
+  for (int i = 0; i < TPW; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(S[i][r]), Srs, so, (32 * i + 8 * (r >> 2) + (r & 3)) * (D * 4), 0);
+  zsum = add_xor32(zsum);
+  if (z_mine && hi == 0) a.z[(size_t)bh * D + z_f] = z_old + zsum;
   // the next group opens with the kept drafts beyond the completed one: drafts 64-n .. m-1 -> rows 0 ..
+  // (every read of the old window rows is behind the barriers above)
   const int first = GC - n;
   for (int e = tid; e < (m - first) * D; e += 256) {
     wk[e] = dk[(size_t)first * D + e];
