@@ -337,7 +337,7 @@ BackwardPlan plan_backward(const linattn_desc* d, int32_t L) {
   BackwardPlan p{};
   const size_t BH = (size_t)d->B * d->H, slot = (size_t)d->d * d->d + d->d;
   p.ng = L > 0 ? (L + d->chunk - 1) / d->chunk : 0;
-  p.nwb = grouped_bwd_dw_blocks(L);
+  p.nwb = conv_mfma_blocks(L, d->B * d->H, d->d);
   p.off_P = 0;
   p.off_D = round256(BH * (p.ng > 0 ? p.ng : 1) * slot * sizeof(float));
   p.off_stats = p.off_D + round256(BH * (p.ng > 0 ? p.ng : 1) * slot * sizeof(float));
@@ -401,11 +401,12 @@ linattn_status linattn_prefill_grouped_backward(const linattn_desc* desc, int32_
   if (e == hipSuccess && L > 0) {
     ConvLongArgs c{};
     c.v = dout; c.conv_w = conv_w; c.out = dv;
-    c.B = a.B; c.H = a.H; c.L = L; c.Kc = a.Kc; c.sb = a.sb; c.sh = a.sh; c.st = a.st; c.m = 1; c.rev = 1; c.assign = 1;
-    e = launch_conv_long(c, true, desc->d, cs);
+    c.B = a.B; c.H = a.H; c.L = L; c.Kc = a.Kc; c.sb = a.sb; c.sh = a.sh; c.st = a.st; c.m = 1; c.bwd = 1;
+    c.dw_v = v; c.dw_part = dconv_w ? a.dw_part : nullptr;
+    e = launch_conv_mfma(c, desc->d, cs);
     if (e == hipSuccess && lane) e = hipEventRecord(lane->mid, cs);
   }
-  if (e == hipSuccess) e = launch_grouped_bwd_dw(a, desc->d, cs);            // no tokens: the sums over nothing
+  if (e == hipSuccess && dconv_w) e = launch_grouped_bwd_dw(a, desc->d, cs); // no tokens: the sums over nothing
   if (e == hipSuccess) e = launch_grouped_bwd_core(a, desc->d, stream, lane ? lane->mid : nullptr);
   if (lane) {                                              // joined whatever happened, so that nothing stays forked
     const hipError_t ej = join_side(lane, stream);

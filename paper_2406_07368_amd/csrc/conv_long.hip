@@ -2,13 +2,12 @@
 // DWConv with kernel size 63), as a pass of its own behind the attention kernels:
 //
 //   out[t][c] += sum_{j < Kc} w[h][c][j] * Vext[t - j][c]        Vext = hist_in ++ V, zeros before that
-//   (or out = ..., when the pass runs ahead of the kernel that adds the rest)
 //
+// fp32 rows on the vector ALUs (exact fp32 products); bf16 rows run on the matrix cores (conv_mfma.hip).
 // The attention kernels keep an 8-row halo of V in LDS and gather the taps per token; a 62-row halo does not
 // fit next to their row buffers, and 63 taps per output are a vector-ALU workload of the size of the attention
 // itself.  So long kernels are register-blocked here instead: a thread owns one channel, holds its taps in
-// registers and slides over 16 (adding to out: 8) outputs at a time, every value row read from LDS feeding that many
-// multiply-adds.
+// registers and slides over 8 outputs at a time, every value row read from LDS feeding that many multiply-adds.
 // One workgroup = 64 (or 32) tokens of one (b, h); rows t0-62 .. t0+63 of V are staged in LDS as they lie in memory.
 #include "common.h"
 #include "kernels.h"
@@ -21,7 +20,7 @@ constexpr int CL_TOK = 64;        // tokens per workgroup (32 when that still le
                                   // worth more then than the halo rows it reads twice)
 constexpr int CL_HALO = 62;       // rows before them that the longest kernel reaches
 constexpr int CL_MAXK = 63;
-constexpr int CL_BLK = 16;        // outputs a thread carries at once (fewer if it has fewer tokens; half when adding to out)
+constexpr int CL_BLK = 8;         // outputs a thread carries at once (fewer if it has fewer tokens)
 }  // namespace
 
 // KMAX: tap capacity of the instantiation (taps beyond Kc are zeros; the loops below are straight-line code for
@@ -30,7 +29,7 @@ constexpr int CL_BLK = 16;        // outputs a thread carries at once (fewer if 
 static __device__ __forceinline__ float elem_to_f32(float x) { return x; }
 static __device__ __forceinline__ float elem_to_f32(uint16_t x) { return bf16_bits_to_f32(x); }
 
-template <typename Io, int D, int KMAX, bool ASSIGN, int TOK>
+template <typename Io, int D, int KMAX, int TOK>
 __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
   // the value rows [CL_HALO + TOK][D] as they lie in memory (bf16 rows stay bf16: half the LDS of fp32 rows, so
   // twice the workgroups per compute unit); before them, for a moment, the taps as fp32
@@ -39,10 +38,8 @@ __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
   typename Io::elem* xe = reinterpret_cast<typename Io::elem*>(smem_cl);
   constexpr int NG = 256 / D;                 // token groups of threads
   constexpr int TPT = TOK / NG;            // tokens per thread
-  // (adding to out, a block also holds its own and the next block's elements of out: with sixteen the registers allow
-  // two workgroups per compute unit instead of three, which costs 13 % at a chip-filling size)
-  constexpr int BLK_MAX = ASSIGN ? CL_BLK : CL_BLK / 2;
-  constexpr int BLK = TPT < BLK_MAX ? TPT : BLK_MAX;
+  // (a block also holds its own and the next block's elements of out)
+  constexpr int BLK = TPT < CL_BLK ? TPT : CL_BLK;
   const int tid = threadIdx.x;
   // one (b, h, value block of D channels); d_v = D: one block per head
   const int bh = blockIdx.y / a.m, blk = blockIdx.y % a.m, b = bh / a.H, h = bh % a.H;
@@ -78,7 +75,7 @@ __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
       const bool in_seq = tok >= 0 && tok < L;
       const bool in_hist = tok < 0 && a.hist_in != nullptr && Kc - 1 + tok >= 0;
       const void* src = in_hist ? a.hist_in : a.v;
-      const int mt = in_seq ? (a.rev ? L - 1 - tok : tok) : 0;     // where the token lies in memory
+      const int mt = in_seq ? tok : 0;     // where the token lies in memory
       const int64_t idx = in_hist ? hist_base + (int64_t)(Kc - 1 + tok) * DVT + i0 : base + (int64_t)mt * a.st + i0;
       raw[i] = Io::load_raw8(src, idx);
       have[i] = in_seq || in_hist;
@@ -88,12 +85,12 @@ __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
   // time: the first block with the first requests, the next while the current ones are being computed (all 32
   // at once would cost the registers that let a second and third workgroup share the compute unit).  Past the end: the
   // first token's element, never stored.
-  [[maybe_unused]] typename Io::elem prev[BLK];
+  typename Io::elem prev[BLK];
   auto issue_prev = [&](int blk8, typename Io::elem (&dst)[BLK]) __attribute__((always_inline)) {
 #pragma unroll
     for (int e = 0; e < BLK; ++e) {
       const int tok = t0 + tg * TPT + blk8 * BLK + e;
-      const int mt = tok < L ? (a.rev ? L - 1 - tok : tok) : 0;
+      const int mt = tok < L ? tok : 0;
       dst[e] = static_cast<const typename Io::elem*>(a.out)[base + (int64_t)mt * a.st + c];
     }
   };
@@ -114,7 +111,7 @@ __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
       const int e = tid + 256 * i;
       if (e < D * Kc / 4) *reinterpret_cast<f32x4*>(xs + 4 * e) = wt[i];
     }
-    if constexpr (!ASSIGN) issue_prev(0, prev);   // ... and the first of what is already in out
+    issue_prev(0, prev);                      // ... and the first of what is already in out
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < KMAX; ++j) wreg[j] = j < Kc ? xs[c * Kc + j] : 0.f;
@@ -156,8 +153,8 @@ __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
   for (int blk8 = 0; blk8 < TPT / BLK; ++blk8) {
     const int tb0 = tg * TPT + blk8 * BLK;
     float acc[BLK];
-    [[maybe_unused]] typename Io::elem next[BLK];
-    if constexpr (!ASSIGN) issue_prev(blk8 + 1 < TPT / BLK ? blk8 + 1 : blk8, next);
+    typename Io::elem next[BLK];
+    issue_prev(blk8 + 1 < TPT / BLK ? blk8 + 1 : blk8, next);
 #pragma unroll
     for (int e = 0; e < BLK; ++e) acc[e] = 0.f;
     // value rows from the newest output's own row backwards: row m feeds output e through tap e - 7 + m
@@ -177,12 +174,10 @@ __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
     for (int e = 0; e < BLK; ++e) {
       const int tok = t0 + tb0 + e;
       if (tok < L)
-        Io::store1(a.out, base + (int64_t)(a.rev ? L - 1 - tok : tok) * a.st + c, ASSIGN ? acc[e] : elem_to_f32(prev[e]) + acc[e]);
+        Io::store1(a.out, base + (int64_t)tok * a.st + c, elem_to_f32(prev[e]) + acc[e]);
     }
-    if constexpr (!ASSIGN) {
 #pragma unroll
-      for (int e = 0; e < BLK; ++e) prev[e] = next[e];
-    }
+    for (int e = 0; e < BLK; ++e) prev[e] = next[e];
   }
 }
 
@@ -231,35 +226,38 @@ __global__ __launch_bounds__(256) void conv_long_hist_kernel(ConvLongArgs a) {
   }
 }
 
-template <typename Io, int D, int KMAX, bool ASSIGN, int TOK>
+template <typename Io, int D, int KMAX, int TOK>
 static hipError_t launch_cl_t(const ConvLongArgs& a, hipStream_t st) {
   constexpr int LDS_ROWS = (CL_HALO + TOK) * D * (int)sizeof(typename Io::elem), LDS_TAPS = D * KMAX * (int)sizeof(float);
   constexpr int LDS = LDS_ROWS > LDS_TAPS ? LDS_ROWS : LDS_TAPS;
-  auto kern = conv_long_kernel<Io, D, KMAX, ASSIGN, TOK>;
+  auto kern = conv_long_kernel<Io, D, KMAX, TOK>;
   hipError_t e = LINATTN_MAX_LDS_ONCE(kern, LDS);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)((a.L + TOK - 1) / TOK), (unsigned)(a.B * a.H * a.m)), dim3(256), LDS, st, a);
   return hipGetLastError();
 }
 
-template <typename Io, int D, int KMAX, bool ASSIGN>
+template <typename Io, int D, int KMAX>
 static hipError_t launch_cl_k(const ConvLongArgs& a, hipStream_t st) {
   // fewer 64-token workgroups than compute units: 32 tokens each
   const int64_t wgs = (int64_t)((a.L + CL_TOK - 1) / CL_TOK) * a.B * a.H * a.m;
-  return wgs < 256 ? launch_cl_t<Io, D, KMAX, ASSIGN, CL_TOK / 2>(a, st) : launch_cl_t<Io, D, KMAX, ASSIGN, CL_TOK>(a, st);
+  return wgs < 256 ? launch_cl_t<Io, D, KMAX, CL_TOK / 2>(a, st) : launch_cl_t<Io, D, KMAX, CL_TOK>(a, st);
 }
 
-template <typename Io, int D, bool ASSIGN>
+template <typename Io, int D>
 static hipError_t launch_cl(const ConvLongArgs& a_in, hipStream_t st) {
+  constexpr bool BF16 = sizeof(typename Io::elem) == 2;
   hipError_t e = hipSuccess;
   // The history can be handed on by the conv kernel itself unless hist_out is hist_in and several workgroups share a
-  // head: the first of them reads the old rows, the last would overwrite them, and nothing orders the two.
+  // head: the first of them reads the old rows, the last would overwrite them, and nothing orders the two.  (The bf16
+  // kernel writes it while its own waves may still be reading: never when hist_out is hist_in.)
   ConvLongArgs a = a_in;
-  a.hist_fused = a.hist_out != nullptr && !a.rev && a.L > 0 && (a.hist_out != a.hist_in || a.L <= CL_TOK / 2);
+  a.hist_fused = a.hist_out != nullptr && a.L > 0 && (a.hist_out != a.hist_in || (!BF16 && a.L <= CL_TOK / 2));
   if (a.L > 0) {
-    e = a.Kc <= 16   ? launch_cl_k<Io, D, 16, ASSIGN>(a, st)
-        : a.Kc <= 32 ? launch_cl_k<Io, D, 32, ASSIGN>(a, st)
-                     : launch_cl_k<Io, D, CL_MAXK, ASSIGN>(a, st);
+    if constexpr (BF16) e = launch_conv_mfma(a, D, st);
+    else e = a.Kc <= 16   ? launch_cl_k<Io, D, 16>(a, st)
+             : a.Kc <= 32 ? launch_cl_k<Io, D, 32>(a, st)
+                          : launch_cl_k<Io, D, CL_MAXK>(a, st);
     if (e != hipSuccess) return e;
   }
   if (a.hist_out && !a.hist_fused) {
@@ -270,12 +268,8 @@ static hipError_t launch_cl(const ConvLongArgs& a_in, hipStream_t st) {
 }
 
 hipError_t launch_conv_long(const ConvLongArgs& a, bool bf16, int d, hipStream_t st) {
-  if (a.assign) {
-    if (!bf16) return hipErrorInvalidValue;
-    return d == 128 ? launch_cl<IoBf16, 128, true>(a, st) : launch_cl<IoBf16, 64, true>(a, st);
-  }
-  if (bf16) return d == 128 ? launch_cl<IoBf16, 128, false>(a, st) : launch_cl<IoBf16, 64, false>(a, st);
-  return d == 128 ? launch_cl<IoF32, 128, false>(a, st) : launch_cl<IoF32, 64, false>(a, st);
+  if (bf16) return d == 128 ? launch_cl<IoBf16, 128>(a, st) : launch_cl<IoBf16, 64>(a, st);
+  return d == 128 ? launch_cl<IoF32, 128>(a, st) : launch_cl<IoF32, 64>(a, st);
 }
 
 }  // namespace linattn

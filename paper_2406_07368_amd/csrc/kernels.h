@@ -133,11 +133,15 @@ struct ConvLongArgs {
   int B, H, L, Kc;
   int64_t sb, sh, st;       // strides of v and out
   int m;                    // value blocks of d channels per head (d_v = m d)
-  int rev;                  // the token axis runs backwards (out[t] += sum_j w[j] v[t + j]): the conv's share of the
-                            // gradient with respect to its input; no history then
   int hist_fused;           // set by the launcher: the conv kernel writes hist_out itself (no launch of its own)
   int assign;               // out = conv instead of out += conv (bf16 rows only): the pass then runs ahead of the
                             // kernel that adds the rest, and needs nothing from it
+  // bf16 rows, the conv's part of a training step: v holds the gradient rows, out = dv gets the conv's share of the
+  // gradient with respect to the values (out[t] = sum_j w[j] v[t + j]), and dw_part, if not null, the conv-weight sums of
+  // every token block
+  int bwd;
+  const void* dw_v;         // value rows
+  float* dw_part;           // [H][B * blocks][d * Kc]
 };
 
 // Gradient of the three-branch form for a sequence that starts from nothing (training): bf16 rows, one set of strides
@@ -201,8 +205,11 @@ hipError_t launch_state_through(const PrefillArgs& a, int d, int elem_bytes, hip
 // conv_long.hip : out += causal depthwise conv with 9..63 taps, and the history that goes with it
 hipError_t launch_conv_long(const ConvLongArgs& a, bool bf16, int d, hipStream_t st);
 
+// conv_mfma.hip : the same for bf16 rows on the matrix cores, and its gradients
+int conv_mfma_blocks(int L, int heads, int d);             // token blocks per sequence
+hipError_t launch_conv_mfma(const ConvLongArgs& a, int d, hipStream_t st);
+
 // prefill_grouped_bwd.hip : gradient of the three-branch form (bf16 rows, groups of 64 or 256)
-int grouped_bwd_dw_blocks(int L);
 // ... in two parts that need nothing from each other: everything but the conv-weight sums (dv is added to what it
 // holds: the conv's share is written first; `before_dkdv`, if not null, is waited for ahead of the kernel that does
 // so), and the conv-weight sums

@@ -667,126 +667,7 @@ __global__ __launch_bounds__(GT * 2) void grouped_bwd_dkdv_kernel(GroupedBwdArgs
   store_rows<D, GT>(acc4, Ol, gout, a.st, tok0, nt, tid, ktile, l32, hi, role == 0);
 }
 
-// ---- dw: per workgroup the products of its tokens, then one sum over batch rows and token blocks --------------------
-// dw[h][c][j] = sum_b sum_t dO[b,h,t,c] v[b,h,t-j,c].  One workgroup = DW_TOK tokens of one (b, h); a thread owns one
-// channel and a quarter (d = 64) or half (d = 128) of the tokens, holds the sums of all taps in registers and walks its
-// tokens sixteen at a time.  Both factors are bf16, so two products per instruction come for free: the gradients of
-// tokens (t, t+1) and the values of tokens (s, s+1), each pair in one register, meet in one v_dot2 (exact products,
-// fp32 sum) and both products belong to tap t - s.  The value pairs of all alignments are made on the way: every
-// value read from LDS joins the one read before it.  (The loops are straight-line code for the tap capacity of the
-// instantiation, as in the forward long conv.)
-namespace {
-constexpr int DW_TOK = 128;
-constexpr int DW_HALO = 62;
-constexpr int DW_BLK = 16;
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {
-  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), c, false);
-}
-}  // namespace
-
-template <int D, int KMAX>
-__global__ __launch_bounds__(256) void grouped_bwd_dw_kernel(GroupedBwdArgs a) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char dw_smem[];
-  uint16_t* xs = reinterpret_cast<uint16_t*>(dw_smem);     // [DW_HALO + DW_TOK][D] value rows (bf16) ...
-  float* red = reinterpret_cast<float*>(dw_smem);          // ... then [NG - 1][D][KMAX] sums
-  constexpr int NG = 256 / D, TPT = DW_TOK / NG;
-  static_assert(TPT % DW_BLK == 0, "whole blocks of gradients per thread");
-  const int tid = threadIdx.x;
-  const int bh = blockIdx.y, b = bh / a.H, h = bh % a.H;
-  // (neighbouring token blocks share 62 value rows: block indices 8 apart, which land on the same chiplet, get
-  // neighbouring token blocks when the count is a multiple of 8)
-  const int nblk = gridDim.x;
-  const int tblk = nblk % 8 == 0 ? (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3) : (int)blockIdx.x;
-  const int t0 = tblk * DW_TOK;
-  const int L = a.L, Kc = a.Kc;
-  const int64_t base = (int64_t)b * a.sb + (int64_t)h * a.sh;
-  const uint16_t* gv = static_cast<const uint16_t*>(a.v) + base;
-  const uint16_t* gdo = static_cast<const uint16_t*>(a.dout) + base;
-  const int c = tid % D, tg = tid / D;
-  // this thread's gradients (a token past the end: zero), two tokens per register, and the value rows
-  // t0 - 62 .. t0 + DW_TOK - 1, all requested first
-  uint32_t gp[TPT / 2];
-  {
-    uint16_t go_raw[TPT];
-#pragma unroll
-    for (int e = 0; e < TPT; ++e) {
-      const int tok = t0 + tg * TPT + e;
-      go_raw[e] = gdo[(int64_t)(tok < L ? tok : L - 1) * a.st + c];
-    }
-    constexpr int RIT = ((DW_HALO + DW_TOK) * (D / 8) + 255) / 256;
-    u32x4 raw[RIT];
-#pragma unroll
-    for (int i = 0; i < RIT; ++i) {
-      const int e = tid + 256 * i;
-      const int row = e / (D / 8), i0 = 8 * (e % (D / 8));
-      const int tok = t0 - DW_HALO + row;
-      raw[i] = *reinterpret_cast<const u32x4*>(gv + (int64_t)((tok >= 0 && tok < L) ? tok : 0) * a.st + i0);
-    }
-#pragma unroll
-    for (int i = 0; i < RIT; ++i) {
-      const int e = tid + 256 * i;
-      const int row = e / (D / 8), i0 = 8 * (e % (D / 8));
-      const int tok = t0 - DW_HALO + row;
-      if (e < (DW_HALO + DW_TOK) * (D / 8))
-        *reinterpret_cast<u32x4*>(xs + row * D + i0) = (tok >= 0 && tok < L) ? raw[i] : u32x4{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int e = 0; e < TPT; e += 2) {
-      const int tok = t0 + tg * TPT + e;
-      const uint32_t lo = tok < L ? go_raw[e] : 0u, hi = tok + 1 < L ? go_raw[e + 1] : 0u;
-      gp[e / 2] = lo | (hi << 16);
-    }
-  }
-  __syncthreads();
-  float acc[KMAX];
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) acc[j] = 0.f;
-#pragma unroll 1
-  for (int blk = 0; blk < TPT / DW_BLK; ++blk) {
-    const int tb0 = tg * TPT + blk * DW_BLK;
-    // value rows from the block's newest token backwards: x(m) = v[newest - m].  The pair (x(m), x(m-1)) = tokens
-    // (s, s+1) meets the gradients of tokens (tb0 + e, tb0 + e + 1), e even, through tap e - (DW_BLK - 1) + m.
-    const uint16_t* newest = xs + (DW_HALO + tb0 + DW_BLK - 1) * D + c;
-    uint32_t newer = newest[0];
-#pragma unroll
-    for (int m = 1; m < KMAX + DW_BLK - 1; ++m) {
-      const uint32_t x = newest[-m * D];
-      const uint32_t pair = x | (newer << 16);
-      newer = x;
-#pragma unroll
-      for (int e = 0; e < DW_BLK; e += 2) {
-        const int j = e - (DW_BLK - 1) + m;
-        if (j >= 0 && j < KMAX) acc[j] = dot2_bf16(gp[e / 2], pair, acc[j]);
-      }
-    }
-#pragma unroll
-    for (int e = 0; e + DW_BLK / 2 < TPT / 2; ++e) gp[e] = gp[e + DW_BLK / 2];
-  }
-  // the token groups of threads add up through LDS (fixed order), then one row of partial sums per workgroup
-  __syncthreads();
-  if (tg > 0) {
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j) red[((tg - 1) * D + c) * KMAX + j] = acc[j];
-  }
-  __syncthreads();
-  if (tg == 0) {
-#pragma unroll
-    for (int q = 0; q < NG - 1; ++q)
-#pragma unroll
-      for (int j = 0; j < KMAX; ++j) acc[j] += red[(q * D + c) * KMAX + j];
-  }
-  __syncthreads();
-  if (tg == 0) {
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j) red[c * KMAX + j] = acc[j];
-  }
-  __syncthreads();
-  // partial sums of a head lie together: [H][B * nwb][D * Kc]
-  float* part = a.dw_part + (((size_t)h * a.B + b) * a.nwb + tblk) * D * Kc;
-  for (int e = tid; e < D * Kc; e += 256) part[e] = red[(e / Kc) * KMAX + e % Kc];
-}
-
+// ---- dw: the partial sums of the token blocks (conv_mfma.hip) -------------------------------------------------------
 // Sums over batch rows and token blocks in a fixed order, DW_RED partial sums at a time: in [H][n][per_head] ->
 // out [H][ceil(n / DW_RED)][per_head]; the last stage writes dconv_w (n = 0: zeros).
 namespace { constexpr int DW_RED = 32; }
@@ -801,8 +682,6 @@ __global__ __launch_bounds__(256) void grouped_bwd_dw_reduce_kernel(const float*
   for (int i = i0; i < i1; ++i, p += per_head) s += *p;
   out[((size_t)h * (nout > 0 ? nout : 1) + c) * per_head + e] = s;
 }
-
-int grouped_bwd_dw_blocks(int L) { return (L + DW_TOK - 1) / DW_TOK; }
 
 template <int D, int GT>
 static hipError_t launch_bwd_core(const GroupedBwdArgs& a, hipStream_t st, hipEvent_t before_dkdv) {
@@ -840,17 +719,10 @@ static hipError_t launch_bwd_core(const GroupedBwdArgs& a, hipStream_t st, hipEv
   return hipGetLastError();
 }
 
-template <int D, int KMAX>
-static hipError_t launch_bwd_dw(const GroupedBwdArgs& a, hipStream_t st) {
-  constexpr int LDS_ROWS = (DW_HALO + DW_TOK) * D * (int)sizeof(uint16_t);
-  constexpr int LDS_RED = (256 / D > 2 ? 256 / D - 1 : 1) * D * KMAX * (int)sizeof(float);
-  constexpr int LDS = LDS_ROWS > LDS_RED ? LDS_ROWS : LDS_RED;
-  auto kern = grouped_bwd_dw_kernel<D, KMAX>;
-  hipError_t e = LINATTN_MAX_LDS_ONCE(kern, LDS);
-  if (e != hipSuccess) return e;
-  if (a.nwb > 0) hipLaunchKernelGGL(kern, dim3((unsigned)a.nwb, (unsigned)(a.B * a.H)), dim3(256), LDS, st, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int per_head = D * a.Kc;
+// The conv-weight sums over batch rows and token blocks (no tokens: zeros).
+hipError_t launch_grouped_bwd_dw(const GroupedBwdArgs& a, int d, hipStream_t st) {
+  hipError_t e;
+  const int per_head = d * a.Kc;
   // stages of 32: the partial sums ping-pong between the two halves of the buffer until one row per head is left
   const float* in = a.dw_part;
   float* other = a.dw_part + (size_t)a.B * a.H * (a.nwb > 0 ? a.nwb : 1) * per_head;
@@ -874,13 +746,6 @@ hipError_t launch_grouped_bwd_core(const GroupedBwdArgs& a, int d, hipStream_t s
   if (a.L <= 0) return hipSuccess;
   if (d == 128) return a.group == 256 ? launch_bwd_core<128, 256>(a, st, before_dkdv) : launch_bwd_core<128, 64>(a, st, before_dkdv);
   return a.group == 256 ? launch_bwd_core<64, 256>(a, st, before_dkdv) : launch_bwd_core<64, 64>(a, st, before_dkdv);
-}
-
-// The conv-weight sums (no tokens: zeros).
-hipError_t launch_grouped_bwd_dw(const GroupedBwdArgs& a, int d, hipStream_t st) {
-  if (!a.dconv_w) return hipSuccess;
-  if (d == 128) return a.Kc <= 16 ? launch_bwd_dw<128, 16>(a, st) : a.Kc <= 32 ? launch_bwd_dw<128, 32>(a, st) : launch_bwd_dw<128, 63>(a, st);
-  return a.Kc <= 16 ? launch_bwd_dw<64, 16>(a, st) : a.Kc <= 32 ? launch_bwd_dw<64, 32>(a, st) : launch_bwd_dw<64, 63>(a, st);
 }
 
 }  // namespace linattn

@@ -176,3 +176,24 @@ def test_flash_shaped_workload_every_head(name):
     e2 = compare((host(gout), host(gS), host(gz), host(gh)), gwant, "bf16", name + " three-branch form")
     print(f"{name}: token-level form {e1:.2e} (un-floored 99th percentile {p1:.2e}), three-branch form in groups of "
           f"{wl.chunk}: {e2:.2e}", flush=True)
+
+
+@pytest.mark.parametrize("B,H,L,d,Kc,with_state", [
+    (1, 2, 255, 64, 17, True), (1, 2, 257, 128, 18, False), (2, 2, 513, 64, 49, True), (1, 2, 529, 128, 50, True),  # edges of tiles and tap capacities
+    (1, 64, 513, 128, 63, False), (1, 64, 530, 128, 9, True)])                                                     # two tiles per workgroup
+def test_long_conv_and_its_gradients_at_the_edges_of_tiles(B, H, L, d, Kc, with_state):
+    """The conv added to what the token-level kernel left, written ahead of the groups of 256, and met from the other
+    side (its share of dv, the gradient of the taps: fp32 sums of exact products, so 1e-4 of their rms)."""
+    q, k, v, w, state = small_case(7800 + L + Kc, B, H, L, d, Kc, "bf16", with_state)
+    args = () if state is None else state
+    compare(run(q, k, v, w, state, "bf16", 256, 1e-3), oracle.prefill_recurrent(q, k, v, w, *args, eps=1e-3), "bf16", f"added, L={L} Kc={Kc}")
+    want = oracle.prefill_grouped(q, k, v, w, 256, 0.7, *((None,) * 3 if state is None else state), eps=1e-3)
+    compare(run(q, k, v, w, state, "bf16", 256, 1e-3, alpha=0.7), want, "bf16", f"written first, L={L} Kc={Kc}")
+    dout = workloads.upstream_gradient(q.shape, "bf16", 7801)
+    want = oracle.prefill_grouped_backward(q, k, v, w, dout, 256, alpha=0.7, eps=1e-3)
+    bf = torch.bfloat16
+    _, _, dv, dw = binding.prefill_grouped_backward(dev(q, bf), dev(k, bf), dev(v, bf), dev(w), dev(dout, bf), 0.7, 1e-3, group=256)
+    torch.cuda.synchronize()
+    check(host(dv), want["dv"], TOL["bf16"], f"dv, L={L} Kc={Kc}")
+    err = float(np.max(np.abs(host(dw) - want["dw"])) / np.sqrt(np.mean(want["dw"] ** 2)))
+    assert err <= TOL["f32"], f"dw, L={L} Kc={Kc}: {err:.2e}"
