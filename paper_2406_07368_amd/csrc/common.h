@@ -139,4 +139,19 @@ __device__ __forceinline__ float max_lanes(float x) {
   return x;
 }
 
+// x[l] + x[l ^ 8] (rotation by 8 inside a row of 16)
+__device__ __forceinline__ float add_xor8(float x) { return dpp_add<0x128>(x); }
+// x[l] + x[l ^ 16]: rows 0,1 and rows 2,3 of the wave are swapped against each other
+__device__ __forceinline__ float add_xor16(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// x[l] + x[l ^ 32]
+__device__ __forceinline__ float add_xor32(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 }  // namespace linattn

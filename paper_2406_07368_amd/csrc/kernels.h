@@ -166,6 +166,20 @@ struct GroupedBwdArgs {
   int nwb;                  // token blocks of the conv-weight pass per sequence
 };
 
+// The group-level sums of the three-branch form (group_sums.hip): [B*H][ng] slots of d*d + d floats
+struct GroupSumsArgs {
+  const void* a; const void* b;  // left rows (keys; backward: queries) and right rows (values; gradients), bf16, by strides
+  const float* w; const float* wz;   // backward: weight of a left row in the matrix and in the vector part, [B*H][L]
+  float* slots;
+  const float* S_in; const float* z_in;   // forward: what came before the sequence; null = zeros
+  float* S_out; float* z_out;             // forward: the sums over everything; null = not wanted
+  int B, H, L, ng, relu;
+  int64_t sb, sh, st;
+};
+// one walk per head (pays when there are heads enough, or few groups) against one workgroup per group and a prefix sum
+bool group_sums_pays(int heads, int ng, int d, int group);
+hipError_t launch_group_sums(const GroupSumsArgs& a, int d, int group, bool back, hipStream_t st);
+
 // verify.hip
 int verify_pick_split(int BH);
 hipError_t launch_verify(const VerifyArgs& a, bool bf16, int d, int nsplit, hipStream_t st);

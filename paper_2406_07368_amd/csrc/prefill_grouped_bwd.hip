@@ -21,6 +21,8 @@
 //                             the grouped branch with S_g in LDS as bf16.  Hands the per-token scalars on.
 //   grouped_bwd_gs_kernel     G_g = (f phi(Q))^T dO and gz_g, contraction over the group's tokens.
 //   grouped_bwd_suffix_kernel D_g = sum over the later groups, in place.
+//                             (With heads enough, or few groups, one walk over the groups takes the place of these two and
+//                             of the sums and their prefix sum: group_sums.hip.)
 //   grouped_bwd_dkdv_kernel   wave = 32 keys; the group's Q and dO rows in LDS; one workgroup for dV, one for dK (the
 //                             accumulators of both do not fit next to the operands of both).
 #include "common.h"
@@ -696,19 +698,27 @@ static hipError_t launch_bwd_core(const GroupedBwdArgs& a, hipStream_t st, hipEv
   if ((e = LINATTN_MAX_LDS_ONCE(kg, G::TOTAL)) != hipSuccess) return e;
   if ((e = LINATTN_MAX_LDS_ONCE(kk, G::TOTAL)) != hipSuccess) return e;
   if ((e = LINATTN_MAX_LDS_ONCE(ks, G::TOTAL)) != hipSuccess) return e;
-  // the sums before every group: every group's own sums, then the prefix sum (which also writes the zeros before group 0)
-  if (a.ng > 1) {
+  GroupSumsArgs s{};
+  s.B = a.B; s.H = a.H; s.L = a.L; s.ng = a.ng; s.relu = a.relu; s.sb = a.sb; s.sh = a.sh; s.st = a.st;
+  const bool walk = group_sums_pays(BH, a.ng, D, GT);
+  if (walk) {
+    s.a = a.k; s.b = a.v; s.slots = a.P;
+    if ((e = launch_group_sums(s, D, GT, false, st)) != hipSuccess) return e;
+  } else {
+    // the sums before every group: every group's own sums, then the prefix sum (which also writes the zeros before group 0)
     hipLaunchKernelGGL(ks, dim3((unsigned)(a.ng - 1), (unsigned)BH), dim3(G::NT), G::TOTAL, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  {
     PrefillArgs f{};
     f.ws = a.P; f.B = a.B; f.H = a.H; f.m = 1; f.nseg = a.ng;
     if ((e = launch_segment_scan(f, D, st)) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(kq, dim3((unsigned)a.ng, (unsigned)BH), dim3(G::NT), G::TOTAL, st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (a.ng > 1) {
+  if (walk && a.ng > 1) {
+    const size_t n = (size_t)BH * a.L;
+    s.a = a.q; s.b = a.dout; s.w = a.stats + 3 * n; s.wz = a.stats + 4 * n; s.slots = a.Dg;
+    if ((e = launch_group_sums(s, D, GT, true, st)) != hipSuccess) return e;
+  } else if (a.ng > 1) {
     hipLaunchKernelGGL(kg, dim3((unsigned)(a.ng - 1), (unsigned)BH), dim3(G::NT), G::TOTAL, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(grouped_bwd_suffix_kernel, dim3((unsigned)((G::SLOT + 255) / 256), (unsigned)BH), dim3(256), 0, st, a, (int)G::SLOT);

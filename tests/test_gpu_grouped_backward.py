@@ -158,3 +158,12 @@ def test_flash_shape_on_a_batch_one_head_of_every_batch_row():
     compare(got, want, f"{wl.name} head {hsel}")
     for n in ("dq", "dk", "dv"):
         check_unfloored(got[n], want[n], TOL["bf16"], f"{wl.name} head {hsel} {n}")
+
+
+@pytest.mark.parametrize("B,H,L,d,group", [(2, 16, 1700, 128, 256),   # walk over seven groups, the last one ragged
+                                           (4, 12, 450, 128, 64),     # walk over eight groups of 64
+                                           (1, 3, 1500, 64, 256), (1, 3, 420, 64, 64)])   # one workgroup per group, prefix sums
+def test_gradient_with_the_sums_walked_or_scanned(B, H, L, d, group):
+    q, k, v, w, dout = case(9600 + L + d, B, H, L, d, 3, d ** -0.5)
+    want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, alpha=0.9, eps=0.0)
+    compare(run(q, k, v, w, dout, group, 0.9, 0.0), want, f"d={d} group={group} L={L}")
