@@ -228,6 +228,8 @@ hipError_t launch_conv_mfma(const ConvLongArgs& a, int d, hipStream_t st);
 // holds: the conv's share is written first; `before_dkdv`, if not null, is waited for ahead of the kernel that does
 // so), and the conv-weight sums
 hipError_t launch_grouped_bwd_core(const GroupedBwdArgs& a, int d, hipStream_t st, hipEvent_t before_dkdv);
+// grouped_bwd_rows.hip: dq and the per-token scalars, or dk and dv (keys)
+hipError_t launch_grouped_bwd_rows(const GroupedBwdArgs& a, int d, bool keys, hipStream_t st);
 hipError_t launch_grouped_bwd_dw(const GroupedBwdArgs& a, int d, hipStream_t st);
 
 // prefill_mfma.hip : launch plan of the bf16 prefill (segments, prefix sum over segment states)

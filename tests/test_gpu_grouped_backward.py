@@ -167,3 +167,12 @@ def test_gradient_with_the_sums_walked_or_scanned(B, H, L, d, group):
     q, k, v, w, dout = case(9600 + L + d, B, H, L, d, 3, d ** -0.5)
     want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, alpha=0.9, eps=0.0)
     compare(run(q, k, v, w, dout, group, 0.9, 0.0), want, f"d={d} group={group} L={L}")
+
+
+@pytest.mark.parametrize("L", [15, 17, 33, 127, 128, 129, 145, 255, 384, 400])
+@pytest.mark.parametrize("d,group", [(64, 64), (128, 64), (64, 256), (128, 256)])
+def test_gradient_at_the_edges_of_runs_and_tiles(d, group, L):
+    """Tiles of 16 tokens, runs of 128 (a group of 256 is two, the second short or missing), passes of 32 rows."""
+    q, k, v, w, dout = case(9700 + L + d + group, 1, 2, L, d, 3)
+    want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, alpha=1.1, eps=0.0)
+    compare(run(q, k, v, w, dout, group, 1.1, 0.0), want, f"d={d} group={group} L={L}")
