@@ -86,6 +86,11 @@ struct PrefillPlan {
   bool direct;              // fp32 rows: see F32Plan
   int nseg, seg_len;
   size_t ws_bytes;
+  void cut(int L, int chunk, int n) {       // n segments or fewer, on multiples of the group size
+    const int chunks = (L + chunk - 1) / chunk;
+    seg_len = (chunks + n - 1) / n * chunk;
+    nseg = (L + seg_len - 1) / seg_len;
+  }
 };
 
 // How a prefill call is laid out on the chip.  fp32 inputs go to the kernel on the fp32
@@ -108,10 +113,7 @@ PrefillPlan plan_prefill(const linattn_desc* d, int32_t L, bool grouped = false)
   }
   if (L > 0) {
     p.nseg = g256 ? prefill_grouped256_pick_segments(heads, L) : prefill_mfma_pick_segments(heads, L, d->chunk, d->d);
-    const int chunks = (L + d->chunk - 1) / d->chunk;
-    const int cps = (chunks + p.nseg - 1) / p.nseg;
-    p.seg_len = cps * d->chunk;
-    p.nseg = (L + p.seg_len - 1) / p.seg_len;
+    p.cut(L, d->chunk, p.nseg);
   }
   p.ws_bytes = g256 ? prefill_grouped256_workspace_bytes(heads, d->d, p.nseg)
                                   : prefill_mfma_workspace_bytes(heads, d->d, p.nseg);
@@ -208,6 +210,13 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
   const bool in_place = (S_in && S_in == S_out) || (z_in && z_in == z_out) || (hist_in && hist_in == hist_out);
   if (no_ws || (plan.direct && in_place)) { plan.nseg = 1; plan.seg_len = L; plan.direct = false; }
 
+  bool fold = false;
+  if (plan.mfma && !cont && !(grouped && desc->chunk == 256)) {
+    const int n = prefill_mfma_fold_segments(plan.nseg, L);
+    fold = n > 0;
+    if (fold) plan.cut(L, desc->chunk, n);               // never more segments than the workspace was sized for
+  }
+
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   PrefillArgs a{};
   // More than 8 taps: the attention kernels run without the convolution (one tap, taken as zero, no history) and
@@ -226,7 +235,7 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
   a.sh_v = m > 1 ? desc->stride_h_v : desc->stride_h;
   a.st_v = m > 1 ? desc->stride_t_v : desc->stride_t;
   a.nseg = plan.nseg; a.seg_len = plan.seg_len; a.direct = plan.direct; a.f32 = !plan.mfma;
-  a.alpha = alpha;
+  a.alpha = alpha; a.fold = fold;
   a.wait_spins = g_wait_spins.load(std::memory_order_relaxed);
   hipError_t e;
   const bool bf16 = desc->io_dtype == LINATTN_BF16;

@@ -102,6 +102,7 @@ struct PrefillArgs {
   int f32;                  // fp32 rows (the history rows staged by the prefix sum are floats)
   int no_conv;              // the taps are taken as zero: a convolution with more than 8 taps runs as a pass of its own
   int group;                // three-branch form: tokens per group (64 or 256)
+  int fold;                 // bf16 rows: the full pass adds up the segments' increments itself
   // Value rows wider than key rows: d_v = m d.  The kernels then see B*H*m heads of d value channels each, head
   // (b, h, block) sharing q, k, z with its siblings and owning channels block*d .. block*d + d - 1 of v, out, hist,
   // conv_w and of the rows of S.  m = 1: nothing changes.
@@ -235,6 +236,7 @@ hipError_t launch_grouped_bwd_dw(const GroupedBwdArgs& a, int d, hipStream_t st)
 // prefill_mfma.hip : launch plan of the bf16 prefill (segments, prefix sum over segment states)
 hipError_t launch_segment_scan(const PrefillArgs& a, int d, hipStream_t st);   // the prefix sum alone
 int prefill_mfma_pick_segments(int BH, int L, int chunk, int d);
+int prefill_mfma_fold_segments(int nseg, int L);
 size_t prefill_mfma_workspace_bytes(int BH, int d, int nseg);
 hipError_t launch_prefill_mfma(const PrefillArgs& a, int d, int chunk, bool grouped, hipStream_t st);
 

@@ -90,6 +90,20 @@ int prefill_mfma_pick_segments(int BH, int L, int chunk, int d) {
   return want < 1 ? 1 : want;
 }
 
+// A new sequence (no state and no history come in: nothing that an output could overwrite while another workgroup still
+// reads it) needs no prefix sum as a launch of its own: every workgroup of the full pass adds up the increments of the
+// segments before it while its first rows are on their way.  Returns the segments to use, 0: keep the prefix sum.
+// What it costs is the last segment's reads, one slot (64 KB at d = 128) per segment through one compute unit, against
+// a launch of 4 us and more.  Up to 6 segments it pays (us a call, prefix sum / this: 2 segments 100 / 93, 4 segments of
+// 64 heads 69 / 65, 6 segments of 84 heads of 64 40.5 / 37, of 40 heads 78 / 75); at 8 it does not (d = 128, 32 heads:
+// L = 1024 42 / 46, L = 8192 105 / 109).  Sequences of up to 16 groups are therefore cut into 6 at most (L = 1024: d = 128,
+// 32 heads 42 / 37; d = 64, 48 heads 31 / 28); longer ones would lose more by the compute units left idle.
+int prefill_mfma_fold_segments(int nseg, int L) {
+  if (nseg <= 1) return 0;
+  if (nseg <= 6) return nseg;
+  return L <= 16 * 64 ? 6 : 0;
+}
+
 size_t prefill_mfma_workspace_bytes(int BH, int d, int nseg) {
   if (nseg <= 1) return 0;
   return (size_t)BH * nseg * ((size_t)d * d + d) * sizeof(float) + (size_t)BH * HALO * d * sizeof(uint16_t);
@@ -130,7 +144,7 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a, int d, int chunk, bool grou
   hipError_t e;
   if (a.nseg > 1) {
     if ((e = launch_prefill_mfma_ws(a, d, true, false, st)) != hipSuccess) return e;
-    if ((e = launch_segment_scan(a, d, st)) != hipSuccess) return e;
+    if (!a.fold && (e = launch_segment_scan(a, d, st)) != hipSuccess) return e;
   }
   if (grouped && chunk == 256) return launch_prefill_grouped256(a, d, st);
   return launch_prefill_mfma_ws(a, d, false, grouped, st);

@@ -299,3 +299,33 @@ def test_fp32_rows_on_either_side_of_the_dispatch(grouped, B, H, L, d, Kc, with_
             binding.linattn_prefill(desc, L, gq, gk, gv, gw, *st, out, *res, ws, need)
         torch.cuda.synchronize()
         compare((host(out), *(host(x) for x in res)), want, "f32", f"grouped={grouped} L={L} d={d} in place={in_place}")
+
+
+@pytest.mark.parametrize("form", ["tokens", "grouped"])
+@pytest.mark.parametrize("B,H,L,d", [(8, 16, 1100, 128), (8, 8, 1531, 128), (5, 8, 1100, 128),   # 2, 4, 6 segments
+                                     (7, 12, 1197, 64), (1, 32, 1100, 128), (1, 4, 1000, 64), (1, 3, 520, 128)])
+def test_segments_summed_in_the_full_pass_or_by_the_prefix_sum(form, B, H, L, d):
+    """A new sequence of few segments adds their increments up in the full pass; handed zeros as its state the same
+    sequence takes the prefix sum.  Same order of additions; the segments differ up to 1024 tokens only."""
+    q, k, v, w, _ = small_case(3100 + L + H, B, H, L, d, 3, "bf16", False, d ** -0.5)
+    bf = torch.bfloat16
+    args = (dev(q, bf), dev(k, bf), dev(v, bf), dev(w))
+    zeros = (torch.zeros((B, H, d, d), device="cuda"), torch.zeros((B, H, d), device="cuda"),
+             torch.zeros((B, H, 2, d), dtype=bf, device="cuda"))
+    if form == "tokens":
+        one, two = binding.prefill(*args), binding.prefill(*args, zeros)
+    else:
+        one, two = binding.prefill_grouped(*args, 1.0), binding.prefill_grouped(*args, 1.0, zeros)
+    torch.cuda.synchronize()
+    for a, b in zip((one[0], *one[1]), (two[0], *two[1])):
+        if L > 1024:
+            assert torch.equal(a, b)
+        else:                                        # increments of other segments: fp32 sums and one rounding apart
+            assert (a.float() - b.float()).norm() <= TOL["bf16"] * b.float().norm()
+    h = slice(H - 1, H)
+    if form == "tokens":
+        want = oracle.prefill_recurrent(q[:, h], k[:, h], v[:, h], w[h])
+    else:
+        want = oracle.prefill_grouped(q[:, h], k[:, h], v[:, h], w[h], 64, alpha=1.0)
+    check(host(one[0][:, h]), want[0], TOL["bf16"], "out")
+    check(host(one[1][0][:, h]), want[1], TOL["bf16"], "S")
