@@ -5,7 +5,7 @@
 // the chip the sequence axis is cut into segments: a first pass reduces each segment's
 // K, V to its state increment, a prefix sum over the segments (here) turns the
 // increments into segment start states, and the full pass starts every segment from its
-// prefix.
+// prefix (for a new sequence in few segments it adds the increments up itself).
 #include "common.h"
 #include "kernels.h"
 #include "mfma_util.h"
