@@ -30,6 +30,13 @@ constexpr int FT = 32;                       // tokens per step
 constexpr int FGROUP = 64;                   // tokens per group of the three-branch form: two steps
 
 __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+// phi for fp32 rows: the map of the fp32 generation step (under elu + 1 a NaN stays one), without a branch on the feature
+// map: one = 1 for elu + 1 and 0 for max(x, 0), whose lower branch is 0 whatever x is.
+__device__ __forceinline__ float phi_f32(float x, float one) {
+  const uint32_t keep = one != 0.f ? 0xffffffffu : 0u;
+  const float e = __uint_as_float(__float_as_uint(__expf(x)) & keep);
+  return x > 0.f ? x + one : e;
+}
 // row of accumulator register r in a lane of half hi
 __device__ __forceinline__ constexpr int acc_row(int r, int hi) { return 8 * (r >> 2) + 4 * hi + (r & 3); }
 
@@ -158,7 +165,7 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
       for (int r = 0; r < 16; ++r) {
         float x = Kl[(32 * p + acc_row(r, hi)) * ST + 32 * ib + l32];
         if constexpr (GROUPED) {                           // raw rows
-          x = phi_nb(x, one);
+          x = phi_f32(x, one);
           x = acc_row(r, hi) < n ? x : 0.f;
         }
         Sa[ib] = mfma32(x, vr[r], Sa[ib]);
@@ -187,9 +194,9 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
       f32x4 q4, k4, v4;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        k4[e] = is ? (GROUPED ? xk[i][e] : phi_nb(xk[i][e], one)) : 0.f;
+        k4[e] = is ? (GROUPED ? xk[i][e] : phi_f32(xk[i][e], one)) : 0.f;
         v4[e] = is ? xv[i][e] : 0.f;
-        if constexpr (!STATE_ONLY) q4[e] = GROUPED ? xq[i][e] : phi_nb(xq[i][e], one);
+        if constexpr (!STATE_ONLY) q4[e] = GROUPED ? xq[i][e] : phi_f32(xq[i][e], one);
       }
       *reinterpret_cast<f32x4*>(Kl + (32 * p + r) * ST + pc) = k4;
       *reinterpret_cast<f32x4*>(Vl + (HALO + 32 * p + r) * ST + pc) = v4;
@@ -226,7 +233,7 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
       for (int j = 0; j < 4; ++j) {
         const f32x4 z4 = *reinterpret_cast<const f32x4*>(zl + 32 * w + 8 * j + 4 * hi);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) qz = fmaf(GROUPED ? phi_nb(qf[j][e], one) : qf[j][e], z4[e], qz);
+        for (int e = 0; e < 4; ++e) qz = fmaf(GROUPED ? phi_f32(qf[j][e], one) : qf[j][e], z4[e], qz);
       }
       qz += __shfl_xor(qz, 32);
       if (hi == 0) Pz[32 * w + l32] = qz;
@@ -240,7 +247,7 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
         for (int j = 0; j < 4; ++j) {
           const f32x4 qa = *reinterpret_cast<const f32x4*>(Ql + l32 * ST + 32 * ib + 8 * j + 4 * hi);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o = mfma32(GROUPED ? phi_nb(qa[e], one) : qa[e], Sa[ib][4 * j + e], o);
+          for (int e = 0; e < 4; ++e) o = mfma32(GROUPED ? phi_f32(qa[e], one) : qa[e], Sa[ib][4 * j + e], o);
         }
       __syncthreads();
       // ---- the scores of the step: pr_[kt][r] = key 32kt + acc_row(r), query l32 --------------------------------
@@ -449,7 +456,7 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float x = FT * kt + acc_row(r, hi) < L ? phi_nb(kx[r], one) : 0.f;
+        const float x = FT * kt + acc_row(r, hi) < L ? phi_f32(kx[r], one) : 0.f;
         zs += x;
 #pragma unroll
         for (int cb = 0; cb < IB; ++cb) acc[cb] = mfma32(x, vx[cb][r], acc[cb]);
@@ -491,6 +498,14 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
 #pragma unroll
       for (int j = 0; j < 4; ++j) qf[ib][j] = *reinterpret_cast<const f32x4*>(p + 32 * ib + 8 * j);
   }
+  if (!GROUPED || w != 0) {                                // only the softmax of the query's own group takes the raw rows
+#pragma unroll
+    for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) qf[ib][j][e] = phi_f32(qf[ib][j][e], one);
+  }
   static_assert(D == 64 || D == 128, "1 / sqrt(d) below");
   constexpr float to_log2 = 1.44269504088896340736f * (D == 64 ? 0.125f : 0.08838834764831845f);
   // scores of key tile kt: sc[r] = key acc_row(r), query l32; raw: the rows as they are, else under the feature map
@@ -515,7 +530,7 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
       for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          sc = mfma32(raw ? kf[ib][j][e] : phi_nb(kf[ib][j][e], one), raw ? qf[ib][j][e] : phi_nb(qf[ib][j][e], one), sc);
+          sc = mfma32(raw ? kf[ib][j][e] : phi_f32(kf[ib][j][e], one), qf[ib][j][e], sc);
   };
   auto weigh = [&](const f32x16& sc, const float (&vx)[IB][16]) __attribute__((always_inline)) {
 #pragma unroll
@@ -572,7 +587,7 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
           const f32x4 z4 = *reinterpret_cast<const f32x4*>(a.z_in + (size_t)hx.bh * D + 32 * ib + 8 * j + 4 * hi);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float x = phi_nb(qf[ib][j][e], one);
+            const float x = qf[ib][j][e];
             rs = fmaf(x, z4[e], rs);
             const float* sp = a.S_in + S_base + (int64_t)(32 * ib + 8 * j + 4 * hi + e) * hx.dvt + l32;
 #pragma unroll

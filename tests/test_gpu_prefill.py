@@ -329,3 +329,37 @@ def test_segments_summed_in_the_full_pass_or_by_the_prefix_sum(form, B, H, L, d)
         want = oracle.prefill_grouped(q[:, h], k[:, h], v[:, h], w[h], 64, alpha=1.0)
     check(host(one[0][:, h]), want[0], TOL["bf16"], "out")
     check(host(one[1][0][:, h]), want[1], TOL["bf16"], "S")
+
+
+NON_FINITE = [(2, 4, 130, 64, 3), (2, 4, 130, 128, 4),           # quadratic kernel
+              (1, 4, 1700, 64, 3), (1, 3, 1700, 128, 5),         # segmented walk
+              (8, 40, 97, 64, 2), (3, 100, 65, 128, 8)]          # one workgroup per head
+
+
+def same_pattern(got, want, tol, what):
+    """NaN and infinities exactly where the oracle has them, the rest to the tolerance."""
+    for g, w, name in zip(got, want, ("out", "S", "z")):
+        assert np.array_equal(np.isnan(g), np.isnan(w)), f"{what} {name}: NaN elsewhere"
+        inf = np.isinf(w)
+        assert np.array_equal(np.isinf(g), inf) and np.array_equal(g[inf], w[inf]), f"{what} {name}: infinities elsewhere"
+        ok = np.isfinite(w)
+        check(np.where(ok, g, 0.0), np.where(ok, w, 0.0), tol, f"{what} {name}")
+
+
+@pytest.mark.parametrize("grouped", [False, True])
+@pytest.mark.parametrize("B,H,L,d,Kc", NON_FINITE)
+@pytest.mark.parametrize("which", ["q", "k"])
+def test_fp32_nan_in_q_or_k_reaches_what_it_should(which, B, H, L, d, Kc, grouped):
+    q, k, v, w, state = small_case(6300 + L + d, B, H, L, d, Kc, "f32", True)
+    x = q if which == "q" else k
+    x[0, 1, 45, 7] = np.nan
+    x[B - 1, H - 1, L - 2, d - 1] = np.nan
+    args = dict(S0=state[0], z0=state[1], hist0=state[2])
+    want = oracle.prefill_grouped(q, k, v, w, 64, alpha=0.7, eps=1e-2, **args) if grouped else oracle.prefill_recurrent(q, k, v, w, eps=1e-2, **args)
+    st = tuple(dev(x) for x in state)
+    gq, gk, gv, gw = dev(q), dev(k), dev(v), dev(w)
+    out, new = (binding.prefill_grouped(gq, gk, gv, gw, 0.7, st, 1e-2) if grouped else binding.prefill(gq, gk, gv, gw, st, 64, 1e-2))
+    torch.cuda.synchronize()
+    got = (host(out), host(new[0]), host(new[1]))
+    assert np.isnan(want[0]).any()
+    same_pattern(got, want, TOL["f32"], f"NaN in {which}")
