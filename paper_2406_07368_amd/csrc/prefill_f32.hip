@@ -40,6 +40,28 @@ __device__ __forceinline__ float phi_f32(float x, float one) {
 // row of accumulator register r in a lane of half hi
 __device__ __forceinline__ constexpr int acc_row(int r, int hi) { return 8 * (r >> 2) + 4 * hi + (r & 3); }
 
+// Values that are not finite.  In the tile that holds the queries themselves a key later than the query has weight 0, but 0
+// times an infinity or a NaN is a NaN in an earlier token's output.  The products therefore take the largest finite numbers
+// in the place of such values, and what the values themselves give the queries that see them is added behind a tile, key by
+// key; weights are not negative, so what the replacement has added of itself has the infinity's sign (or meets a NaN).
+// (A branch behind the products: ahead of them it would keep the requests of a tile from being spread over the products
+// before, and cost spills.)  t becomes a NaN with the first such value.
+__device__ __forceinline__ float finite_part(float v, float& t) {
+  t = fmaf(v, 0.f, t);
+  return __builtin_amdgcn_fmed3f(v, -3.402823466e38f, 3.402823466e38f);
+}
+// w: the key's weights by query; v: the key's value in this lane's channel; o[r]: query acc_row(r) of the tile, `seen` of
+// them on see the key.
+__device__ __forceinline__ void add_non_finite(const float* w, float v, int seen, f32x16& o, int hi) {
+  const bool is = !__builtin_isfinite(v);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 w4 = *reinterpret_cast<const f32x4*>(w + 8 * g + 4 * hi);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[4 * g + e] = is && 8 * g + 4 * hi + e >= seen ? fmaf(w4[e], v, o[4 * g + e]) : o[4 * g + e];
+  }
+}
+
 template <int D, bool GROUPED>
 struct F32Cfg {
   static constexpr int NW = D / 32, NT = 64 * NW;
@@ -110,6 +132,7 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
   }
   if (hi == 0) zl[ch] = zr;
 
+  const int taps = a.no_conv ? 0 : Kc;
   float wreg[KCM];
 #pragma unroll
   for (int j = 0; j < KCM; ++j) wreg[j] = 0.f;
@@ -314,8 +337,24 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
       for (int kt = 0; kt < G::TILES; ++kt) {
         if (kt > p) break;
         value_regs(kt);
+        float odd = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o = mfma32(pt[kt][r], vr[r], o);
+        for (int r = 0; r < 16; ++r) o = mfma32(pt[kt][r], finite_part(vr[r], odd), o);
+        if (__any(odd != odd)) {                                  // uniform; two keys at a time through the wave's own 32 floats
+#pragma unroll 1
+          for (int s = 0; s < 16; ++s) {
+#pragma unroll
+            for (int h2 = 0; h2 < 2; ++h2) {
+              const int key = acc_row(s, h2);
+              asm volatile("" ::: "memory");
+              if (hi == h2) sc0[32 + l32] = pt[kt][0];
+              asm volatile("" ::: "memory");
+              add_non_finite(sc0 + 32, Vl[(HALO + 32 * kt + key) * ST + ch], kt == p ? key : 0, o, hi);
+            }
+#pragma unroll
+            for (int i = 0; i < 15; ++i) pt[kt][i] = pt[kt][i + 1];
+          }
+        }
       }
       // ---- outputs: o[r] = token t0 + acc_row(r), channel ch ----------------------------------------------------
 #pragma unroll
@@ -329,7 +368,10 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
         for (int e = 0; e < 4; ++e) {
           float u = o[4 * g + e] * iv[e];
 #pragma unroll
-          for (int j = 0; j < KCM; ++j) u = fmaf(wreg[j], e - j >= 0 ? vr[4 * g + e - j < 0 ? 0 : 4 * g + e - j] : back[j - e > 0 ? j - e : 1], u);
+          for (int j = 0; j < KCM; ++j) {                  // (a tap that does not exist is left out: 0 times an infinity is none)
+            const float x = e - j >= 0 ? vr[4 * g + e - j < 0 ? 0 : 4 * g + e - j] : back[j - e > 0 ? j - e : 1];
+            u = j < taps ? fmaf(wreg[j], x, u) : u;
+          }
           const int row = 8 * g + 4 * hi + e;
           if (row < nt) go[(int64_t)(t0 + row) * a.st_v + ch] = u;
         }
@@ -454,6 +496,12 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
 #pragma unroll
         for (int cb = 0; cb < IB; ++cb) vx[cb][r] = gv[t * a.st_v + 32 * cb + l32];
       }
+      if (kt == nq - 1) {                                  // uniform: rows past the end are zero rows
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+          for (int cb = 0; cb < IB; ++cb) vx[cb][r] = FT * kt + acc_row(r, hi) < L ? vx[cb][r] : 0.f;
+      }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float x = FT * kt + acc_row(r, hi) < L ? phi_f32(kx[r], one) : 0.f;
@@ -538,6 +586,29 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
 #pragma unroll
       for (int cb = 0; cb < IB; ++cb) acc[cb] = mfma32(sc[r], vx[cb][r], acc[cb]);
   };
+  // the same with values that may not be finite, and what those add
+  auto weigh_finite = [&](const f32x16& sc, const float (&vx)[IB][16]) __attribute__((always_inline)) {
+    float odd = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int cb = 0; cb < IB; ++cb) acc[cb] = mfma32(sc[r], finite_part(vx[cb][r], odd), acc[cb]);
+    return odd;
+  };
+  auto weigh_rest = [&](float odd, int kt, const f32x16& sc) __attribute__((always_inline)) {
+    if (!__any(odd != odd)) return;                        // uniform
+    float* own = smf + G::O + w * 32 * D;                  // the wave's part of the outputs, free until they go there
+#pragma unroll
+    for (int r = 0; r < 16; ++r) own[32 * acc_row(r, hi) + l32] = sc[r];
+    asm volatile("" ::: "memory");
+#pragma unroll 1
+    for (int key = 0; key < FT; ++key) {
+      const float* vp = gv + (int64_t)(FT * kt + key < L ? FT * kt + key : L - 1) * a.st_v + l32;
+#pragma unroll
+      for (int cb = 0; cb < IB; ++cb) add_non_finite(own + 32 * key, vp[32 * cb], kt == qt ? key : 0, acc[cb], hi);
+    }
+    asm volatile("" ::: "memory");
+  };
   float rs = 0.f;                                          // what the wave's tiles add to the normaliser of query l32
   const int first = GROUPED ? w - 1 : w;                   // three-branch form: wave 0 has the query's own group
   const int step = GROUPED ? DW - 1 : DW;
@@ -565,8 +636,9 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
     }
     mass += __shfl_xor(mass, 32);                          // the token itself is always seen: mass >= 1
     if (hi == 0) smf[G::SC + l32] = mass;
-    weigh(s1, v1);
+    const float odd = weigh_finite(s1, v1);
     if (two) weigh(s0, v0);
+    weigh_rest(odd, qt, s1);
   } else {
     for (int kt = first; kt < kt0; kt += step) {
       f32x16 sc;
@@ -577,7 +649,8 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
         if (!GROUPED) sc[r] = (kt < qt || acc_row(r, hi) <= l32) ? sc[r] : 0.f;
         rs += sc[r];
       }
-      weigh(sc, vx);
+      if constexpr (GROUPED) weigh(sc, vx);                // whole tiles of earlier groups
+      else weigh_rest(weigh_finite(sc, vx), kt, sc);
     }
     if (w == DW - 1 && a.S_in) {                           // the incoming state
 #pragma unroll
@@ -623,7 +696,7 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int i = 0; i < NO; ++i) u[i] = fmaf(jb + j < Kc ? wt[j] : 0.f, x[i][j], u[i]);
+        for (int i = 0; i < NO; ++i) u[i] = jb + j < Kc ? fmaf(wt[j], x[i][j], u[i]) : u[i];
     }
   }
   __syncthreads();

@@ -363,3 +363,27 @@ def test_fp32_nan_in_q_or_k_reaches_what_it_should(which, B, H, L, d, Kc, groupe
     got = (host(out), host(new[0]), host(new[1]))
     assert np.isnan(want[0]).any()
     same_pattern(got, want, TOL["f32"], f"NaN in {which}")
+
+
+@pytest.mark.parametrize("grouped", [False, True])
+@pytest.mark.parametrize("B,H,L,d,Kc", NON_FINITE)
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_fp32_value_row_that_is_not_finite_stays_out_of_earlier_tokens(value, B, H, L, d, Kc, grouped):
+    """No output depends on a later token, whatever that token holds: masked keys and taps that do not exist may not enter
+    with weight zero.  One such value in the middle of a tile, one near the end, one in the oldest row of the history."""
+    q, k, v, w, state = small_case(6400 + L + d, B, H, L, d, Kc, "f32", True)
+    def call():
+        st = tuple(dev(x) for x in state)
+        gq, gk, gv, gw = dev(q), dev(k), dev(v), dev(w)
+        out, new = (binding.prefill_grouped(gq, gk, gv, gw, 0.7, st, 1e-2) if grouped else binding.prefill(gq, gk, gv, gw, st, 64, 1e-2))
+        torch.cuda.synchronize()
+        return out, host(out), host(new[0]), host(new[1])
+    clean = call()[0].clone()
+    v[0, 1, 45, 7] = value
+    v[B - 1, H - 1, L - 2, d - 1] = value
+    state[2][B - 1, H - 1, 0, 5] = value
+    args = dict(S0=state[0], z0=state[1], hist0=state[2])
+    want = oracle.prefill_grouped(q, k, v, w, 64, alpha=0.7, eps=1e-2, **args) if grouped else oracle.prefill_recurrent(q, k, v, w, eps=1e-2, **args)
+    out, *got = call()
+    assert torch.equal(out[0, 1, :45], clean[0, 1, :45])
+    same_pattern(got, want, TOL["f32"], f"{value} in v")
