@@ -9,7 +9,7 @@
 // the tokens of a channel cut into blocks of 16 (t = 16a + i), U[i][a] = sum_k W[i][k] X[k][a], X[k][a] = v[16a - OFF + k]:
 // 16 x 16 x 32 instructions with 16 blocks in the columns, so 256 tokens of one channel at a time; 63 taps are three
 // contraction steps (96 token offsets, OFF = 80), up to 49 taps two, up to 17 one.  The taps enter as the sum of three
-// bf16 terms, which is all 24 bits of the fp32 tap: products exact, sums fp32, like the fp32 multiply-adds they replace.
+// bf16 terms, which is all 24 bits of a finite fp32 tap: products exact, sums fp32, like the fp32 multiply-adds they replace.
 // The gradient of the taps is the same picture the other way round, D[i][r] = sum_a dO[16a + i] v[16(a - b) + r] (16 x 16 x
 // 16, both factors bf16 as they are), summed along its diagonals: first over the four accumulator registers by shifts
 // inside a row of 16 lanes, then over the four rows through LDS.
@@ -23,6 +23,8 @@
 // two tiles of 256 tokens where there are enough of them (104 -> 84 us below).  Measured on B8 H8 L8192 d128 with 63 taps:
 // forward 84 us for 290 MB (158 us on the vector ALUs, a thread per channel: 63 multiply-adds per element); backward 185 us
 // for both gradients beside the kernels of the other stream (158 + 355 us and more as two passes).
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "mfma_util.h"
@@ -35,6 +37,8 @@ constexpr int CM_CB = 32;                                  // channels per workg
 constexpr int CM_NW = 4, CM_CPW = CM_CB / CM_NW;           // waves, channels per wave
 constexpr int CM_SKEW = 16;                                // dwords per 8 channels
 typedef uint32_t __attribute__((may_alias)) u32_any;      // dwords of an array that is written in 16-bit pieces
+typedef uint16_t __attribute__((may_alias)) u16_any;      // and the other way round
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 enum { CM_ASSIGN = 0, CM_ADD = 1, CM_BWD = 2 };
 
 template <int KS, int MODE, int T>
@@ -53,7 +57,8 @@ struct ConvCfg {
   static constexpr int WB = ((3 * XN / 2 + 31) / 64) * 64 + 32;              // the copy shifted by one entry: other banks than the first
   static constexpr int WLEN = WB + 3 * XN / 2;
   static constexpr int WD = WLEN > ED ? WLEN : ED;
-  static constexpr int TOTAL = W + CM_NW * WD;             // dwords
+  static constexpr int ODD = W + CM_NW * WD;                // [waves]: rows that are not finite
+  static constexpr int TOTAL = ODD + CM_NW;                // dwords
 };
 
 __device__ __forceinline__ int cm_row(int c, int dwords) { return c * dwords + (c >> 3) * CM_SKEW; }
@@ -90,9 +95,11 @@ struct RowPairs {
         x[i][u] = y;
       }
   }
+  // returns whether one of the thread's elements is an infinity or a NaN
   template <typename Row>
-  __device__ __forceinline__ void store(uint32_t* lds, int dwords, int tok0, int tid, Row row) {
+  __device__ __forceinline__ bool store(uint32_t* lds, int dwords, int tok0, int tid, Row row) {
     const int g = tid % NG;
+    u16x2 top = {0, 0};
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
       const int p = tid / NG + PPI * i;
@@ -105,9 +112,12 @@ struct RowPairs {
           const uint32_t a = ok0 ? x[i][0][e] : 0u, b = ok1 ? x[i][1][e] : 0u;
           lds[cm_row(8 * g + 2 * e, dwords) + p] = low_halves(a, b);
           lds[cm_row(8 * g + 2 * e + 1, dwords) + p] = high_halves(a, b);
+          top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, a & 0x7fff7fffu));
+          top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, b & 0x7fff7fffu));
         }
       }
     }
+    return top[0] >= 0x7f80 || top[1] >= 0x7f80;
   }
 };
 }  // namespace
@@ -163,7 +173,8 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvLongArgs a) {
   float tap = wsrc[0];
   for (int i = lane; i < G::WD; i += 64) reinterpret_cast<u32_any*>(wl)[i] = 0u;
 
-  xr.store(Xl, G::XD, x0, tid, x_row);
+  const int odd_rows = __any(xr.store(Xl, G::XD, x0, tid, x_row));
+  if (lane == 0) smu[G::ODD + w] = odd_rows;
   if constexpr (BWD) vr.store(Vl, G::VD, t0 - G::VOFF, tid, v_row);
   // the history handed on, by the workgroups that own its rows (the launcher sees to it that nobody still reads it)
   if (!BWD && a.hist_fused) {
@@ -181,102 +192,121 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvLongArgs a) {
   }
   __syncthreads();
 
+  // A row of the Toeplitz operand also holds the zeros of the tokens that an output does not see, and 0 times an infinity or a
+  // NaN is a NaN: a workgroup that has met such an element sums its outputs tap by tap on the vector ALUs (rare).
+  static_assert(CM_NW == 4, "flags");
+  const bool by_tap = (smu[G::ODD] | smu[G::ODD + 1] | smu[G::ODD + 2] | smu[G::ODD + 3]) != 0;
+
   // Toeplitz operand: lane (i = col, q) takes entries x = 8q + 32ks - i + 15 + 0..7 of the tap line; odd starts read the
   // copy that is shifted by one entry, so that every read is whole dwords
   const int xs = 8 * q - col + 15;
   const u32_any* wop = reinterpret_cast<const u32_any*>(wl) + (xs & 1 ? G::WB : 0) + (xs >> 1);
   const int at = BWD ? lane + 15 : G::OFF + 15 - lane;     // where this lane's tap sits in the line
+  auto channels = [&](auto taps_alone) __attribute__((always_inline)) {
 #pragma unroll 1
-  for (int cc = 0; cc < CM_CPW; ++cc) {
-    const int c = w * CM_CPW + cc;
-    uint32_t* xrow = Xl + cm_row(c, G::XD);
-    if constexpr (BWD) {
-      if (a.dw_part) {                                     // uniform
-        // D_b[i][r] = sum over the blocks a of dO[16a + i] v[16(a + b) - VOFF + r]: lag 16(NB-1-b) + i - r
-        const uint16_t* grow = reinterpret_cast<const uint16_t*>(xrow) + 4 * lane;
-        const uint16_t* vrow = reinterpret_cast<const uint16_t*>(Vl + cm_row(c, G::VD)) + 4 * lane;
-        f32x4 dacc[G::NB];
+    for (int cc = 0; cc < CM_CPW; ++cc) {
+      const int c = w * CM_CPW + cc;
+      uint32_t* xrow = Xl + cm_row(c, G::XD);
+      if constexpr (BWD) {
+        if (a.dw_part) {                                     // uniform
+          // D_b[i][r] = sum over the blocks a of dO[16a + i] v[16(a + b) - VOFF + r]: lag 16(NB-1-b) + i - r
+          const uint16_t* grow = reinterpret_cast<const uint16_t*>(xrow) + 4 * lane;
+          const uint16_t* vrow = reinterpret_cast<const uint16_t*>(Vl + cm_row(c, G::VD)) + 4 * lane;
+          f32x4 dacc[G::NB];
 #pragma unroll
-        for (int bb = 0; bb < G::NB; ++bb) dacc[bb] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int bb = 0; bb < G::NB; ++bb) dacc[bb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int sub = 0; sub < T / CM_SUB; ++sub) {
-          const s16x4 ga = __builtin_bit_cast(s16x4, lds_tr4(grow + CM_SUB * sub));
+          for (int sub = 0; sub < T / CM_SUB; ++sub) {
+            const s16x4 ga = __builtin_bit_cast(s16x4, lds_tr4(grow + CM_SUB * sub));
 #pragma unroll
-          for (int bb = 0; bb < G::NB; ++bb)
-            dacc[bb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ga, __builtin_bit_cast(s16x4, lds_tr4(vrow + CM_SUB * sub + 16 * bb)), dacc[bb], 0, 0, 0);
+            for (int bb = 0; bb < G::NB; ++bb)
+              dacc[bb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ga, __builtin_bit_cast(s16x4, lds_tr4(vrow + CM_SUB * sub + 16 * bb)), dacc[bb], 0, 0, 0);
+          }
+          // register e of row q: i = 4q + e.  Shifted by e lanes, every register has lag 16(NB-1-b) + 4q - s in lane s; what
+          // leaves the row belongs to the block of the next larger lag (beyond the last tap for block 0)
+#pragma unroll
+          for (int bb = 0; bb < G::NB; ++bb) {
+            float y = dacc[bb][0] + row_shl<1>(dacc[bb][1]) + row_shl<2>(dacc[bb][2]) + row_shl<3>(dacc[bb][3]);
+            if (bb + 1 < G::NB) y += row_shr<15>(dacc[bb + 1 < G::NB ? bb + 1 : bb][1]) + row_shr<14>(dacc[bb + 1 < G::NB ? bb + 1 : bb][2]) +
+                                     row_shr<13>(dacc[bb + 1 < G::NB ? bb + 1 : bb][3]);
+            el[80 * q + 16 * (G::NB - 1 - bb) - col + 15] = y;
+          }
+          if (lane < Kc) {
+            float y = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) y += el[80 * r + lane - 4 * r + 15];
+            a.dw_part[((((size_t)h * a.B + b) * nblk + tblk) * D + ch0 + c) * Kc + lane] = y;
+          }
+          // the tap line takes its place back (its entries around the taps are zeros)
+          asm volatile("" ::: "memory");
+          for (int i = lane; i < G::WLEN; i += 64) reinterpret_cast<u32_any*>(wl)[i] = 0u;
+          asm volatile("" ::: "memory");
         }
-        // register e of row q: i = 4q + e.  Shifted by e lanes, every register has lag 16(NB-1-b) + 4q - s in lane s; what
-        // leaves the row belongs to the block of the next larger lag (beyond the last tap for block 0)
+      }
+      if (lane < Kc) {
+        // (cut, not rounded: a tap at the end of the range stays finite; an infinity has no rest)
+        const uint16_t w1 = (uint16_t)(__float_as_uint(tap) >> 16);
+        const float r1 = __builtin_isinf(tap) ? 0.f : tap - bf16_bits_to_f32(w1);
+        const uint16_t w2 = (uint16_t)(__float_as_uint(r1) >> 16);
+        const uint16_t w3 = (uint16_t)(__float_as_uint(r1 - bf16_bits_to_f32(w2)) >> 16);
+        const uint16_t t3[3] = {w1, w2, w3};
 #pragma unroll
-        for (int bb = 0; bb < G::NB; ++bb) {
-          float y = dacc[bb][0] + row_shl<1>(dacc[bb][1]) + row_shl<2>(dacc[bb][2]) + row_shl<3>(dacc[bb][3]);
-          if (bb + 1 < G::NB) y += row_shr<15>(dacc[bb + 1 < G::NB ? bb + 1 : bb][1]) + row_shr<14>(dacc[bb + 1 < G::NB ? bb + 1 : bb][2]) +
-                                   row_shr<13>(dacc[bb + 1 < G::NB ? bb + 1 : bb][3]);
-          el[80 * q + 16 * (G::NB - 1 - bb) - col + 15] = y;
+        for (int t = 0; t < 3; ++t) {
+          wl[G::XN * t + at] = t3[t];
+          wl[2 * G::WB + G::XN * t + at - 1] = t3[t];        // at >= 15
         }
-        if (lane < Kc) {
-          float y = 0.f;
+      }
+      tap = wsrc[(cc + 1 < CM_CPW ? cc + 1 : cc) * Kc];
+      bf16x8 wf[3][KS];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) y += el[80 * r + lane - 4 * r + 15];
-          a.dw_part[((((size_t)h * a.B + b) * nblk + tblk) * D + ch0 + c) * Kc + lane] = y;
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const u32_any* p = wop + G::XN / 2 * t + 16 * ks;
+          wf[t][ks] = __builtin_bit_cast(bf16x8, u32x4{p[0], p[1], p[2], p[3]});
         }
-        // the tap line takes its place back (its entries around the taps are zeros)
-        asm volatile("" ::: "memory");
-        for (int i = lane; i < G::WLEN; i += 64) reinterpret_cast<u32_any*>(wl)[i] = 0u;
-        asm volatile("" ::: "memory");
+#pragma unroll
+      for (int sub = 0; sub < T / CM_SUB; ++sub) {
+        uint32_t* xs_row = xrow + CM_SUB / 2 * sub;
+        f32x4 u1 = {0.f, 0.f, 0.f, 0.f}, u2 = u1, u3 = u1;
+        if constexpr (decltype(taps_alone)::value) {
+          const u16_any* xe = reinterpret_cast<const u16_any*>(xs_row) + 16 * col + 4 * q + (BWD ? 0 : G::OFF);
+          const float* wc = a.conv_w + ((size_t)h * DVT + ch0 + c) * Kc;
+#pragma unroll 1
+          for (int j = 0; j < Kc; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) u1[i] = fmaf(wc[j], bf16_bits_to_f32(xe[BWD ? i + j : i - j]), u1[i]);
+        } else {
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) {
+            const bf16x8 xb = *reinterpret_cast<const bf16x8*>(xs_row + 8 * col + 4 * q + 16 * ks);
+            u1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[0][ks], xb, u1, 0, 0, 0);
+            u2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[1][ks], xb, u2, 0, 0, 0);
+            u3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[2][ks], xb, u3, 0, 0, 0);
+          }
+          u1 += u2 + u3;
+        }
+        // tokens 16col + 4q + 0..3 of the tile: over the row they came from (nobody else reads it, and this wave is done
+        // with this part of it)
+        u32x2 hv;
+        if constexpr (MODE == CM_ADD) {                      // the fp32 sum in two halves: it is rounded when out is added
+          u32x2 lv;
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const uint32_t x = __float_as_uint(u1[2 * i]), y = __float_as_uint(u1[2 * i + 1]);
+            hv[i] = high_halves(x, y);
+            lv[i] = low_halves(x, y);
+          }
+          *reinterpret_cast<u32x2*>(Vl + cm_row(c, G::VD) + CM_SUB / 2 * sub + 8 * col + 2 * q) = lv;
+        } else {
+          hv = u32x2{pack_bf16x2(u1[0], u1[1]), pack_bf16x2(u1[2], u1[3])};
+        }
+        *reinterpret_cast<u32x2*>(xs_row + 8 * col + 2 * q) = hv;
       }
     }
-    if (lane < Kc) {
-      const uint16_t w1 = f32_to_bf16_bits(tap);
-      const float r1 = tap - bf16_bits_to_f32(w1);
-      const uint16_t w2 = f32_to_bf16_bits(r1);
-      const uint16_t w3 = f32_to_bf16_bits(r1 - bf16_bits_to_f32(w2));
-      const uint16_t t3[3] = {w1, w2, w3};
-#pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        wl[G::XN * t + at] = t3[t];
-        wl[2 * G::WB + G::XN * t + at - 1] = t3[t];        // at >= 15
-      }
-    }
-    tap = wsrc[(cc + 1 < CM_CPW ? cc + 1 : cc) * Kc];
-    bf16x8 wf[3][KS];
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const u32_any* p = wop + G::XN / 2 * t + 16 * ks;
-        wf[t][ks] = __builtin_bit_cast(bf16x8, u32x4{p[0], p[1], p[2], p[3]});
-      }
-#pragma unroll
-    for (int sub = 0; sub < T / CM_SUB; ++sub) {
-      uint32_t* xs_row = xrow + CM_SUB / 2 * sub;
-      f32x4 u1 = {0.f, 0.f, 0.f, 0.f}, u2 = u1, u3 = u1;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 xb = *reinterpret_cast<const bf16x8*>(xs_row + 8 * col + 4 * q + 16 * ks);
-        u1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[0][ks], xb, u1, 0, 0, 0);
-        u2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[1][ks], xb, u2, 0, 0, 0);
-        u3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[2][ks], xb, u3, 0, 0, 0);
-      }
-      u1 += u2 + u3;
-      // tokens 16col + 4q + 0..3 of the tile: over the row they came from (nobody else reads it, and this wave is done
-      // with this part of it)
-      u32x2 hv;
-      if constexpr (MODE == CM_ADD) {                      // the fp32 sum in two halves: it is rounded when out is added
-        u32x2 lv;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const uint32_t x = __float_as_uint(u1[2 * i]), y = __float_as_uint(u1[2 * i + 1]);
-          hv[i] = high_halves(x, y);
-          lv[i] = low_halves(x, y);
-        }
-        *reinterpret_cast<u32x2*>(Vl + cm_row(c, G::VD) + CM_SUB / 2 * sub + 8 * col + 2 * q) = lv;
-      } else {
-        hv = u32x2{pack_bf16x2(u1[0], u1[1]), pack_bf16x2(u1[2], u1[3])};
-      }
-      *reinterpret_cast<u32x2*>(xs_row + 8 * col + 2 * q) = hv;
-    }
-  }
+  };
+  if (by_tap) channels(std::true_type{});                  // uniform
+  else channels(std::false_type{});
 
   // ---- whole rows out ------------------------------------------------------------------------------------------------
   constexpr int NG = CM_CB / 8, PPI = 256 / NG, OIT = T / 2 / PPI;

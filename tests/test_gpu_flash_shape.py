@@ -8,7 +8,7 @@ import torch
 import oracle
 from parity import TOL, check, check_unfloored, dev, host
 from paper_2406_07368_amd import binding, workloads
-from test_gpu_prefill import IO, small_case
+from test_gpu_prefill import IO, same_pattern, small_case
 
 pytestmark = pytest.mark.gpu
 
@@ -197,3 +197,45 @@ def test_long_conv_and_its_gradients_at_the_edges_of_tiles(B, H, L, d, Kc, with_
     check(host(dv), want["dv"], TOL["bf16"], f"dv, L={L} Kc={Kc}")
     err = float(np.max(np.abs(host(dw) - want["dw"])) / np.sqrt(np.mean(want["dw"] ** 2)))
     assert err <= TOL["f32"], f"dw, L={L} Kc={Kc}: {err:.2e}"
+
+
+@pytest.mark.parametrize("alpha", [None, 0.7])                   # added to the rows, written ahead of them
+@pytest.mark.parametrize("B,H,L,d,Kc", [(2, 2, 300, 64, 63), (1, 2, 270, 128, 50), (1, 2, 200, 64, 9), (1, 64, 513, 128, 63)])
+def test_long_conv_of_rows_and_taps_that_are_not_finite(B, H, L, d, Kc, alpha):
+    """A history row or a tap that is an infinity or a NaN reaches the tokens that see it and no others; a tap at the end of
+    the range is a finite one."""
+    q, k, v, w, state = small_case(7900 + L + Kc, B, H, L, d, Kc, "bf16", True)
+    state[2][0, 0, 0, 5] = np.inf
+    state[2][B - 1, H - 1, Kc // 2, d - 1] = np.nan
+    v[:, H - 1, :, :2] *= 2.0 ** -20
+    state[2][:, H - 1, :, :2] *= 2.0 ** -20
+    w[H - 1, 0, Kc - 1] = np.inf
+    w[H - 1, 1, 2] = 3.4e38
+    want = oracle.prefill_recurrent(q, k, v, w, *state, eps=1e-3) if alpha is None else oracle.prefill_grouped(q, k, v, w, 256, alpha, *state, eps=1e-3)
+    got = run(q, k, v, w, state, "bf16", 256, 1e-3, alpha=alpha)
+    assert np.isnan(want[0]).any() and np.isinf(want[0]).any()
+    # (that tap's channel lies thirty orders of magnitude above the rest of its head: held to the bar by itself)
+    big = (slice(None), slice(H - 1, H), slice(None), slice(1, 2))
+    check(got[0][big], want[0][big], TOL["bf16"], "tap at the end of the range")
+    got[0][big] = want[0][big] = 0.0
+    same_pattern(got[:3], want[:3], TOL["bf16"], f"L={L} Kc={Kc}")
+
+
+def test_gradient_of_the_long_conv_with_a_gradient_row_that_is_not_finite():
+    """dv is the conv's share and a product along the tokens: an infinity in one channel of dout stays in that channel, and
+    in the group of its token and the window of taps before it."""
+    B, H, L, d, Kc = 1, 2, 700, 64, 63
+    q, k, v, w, _ = small_case(7950, B, H, L, d, Kc, "bf16", False, d ** -0.5)
+    dout = workloads.upstream_gradient(q.shape, "bf16", 7951)
+    want = oracle.prefill_grouped_backward(q, k, v, w, dout, 256, alpha=0.7, eps=1e-3)
+    dout[0, 1, 100, 9] = np.inf
+    bf = torch.bfloat16
+    _, _, dv, dw = binding.prefill_grouped_backward(dev(q, bf), dev(k, bf), dev(v, bf), dev(w), dev(dout, bf), 0.7, 1e-3, group=256)
+    torch.cuda.synchronize()
+    dv, dw = host(dv), host(dw)
+    assert not np.isfinite(dv[0, 1, 100 - Kc + 1:101, 9]).any() and not np.isfinite(dw[1, 9]).any()
+    dv[0, 1, :256, 9] = want["dv"][0, 1, :256, 9]
+    dw[1, 9] = want["dw"][1, 9]
+    check(dv, want["dv"], TOL["bf16"], "dv")
+    err = float(np.max(np.abs(dw - want["dw"])) / np.sqrt(np.mean(want["dw"] ** 2)))
+    assert err <= TOL["f32"], f"dw: {err:.2e}"
