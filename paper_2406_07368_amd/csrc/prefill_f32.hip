@@ -96,8 +96,8 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
-  const int seg = blockIdx.x;
-  const HeadIndex hx = head_index(a, blockIdx.y, D);       // one (b, h, value block)
+  const int seg = blockIdx.y;                              // (heads along x: there may be more of them than y can count)
+  const HeadIndex hx = head_index(a, blockIdx.x, D);       // one (b, h, value block)
   const int L = a.L, Kc = a.Kc;
   const int t_beg = seg * a.seg_len;
   const int t_end = (L - t_beg) < a.seg_len ? L : t_beg + a.seg_len;
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
-  const HeadIndex hx = head_index(a, blockIdx.y, D);
+  const HeadIndex hx = head_index(a, blockIdx.x, D);
   const int L = a.L, Kc = a.Kc, nq = (L + FT - 1) / FT;
   const float one = a.relu ? 0.f : 1.f;
   const float* gq = static_cast<const float*>(a.q) + (int64_t)hx.b * a.sb + (int64_t)hx.h * a.sh;
@@ -482,9 +482,9 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
             f32x4{acc[cb][4 * g], acc[cb][4 * g + 1], acc[cb][4 * g + 2], acc[cb][4 * g + 3]};
   };
 
-  if ((int)blockIdx.x >= nq) {
+  if ((int)blockIdx.y >= nq) {
     // ---- what is handed on: features 32ib .. of S (all the block's channels) and z, and the history --------------
-    const int ib = blockIdx.x - nq;
+    const int ib = blockIdx.y - nq;
     float zs = 0.f;
     for (int kt = w; kt < nq; kt += DW) {
       float kx[16], vx[IB][16];
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
   }
 
   // ---- one query tile (the longest first) ------------------------------------------------------------------------
-  const int qt = nq - 1 - blockIdx.x;
+  const int qt = nq - 1 - blockIdx.y;
   const int kt0 = GROUPED ? qt & ~1 : qt + 1;              // tiles from here on belong to the query's own group
   f32x4 qf[IB][4];                                         // query l32, features 32ib + 8j + 4hi + e
   {
@@ -761,7 +761,7 @@ static hipError_t launch_f32_one(const PrefillArgs& a, hipStream_t st) {
   auto kern = prefill_f32_kernel<D, KCM, STATE_ONLY, GROUPED>;
   hipError_t e = LINATTN_MAX_LDS_ONCE(kern, bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(STATE_ONLY ? a.nseg - 1 : a.nseg), (unsigned)(a.B * a.H * a.m)), dim3(G::NT), bytes, st, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(a.B * a.H * a.m), (unsigned)(STATE_ONLY ? a.nseg - 1 : a.nseg)), dim3(G::NT), bytes, st, a);
   return hipGetLastError();
 }
 
@@ -773,7 +773,7 @@ static hipError_t launch_f32_direct(const PrefillArgs& a, hipStream_t st) {
   hipError_t e = LINATTN_MAX_LDS_ONCE(kern, bytes);
   if (e != hipSuccess) return e;
   const bool hand_on = a.S_out || a.z_out || a.hist_out;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((a.L + FT - 1) / FT + (hand_on ? D / 32 : 0)), (unsigned)(a.B * a.H * a.m)), dim3(64 * DW), bytes, st, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(a.B * a.H * a.m), (unsigned)((a.L + FT - 1) / FT + (hand_on ? D / 32 : 0))), dim3(64 * DW), bytes, st, a);
   return hipGetLastError();
 }
 

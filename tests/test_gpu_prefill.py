@@ -387,3 +387,27 @@ def test_fp32_value_row_that_is_not_finite_stays_out_of_earlier_tokens(value, B,
     out, *got = call()
     assert torch.equal(out[0, 1, :45], clean[0, 1, :45])
     same_pattern(got, want, TOL["f32"], f"{value} in v")
+
+
+@pytest.mark.parametrize("grouped", [False, True])
+@pytest.mark.parametrize("B,H,d_v", [(1100, 60, 64), (550, 60, 128)])
+def test_fp32_more_heads_than_a_grid_axis_counts(grouped, B, H, d_v):
+    """B H (d_v / d) beyond 65535: the descriptor takes B H up to 2^24."""
+    if grouped and d_v != 64:
+        return                                                   # the three-branch form takes d_v = d only
+    L, d, Kc = 3, 64, 3
+    rng = np.random.default_rng(6500)
+    q, k, v = (rng.standard_normal((B, H, L, n)).astype(np.float32) for n in (d, d, d_v))
+    w = workloads.conv_weights(rng, H, d_v, Kc)
+    if grouped:
+        out, _ = binding.prefill_grouped(dev(q), dev(k), dev(v), dev(w), 0.7, None, 1e-2, want_state=False)
+    else:
+        out, _ = binding.prefill(dev(q), dev(k), dev(v), dev(w), None, 64, 1e-2, want_state=False)
+    torch.cuda.synchronize()
+    out = host(out)
+    for b in (slice(0, 2), slice(B - 2, B)):
+        if grouped:
+            want = oracle.prefill_grouped(q[b], k[b], v[b], w, 64, alpha=0.7, eps=1e-2)
+        else:
+            want = oracle.prefill_recurrent(q[b], k[b], v[b], w, eps=1e-2)
+        check(out[b], want[0], TOL["f32"], f"B={B} rows {b}")
