@@ -239,13 +239,19 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
       for (int kt = 0; kt < G::TILES; ++kt) {
         if (kt > p) break;                                 // uniform
         f32x16 sc;
+        constexpr int CH = GROUPED && D == 64 ? 2 : 1;     // logits: chains of D / 4 features (see the quadratic kernel)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+        for (int c = 0; c < CH; ++c) {
+          f32x16 part;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const f32x4 kf = *reinterpret_cast<const f32x4*>(Kl + (32 * kt + l32) * ST + 32 * w + 8 * j + 4 * hi);
+          for (int r = 0; r < 16; ++r) part[r] = 0.f;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) sc = mfma32(kf[e], qf[j][e], sc);
+          for (int j = 4 / CH * c; j < 4 / CH * (c + 1); ++j) {
+            const f32x4 kf = *reinterpret_cast<const f32x4*>(Kl + (32 * kt + l32) * ST + 32 * w + 8 * j + 4 * hi);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part = mfma32(kf[e], qf[j][e], part);
+          }
+          sc = c == 0 ? part : sc + part;
         }
 #pragma unroll
         for (int g = 0; g < 4; ++g)
@@ -556,8 +562,19 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
   }
   static_assert(D == 64 || D == 128, "1 / sqrt(d) below");
   constexpr float to_log2 = 1.44269504088896340736f * (D == 64 ? 0.125f : 0.08838834764831845f);
-  // scores of key tile kt: sc[r] = key acc_row(r), query l32; raw: the rows as they are, else under the feature map
-  auto scores = [&](int kt, bool raw, f32x16& sc, float (&vx)[IB][16]) __attribute__((always_inline)) {
+  // value rows of key tile kt
+  auto values = [&](int kt, float (&vx)[IB][16]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int tv = FT * kt + acc_row(r, hi);
+#pragma unroll
+      for (int cb = 0; cb < IB; ++cb) vx[cb][r] = gv[(int64_t)(tv < L ? tv : L - 1) * a.st_v + 32 * cb + l32];
+    }
+  };
+  // scores of key tile kt: sc[r] = key acc_row(r), query l32; raw: the rows as they are, else under the feature map.  Raw
+  // ones in four chains of D / 4 features: a logit may be a small difference of large products, and the rounding of one long
+  // chain showed (rows of unit normals, d = 128: 9.9e-8 of the result against 6.7e-8).
+  auto scores = [&](int kt, bool raw, f32x16& sc) __attribute__((always_inline)) {
     f32x4 kf[IB][4];
     const int tok = FT * kt + l32;
     const float* p = gk + (int64_t)(tok < L ? tok : L - 1) * a.st + 4 * hi;
@@ -565,20 +582,20 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
     for (int ib = 0; ib < IB; ++ib)
 #pragma unroll
       for (int j = 0; j < 4; ++j) kf[ib][j] = *reinterpret_cast<const f32x4*>(p + 32 * ib + 8 * j);
+    const int chains = raw ? 4 : 1;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int tv = FT * kt + acc_row(r, hi);
+    for (int c = 0; c < chains; ++c) {
+      f32x16 part;
 #pragma unroll
-      for (int cb = 0; cb < IB; ++cb) vx[cb][r] = gv[(int64_t)(tv < L ? tv : L - 1) * a.st_v + 32 * cb + l32];
-      sc[r] = 0.f;
+      for (int r = 0; r < 16; ++r) part[r] = 0.f;
+#pragma unroll
+      for (int j = 0; j < 4 * IB / chains; ++j) {
+        const int ib = (4 * IB / chains * c + j) / 4, jj = (4 * IB / chains * c + j) % 4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part = mfma32(raw ? kf[ib][jj][e] : phi_f32(kf[ib][jj][e], one), qf[ib][jj][e], part);
+      }
+      sc = c == 0 ? part : sc + part;
     }
-#pragma unroll
-    for (int ib = 0; ib < IB; ++ib)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          sc = mfma32(raw ? kf[ib][j][e] : phi_f32(kf[ib][j][e], one), qf[ib][j][e], sc);
   };
   auto weigh = [&](const f32x16& sc, const float (&vx)[IB][16]) __attribute__((always_inline)) {
 #pragma unroll
@@ -616,9 +633,18 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
     // causal softmax over the group's own tiles; unnormalised weights, their sum to LDS
     f32x16 s0, s1;
     float v0[IB][16], v1[IB][16];
-    scores(qt, true, s1, v1);
     const bool two = qt > kt0;                             // uniform
-    if (two) scores(kt0, true, s0, v0);
+    if (D == 64) {
+      values(qt, v1);
+      values(kt0, v0);
+    }
+    scores(qt, true, s1);
+    scores(kt0, true, s0);
+    if (D == 128) {                                        // (all requests at once would not fit)
+      __builtin_amdgcn_sched_barrier(0);
+      values(qt, v1);
+      values(kt0, v0);
+    }
     float top = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -643,7 +669,8 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
     for (int kt = first; kt < kt0; kt += step) {
       f32x16 sc;
       float vx[IB][16];
-      scores(kt, false, sc, vx);
+      values(kt, vx);
+      scores(kt, false, sc);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         if (!GROUPED) sc[r] = (kt < qt || acc_row(r, hi) <= l32) ? sc[r] : 0.f;
