@@ -36,10 +36,11 @@ struct VgScore {
   float red[KP][D];           // phi(q_j)^T S
   float loc[KP][D];           // sum_r W[j][r] v_r
 };
-template <typename Elem, int D>
-struct VgStage {              // completion of a group: its raw rows
-  Elem k[GC][D + 16 / sizeof(Elem)];
-  Elem v[GC][D + 16 / sizeof(Elem)];
+template <typename Elem, int D, int KP>
+struct VgStage {              // completion of a group: its raw rows, as many at a time as the step's own arrays leave room for
+  static constexpr int ROWS = sizeof(Elem) == 2 || KP > 8 ? GC : 16;
+  Elem k[ROWS][D + 16 / sizeof(Elem)];
+  Elem v[ROWS][D + 16 / sizeof(Elem)];
 };
 template <int D, int KP>
 struct VgStep {
@@ -55,7 +56,7 @@ struct VgStep {
 template <typename Elem, int D, int KP>
 union VgSmem {                // the completion runs when the outputs are stored
   VgStep<D, KP> step;
-  VgStage<Elem, D> st;
+  VgStage<Elem, D, KP> st;
 };
 
 // x[l] + x[l ^ off] for the strides that occur here
@@ -451,23 +452,33 @@ __global__ __launch_bounds__(256, (sizeof(typename Io::elem) != 2 ? 2 : KP <= 8 
   const bool z_mine = TPW > 1 || cb == 0;                           // D = 64: two waves see the same features
   const int z_f = 32 * (TPW > 1 ? wv : ib0) + l32;
   const float z_old = sm.zz[z_f];
-  __syncthreads();                                                  // outputs and history are done with LDS
-#pragma unroll
-  for (int t = 0; t < CRT; ++t) {
-    *reinterpret_cast<typename Io::raw8*>(&smem.st.k[part + NPART * t][8 * c8]) = ck[t];
-    *reinterpret_cast<typename Io::raw8*>(&smem.st.v[part + NPART * t][8 * c8]) = cv[t];
-  }
-  __syncthreads();
+  // fp32 rows pass through LDS sixteen at a time: all 64 would be LDS that every launch holds (67 KB at D = 128, two
+  // workgroups per compute unit instead of three: 2048 heads of 128 took 42 us a step, with eight drafts 88; so 38 and 72).
+  // With more than eight drafts the registers allow two workgroups at most.
+  constexpr int SR = VgStage<typename Io::elem, D, KP>::ROWS;
   float zsum = 0.f;
-#pragma unroll 4
-  for (int j = 0; j < GC / 2; ++j) {                                // two rows per instruction, four apart (banks)
-    const int r = 8 * (j >> 2) + 4 * hi + (j & 3);
-    const float x = Io::load1(&smem.st.v[r][0], 32 * cb + l32);
 #pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const float y = phi_any(Io::load1(&smem.st.k[r][0], 32 * (ib0 + i) + l32), a.relu);
-      S[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(y, x, S[i], 0, 0, 0);
-      if (ib0 + i == z_f / 32) zsum += y;                           // uniform
+  for (int c = 0; c < GC / SR; ++c) {
+    __syncthreads();                                                // outputs, history or the rows before are done with LDS
+#pragma unroll
+    for (int t = 0; t < CRT; ++t) {
+      const int r = part + NPART * t - SR * c;
+      if (SR == GC || (r >= 0 && r < SR)) {
+        *reinterpret_cast<typename Io::raw8*>(&smem.st.k[r][8 * c8]) = ck[t];
+        *reinterpret_cast<typename Io::raw8*>(&smem.st.v[r][8 * c8]) = cv[t];
+      }
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int j = 0; j < SR / 2; ++j) {                              // two rows per instruction, four apart (banks)
+      const int r = 8 * (j >> 2) + 4 * hi + (j & 3);
+      const float x = Io::load1(&smem.st.v[r][0], 32 * cb + l32);
+#pragma unroll
+      for (int i = 0; i < TPW; ++i) {
+        const float y = phi_any(Io::load1(&smem.st.k[r][0], 32 * (ib0 + i) + l32), a.relu);
+        S[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(y, x, S[i], 0, 0, 0);
+        if (ib0 + i == z_f / 32) zsum += y;                         // uniform
+      }
     }
   }
 #pragma unroll
