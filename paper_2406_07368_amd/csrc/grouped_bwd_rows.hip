@@ -487,9 +487,11 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
 }
 
 // ---- dk, dv ---------------------------------------------------------------------------------------------------------
-template <int D, int GT>
+// SPLIT: dk and dv in workgroups of their own (see split_pays); otherwise both from one pass over the scores.
+template <int D, int GT, bool SPLIT>
 __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kernel(GroupedBwdArgs a) {
   using G = RowsCfg<D, GT>;
+  const bool with_dv = !SPLIT || blockIdx.z != 0, with_dk = !SPLIT || blockIdx.z == 0;   // uniform
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint16_t* Ql = reinterpret_cast<uint16_t*>(smem);
   uint16_t* Dl = reinterpret_cast<uint16_t*>(smem + G::OFF_B);
@@ -556,11 +558,12 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
     }
   }
   // dka, dva [n][ct][r] = dK, dV [key 16 tile[n] + lane % 16][column 16ct + 4 (lane / 16) + r]
-  f32x4 dka[2][G::CT], dva[2][G::CT];
+  f32x4 dkb[2][G::CT], dva[2][G::CT];
 #pragma unroll
   for (int n = 0; n < 2; ++n)
 #pragma unroll
-    for (int ct = 0; ct < G::CT; ++ct) dka[n][ct] = dva[n][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int ct = 0; ct < G::CT; ++ct) dkb[n][ct] = dva[n][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 (&dka)[2][G::CT] = SPLIT ? dva : dkb;              // (a workgroup with one of them has one set of accumulators)
 
   // 32 queries against tiles 0 .. N1 - 1
   auto unit = [&](auto n1, int qt, bool diag) __attribute__((always_inline)) {
@@ -607,17 +610,19 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
         }
       }
     }
-    gather(Dl, sc, dva);                                   // dV^T += dO^T P
-    product(Dl, vop, dp);
+    if (with_dv) gather(Dl, sc, dva);                      // dV^T += dO^T P
+    if (with_dk) {
+      product(Dl, vop, dp);
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const f32x4 pb = *reinterpret_cast<const f32x4*>(pl + 32 * qt + 16 * s + 4 * g4);
+      for (int s = 0; s < 2; ++s) {
+        const f32x4 pb = *reinterpret_cast<const f32x4*>(pl + 32 * qt + 16 * s + 4 * g4);
 #pragma unroll
-      for (int n = 0; n < N1; ++n)
+        for (int n = 0; n < N1; ++n)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) dp[n][s][r] = sc[n][s][r] * (dp[n][s][r] - pb[r]);
+          for (int r = 0; r < 4; ++r) dp[n][s][r] = sc[n][s][r] * (dp[n][s][r] - pb[r]);
+      }
+      gather(Ql, dp, dka);                                 // dK^T += Q^T ds (the 1 / sqrt(d) once, behind the loop)
     }
-    gather(Ql, dp, dka);                                   // dK^T += Q^T ds (the 1 / sqrt(d) once, behind the loop)
   };
   using One = std::integral_constant<int, 1>;
   using Both = std::integral_constant<int, 2>;
@@ -635,7 +640,7 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
   __syncthreads();
   walk(nk, true);
   if (G::NH > 1 && half == 0 && nt > G::RC) {              // uniform: the later queries
-    constexpr int PARTS = 2;                               // what fits beside the accumulators
+    constexpr int PARTS = SPLIT ? 1 : 2;                   // what fits beside the accumulators
     RowLoad<D, GT, PARTS> more;
     const int nr = nt - G::RC;
     const uint16_t *gq1 = gq + (int64_t)G::RC * a.st, *gdo1 = gdo + (int64_t)G::RC * a.st;
@@ -652,10 +657,11 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
     __syncthreads();
     walk(nr, false);
   }
+  if (with_dk)
 #pragma unroll
-  for (int n = 0; n < 2; ++n)
+    for (int n = 0; n < 2; ++n)
 #pragma unroll
-    for (int ct = 0; ct < G::CT; ++ct) dka[n][ct] *= kInvSqrt<D>;
+      for (int ct = 0; ct < G::CT; ++ct) dka[n][ct] *= kInvSqrt<D>;
 
   // ---- the group's keys and values entered the sums every later group read ---------------------------------------
   if (g + 1 < a.ng) {                                      // uniform; after the last group nothing reads the sums
@@ -676,65 +682,84 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
 #pragma unroll
       for (int ft = 0; ft < G::CT; ++ft) kx[n][ft] = *reinterpret_cast<const u32x2*>(gk + koff[n] + 16 * ft + 4 * g4);
     __syncthreads();
+    if (with_dv) {
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+      for (int n = 0; n < 2; ++n)
 #pragma unroll
-      for (int ks = 0; ks < G::KSD; ++ks) kop[n][ks] = phi_pack8_nb(kop[n][ks], one);
+        for (int ks = 0; ks < G::KSD; ++ks) kop[n][ks] = phi_pack8_nb(kop[n][ks], one);
 #pragma unroll
-    for (int ct = 0; ct < G::CT; ++ct) {                   // dV^T += D.S^T phi(K)^T
+      for (int ct = 0; ct < G::CT; ++ct) {                   // dV^T += D.S^T phi(K)^T
 #pragma unroll
-      for (int ks = 0; ks < G::KSD; ++ks) {
-        const bf16x8 sh = tr16(Sl, G::KS, 32 * ks, 16 * ct, lane);
-        const bf16x8 sl = tr16(Sl + D * G::KS, G::KS, 32 * ks, 16 * ct, lane);
+        for (int ks = 0; ks < G::KSD; ++ks) {
+          const bf16x8 sh = tr16(Sl, G::KS, 32 * ks, 16 * ct, lane);
+          const bf16x8 sl = tr16(Sl + D * G::KS, G::KS, 32 * ks, 16 * ct, lane);
 #pragma unroll
-        for (int n = 0; n < 2; ++n) dva[n][ct] = mfma16(sh, __builtin_bit_cast(bf16x8, kop[n][ks]), dva[n][ct]);
+          for (int n = 0; n < 2; ++n) dva[n][ct] = mfma16(sh, __builtin_bit_cast(bf16x8, kop[n][ks]), dva[n][ct]);
 #pragma unroll
-        for (int n = 0; n < 2; ++n) dva[n][ct] = mfma16(sl, __builtin_bit_cast(bf16x8, kop[n][ks]), dva[n][ct]);
+          for (int n = 0; n < 2; ++n) dva[n][ct] = mfma16(sl, __builtin_bit_cast(bf16x8, kop[n][ks]), dva[n][ct]);
+        }
+        if (ct % 2) __builtin_amdgcn_sched_barrier(0);       // (reads of later tiles moved up here would cost spills)
       }
-      if (ct % 2) __builtin_amdgcn_sched_barrier(0);       // (reads of later tiles moved up here would cost spills)
     }
+    if (with_dk) {
 #pragma unroll
-    for (int ft = 0; ft < G::CT; ++ft) {                   // dK += (D.S V^T + D.z) * phi'(K)
-      f32x4 lin[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+      for (int ft = 0; ft < G::CT; ++ft) {                   // dK += (D.S V^T + D.z) * phi'(K)
+        f32x4 lin[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-      for (int ks = 0; ks < G::KSD; ++ks) {
-        const bf16x8 sh = rows16(Sl, G::KS, 16 * ft, 32 * ks, lane);
-        const bf16x8 sl = rows16(Sl + D * G::KS, G::KS, 16 * ft, 32 * ks, lane);
+        for (int ks = 0; ks < G::KSD; ++ks) {
+          const bf16x8 sh = rows16(Sl, G::KS, 16 * ft, 32 * ks, lane);
+          const bf16x8 sl = rows16(Sl + D * G::KS, G::KS, 16 * ft, 32 * ks, lane);
+#pragma unroll
+          for (int n = 0; n < 2; ++n) {
+            lin[n] = mfma16(sh, __builtin_bit_cast(bf16x8, vop[n][ks]), lin[n]);
+            lin[n] = mfma16(sl, __builtin_bit_cast(bf16x8, vop[n][ks]), lin[n]);
+          }
+        }
+        const f32x4 zf = *reinterpret_cast<const f32x4*>(zl + 16 * ft + 4 * g4);
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
-          lin[n] = mfma16(sh, __builtin_bit_cast(bf16x8, vop[n][ks]), lin[n]);
-          lin[n] = mfma16(sl, __builtin_bit_cast(bf16x8, vop[n][ks]), lin[n]);
+          const f32x4 kv = unpack4(kx[n][ft]);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) dka[n][ft][r] = fmaf(lin[n][r] + zf[r], dphi_nb(kv[r], one), dka[n][ft][r]);
         }
+        if (ft % 2) __builtin_amdgcn_sched_barrier(0);
       }
-      const f32x4 zf = *reinterpret_cast<const f32x4*>(zl + 16 * ft + 4 * g4);
-#pragma unroll
-      for (int n = 0; n < 2; ++n) {
-        const f32x4 kv = unpack4(kx[n][ft]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dka[n][ft][r] = fmaf(lin[n][r] + zf[r], dphi_nb(kv[r], one), dka[n][ft][r]);
-      }
-      if (ft % 2) __builtin_amdgcn_sched_barrier(0);
     }
   }
   // dk is written; dv is added to what the conv's share left there (written ahead of this kernel)
   HeldRows<D, GT> held;
-  hold_rows<D, GT>(held, gdv, a.st, nk, tid);
-  store_rows<D, GT, false>(dka, held, Ol, gdk, a.st, nk, tid, tile, lane);
-  store_rows<D, GT, true>(dva, held, Ol, gdv, a.st, nk, tid, tile, lane);
+  if (with_dv) hold_rows<D, GT>(held, gdv, a.st, nk, tid);
+  if (with_dk) store_rows<D, GT, false>(dka, held, Ol, gdk, a.st, nk, tid, tile, lane);
+  if (with_dv) store_rows<D, GT, true>(dva, held, Ol, gdv, a.st, nk, tid, tile, lane);
 }
 
 namespace {
+// dk and dv in workgroups of their own: twice the workgroups, each with half of the products and none of the other half's
+// accumulators, but the scores computed twice.  Pays while all of them fit the chip at once (two to a CU) and the extra ones
+// take CUs that would stand idle.  Measured, us a gradient call, together / apart: D = 128, groups of 64: 64 workgroups 92 / 83,
+// 128 95 / 86, 256 106 / 99, 320 101 / 98, 512 138 / 140; groups of 256: 64 112 / 98, 256 133 / 124, 512 173 / 181.  D = 64, where
+// a workgroup is short: 16 67 / 65, 64 84 / 81, 128 89 / 89, 256 71 / 73, 512 105 / 109.
+template <int D>
+bool split_pays(int64_t wgs) { return wgs <= (D == 128 ? 256 : 128); }
+
 template <int D, int GT>
 hipError_t launch_rows(const GroupedBwdArgs& a, bool keys, hipStream_t st) {
   using G = RowsCfg<D, GT>;
   auto kq = grouped_bwd_dq_kernel<D, GT>;
-  auto kk = grouped_bwd_dkdv_kernel<D, GT>;
+  auto kk = grouped_bwd_dkdv_kernel<D, GT, false>;
   hipError_t e;
   if ((e = LINATTN_MAX_LDS_ONCE(kq, G::TOTAL)) != hipSuccess) return e;
   if ((e = LINATTN_MAX_LDS_ONCE(kk, G::TOTAL)) != hipSuccess) return e;
   const dim3 grid((unsigned)(G::NH * a.ng), (unsigned)(a.B * a.H));
-  if (keys) hipLaunchKernelGGL(kk, grid, dim3(G::NT), G::TOTAL, st, a);
-  else hipLaunchKernelGGL(kq, grid, dim3(G::NT), G::TOTAL, st, a);
+  if (!keys) {
+    hipLaunchKernelGGL(kq, grid, dim3(G::NT), G::TOTAL, st, a);
+  } else if (split_pays<D>((int64_t)G::NH * a.ng * a.B * a.H)) {
+    auto k2 = grouped_bwd_dkdv_kernel<D, GT, true>;
+    if ((e = LINATTN_MAX_LDS_ONCE(k2, G::TOTAL)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k2, dim3(grid.x, grid.y, 2), dim3(G::NT), G::TOTAL, st, a);
+  } else {
+    hipLaunchKernelGGL(kk, grid, dim3(G::NT), G::TOTAL, st, a);
+  }
   return hipGetLastError();
 }
 }  // namespace

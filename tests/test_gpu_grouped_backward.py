@@ -176,3 +176,14 @@ def test_gradient_at_the_edges_of_runs_and_tiles(d, group, L):
     q, k, v, w, dout = case(9700 + L + d + group, 1, 2, L, d, 3)
     want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, alpha=1.1, eps=0.0)
     compare(run(q, k, v, w, dout, group, 1.1, 0.0), want, f"d={d} group={group} L={L}")
+
+
+@pytest.mark.parametrize("B,H,L,d,group", [(2, 16, 510, 128, 64), (3, 11, 511, 128, 64),     # 256 and 264 runs of keys
+                                           (2, 32, 300, 128, 256), (1, 65, 300, 128, 256),   # 256 and 260
+                                           (2, 8, 508, 64, 64), (1, 17, 505, 64, 64),        # 128 and 136
+                                           (1, 32, 290, 64, 256), (3, 11, 300, 64, 256)])    # 128 and 132
+def test_gradient_with_dk_and_dv_together_or_apart(B, H, L, d, group):
+    """Workgroups of their own for dk and for dv while all of them fit the chip, one for both beyond."""
+    q, k, v, w, dout = case(9800 + H + d, B, H, L, d, 3, d ** -0.5)
+    want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, alpha=0.9, eps=0.0)
+    compare(run(q, k, v, w, dout, group, 0.9, 0.0), want, f"B={B} H={H} d={d} group={group} L={L}")
