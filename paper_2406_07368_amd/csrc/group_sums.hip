@@ -227,11 +227,13 @@ static hipError_t launch_sums_dir(const GroupSumsArgs& a, bool back, hipStream_t
 
 // Against one workgroup per group and a prefix sum over the slots, which has no chain over the groups but moves every slot
 // three times: the walk pays with workgroups for half the chip (groups of 64: three quarters), or few groups.  Measured, us
-// per gradient call, per-group kernels / walk: groups of 256, D = 128: 4 groups 103 / 95, 6 groups 105 / 107, 32 groups of 8
-// heads 179 / 295, of 32 heads 645 / 615; D = 64, 16 groups of 48 heads (48 workgroups) 248 / 279; groups of 64, D = 128, 64
+// per gradient call, per-group kernels / walk.  Few heads, by the number of groups: groups of 64, 8 heads: D = 64: 4 62 / 60, 5
+// 73 / 68, 6 61 / 66; D = 128: 4 81 / 72, 5 81 / 74, 6 82 / 78, 8 84 / 83, 12 85 / 96; groups of 256: D = 64: 3 79 / 75, 4 80 / 81, 5 81 / 87;
+// D = 128: 4 110 / 99, 5 111 / 106, 6 111 / 111, 8 112 / 123.  Many groups, by the number of heads: groups of 256, D = 128, 32
+// groups: 8 heads 179 / 295, 32 heads 645 / 615; D = 64, 16 groups of 48 heads (48 workgroups) 248 / 279; groups of 64, D = 128, 64
 // groups: 32 heads 426 / 456, 64 heads 851 / 712.
 bool group_sums_pays(int heads, int ng, int d, int group) {
-  return ng <= 5 || heads * (d == 128 ? 4 : 1) >= (group == 256 ? 128 : 192);
+  return ng <= (d == 64 && group == 256 ? 4 : 5) || heads * (d == 128 ? 4 : 1) >= (group == 256 ? 128 : 192);
 }
 
 hipError_t launch_group_sums(const GroupSumsArgs& a, int d, int group, bool back, hipStream_t st) {
