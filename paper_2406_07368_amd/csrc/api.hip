@@ -212,7 +212,7 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
 
   bool fold = false;
   if (plan.mfma && !cont && !(grouped && desc->chunk == 256)) {
-    const int n = prefill_mfma_fold_segments(plan.nseg, L);
+    const int n = prefill_mfma_fold_segments(plan.nseg, L, desc->B * desc->H * m, desc->d);
     fold = n > 0;
     if (fold) plan.cut(L, desc->chunk, n);               // never more segments than the workspace was sized for
   }

@@ -236,7 +236,7 @@ hipError_t launch_grouped_bwd_dw(const GroupedBwdArgs& a, int d, hipStream_t st)
 // prefill_mfma.hip : launch plan of the bf16 prefill (segments, prefix sum over segment states)
 hipError_t launch_segment_scan(const PrefillArgs& a, int d, hipStream_t st);   // the prefix sum alone
 int prefill_mfma_pick_segments(int BH, int L, int chunk, int d);
-int prefill_mfma_fold_segments(int nseg, int L);   // 0: the prefix sum is a launch of its own
+int prefill_mfma_fold_segments(int nseg, int L, int heads, int d);   // 0: the prefix sum is a launch of its own
 size_t prefill_mfma_workspace_bytes(int BH, int d, int nseg);
 hipError_t launch_prefill_mfma(const PrefillArgs& a, int d, int chunk, bool grouped, hipStream_t st);
 

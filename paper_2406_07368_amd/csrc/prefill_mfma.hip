@@ -96,12 +96,16 @@ int prefill_mfma_pick_segments(int BH, int L, int chunk, int d) {
 // What it costs is the last segment's reads, one slot (64 KB at d = 128) per segment through one compute unit, against
 // a launch of 4 us and more.  Up to 6 segments it pays (us a call, prefix sum / this: 2 segments 100 / 93, 4 segments of
 // 64 heads 69 / 65, 6 segments of 84 heads of 64 40.5 / 37, of 40 heads 78 / 75); at 8 it does not (d = 128, 32 heads:
-// L = 1024 42 / 46, L = 8192 105 / 109).  Sequences of up to 16 groups are therefore cut into 6 at most (L = 1024: d = 128,
-// 32 heads 42 / 37; d = 64, 48 heads 31 / 28); longer ones would lose more by the compute units left idle.
-int prefill_mfma_fold_segments(int nseg, int L) {
+// L = 1024 42 / 46, L = 8192 105 / 109).  Sequences of up to 16 groups are therefore cut into 6 at most, three groups each
+// where the plan has two (L = 1024, us a call: d = 128, 32 heads 41 / 34, 16 heads 32 / 29.5, 12 heads 30 / 29; d = 64, 48 heads
+// 29.7 / 26.6, 8 heads 25.7 / 23.0, and 23.5 / 23.8 as a graph, where launches cost less) -- at d = 128, where a group takes
+// longer, not below 12 heads: 8 heads 27.1 / 27.2, as a graph 30.4 / 30.9, three-branch form 29.2 / 30.3; 4 heads 25.8 / 25.9, 27.7 /
+// 29.3, 26.7 / 29.1.  Beyond 16 groups six segments have four groups and more: some gain (d = 128, 32 heads, L = 1300
+// 42 / 40), others lose (three-branch form, 48 heads of 64, L = 1300 46 / 51; 12 heads of 128, L = 1200 31 / 32): the plan stays.
+int prefill_mfma_fold_segments(int nseg, int L, int heads, int d) {
   if (nseg <= 1) return 0;
   if (nseg <= 6) return nseg;
-  return L <= 16 * 64 ? 6 : 0;
+  return L <= 16 * 64 && (d == 64 || heads >= 12) ? 6 : 0;
 }
 
 size_t prefill_mfma_workspace_bytes(int BH, int d, int nseg) {

@@ -669,11 +669,35 @@ __global__ __launch_bounds__(D * 4) void prefill_mfma_ws_kernel(PrefillArgs a) {
 
   // Sacc[ib][r] = S[32ib + 8(r/4) + 4hi + r%4][cw];  Zacc[r] = z[32w + 8(r/4) + 4hi + r%4] (every lane)
   f32x16 Sacc[G::IB], Zacc;
-  {
+  if (!STATE_ONLY && a.fold) {
+    // The increments of the segments before this one, added up here while the front-end waves fetch and map the first
+    // rows (see prefill_mfma_fold_segments): in the prefix sum's order, so the same bits.
+#pragma unroll
+    for (int ib = 0; ib < G::IB; ++ib)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) Sacc[ib][r] = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) Zacc[r] = 0.f;
+    const float* src = ws_bh + SLOT + 4 * hi * D + cw;
+    const float* zp = ws_bh + SLOT + D * D + 32 * w + 4 * hi;
+#pragma unroll 1
+    for (int g = 0; g < seg; ++g, src += SLOT, zp += SLOT) {
+      f32x16 si[G::IB], zi;                            // every request before the first sum
+#pragma unroll
+      for (int ib = 0; ib < G::IB; ++ib)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) si[ib][r] = src[(32 * ib + 8 * (r >> 2) + (r & 3)) * D];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) zi[r] = zp[8 * (r >> 2) + (r & 3)];
+#pragma unroll
+      for (int ib = 0; ib < G::IB; ++ib) Sacc[ib] += si[ib];
+      Zacc += zi;
+    }
+  } else {
     const float* Ssrc = nullptr;
     const float* zsrc = nullptr;
     int srow = D;                                      // row length of the source: a workspace slot, or the caller's S
-    if (STATE_ONLY || a.fold) {}
+    if (STATE_ONLY) {}
     else if (a.nseg > 1) { Ssrc = ws_bh + (size_t)seg * SLOT; zsrc = Ssrc + D * D; }
     else if (a.S_in) { Ssrc = a.S_in + S_base; zsrc = a.z_in + (size_t)bh * D; srow = DVT; }
 #pragma unroll
@@ -685,25 +709,6 @@ __global__ __launch_bounds__(D * 4) void prefill_mfma_ws_kernel(PrefillArgs a) {
       }
 #pragma unroll
     for (int r = 0; r < 16; ++r) Zacc[r] = zsrc ? zsrc[32 * w + 8 * (r >> 2) + 4 * hi + (r & 3)] : 0.f;
-    // The increments of the segments before this one, added up here while the front-end waves fetch and map the first
-    // rows (see prefill_mfma_fold_segments): in the prefix sum's order, so the same bits.
-    if (!STATE_ONLY && a.fold) {
-      const float* src = ws_bh + SLOT + 4 * hi * D + cw;
-      const float* zp = ws_bh + SLOT + D * D + 32 * w + 4 * hi;
-#pragma unroll 1
-      for (int g = 0; g < seg; ++g, src += SLOT, zp += SLOT) {
-        f32x16 si[G::IB], zi;                          // every request before the first sum
-#pragma unroll
-        for (int ib = 0; ib < G::IB; ++ib)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) si[ib][r] = src[(32 * ib + 8 * (r >> 2) + (r & 3)) * D];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) zi[r] = zp[8 * (r >> 2) + (r & 3)];
-#pragma unroll
-        for (int ib = 0; ib < G::IB; ++ib) Sacc[ib] += si[ib];
-        Zacc += zi;
-      }
-    }
   }
   bf16x8 ones;
 #pragma unroll

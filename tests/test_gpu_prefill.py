@@ -303,7 +303,8 @@ def test_fp32_rows_on_either_side_of_the_dispatch(grouped, B, H, L, d, Kc, with_
 
 @pytest.mark.parametrize("form", ["tokens", "grouped"])
 @pytest.mark.parametrize("B,H,L,d", [(8, 16, 1100, 128), (8, 8, 1531, 128), (5, 8, 1100, 128),   # 2, 4, 6 segments
-                                     (7, 12, 1197, 64), (1, 32, 1100, 128), (1, 4, 1000, 64), (1, 3, 520, 128)])
+                                     (7, 12, 1197, 64), (1, 32, 1100, 128), (1, 4, 1000, 64), (1, 3, 520, 128),
+                                     (1, 11, 1000, 128), (1, 12, 1000, 128)])             # eight segments, six
 def test_segments_summed_in_the_full_pass_or_by_the_prefix_sum(form, B, H, L, d):
     """A new sequence of few segments adds their increments up in the full pass; handed zeros as its state the same
     sequence takes the prefix sum.  Same order of additions; the segments differ up to 1024 tokens only."""
