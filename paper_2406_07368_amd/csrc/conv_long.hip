@@ -3,7 +3,8 @@
 //
 //   out[t][c] += sum_{j < Kc} w[h][c][j] * Vext[t - j][c]        Vext = hist_in ++ V, zeros before that
 //
-// fp32 rows on the vector ALUs (exact fp32 products); bf16 rows run on the matrix cores (conv_mfma.hip).
+// on the vector ALUs: fp32 rows (exact fp32 products), and bf16 rows with few taps or in short sequences (conv_vector_pays);
+// the other bf16 rows run on the matrix cores (conv_mfma.hip).
 // The attention kernels keep an 8-row halo of V in LDS and gather the taps per token; a 62-row halo does not
 // fit next to their row buffers, and 63 taps per output are a vector-ALU workload of the size of the attention
 // itself.  So long kernels are register-blocked here instead: a thread owns one channel, holds its taps in
@@ -29,6 +30,33 @@ constexpr int CL_BLK = 8;         // outputs a thread carries at once (fewer if 
 static __device__ __forceinline__ float elem_to_f32(float x) { return x; }
 static __device__ __forceinline__ float elem_to_f32(uint16_t x) { return bf16_bits_to_f32(x); }
 
+// bytes of the value rows, or of the taps before them
+template <typename Elem, int D, int KMAX, int TOK>
+static constexpr int conv_long_lds() {
+  constexpr int rows = (CL_HALO + TOK) * D * (int)sizeof(Elem), taps = D * KMAX * (int)sizeof(float);
+  return rows > taps ? rows : taps;
+}
+
+// Infinities and NaN among eight elements as they lie in memory: running maxima of the magnitudes' bits (bf16: two at a time).
+typedef uint16_t cl_u16x2 __attribute__((ext_vector_type(2)));
+static __device__ __forceinline__ uint32_t top_exponent(const u32x4& x, uint32_t top) {
+  cl_u16x2 t = __builtin_bit_cast(cl_u16x2, top);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) t = __builtin_elementwise_max(t, __builtin_bit_cast(cl_u16x2, x[i] & 0x7fff7fffu));
+  return __builtin_bit_cast(uint32_t, t);
+}
+static __device__ __forceinline__ bool not_finite(uint32_t top, const u32x4&) { return (top >> 16) >= 0x7f80u || (top & 0xffffu) >= 0x7f80u; }
+static __device__ __forceinline__ uint32_t top_exponent(const F32Raw8& x, uint32_t top) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t a = __float_as_uint(x.lo[i]) & 0x7fffffffu, b = __float_as_uint(x.hi[i]) & 0x7fffffffu;
+    top = a > top ? a : top;
+    top = b > top ? b : top;
+  }
+  return top;
+}
+static __device__ __forceinline__ bool not_finite(uint32_t top, const F32Raw8&) { return top >= 0x7f800000u; }
+
 template <typename Io, int D, int KMAX, int TOK>
 __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
   // the value rows [CL_HALO + TOK][D] as they lie in memory (bf16 rows stay bf16: half the LDS of fp32 rows, so
@@ -36,6 +64,7 @@ __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_cl[];
   float* xs = reinterpret_cast<float*>(smem_cl);
   typename Io::elem* xe = reinterpret_cast<typename Io::elem*>(smem_cl);
+  int* odd = reinterpret_cast<int*>(smem_cl + conv_long_lds<typename Io::elem, D, KMAX, TOK>());   // [waves]
   constexpr int NG = 256 / D;                 // token groups of threads
   constexpr int TPT = TOK / NG;            // tokens per thread
   // (a block also holds its own and the next block's elements of out)
@@ -119,6 +148,7 @@ __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
   }
 
   {
+    uint32_t top = 0u;                        // largest exponent met, in the place where the type has it
 #pragma unroll
     for (int i = 0; i < RIT; ++i) {
       const int e = tid + 256 * i;
@@ -127,10 +157,15 @@ __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
         typename Io::raw8 y = raw[i];
         if (!have[i]) y = typename Io::raw8{};
         *reinterpret_cast<typename Io::raw8*>(xe + row * D + i0) = y;
+        top = top_exponent(y, top);
       }
     }
+    const int any = __any(not_finite(top, typename Io::raw8{}));
+    if ((tid & 63) == 0) odd[tid >> 6] = any;
   }
   __syncthreads();
+  // the zero taps beyond Kc would make a NaN of an infinity that lies beyond the window: such workgroups go tap by tap
+  const bool by_tap = (odd[0] | odd[1] | odd[2] | odd[3]) != 0;
 
   // The history handed on (the last Kc - 1 rows of history ++ sequence), when the launcher asked for it here: every
   // workgroup writes the rows whose tokens it owns (t0 <= token < t0 + 64; the first one also the rows that stay
@@ -159,15 +194,23 @@ __global__ __launch_bounds__(256) void conv_long_kernel(ConvLongArgs a) {
     for (int e = 0; e < BLK; ++e) acc[e] = 0.f;
     // value rows from the newest output's own row backwards: row m feeds output e through tap e - 7 + m
     const typename Io::elem* newest = xe + (CL_HALO + tb0 + BLK - 1) * D + c;
-    // (fully unrolled, so that every tap index is a constant and the taps stay in registers)
+    if (by_tap) {                               // uniform
+      const float* wc = a.conv_w + ((size_t)h * DVT + blk * D + c) * Kc;
+#pragma unroll 1
+      for (int j = 0; j < Kc; ++j)
 #pragma unroll
-    for (int m = 0; m < KMAX + BLK - 1; ++m) {
-      const float x = elem_to_f32(newest[-m * D]);
+        for (int e = 0; e < BLK; ++e) acc[e] = fmaf(wc[j], elem_to_f32(newest[-(BLK - 1 - e + j) * D]), acc[e]);
+    } else {
+      // (fully unrolled, so that every tap index is a constant and the taps stay in registers)
 #pragma unroll
-      for (int e = 0; e < BLK; ++e) {
-        constexpr int J0 = -(BLK - 1);
-        const int j = e + J0 + m;
-        if (j >= 0 && j < KMAX) acc[e] = fmaf(wreg[j], x, acc[e]);
+      for (int m = 0; m < KMAX + BLK - 1; ++m) {
+        const float x = elem_to_f32(newest[-m * D]);
+#pragma unroll
+        for (int e = 0; e < BLK; ++e) {
+          constexpr int J0 = -(BLK - 1);
+          const int j = e + J0 + m;
+          if (j >= 0 && j < KMAX) acc[e] = fmaf(wreg[j], x, acc[e]);
+        }
       }
     }
 #pragma unroll
@@ -228,8 +271,7 @@ __global__ __launch_bounds__(256) void conv_long_hist_kernel(ConvLongArgs a) {
 
 template <typename Io, int D, int KMAX, int TOK>
 static hipError_t launch_cl_t(const ConvLongArgs& a, hipStream_t st) {
-  constexpr int LDS_ROWS = (CL_HALO + TOK) * D * (int)sizeof(typename Io::elem), LDS_TAPS = D * KMAX * (int)sizeof(float);
-  constexpr int LDS = LDS_ROWS > LDS_TAPS ? LDS_ROWS : LDS_TAPS;
+  constexpr int LDS = conv_long_lds<typename Io::elem, D, KMAX, TOK>() + 4 * (int)sizeof(int);
   auto kern = conv_long_kernel<Io, D, KMAX, TOK>;
   hipError_t e = LINATTN_MAX_LDS_ONCE(kern, LDS);
   if (e != hipSuccess) return e;
@@ -244,6 +286,21 @@ static hipError_t launch_cl_k(const ConvLongArgs& a, hipStream_t st) {
   return wgs < 256 ? launch_cl_t<Io, D, KMAX, CL_TOK / 2>(a, st) : launch_cl_t<Io, D, KMAX, CL_TOK>(a, st);
 }
 
+// bf16 rows added to out: this kernel or the matrix cores?  The matrix-core kernel works on tiles of 256 tokens and takes
+// about as long for 9 taps as for 17, for 18 as for 49; this one pays for the tokens and the taps there are (capacities of
+// 16, 32 and 63; of those of 32 not 32 itself, whose taps come through LDS on one bank).  Measured, us a prefill call, this / matrix
+// cores.  Up to 16 taps: d = 64: 1 head, 300 tokens 27.2 / 27.6, 32 heads, 1100 tokens 37.2 / 40.4, 256 heads, 300 tokens
+// 37.3 / 44.7; d = 128: 16 heads, 300 tokens 32.0 / 33.1, 128 heads, 1100 tokens 97 / 107, 256 heads, 4096 tokens 442 / 438, but 1 head,
+// 300 tokens 31.4 / 30.2.  Fewer than 32 taps, heads enough to fill the chip: d = 64: 32 heads, 300 tokens 29.1 / 31.1, 128 heads,
+// 1100 tokens 64 / 72, 64 heads, 4000 tokens 95 / 91; d = 128: 64 heads, 300 tokens 39.0 / 40.5, 128 heads, 1100 tokens 103 / 107, 32
+// heads, 500 tokens 41.3 / 39.2.  Any number of taps, sequences of half a tile: 63 taps, d = 64, 256 heads, 60 tokens 22.3 / 25.3, 120
+// tokens 26.7 / 29.6, 200 tokens 38.8 / 40.6, 32 heads, 60 tokens 19.1 / 18.1; d = 128, 256 heads, 60 tokens 32 / 36, 200 tokens 56 / 52, 64
+// heads, 60 tokens 23.4 / 22.9.
+static bool conv_vector_pays(const ConvLongArgs& a, int d) {
+  const int64_t heads = (int64_t)a.B * a.H * a.m, tiles = (int64_t)((a.L + 255) / 256) * heads * (d / 32);
+  return (a.Kc <= 16 && (d == 64 || tiles >= 64)) || (a.Kc < 32 && a.L <= 2048 && 2 * heads >= d) || (a.L <= 128 && heads >= d);
+}
+
 template <typename Io, int D>
 static hipError_t launch_cl(const ConvLongArgs& a_in, hipStream_t st) {
   constexpr bool BF16 = sizeof(typename Io::elem) == 2;
@@ -252,9 +309,10 @@ static hipError_t launch_cl(const ConvLongArgs& a_in, hipStream_t st) {
   // head: the first of them reads the old rows, the last would overwrite them, and nothing orders the two.  (The bf16
   // kernel writes it while its own waves may still be reading: never when hist_out is hist_in.)
   ConvLongArgs a = a_in;
-  a.hist_fused = a.hist_out != nullptr && a.L > 0 && (a.hist_out != a.hist_in || (!BF16 && a.L <= CL_TOK / 2));
+  const bool vector = !BF16 || (!a.assign && conv_vector_pays(a, D));
+  a.hist_fused = a.hist_out != nullptr && a.L > 0 && (a.hist_out != a.hist_in || (vector && a.L <= CL_TOK / 2));
   if (a.L > 0) {
-    if constexpr (BF16) e = launch_conv_mfma(a, D, st);
+    if (!vector) e = launch_conv_mfma(a, D, st);
     else e = a.Kc <= 16   ? launch_cl_k<Io, D, 16>(a, st)
              : a.Kc <= 32 ? launch_cl_k<Io, D, 32>(a, st)
                           : launch_cl_k<Io, D, CL_MAXK>(a, st);

@@ -14,7 +14,7 @@
 // 16, both factors bf16 as they are), summed along its diagonals: first over the four accumulator registers by shifts
 // inside a row of 16 lanes, then over the four rows through LDS.
 //
-// One workgroup = 256 or 512 tokens of 32 channels of one (b, h[, value block]), four waves of 8 channels.  The rows are turned
+// One workgroup = 256 or 512 tokens of 32 channels (16 or 8 where few would run) of one (b, h[, value block]), four waves.  The rows are turned
 // around on their way into LDS ([channel][token], two tokens per dword: a thread takes 8 channels of two neighbouring
 // tokens), so that an operand of eight consecutive tokens is one 16-byte read and one of every sixteenth token one
 // transpose read; the results go back the same way.  The LDS rows are skewed per 8 channels so that those accesses hit 64
@@ -33,15 +33,14 @@ namespace linattn {
 
 namespace {
 constexpr int CM_SUB = 256;                                // tokens of one 16 x 16 tile; a workgroup takes one or two
-constexpr int CM_CB = 32;                                  // channels per workgroup
-constexpr int CM_NW = 4, CM_CPW = CM_CB / CM_NW;           // waves, channels per wave
+constexpr int CM_NW = 4;                                   // waves; channels are dealt out over them
 constexpr int CM_SKEW = 16;                                // dwords per 8 channels
 typedef uint32_t __attribute__((may_alias)) u32_any;      // dwords of an array that is written in 16-bit pieces
 typedef uint16_t __attribute__((may_alias)) u16_any;      // and the other way round
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 enum { CM_ASSIGN = 0, CM_ADD = 1, CM_BWD = 2 };
 
-template <int KS, int MODE, int T>
+template <int KS, int MODE, int T, int CB>
 struct ConvCfg {
   static constexpr int OFF = 32 * KS - 16;                 // tokens beyond the block that the taps reach; taps <= OFF + 1
   static constexpr int NB = KS == 1 ? 2 : KS == 2 ? 4 : 5; // 16-token lags of the tap gradient
@@ -51,8 +50,8 @@ struct ConvCfg {
   static constexpr int VD = MODE == CM_BWD ? (T + VOFF) / 2 : MODE == CM_ADD ? T / 2 : 0;
   static_assert(XD % 8 == 0 && VD % 8 == 0, "bank skew");
   static constexpr int X = 0;
-  static constexpr int V = X + CM_CB * XD + CM_SKEW * (CM_CB / 8);            // value rows (backward), low halves of the results (add)
-  static constexpr int W = V + (VD ? CM_CB * VD + CM_SKEW * (CM_CB / 8) : 0); // per wave: [2 copies][3 terms][XN] u16
+  static constexpr int V = X + CB * XD + CM_SKEW * (CB / 8);            // value rows (backward), low halves of the results (add)
+  static constexpr int W = V + (VD ? CB * VD + CM_SKEW * (CB / 8) : 0); // per wave: [2 copies][3 terms][XN] u16
   static constexpr int ED = MODE == CM_BWD ? 4 * 80 : 0;                      // backward: the tap sums' rows, [4][80] float, in the same place
   static constexpr int WB = ((3 * XN / 2 + 31) / 64) * 64 + 32;              // the copy shifted by one entry: other banks than the first
   static constexpr int WLEN = WB + 3 * XN / 2;
@@ -76,10 +75,10 @@ __device__ __forceinline__ float row_shr(float x) {
   return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x110 + N, 0xf, 0xf, true));
 }
 
-// Rows tok0 .. tok0 + 2 NP - 1 of 32 channels on their way to LDS: requested, then turned around and stored.
-template <int NP>
+// Rows tok0 .. tok0 + 2 NP - 1 of CB channels on their way to LDS: requested, then turned around and stored.
+template <int NP, int CB>
 struct RowPairs {
-  static constexpr int NG = CM_CB / 8, PPI = 256 / NG, IT = (NP + PPI - 1) / PPI;
+  static constexpr int NG = CB / 8, PPI = 256 / NG, IT = (NP + PPI - 1) / PPI;
   u32x4 x[IT][2];
   // row(tok, &ok): the memory row of a token and whether it exists (a row that does not is requested all the same)
   template <typename Row>
@@ -122,9 +121,10 @@ struct RowPairs {
 };
 }  // namespace
 
-template <int D, int KS, int MODE, int T>
+template <int D, int KS, int MODE, int T, int CB>
 __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvLongArgs a) {
-  using G = ConvCfg<KS, MODE, T>;
+  using G = ConvCfg<KS, MODE, T, CB>;
+  constexpr int CPW = CB / CM_NW;                          // channels per wave
   constexpr bool BWD = MODE == CM_BWD;
   extern __shared__ __attribute__((aligned(16))) uint32_t smu[];
   uint32_t* Xl = smu + G::X;
@@ -135,16 +135,16 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvLongArgs a) {
   uint16_t* wl = reinterpret_cast<uint16_t*>(smu + G::W + w * G::WD);
   float* el = reinterpret_cast<float*>(wl);
 
-  // 32 channels of one (b, h, value block)
+  // CB channels of one (b, h, value block)
   const int bh = blockIdx.y / a.m, b = bh / a.H, h = bh % a.H;
   // Block indices 8 apart land on the same chiplet.  The channel blocks of a token block share its memory lines and
   // neighbouring token blocks share rows, so both are kept on one chiplet, close together in time (when the number of
   // token blocks is a multiple of 8; otherwise the channel blocks of a token block lie side by side).
-  constexpr int CBLK = D / CM_CB;
+  constexpr int CBLK = D / CB;
   const int nblk = (a.L + T - 1) / T, bx = blockIdx.x;
   const int seq = nblk % 8 == 0 ? bx >> 3 : bx;
   const int tblk = seq / CBLK + (nblk % 8 == 0 ? (bx & 7) * (nblk >> 3) : 0);
-  const int DVT = a.m * D, cblk = seq % CBLK * CM_CB, ch0 = (blockIdx.y % a.m) * D + cblk;
+  const int DVT = a.m * D, cblk = seq % CBLK * CB, ch0 = (blockIdx.y % a.m) * D + cblk;
   const int t0 = tblk * T;
   const int L = a.L, Kc = a.Kc, R = Kc - 1;
   const int64_t base = (int64_t)b * a.sb + (int64_t)h * a.sh + ch0;
@@ -165,11 +165,11 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvLongArgs a) {
     return gv + (int64_t)(ok ? tok : 0) * a.st;
   };
   const int x0 = BWD ? t0 : t0 - G::OFF;                   // first token of the rows at hand
-  RowPairs<G::XD> xr;
+  RowPairs<G::XD, CB> xr;
   xr.request(x0, tid, x_row);
-  [[maybe_unused]] RowPairs<BWD ? G::VD : 1> vr;
+  [[maybe_unused]] RowPairs<BWD ? G::VD : 1, CB> vr;
   if constexpr (BWD) vr.request(t0 - G::VOFF, tid, v_row);
-  const float* wsrc = a.conv_w + ((size_t)h * DVT + ch0 + w * CM_CPW) * Kc + (lane < Kc ? lane : 0);
+  const float* wsrc = a.conv_w + ((size_t)h * DVT + ch0 + w * CPW) * Kc + (lane < Kc ? lane : 0);
   float tap = wsrc[0];
   for (int i = lane; i < G::WD; i += 64) reinterpret_cast<u32_any*>(wl)[i] = 0u;
 
@@ -204,8 +204,8 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvLongArgs a) {
   const int at = BWD ? lane + 15 : G::OFF + 15 - lane;     // where this lane's tap sits in the line
   auto channels = [&](auto taps_alone) __attribute__((always_inline)) {
 #pragma unroll 1
-    for (int cc = 0; cc < CM_CPW; ++cc) {
-      const int c = w * CM_CPW + cc;
+    for (int cc = 0; cc < CPW; ++cc) {
+      const int c = w * CPW + cc;
       uint32_t* xrow = Xl + cm_row(c, G::XD);
       if constexpr (BWD) {
         if (a.dw_part) {                                     // uniform
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvLongArgs a) {
           wl[2 * G::WB + G::XN * t + at - 1] = t3[t];        // at >= 15
         }
       }
-      tap = wsrc[(cc + 1 < CM_CPW ? cc + 1 : cc) * Kc];
+      tap = wsrc[(cc + 1 < CPW ? cc + 1 : cc) * Kc];
       bf16x8 wf[3][KS];
 #pragma unroll
       for (int t = 0; t < 3; ++t)
@@ -309,7 +309,7 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvLongArgs a) {
   else channels(std::false_type{});
 
   // ---- whole rows out ------------------------------------------------------------------------------------------------
-  constexpr int NG = CM_CB / 8, PPI = 256 / NG, OIT = T / 2 / PPI;
+  constexpr int NG = CB / 8, PPI = 256 / NG, OIT = (T / 2 + PPI - 1) / PPI;
   const int g = tid % NG;
   [[maybe_unused]] u32x4 held[OIT][2];
   if constexpr (MODE == CM_ADD) {
@@ -325,6 +325,7 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvLongArgs a) {
 #pragma unroll
   for (int i = 0; i < OIT; ++i) {
     const int p = tid / NG + PPI * i;
+    if (T / 2 % PPI != 0 && p >= T / 2) break;
     uint32_t d[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) d[e] = Xl[cm_row(8 * g + e, G::XD) + p];
@@ -357,34 +358,44 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvLongArgs a) {
   }
 }
 
-// Tokens per workgroup: two tiles share the tap operands (104 -> 84 us at a chip-filling size); one where two would leave
-// less than two workgroups per compute unit (B1 H8 L1000: 128 workgroups of one tile, 8 us).
+// Tokens per workgroup: two tiles share the tap operands (104 -> 84 us at a chip-filling size, 0.81 of the time per tile);
+// one where two would leave less than two workgroups per compute unit (B1 H8 L1000: 128 workgroups of one tile, 8 us), or
+// where the second would be padding (256 heads of 128, 60 tokens: call of 43.7 us with two, 36.3 with one).
 static int cm_tokens(int L, int heads, int d) {
-  const int64_t wgs = (int64_t)((L + 2 * CM_SUB - 1) / (2 * CM_SUB)) * heads * (d / CM_CB);
-  return wgs >= 512 ? 2 * CM_SUB : CM_SUB;
+  const int64_t two = (L + 2 * CM_SUB - 1) / (2 * CM_SUB), one = (L + CM_SUB - 1) / CM_SUB;
+  return two * heads * (d / 32) >= 512 && 162 * two < 100 * one ? 2 * CM_SUB : CM_SUB;
 }
 int conv_mfma_blocks(int L, int heads, int d) {
   const int t = cm_tokens(L, heads, d);
   return (L + t - 1) / t;
 }
 
-template <int D, int KS, int MODE, int T>
+template <int D, int KS, int MODE, int T, int CB>
 static hipError_t launch_cm_one(const ConvLongArgs& a, hipStream_t st) {
-  constexpr int bytes = ConvCfg<KS, MODE, T>::TOTAL * 4;
-  auto kern = conv_mfma_kernel<D, KS, MODE, T>;
+  constexpr int bytes = ConvCfg<KS, MODE, T, CB>::TOTAL * 4;
+  auto kern = conv_mfma_kernel<D, KS, MODE, T, CB>;
   hipError_t e = LINATTN_MAX_LDS_ONCE(kern, bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((a.L + T - 1) / T * (D / CM_CB)), (unsigned)(a.B * a.H * a.m)), dim3(256), bytes, st, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((a.L + T - 1) / T * (D / CB)), (unsigned)(a.B * a.H * a.m)), dim3(256), bytes, st, a);
   return hipGetLastError();
 }
 
-template <int D, int MODE, int T>
+template <int D, int MODE, int T, int CB>
 static hipError_t launch_cm_t(const ConvLongArgs& a, hipStream_t st) {
-  return a.Kc <= 17 ? launch_cm_one<D, 1, MODE, T>(a, st) : a.Kc <= 49 ? launch_cm_one<D, 2, MODE, T>(a, st) : launch_cm_one<D, 3, MODE, T>(a, st);
+  return a.Kc <= 17 ? launch_cm_one<D, 1, MODE, T, CB>(a, st)
+                    : a.Kc <= 49 ? launch_cm_one<D, 2, MODE, T, CB>(a, st) : launch_cm_one<D, 3, MODE, T, CB>(a, st);
 }
+// Channels per workgroup: a wave takes its channels one after another, so with few workgroups fewer channels each (and more
+// workgroups) shorten the call: 32 / 16 / 8 channels, us a prefill call of 63 taps: 32 workgroups of 32 channels (B1 H4 L300 d128)
+// 34.5 / 32.5 / 31.3, 64 (B1 H8 L1000 d64) 32.7 / 31.0 / 30.8, 96 32.7 / 32.1 / 32.3, 128 (B1 H4 L2000 d128) 37.8 / 35.7 / 36.4, 160 (B1 H32 L1000
+// d64, two rounds of half a chip) 37.8 / 41.6 / 43.0.  More share the memory lines of a row.
 template <int D, int MODE>
 static hipError_t launch_cm(const ConvLongArgs& a, hipStream_t st) {
-  return cm_tokens(a.L, a.B * a.H * a.m, D) == CM_SUB ? launch_cm_t<D, MODE, CM_SUB>(a, st) : launch_cm_t<D, MODE, 2 * CM_SUB>(a, st);
+  const int heads = a.B * a.H * a.m;
+  if (cm_tokens(a.L, heads, D) == 2 * CM_SUB) return launch_cm_t<D, MODE, 2 * CM_SUB, 32>(a, st);
+  const int64_t wgs = (int64_t)((a.L + CM_SUB - 1) / CM_SUB) * heads * (D / 32);
+  return wgs <= 64 ? launch_cm_t<D, MODE, CM_SUB, 8>(a, st)
+                   : wgs <= 128 ? launch_cm_t<D, MODE, CM_SUB, 16>(a, st) : launch_cm_t<D, MODE, CM_SUB, 32>(a, st);
 }
 
 hipError_t launch_conv_mfma(const ConvLongArgs& a, int d, hipStream_t st) {

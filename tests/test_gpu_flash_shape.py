@@ -221,6 +221,17 @@ def test_long_conv_of_rows_and_taps_that_are_not_finite(B, H, L, d, Kc, alpha):
     same_pattern(got[:3], want[:3], TOL["bf16"], f"L={L} Kc={Kc}")
 
 
+@pytest.mark.parametrize("io,B,H,L,d,Kc", [("f32", 1, 2, 300, 64, 50), ("f32", 1, 2, 70, 128, 9), ("bf16", 2, 32, 100, 64, 20)])
+def test_long_conv_on_the_vector_alus_of_rows_that_are_not_finite(io, B, H, L, d, Kc):
+    """Taps beyond the last one are zeros there; a row beyond the window may not meet them."""
+    q, k, v, w, state = small_case(7960 + L + Kc, B, H, L, d, Kc, io, True)
+    state[2][0, 0, 0, 5] = np.inf
+    state[2][B - 1, H - 1, Kc // 2, d - 1] = np.nan
+    want = oracle.prefill_recurrent(q, k, v, w, *state, eps=1e-3)
+    got = run(q, k, v, w, state, io, 64, 1e-3)
+    same_pattern(got[:3], want[:3], TOL[io], f"{io} L={L} Kc={Kc}")
+
+
 def test_gradient_of_the_long_conv_with_a_gradient_row_that_is_not_finite():
     """dv is the conv's share and a product along the tokens: an infinity in one channel of dout stays in that channel, and
     in the group of its token and the window of taps before it."""
@@ -239,3 +250,21 @@ def test_gradient_of_the_long_conv_with_a_gradient_row_that_is_not_finite():
     check(dv, want["dv"], TOL["bf16"], "dv")
     err = float(np.max(np.abs(dw - want["dw"])) / np.sqrt(np.mean(want["dw"] ** 2)))
     assert err <= TOL["f32"], f"dw: {err:.2e}"
+
+
+@pytest.mark.parametrize("B,H,L,d,Kc", [
+    (1, 2, 256, 128, 16), (1, 16, 257, 128, 16),          # up to 16 taps: matrix cores below 64 tiles, vector ALUs from there on
+    (1, 31, 100, 64, 31), (1, 32, 100, 64, 31), (1, 32, 100, 64, 32),   # fewer than 32 taps and heads enough, 32 taps
+    (2, 32, 128, 64, 40), (2, 32, 129, 64, 40),           # half a tile and more
+    (2, 64, 600, 128, 63), (2, 64, 513, 128, 33)])        # one tile per workgroup where the second would be padding
+def test_long_conv_on_either_side_of_its_dispatch(B, H, L, d, Kc):
+    q, k, v, w, state = small_case(8100 + L + Kc, B, H, L, d, Kc, "bf16", True)
+    h = [0, H - 1]
+    want = oracle.prefill_recurrent(q[:, h], k[:, h], v[:, h], w[h], *(x[:, h] for x in state), eps=1e-3)
+    got = run(q, k, v, w, state, "bf16", 256, 1e-3)
+    compare(tuple(x[:, h] for x in got), want, "bf16", f"added, H={H} L={L} Kc={Kc}")
+    got = run(q, k, v, w, state, "bf16", 256, 1e-3, alias_hist=True)
+    compare(tuple(x[:, h] for x in got), want, "bf16", f"history in place, H={H} L={L} Kc={Kc}")
+    want = oracle.prefill_grouped(q[:, h], k[:, h], v[:, h], w[h], 256, 0.7, *(x[:, h] for x in state), eps=1e-3)
+    got = run(q, k, v, w, state, "bf16", 256, 1e-3, alpha=0.7)
+    compare(tuple(x[:, h] for x in got), want, "bf16", f"written first, H={H} L={L} Kc={Kc}")
