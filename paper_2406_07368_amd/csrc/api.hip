@@ -20,9 +20,10 @@ constexpr int32_t kDefaultWaitSpins = 1 << 20;
 std::atomic<int32_t> g_wait_spins{kDefaultWaitSpins};
 
 // Scratch of linattn_prefill_noalloc: the workspace of a segmented prefill, held by every GPU the library runs
-// on until the process ends.  Sized for the largest workspace any descriptor can ask for: the launch plan never
-// puts more than 256 (b, h, segment) slots of d*d + d floats on the chip, plus 8 staged history rows per (b, h)
-// for fewer than 256 of those.
+// on until the process ends.  Sized for the largest workspace any descriptor can ask for: the launch plans put at most
+// 256 (b, h, segment) slots of d*d + d floats on the chip at d = 128 and 512, a quarter as large each, at d = 64, plus 8
+// staged history rows per head; only calls of at most 128 heads (256 at d = 64) are segmented, so rows of 4 bytes (fp32)
+// take no more than the 256 heads of 2-byte rows of 128 counted here.
 constexpr size_t kScratchBytes = 256 * (128 * 128 + 128) * sizeof(float) + 256 * HALO * 128 * sizeof(uint16_t);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 

@@ -235,3 +235,18 @@ def test_binding_raises_on_refusal():
     with pytest.raises(binding.LinattnError) as ei:
         binding.linattn_verify(good_desc(), 0, P, P, P, P, P, P, P, None, P, stream=0)
     assert ei.value.status == 2
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_no_plan_asks_for_more_than_the_static_scratch(dtype, d):
+    """linattn_prefill_noalloc accepts whatever linattn_prefill accepts."""
+    import torch
+    io = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    most = 0
+    for heads in list(range(1, 140)) + [160, 192, 255, 256, 257, 300, 511, 512, 513, 4096]:
+        for m in (1, 2, 4, 16):
+            for L in (1, 63, 257, 513, 832, 1024, 1025, 2049, 5000, 20000, 65536, 1 << 20):
+                desc = binding.make_desc(1, heads, d, 3, 64, io, L=L, d_v=m * d)
+                most = max(most, binding.linattn_workspace_bytes(desc, L))
+    assert 0 < most <= binding.linattn_noalloc_scratch_bytes()

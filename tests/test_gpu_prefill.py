@@ -277,10 +277,11 @@ def test_a_wait_that_gives_up_shows_as_nan(grouped, L):
 @pytest.mark.parametrize("grouped", [False, True])
 @pytest.mark.parametrize("B,H,L,d,Kc,with_state", [
     (1, 2, 31, 64, 3, True), (1, 4, 33, 128, 8, False), (1, 4, 512, 64, 5, True),      # quadratic kernel, edges of its tiles
-    (1, 4, 545, 64, 3, True), (2, 8, 289, 128, 4, True), (1, 40, 257, 64, 8, True),    # segmented walk, ragged last segments
-    (8, 40, 97, 64, 3, False), (3, 100, 65, 128, 1, True)])                            # one workgroup per head
+    (1, 4, 545, 64, 3, True), (2, 8, 289, 128, 4, True), (1, 40, 257, 64, 8, True),    # token form: segmented walk, quadratic, segmented
+    (8, 40, 97, 64, 3, False), (3, 100, 65, 128, 1, True)])                            # token form: one workgroup per head
 def test_fp32_rows_on_either_side_of_the_dispatch(grouped, B, H, L, d, Kc, with_state):
-    """The fp32 kernels (quadratic, segmented, whole heads) against the oracle; S and z updated in place take the walk."""
+    """The fp32 kernels (quadratic, segmented, whole heads) against the oracle; the three-branch form is quadratic at all of
+    these sizes.  S and z updated in place take the walk, whole heads at a time."""
     q, k, v, w, state = small_case(6200 + L + d, B, H, L, d, Kc, "f32", with_state)
     args = {} if state is None else dict(S0=state[0], z0=state[1], hist0=state[2])
     want = oracle.prefill_grouped(q, k, v, w, 64, alpha=0.7, eps=1e-2, **args) if grouped else oracle.prefill_recurrent(q, k, v, w, eps=1e-2, **args)
@@ -334,7 +335,7 @@ def test_segments_summed_in_the_full_pass_or_by_the_prefix_sum(form, B, H, L, d)
 
 NON_FINITE = [(2, 4, 130, 64, 3), (2, 4, 130, 128, 4),           # quadratic kernel
               (1, 4, 1700, 64, 3), (1, 3, 1700, 128, 5),         # segmented walk
-              (8, 40, 97, 64, 2), (3, 100, 65, 128, 8)]          # one workgroup per head
+              (8, 40, 130, 64, 2), (3, 100, 129, 128, 8)]        # one workgroup per head
 
 
 def same_pattern(got, want, tol, what):
@@ -412,3 +413,36 @@ def test_fp32_more_heads_than_a_grid_axis_counts(grouped, B, H, d_v):
         else:
             want = oracle.prefill_recurrent(q[b], k[b], v[b], w, eps=1e-2)
         check(out[b], want[0], TOL["f32"], f"B={B} rows {b}")
+
+
+@pytest.mark.parametrize("form,B,H,L,d,d_v,Kc,segments", [
+    ("grouped", 1, 4, 1601, 64, 64, 3, True), ("grouped", 2, 8, 801, 128, 128, 5, True), ("grouped", 1, 40, 577, 64, 64, 8, True),
+    ("grouped", 8, 40, 130, 64, 64, 3, False), ("grouped", 3, 100, 129, 128, 128, 8, False),
+    ("tokens", 1, 3, 700, 64, 128, 5, True), ("tokens", 2, 4, 513, 64, 128, 8, True), ("tokens", 1, 2, 520, 128, 256, 3, True),
+    ("tokens", 8, 40, 70, 64, 128, 4, False)])
+def test_fp32_walk_in_segments_or_whole_heads(form, B, H, L, d, d_v, Kc, segments):
+    """The walk over an incoming state, which segments get through the workspace (history rows as floats behind the sums):
+    the three-branch form beyond its quadratic kernel, and value rows wider than key rows.  A segmented plan leaves its sums in
+    the workspace, so a change of the plan does not leave these cases to another kernel unnoticed."""
+    rng = np.random.default_rng(6600 + L + d)
+    q, k, v = (rng.standard_normal((B, H, L, n)).astype(np.float32) for n in (d, d, d_v))
+    w = workloads.conv_weights(rng, H, d_v, Kc)
+    state = ((rng.standard_normal((B, H, d, d_v)) * 3.0).astype(np.float32), (np.abs(rng.standard_normal((B, H, d))) * 5.0 + 1.0).astype(np.float32),
+             rng.standard_normal((B, H, Kc - 1, d_v)).astype(np.float32))
+    args = dict(S0=state[0], z0=state[1], hist0=state[2])
+    want = oracle.prefill_grouped(q, k, v, w, 64, alpha=0.7, eps=1e-2, **args) if form == "grouped" else oracle.prefill_recurrent(q, k, v, w, eps=1e-2, **args)
+    gq, gk, gv, gw = dev(q), dev(k), dev(v), dev(w)
+    desc = binding.make_desc(B, H, d, Kc, 64, torch.float32, 1e-2, L=L, d_v=d_v)
+    need = binding.linattn_workspace_bytes(desc, L)
+    ws = torch.full((max(need, 16) // 4,), float("nan"), device="cuda")
+    for buf in (ws, None) if segments else (ws,):               # no workspace: the same call, not split
+        st = tuple(dev(x) for x in state)
+        out, res = torch.full_like(gv, float("nan")), tuple(torch.full_like(x, float("nan")) for x in st)
+        nbytes = 0 if buf is None else need
+        if form == "grouped":
+            binding.linattn_prefill_grouped(desc, L, 0.7, gq, gk, gv, gw, *st, out, *res, buf, nbytes)
+        else:
+            binding.linattn_prefill(desc, L, gq, gk, gv, gw, *st, out, *res, buf, nbytes)
+        torch.cuda.synchronize()
+        compare((host(out), *(host(x) for x in res)), want, "f32", f"{form} L={L} d={d} d_v={d_v} workspace={nbytes}")
+    assert bool(torch.isfinite(ws).any()) == segments
