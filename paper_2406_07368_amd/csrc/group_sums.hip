@@ -3,10 +3,10 @@
 //   forward    slot[g] = sums over everything before group g of phi(k) v^T and phi(k)          (S_g, z_g)
 //   backward   slot[g] = sums over everything after group g of f phi(q) dO^T and dden phi(q)   (their gradients)
 //
-// One workgroup walks one (b, h) for 32 features (D = 64: all 64), four waves, a 32 x 32 tile of the sums each (lane =
-// channel, registers = features) in accumulator registers from the first group to the last; at the start of every group
-// they go to the group's slot as they are.  Rows come 128 tokens at a time (64 in groups of 64), requested one step ahead
-// into registers; on their way into one of two LDS buffers the left rows get the feature map and their weight and are
+// One workgroup walks one (b, h) for 32 features (D = 64: all 64) in four 32 x 32 tiles of the sums (lane = channel,
+// registers = features), a wave each (groups of 256: two, see below), in accumulator registers from the first group to the
+// last; at the start of every group they go to the group's slot as they are.  Rows come 128 tokens at a time (64 in groups of
+// 64), requested two steps ahead into registers; on their way into one of two LDS buffers the left rows get the feature map and their weight and are
 // split into two bf16 terms (hi = bf16(x), lo = bf16(x - hi)): once per element, where making the operand as it is read
 // would repeat it in every wave.  Both operands are then transpose reads; the vector part is summed in fp32 by the
 // threads that map the rows.
@@ -72,13 +72,9 @@ __global__ __launch_bounds__(GT == 256 ? 512 : 256) void group_sums_kernel(Group
 
   f32x16 acc;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    acc[r] = 0.f;
-    if (a.S_in && kh == 0) acc[r] = a.S_in[((size_t)bh * D + f0 + 8 * (r >> 2) + 4 * hi + (r & 3)) * D + c0 + l32];
-  }
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
   const int zf = fb * G::FW + tid;                         // threads below FW: the feature whose vector part they carry
   float zrun = 0.f;
-  if (a.z_in && tid < G::FW) zrun = a.z_in[(size_t)bh * D + zf];
 
   // group of step s, first token of step s
   auto group_of = [&](int s) __attribute__((always_inline)) { return BACK ? a.ng - 1 - s / G::CPG : s / G::CPG; };
@@ -188,8 +184,7 @@ __global__ __launch_bounds__(GT == 256 ? 512 : 256) void group_sums_kernel(Group
     if (s + 3 < steps) request(s + 3, x);
     __syncthreads();
   };
-  // the last group of the walk only counts when its sum is handed on
-  const int steps = (a.ng - (a.S_out || a.z_out ? 0 : 1)) * G::CPG;
+  const int steps = (a.ng - 1) * G::CPG;                   // nothing follows the last group of the walk
   if (steps > 0) {
     Rows x0, x1;
     request(0, x1);
@@ -203,12 +198,7 @@ __global__ __launch_bounds__(GT == 256 ? 512 : 256) void group_sums_kernel(Group
     }
   }
   if (steps > 0) take();
-  if (!(a.S_out || a.z_out)) write_slot(group_of(steps));
-  if (a.S_out && kh == 0) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) a.S_out[((size_t)bh * D + f0 + 8 * (r >> 2) + 4 * hi + (r & 3)) * D + c0 + l32] = acc[r];
-  }
-  if (a.z_out && tid < G::FW) a.z_out[(size_t)bh * D + zf] = zrun;
+  write_slot(group_of(steps));
 }
 
 template <int D, int GT, bool BACK>

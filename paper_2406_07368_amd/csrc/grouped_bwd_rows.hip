@@ -640,7 +640,8 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
   __syncthreads();
   walk(nk, true);
   if (G::NH > 1 && half == 0 && nt > G::RC) {              // uniform: the later queries
-    constexpr int PARTS = SPLIT ? 1 : 2;                   // what fits beside the accumulators
+    constexpr int PARTS = SPLIT ? 1 : 2;                   // what fits beside the accumulators (almost: with both sets of them
+                                                           // 34 registers spill at D = 128, 30 in groups of 64)
     RowLoad<D, GT, PARTS> more;
     const int nr = nt - G::RC;
     const uint16_t *gq1 = gq + (int64_t)G::RC * a.st, *gdo1 = gdo + (int64_t)G::RC * a.st;

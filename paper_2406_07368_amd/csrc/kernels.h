@@ -172,8 +172,6 @@ struct GroupSumsArgs {
   const void* a; const void* b;  // left rows (keys; backward: queries) and right rows (values; gradients), bf16, by strides
   const float* w; const float* wz;   // backward: weight of a left row in the matrix and in the vector part, [B*H][L]
   float* slots;
-  const float* S_in; const float* z_in;   // forward: what came before the sequence; null = zeros
-  float* S_out; float* z_out;             // forward: the sums over everything; null = not wanted
   int B, H, L, ng, relu;
   int64_t sb, sh, st;
 };

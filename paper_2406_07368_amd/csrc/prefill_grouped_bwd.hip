@@ -11,7 +11,7 @@
 //                    pbar = sum_i p_i dp_i,  ds_i = p_i (dp_i - pbar) / sqrt(d):
 //                    dq_t += sum_i ds_i k_i,   dk_i += ds_i q_t,   dv_i += p_i dO_t
 //   the sums         D_g = sum_{g' > g} (G_g', gz_g'):  dk_i += (D_g.S v_i + D_g.z) * phi'(k_i),  dv_i += D_g.S^T phi(k_i)
-//   conv             dv_s += sum_j w[c][j] dO[s + j][c],   dw[c][j] = sum_t dO[t][c] v[t - j][c]   (conv_long.hip)
+//   conv             dv_s += sum_j w[c][j] dO[s + j][c],   dw[c][j] = sum_t dO[t][c] v[t - j][c]   (conv_mfma.hip)
 //
 // Rows (dq, dk, dv): grouped_bwd_rows.hip.  Group-level sums, in this file one workgroup per (b, h, group):
 //   grouped_bwd_gs_kernel     G_g = (f phi(Q))^T dO and gz_g, contraction over the group's tokens (32 x 32 x 16 bf16 MFMA).
@@ -42,13 +42,6 @@ struct BwdCfg {
   static_assert(NT >= D, "one thread per feature in the z passes");
 };
 
-// phi(x) without a branch on the feature map (a branch per element would cut the unrolled loops into pieces): with
-// one = 1 for elu + 1 and 0 for max(x, 0), phi = max(x + one, one * min(exp(x), 1)).
-__device__ __forceinline__ float phi_f(float x, int relu) {
-  const float one = relu ? 0.f : 1.f;
-  const float e = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(x * 1.44269504088896340736f), 0.f, 1.f);
-  return fmaxf(x + one, one * e);
-}
 // rows tok0 .. tok0 + GT - 1 of two tensors -> LDS (rows past the end are zero rows); every request before the first store
 template <int D, int GT>
 __device__ __forceinline__ void load_rows2(const uint16_t* ga, const uint16_t* gb, int64_t st, int tok0, int nt,
@@ -102,6 +95,7 @@ __global__ __launch_bounds__(GT * 2) void grouped_bwd_gs_kernel(GroupedBwdArgs a
   const uint16_t* gdo = static_cast<const uint16_t*>(SUMS ? a.v : a.dout) + base;
   float* slot = SUMS ? a.P + ((size_t)bh * a.ng + g + 1) * G::SLOT : a.Dg + ((size_t)bh * a.ng + g) * G::SLOT;
   const size_t n = (size_t)a.B * a.H * a.L, e0 = (size_t)bh * a.L + tok0;
+  const float one = a.relu ? 0.f : 1.f;
 
   float f3 = 0.f, d4 = 0.f;
   if (tid < GT && tid < nt) {
@@ -121,7 +115,7 @@ __global__ __launch_bounds__(GT * 2) void grouped_bwd_gs_kernel(GroupedBwdArgs a
 #pragma unroll 8
     for (int i = 0; i < TPP; ++i) {
       const int t = part * TPP + i;                        // rows past the end are zero rows with weight 0
-      gz = fmaf(phi_f(bf16_bits_to_f32(Ql[t * G::KS + f]), a.relu), dd[t], gz);
+      gz = fmaf(phi_nb(bf16_bits_to_f32(Ql[t * G::KS + f]), one), dd[t], gz);
     }
     zp[part * D + f] = gz;
   }
@@ -153,8 +147,8 @@ __global__ __launch_bounds__(GT * 2) void grouped_bwd_gs_kernel(GroupedBwdArgs a
       u32x4 ah, al;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float x0 = fsp[2 * i] * phi_f(bf16_lo_to_f32(raw[i]), a.relu);
-        const float x1 = fsp[2 * i + 1] * phi_f(bf16_hi_to_f32(raw[i]), a.relu);
+        const float x0 = fsp[2 * i] * phi_nb(bf16_lo_to_f32(raw[i]), one);
+        const float x1 = fsp[2 * i + 1] * phi_nb(bf16_hi_to_f32(raw[i]), one);
         ah[i] = pack_bf16x2(x0, x1);
         al[i] = pack_bf16x2(x0 - bf16_lo_to_f32(ah[i]), x1 - bf16_hi_to_f32(ah[i]));
       }

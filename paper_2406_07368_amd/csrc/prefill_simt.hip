@@ -5,7 +5,11 @@
 
 namespace linattn {
 
-namespace { constexpr int HMAX = 7; }   // history rows kept in LDS: enough for the largest conv kernel (8 taps)
+namespace {
+constexpr int HMAX = 7;            // history rows kept in LDS: enough for the largest conv kernel (8 taps)
+constexpr int D = 64, GCT = 256;   // rows and groups (rows of 128 in groups of 256 would need 266 KB of LDS: no kernel)
+typedef IoF32 Io;
+}  // namespace
 
 // The three-branch form (grouped linear attention over the groups before a token's own, weight alpha + causal
 // softmax attention inside its group + masked conv) with fp32 arithmetic.
@@ -14,9 +18,8 @@ namespace { constexpr int HMAX = 7; }   // history rows kept in LDS: enough for 
 // (thread (c, tg) holds S[i][c] for i = tg, tg + NG, ...), the group's raw key rows and value rows in LDS in
 // the i/o dtype.  Exact to fp32 rounding; not built for speed.
 namespace {
-template <typename Io, int D, int GCT>
 struct GroupedSimtLayout {
-  typedef typename Io::elem elem;
+  typedef Io::elem elem;
   static constexpr int KSTR = D + 4 / (int)sizeof(elem);                  // key row stride: one 4-byte word of padding
   static constexpr int KR = 0;                                             // [GCT][KSTR] raw key rows of the group (elem)
   static constexpr int VV = KR + GCT * KSTR * (int)sizeof(elem);           // [HMAX+GCT][D]: history rows, then the group's value rows (elem)
@@ -30,14 +33,11 @@ struct GroupedSimtLayout {
   static constexpr int NFLOAT = SCAL + 16;
   static constexpr int TOTAL = F0 + NFLOAT * (int)sizeof(float);
 };
-__device__ __forceinline__ float elem_to_f32(float x) { return x; }
-__device__ __forceinline__ float elem_to_f32(uint16_t x) { return bf16_bits_to_f32(x); }
 }  // namespace
 
-template <typename Io, int D, int GCT>
 __global__ __launch_bounds__(256) void prefill_grouped_simt_kernel(PrefillArgs a) {
-  using Lay = GroupedSimtLayout<Io, D, GCT>;
-  typedef typename Io::elem elem;
+  using Lay = GroupedSimtLayout;
+  typedef Io::elem elem;
   constexpr int NG = 256 / D;
   constexpr int NS = D / NG;                           // state rows per thread
   constexpr int KSTR = Lay::KSTR;
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256) void prefill_grouped_simt_kernel(PrefillArgs a
           const elem* y = kr + i * KSTR + sub * (D / 4);
           const float* x = qr + sub * (D / 4);
 #pragma unroll 8
-          for (int f = 0; f < D / 4; ++f) acc = fmaf(x[f], elem_to_f32(y[f]), acc);
+          for (int f = 0; f < D / 4; ++f) acc = fmaf(x[f], y[f], acc);
         }
         acc += __shfl_xor(acc, 1);
         acc += __shfl_xor(acc, 2);
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) void prefill_grouped_simt_kernel(PrefillArgs a
         float lin = 0.f, loc = 0.f;
 #pragma unroll
         for (int m = 0; m < NS; ++m) lin = fmaf(fq[tg + NG * m], Sreg[m], lin);
-        for (int s2 = tg; s2 <= t; s2 += NG) loc = fmaf(lg[s2], elem_to_f32(vv[(HMAX + s2) * D + c]), loc);
+        for (int s2 = tg; s2 <= t; s2 += NG) loc = fmaf(lg[s2], vv[(HMAX + s2) * D + c], loc);
         part[tg * D + c] = fmaf(scal[0], lin, loc);
       }
       __syncthreads();
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256) void prefill_grouped_simt_kernel(PrefillArgs a
         float u = 0.f;
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          if (j < Kc) u = fmaf(wreg[j], elem_to_f32(vv[(HMAX + t - j) * D + tid]), u);
+          if (j < Kc) u = fmaf(wreg[j], vv[(HMAX + t - j) * D + tid], u);
         Io::store1(a.out, base + (int64_t)(t0 + t) * a.st + tid, y + u);
       }
       // the next token's step b writes qr, fq (read in c, e: both behind barriers by then); lg, part and scal are
@@ -163,13 +163,13 @@ __global__ __launch_bounds__(256) void prefill_grouped_simt_kernel(PrefillArgs a
     __syncthreads();
     // f. the group enters the sums: S += phi(K)^T V, z += colsum phi(K); the history slides forward by nt rows
     for (int s2 = 0; s2 < nt; ++s2) {
-      const float x = elem_to_f32(vv[(HMAX + s2) * D + c]);
+      const float x = vv[(HMAX + s2) * D + c];
 #pragma unroll
-      for (int m = 0; m < NS; ++m) Sreg[m] = fmaf(phi_any(elem_to_f32(kr[s2 * KSTR + tg + NG * m]), a.relu), x, Sreg[m]);
+      for (int m = 0; m < NS; ++m) Sreg[m] = fmaf(phi_any(kr[s2 * KSTR + tg + NG * m], a.relu), x, Sreg[m]);
     }
     if (tid < D) {
       float zs = zz[tid];
-      for (int s2 = 0; s2 < nt; ++s2) zs += phi_any(elem_to_f32(kr[s2 * KSTR + tid]), a.relu);
+      for (int s2 = 0; s2 < nt; ++s2) zs += phi_any(kr[s2 * KSTR + tid], a.relu);
       zz[tid] = zs;
       for (int r = 0; r < HMAX; ++r) vv[r * D + tid] = vv[(r + nt) * D + tid];
     }
@@ -188,15 +188,13 @@ __global__ __launch_bounds__(256) void prefill_grouped_simt_kernel(PrefillArgs a
     }
 }
 
-// fp32 rows of 128 elements in groups of 256 would need 266 KB of LDS for the group's rows: no kernel.
 hipError_t launch_prefill_grouped_simt(const PrefillArgs& a, int d, hipStream_t st) {
-  if (d != 64 || a.group != 256) return hipErrorInvalidValue;
-  constexpr int bytes = GroupedSimtLayout<IoF32, 64, 256>::TOTAL;
+  if (d != D || a.group != GCT) return hipErrorInvalidValue;
+  constexpr int bytes = GroupedSimtLayout::TOTAL;
   static_assert(bytes <= 160 * 1024, "LDS");
-  auto kern = prefill_grouped_simt_kernel<IoF32, 64, 256>;
-  hipError_t e = LINATTN_MAX_LDS_ONCE(kern, bytes);
+  hipError_t e = LINATTN_MAX_LDS_ONCE(prefill_grouped_simt_kernel, bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(a.B * a.H)), dim3(256), bytes, st, a);
+  hipLaunchKernelGGL(prefill_grouped_simt_kernel, dim3((unsigned)(a.B * a.H)), dim3(256), bytes, st, a);
   return hipGetLastError();
 }
 
