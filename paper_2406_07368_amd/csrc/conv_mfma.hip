@@ -14,11 +14,11 @@
 // 16, both factors bf16 as they are), summed along its diagonals: first over the four accumulator registers by shifts
 // inside a row of 16 lanes, then over the four rows through LDS.
 //
-// One workgroup = 256 or 512 tokens of 32 channels (16 or 8 where few would run) of one (b, h[, value block]), four waves.  The rows are turned
-// around on their way into LDS ([channel][token], two tokens per dword: a thread takes 8 channels of two neighbouring
-// tokens), so that an operand of eight consecutive tokens is one 16-byte read and one of every sixteenth token one
-// transpose read; the results go back the same way.  The LDS rows are skewed per 8 channels so that those accesses hit 64
-// different banks.
+// One workgroup = 256 or 512 tokens of 32 channels (16 or 8 where few would run) of one (b, h[, value block]), four waves.
+// The rows are turned around on their way into LDS ([channel][token], two tokens per dword: a thread takes 8 channels of
+// two neighbouring tokens), so that an operand of eight consecutive tokens is one 16-byte read and one of every sixteenth
+// token one transpose read; the results go back the same way.  The LDS rows are skewed per 8 channels so that those
+// accesses hit 64 different banks.
 // What bounds it: the LDS port, most of it the tap operands (nine KB per tile and channel), which is why a workgroup takes
 // two tiles of 256 tokens where there are enough of them (104 -> 84 us below).  Measured on B8 H8 L8192 d128 with 63 taps:
 // forward 84 us for 290 MB (158 us on the vector ALUs, a thread per channel: 63 multiply-adds per element); backward 185 us

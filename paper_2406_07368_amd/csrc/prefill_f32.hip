@@ -16,9 +16,8 @@
 // What bounds it: the fp32 matrix rate (160 instructions of 64 cycles per wave, step and SIMD at D = 128), and for short
 // sequences the latency of a step, about 3 us.  Sequences are cut into segments when the heads alone do not fill the
 // chip: three launches (state-only pass, prefix sum, full pass).  Short sequences on few heads take the quadratic kernel
-// below instead, which has no serial chain.  Measured (one call, launches queued; before: one workgroup per head on the
-// vector ALUs): B1 H4 L1024 D64 24 us, B2 H32 L1024 D128 117 us (12 ms before, in the three-branch form); the three-branch
-// form 45 and 139 us.
+// below instead, which has no serial chain.  Measured (us a call, launches queued; before: one workgroup per head on the
+// vector ALUs): B1 H4 L1024 D64 26 (1160 before), B2 H32 L1024 D128 118 (4190); the three-branch form 36 (2830) and 148 (6490).
 #include "common.h"
 #include "kernels.h"
 #include "mfma_util.h"
@@ -434,8 +433,8 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
 // tiles of earlier groups go into a linear sum of their own and one wave takes the group's own (at most two) tiles with
 // the softmax.
 // What bounds it: one trip to memory, then the fp32 matrix rate of one compute unit (0.43 us per pair of tiles at D = 64,
-// 0.85 us at D = 128), quadratic in the length -- hence for short sequences only.  Measured: B1 H4 L256 D64 13 us a call
-// (293 us before, 24 us as the three launches of the walk).
+// 0.85 us at D = 128), quadratic in the length -- hence for short sequences only.  Measured: B1 H4 L256 D64 18 us a call
+// (294 us before, 26 us as the three launches of the walk).
 namespace {
 constexpr int DW = 8;                                      // waves
 template <int D>
@@ -745,9 +744,10 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
 
 // The quadratic kernel or the walk?  The quadratic kernel's time grows with the longest query tile's chain and with the
 // sum of all tile pairs over the chip, the walk's is three launches and hardly moves at these sizes.  Measured, us per call
-// quadratic / walk: D = 64: 1632 pairs 20 / 24, 1728 pairs 26 / 26, 4 heads of 32 tiles 30 / 24; D = 128: 144 pairs 23 / 32,
-// 1088 pairs 35 / 35, 2304 pairs 66 / 44.  Three-branch form (two kinds of steps in the walk): D = 64: 2112 pairs 32 / 45,
-// 4512 pairs 43 / 45, 6336 pairs 57 / 46; D = 128: 1088 pairs 36 / 67, 2304 pairs 76 / 75.
+// quadratic / walk: D = 64: 12 heads of 16 tiles (1632 pairs) 21 / 26, 48 of 8 (1728) 24 / 28, 4 of 24 26 / 25, 4 of 32 32 / 26; D = 128: 4 of
+// 8 (144) 24 / 33, 28 of 8 (1008) 30 / 39, 7 of 16 (952) 36 / 35, 8 of 16 (1088) 36 / 36, 64 of 8 (2304) 51 / 44.  Three-branch form (two
+// kinds of steps in the walk): D = 64: 4 of 32 (2112) 33 / 49, 32 of 16 (4352) 40 / 51, 12 of 32 (6336) 47 / 50; D = 128: 8 of 16 (1088)
+// 36 / 70, 4 of 32 (2112) 59 / 70, 64 of 8 (2304) 59 / 75.
 static bool prefill_f32_direct_pays(int heads, int tiles, int d, bool grouped) {
   const int64_t pairs = (int64_t)heads * tiles * (tiles + 1) / 2;
   if (grouped) return tiles <= 48 && pairs <= (d == 64 ? 4400 : 2200);
