@@ -22,6 +22,8 @@
 #include "kernels.h"
 #include "mfma_util.h"
 
+#include <type_traits>
+
 namespace linattn {
 
 namespace {
@@ -238,7 +240,7 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
       for (int kt = 0; kt < G::TILES; ++kt) {
         if (kt > p) break;                                 // uniform
         f32x16 sc;
-        constexpr int CH = GROUPED && D == 64 ? 2 : 1;     // logits: chains of D / 4 features (see the quadratic kernel)
+        constexpr int CH = !GROUPED ? 1 : D == 64 ? 4 : 2; // logits: chains of D / 8 features (see the quadratic kernel)
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
           f32x16 part;
@@ -318,16 +320,17 @@ __global__ __launch_bounds__(2 * D, GROUPED ? 1 : 2) void prefill_f32_kernel(Pre
           }
         }
         top = fmaxf(top, __shfl_xor(top, 32));
-        float mass = 0.f;
+        float sum[4] = {};
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt) {
           if (kt > p) break;
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             pt[kt][r] = __builtin_amdgcn_exp2f((pt[kt][r] - top) * to_log2);
-            mass += pt[kt][r];
+            sum[r % 4] += pt[kt][r];
           }
         }
+        float mass = (sum[0] + sum[1]) + (sum[2] + sum[3]);
         mass += __shfl_xor(mass, 32);                      // the token itself is always seen: mass >= 1
         const float f = den != 0.f ? a.alpha / den : 0.f;  // nothing before the group: no branch
         if (hi == 0) { sc0[l32] = 1.f / mass; sc0[32 + l32] = f * mass; }
@@ -570,9 +573,14 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
       for (int cb = 0; cb < IB; ++cb) vx[cb][r] = gv[(int64_t)(tv < L ? tv : L - 1) * a.st_v + 32 * cb + l32];
     }
   };
-  // scores of key tile kt: sc[r] = key acc_row(r), query l32; raw: the rows as they are, else under the feature map.  Raw
-  // ones in four chains of D / 4 features: a logit may be a small difference of large products, and the rounding of one long
-  // chain showed (rows of unit normals, d = 128: 9.9e-8 of the result against 6.7e-8).
+  // scores of key tile kt: sc[r] = key acc_row(r), query l32; raw: the rows as they are, else under the feature map.
+  // In the three-branch form all sums are cut into short chains, so that the outputs are no further from the exact ones
+  // than those of the vector ALUs that did this before (logits in four chains per row, weights times values in four): raw
+  // scores eight chains of D / 8 features (a logit may be a small difference of large products), mapped ones four (two
+  // at d = 128, where four spill: 30 us -> 28 at B1 H4 L256 with two), the own group's weights times values chains of 8 keys,
+  // the earlier groups' of 16 at d = 64.  2-norm error, rows of d^-1/2 / unit normals, against 4.8e-8 / 6.0e-8 (d = 64) and
+  // 4.9e-8 / 6.6e-8 (d = 128): one chain each 5.2 / 8.2 and 5.3 / 9.9; as it is 4.8 / 5.9 and 4.9 / 6.2, for 0 to 3 % of the time
+  // (B1 H4 L256 d64 18 us either way, B2 H8 L289 d128 28 -> 28.5).  The token form is closer than the vector ALUs with one chain.
   auto scores = [&](int kt, bool raw, f32x16& sc) __attribute__((always_inline)) {
     f32x4 kf[IB][4];
     const int tok = FT * kt + l32;
@@ -581,7 +589,7 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
     for (int ib = 0; ib < IB; ++ib)
 #pragma unroll
       for (int j = 0; j < 4; ++j) kf[ib][j] = *reinterpret_cast<const f32x4*>(p + 32 * ib + 8 * j);
-    const int chains = raw ? 4 : 1;
+    const int chains = raw ? 8 : !GROUPED ? 1 : D == 64 ? 4 : 2;
 #pragma unroll
     for (int c = 0; c < chains; ++c) {
       f32x16 part;
@@ -596,11 +604,30 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
       sc = c == 0 ? part : sc + part;
     }
   };
+  // acc += weights times value(cb, r), in chains of 32 / n keys, a channel block at a time
+  auto add_in_chains = [&](auto n, const f32x16& sc, auto value) __attribute__((always_inline)) {
+    constexpr int PER = 16 / decltype(n)::value;
+#pragma unroll
+    for (int cb = 0; cb < IB; ++cb)
+#pragma unroll
+      for (int r0 = 0; r0 < 16; r0 += PER) {
+        f32x16 part;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[r] = 0.f;
+#pragma unroll
+        for (int r = r0; r < r0 + PER; ++r) part = mfma32(sc[r], value(cb, r), part);
+        acc[cb] += part;
+      }
+  };
   auto weigh = [&](const f32x16& sc, const float (&vx)[IB][16]) __attribute__((always_inline)) {
+    if constexpr (D == 64) {
+      add_in_chains(std::integral_constant<int, 2>(), sc, [&](int cb, int r) { return vx[cb][r]; });
+    } else {                                               // (no registers left for a second sum)
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
+      for (int r = 0; r < 16; ++r)
 #pragma unroll
-      for (int cb = 0; cb < IB; ++cb) acc[cb] = mfma32(sc[r], vx[cb][r], acc[cb]);
+        for (int cb = 0; cb < IB; ++cb) acc[cb] = mfma32(sc[r], vx[cb][r], acc[cb]);
+    }
   };
   // the same with values that may not be finite, and what those add
   auto weigh_finite = [&](const f32x16& sc, const float (&vx)[IB][16]) __attribute__((always_inline)) {
@@ -652,29 +679,35 @@ __global__ __launch_bounds__(64 * DW, 2) void prefill_f32_direct_kernel(PrefillA
       top = fmaxf(top, fmaxf(s0[r], s1[r]));
     }
     top = fmaxf(top, __shfl_xor(top, 32));
-    float mass = 0.f;
+    float sum[4] = {};
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       s0[r] = __builtin_amdgcn_exp2f((s0[r] - top) * to_log2);
       s1[r] = __builtin_amdgcn_exp2f((s1[r] - top) * to_log2);
-      mass += s0[r] + s1[r];
+      sum[r % 4] += s0[r] + s1[r];
     }
+    float mass = (sum[0] + sum[1]) + (sum[2] + sum[3]);
     mass += __shfl_xor(mass, 32);                          // the token itself is always seen: mass >= 1
     if (hi == 0) smf[G::SC + l32] = mass;
-    const float odd = weigh_finite(s1, v1);
-    if (two) weigh(s0, v0);
+    float odd = 0.f;
+    const std::integral_constant<int, 4> four;
+    add_in_chains(four, s1, [&](int cb, int r) { return finite_part(v1[cb][r], odd); });
+    if (two) add_in_chains(four, s0, [&](int cb, int r) { return v0[cb][r]; });
     weigh_rest(odd, qt, s1);
   } else {
     for (int kt = first; kt < kt0; kt += step) {
       f32x16 sc;
       float vx[IB][16];
-      values(kt, vx);
+      if (!GROUPED || D == 64) values(kt, vx);             // (ahead of the scores where there are registers)
       scores(kt, false, sc);
+      if (GROUPED && D == 128) values(kt, vx);
+      float sum[4] = {};
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         if (!GROUPED) sc[r] = (kt < qt || acc_row(r, hi) <= l32) ? sc[r] : 0.f;
-        rs += sc[r];
+        sum[r % 4] += sc[r];
       }
+      rs += (sum[0] + sum[1]) + (sum[2] + sum[3]);
       if constexpr (GROUPED) weigh(sc, vx);                // whole tiles of earlier groups
       else weigh_rest(weigh_finite(sc, vx), kt, sc);
     }

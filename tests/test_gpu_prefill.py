@@ -446,3 +446,20 @@ def test_fp32_walk_in_segments_or_whole_heads(form, B, H, L, d, d_v, Kc, segment
         torch.cuda.synchronize()
         compare((host(out), *(host(x) for x in res)), want, "f32", f"{form} L={L} d={d} d_v={d_v} workspace={nbytes}")
     assert bool(torch.isfinite(ws).any()) == segments
+
+
+@pytest.mark.parametrize("unit", [False, True])
+@pytest.mark.parametrize("B,H,L,d", [(1, 8, 256, 64), (2, 4, 289, 128), (1, 8, 1200, 64), (2, 16, 400, 128)])   # quadratic kernel, walk
+def test_fp32_three_branch_rounds_no_more_than_short_chains_do(B, H, L, d, unit):
+    """Rows of d^-1/2 or of unit normals (where the logits' rounding shows).  The bound is what fp32 arithmetic reaches with the
+    logits and the local outputs in four chains per row (4.7e-8 to 4.9e-8 and 5.9e-8 to 6.1e-8 at d = 64, 4.9e-8 and 6.6e-8 at
+    d = 128, over lengths of 64 to 4000), and 1 % for the draw; one chain each gives 5.2e-8 and 8.1e-8, 5.3e-8 and 9.9e-8."""
+    rng = np.random.default_rng(6700 + L)
+    scale = 1.0 if unit else d ** -0.5
+    q, k = ((rng.standard_normal((B, H, L, d)) * scale).astype(np.float32) for _ in range(2))
+    v = rng.standard_normal((B, H, L, d)).astype(np.float32)
+    w = (rng.standard_normal((H, d, 3)) * 0.5).astype(np.float32)
+    out, _ = binding.prefill_grouped(dev(q), dev(k), dev(v), dev(w), 1.0, None, 0.0, want_state=False)
+    want = oracle.prefill_grouped(q, k, v, w, 64)[0]
+    err = float(np.linalg.norm(host(out).astype(np.float64) - want) / np.linalg.norm(want))
+    assert err <= {64: (4.95e-8, 6.15e-8), 128: (5.0e-8, 6.7e-8)}[d][unit], err
