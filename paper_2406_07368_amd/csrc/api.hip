@@ -444,13 +444,12 @@ linattn_status linattn_verify(const linattn_desc* desc, int32_t kk, const void* 
   a.B = desc->B; a.H = desc->H; a.kk = kk; a.Kc = desc->conv_k; a.eps = desc->eps; a.relu = desc->phi == LINATTN_PHI_RELU;
   const int m = value_blocks(desc);
   a.dv = m * desc->d;
-  const int nsplit = verify_pick_split(desc->B * desc->H * m);
   const bool bf16 = desc->io_dtype == LINATTN_BF16;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  // whole blocks of d value channels per workgroup on the matrix cores when there are enough of them to fill the
-  // chip (B H m >= 768), column slices of a head's state on the streaming kernel otherwise
-  const hipError_t e = verify_mfma_available(bf16, desc->d, nsplit, kk) ? launch_verify_mfma(a, desc->d, stream)
-                                                                        : launch_verify(a, bf16, desc->d, nsplit, stream);
+  // blocks of d value channels on the matrix cores when there are enough of them to fill the chip, the streaming
+  // kernel otherwise
+  const hipError_t e = verify_mfma_available(bf16, desc->d, desc->B * desc->H * m, kk) ? launch_verify_mfma(a, desc->d, stream)
+                                                                                       : launch_verify(a, bf16, desc->d, stream);
   return e == hipSuccess ? LINATTN_OK : LINATTN_ERR_HIP;
 }
 

@@ -180,12 +180,11 @@ bool group_sums_pays(int heads, int ng, int d, int group);
 hipError_t launch_group_sums(const GroupSumsArgs& a, int d, int group, bool back, hipStream_t st);
 
 // verify.hip
-int verify_pick_split(int BH);
-hipError_t launch_verify(const VerifyArgs& a, bool bf16, int d, int nsplit, hipStream_t st);
+hipError_t launch_verify(const VerifyArgs& a, bool bf16, int d, hipStream_t st);
 hipError_t launch_verify_z(const VerifyArgs& a, bool bf16, int d, hipStream_t st);   // z += accepted phi(k), all heads
 
 // verify_mfma.hip : the same step as one 16-token group on the matrix cores (bf16 drafts, whole heads)
-bool verify_mfma_available(bool bf16, int d, int nsplit, int kk);
+bool verify_mfma_available(bool bf16, int d, int blocks, int kk);   // blocks: B H d_v / d
 hipError_t launch_verify_mfma(const VerifyArgs& a, int d, hipStream_t st);
 
 // verify_grouped.hip : generation with the three-branch form (state of the completed groups + the open group's rows)

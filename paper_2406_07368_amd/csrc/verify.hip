@@ -2,26 +2,35 @@
 // always kept).  Memory-bound: every head's fp32 state S (d x d) is read once
 // and, if any draft is accepted, written once; everything else is tiny.
 //
-// One workgroup of 256 threads owns the column slice S[:, c0 : c0+CW] of one
-// (b, h).  The slice streams through registers in row passes with 16-byte loads
-// (rows are contiguous, so a wave reads whole 128..512 B row segments; nontemporal:
-// the state is touched once per step), a few
+// One workgroup of NT threads owns one (b, h) (value rows wider than 128: the column
+// slice S[:, c0 : c0+CW] of it).  The state streams through registers in row passes
+// with 16-byte loads (rows are contiguous, so a wave reads whole 256..512 B row
+// segments; nontemporal: the state is touched once per step), a few
 // passes in flight at a time: each row adds its term to the kk read-outs
 // phi(q_j)^T S, receives the accepted rank-1 updates and is written straight back.
 // The read-outs are then reduced across the threads that share a column group,
 // completed with the causal in-block term, normalised, and joined with the
 // convolution over (history ++ drafts <= j).
+//
+// What bounds it: with few heads the one launch and its chain of request, products,
+// reduction (6 us of GPU time, behind a host call of about 11); with many the state's
+// traffic.  Few heads get more threads each (pick_threads), so that the whole state
+// is requested at once.  Splitting a head's columns over four workgroups instead put as
+// many requests under way, but then all of them read the old z and a second launch had
+// to advance it, and every slice repeated the drafts' feature maps and scores.  us a call,
+// slices / whole heads: B1 H32 d128 one draft 14.7 / 11.6, eight 14.6 / 11.4; B8 H32 d128 eight 19.8 /
+// 14.9; B8 H32 d64 sixteen 26.8 / 12.7.
 #include "common.h"
 #include "kernels.h"
 
 namespace linattn {
 
-template <int D, int CW, int KP>
+template <int D, int CW, int KP, int NT>
 struct VerifySmem {
   float fq[D][KP];          // phi(q_j)[i], feature-major so one thread reads all drafts of its row
   float fk[D][KP];          // phi(k_j)[i]
   float vv[KP][CW];         // v_j[c0 + c]
-  float red[4][KP][CW];     // per-wave partial read-outs
+  float red[NT / kWave][KP][CW];   // per-wave partial read-outs
   float amat[KP][KP];       // phi(q_j).phi(k_j') for j' <= j, else 0
   float den[KP];            // phi(q_j).z + sum_j' amat + eps
   float zz[D];
@@ -43,16 +52,15 @@ __device__ __forceinline__ void load_row(const float* row, float (&f)[KP]) {
   }
 }
 
-// At most 128 registers per thread for up to 8 drafts, so that four workgroups fit on a compute unit
-// and B*H = 1024 heads are all resident at once (a partial second round would run at a fraction of
-// the bandwidth).
-template <typename Io, int D, int CW, int KP>
-__global__ __launch_bounds__(256, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyArgs a) {
+// At most 128 registers per thread for up to 8 drafts: 16 waves fit on a compute unit, so that B*H = 1024 heads of
+// 256 threads are all resident at once (a partial second round would run at a fraction of the bandwidth).
+template <typename Io, int D, int CW, int KP, int NT>
+__global__ __launch_bounds__(NT, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyArgs a) {
   constexpr int CG = CW / 4;          // float4 column groups per row slice
-  constexpr int RPP = 256 / CG;       // rows covered per pass
+  constexpr int RPP = NT / CG;        // rows covered per pass
   constexpr int NPASS = D / RPP;
   static_assert(NPASS >= 1 && RPP * NPASS == D, "tile shape");
-  __shared__ VerifySmem<D, CW, KP> sm;
+  __shared__ VerifySmem<D, CW, KP, NT> sm;
 
   const int tid = threadIdx.x;
   // value rows of DV = a.dv elements (a multiple of D; DV == D: d_v = d_k): DV / CW column slices per head, and
@@ -72,12 +80,12 @@ __global__ __launch_bounds__(256, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyAr
   const int64_t tok0 = (int64_t)bh * kk * D;              // q, k
   const int64_t vtok0 = (int64_t)bh * kk * DV;            // v, out
   const int64_t hist0 = (int64_t)bh * (Kc - 1) * DV;
-  constexpr int QK_IT = (KP * (D / 8) + 255) / 256;   // 8-element pieces of q and k per thread
-  constexpr int V_IT = (KP * (CW / 8) + 255) / 256;
+  constexpr int QK_IT = (KP * (D / 8) + NT - 1) / NT;   // 8-element pieces of q and k per thread
+  constexpr int V_IT = (KP * (CW / 8) + NT - 1) / NT;
   typename Io::raw8 rq[QK_IT], rk[QK_IT], rv[V_IT];
 #pragma unroll
   for (int m = 0; m < QK_IT; ++m) {
-    const int c8 = tid + 256 * m;
+    const int c8 = tid + NT * m;
     const int j = c8 / (D / 8), i0 = (c8 % (D / 8)) * 8;
     const int64_t off = tok0 + (int64_t)(j < kk ? j : kk - 1) * D + i0;
     rq[m] = Io::load_raw8(a.q, off);
@@ -85,20 +93,20 @@ __global__ __launch_bounds__(256, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyAr
   }
 #pragma unroll
   for (int m = 0; m < V_IT; ++m) {
-    const int c8 = tid + 256 * m;
+    const int c8 = tid + NT * m;
     const int j = c8 / (CW / 8), cc = (c8 % (CW / 8)) * 8;
     rv[m] = Io::load_raw8(a.v, vtok0 + (int64_t)(j < kk ? j : kk - 1) * DV + c0 + cc);
   }
   const float zreg = a.z[(size_t)bh * D + tid % D];
-  // taps and history rows of the slice's channels: element e = tid + 256 m of the [8][CW] arrays in LDS
-  constexpr int TAP_IT = (8 * CW + 255) / 256;
+  // taps and history rows of the slice's channels: element e = tid + NT m of the [8][CW] arrays in LDS
+  constexpr int TAP_IT = (8 * CW + NT - 1) / NT;
   float tap_reg[TAP_IT], hist_reg[TAP_IT];
   // (one tap: no history; the request then reads a draft's value row, which is dropped)
   const void* hsrc = Kc > 1 ? a.hist : a.v;
   const int64_t hbase = (Kc > 1 ? hist0 : vtok0) + c0;
 #pragma unroll
   for (int m = 0; m < TAP_IT; ++m) {
-    const int e = (tid + 256 * m) % (8 * CW);
+    const int e = (tid + NT * m) % (8 * CW);
     const int t = e / CW, cc = e % CW;
     tap_reg[m] = a.conv_w[((size_t)h * DV + c0 + cc) * Kc + (t < Kc ? t : 0)];
     hist_reg[m] = Io::load1(hsrc, hbase + (int64_t)(t < Kc - 1 ? Kc - 2 - t : 0) * DV + cc);
@@ -108,7 +116,7 @@ __global__ __launch_bounds__(256, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyAr
 
   // ---- 0. the state slice streams through a window of PD row passes: the first PD loads are
   //         in flight before anything else, each later one is issued when its slot frees up ----
-  constexpr int PDW = KP >= 8 ? 2 : 4;        // fewer passes in flight when the read-outs need the registers
+  constexpr int PDW = KP == 8 ? 2 : 4;        // fewer passes in flight when the read-outs need the registers
   constexpr int PD = NPASS < PDW ? NPASS : PDW;
   float* Sg = a.S + (size_t)bh * D * DV + c0 + 4 * cg;
   f32x4 s[PD];
@@ -124,7 +132,7 @@ __global__ __launch_bounds__(256, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyAr
   // ---- 1. drafts -> LDS (phi applied), normaliser, taps and history -> LDS -----------------------
 #pragma unroll
   for (int m = 0; m < QK_IT; ++m) {
-    const int c8 = tid + 256 * m;
+    const int c8 = tid + NT * m;
     const int j = c8 / (D / 8), i0 = (c8 % (D / 8)) * 8;
     if (c8 < KP * (D / 8)) {
       float xq[8], xk[8];
@@ -139,7 +147,7 @@ __global__ __launch_bounds__(256, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyAr
   }
 #pragma unroll
   for (int m = 0; m < V_IT; ++m) {
-    const int c8 = tid + 256 * m;
+    const int c8 = tid + NT * m;
     const int j = c8 / (CW / 8), cc = (c8 % (CW / 8)) * 8;
     if (c8 < KP * (CW / 8)) {
       float xv[8];
@@ -151,7 +159,7 @@ __global__ __launch_bounds__(256, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyAr
   if (tid < D) sm.zz[tid] = zreg;
 #pragma unroll
   for (int m = 0; m < TAP_IT; ++m) {
-    const int e = tid + 256 * m;
+    const int e = tid + NT * m;
     if (e < 8 * CW) {
       const int t = e / CW, cc = e % CW;
       sm.wt[t][cc] = t < Kc ? tap_reg[m] : 0.f;
@@ -161,9 +169,33 @@ __global__ __launch_bounds__(256, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyAr
   __syncthreads();
 
   // ---- 2. in-block scores and denominators ----------------------------------------
-  {
+  if constexpr (KP == 16) {
+    // 16 drafts: phi(Q) phi(K)^T on wave 0, phi(Q) z on wave 1, fp32 products on 16 x 16 x 4 matrix instructions (lane =
+    // draft lane % 16 and feature lane / 16 of a step) in four chains over the features.  A thread per pair of drafts
+    // had 64 steps of LDS reads in a row (us a call, d = 128: 4 heads 17.5, now 14.3; 256 heads 22.4, now 17.2).
+    const int wv = tid / kWave, lane = tid % kWave, l16 = lane % 16, g4 = lane / 16;
+    if (wv < 2) {                                          // uniform per wave
+      f32x4 part[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) part[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+      for (int i = 0; i < D; i += 16)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int f = i + 4 * c + g4;
+          part[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(sm.fq[f][l16], wv == 0 ? sm.fk[f][l16] : sm.zz[f], part[c], 0, 0, 0);
+        }
+      const f32x4 x = (part[0] + part[1]) + (part[2] + part[3]);   // row (draft of q) 4 g4 + e, column (draft of k) l16
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = 4 * g4 + e;
+        if (wv == 0) sm.amat[j][l16] = (l16 <= j && j < kk) ? x[e] : 0.f;
+        else if (l16 == 0) sm.den[j] = x[e];               // completed below
+      }
+    }
+  } else {
     constexpr int NPAIR = KP * KP;
-    constexpr int TPP = (256 / NPAIR) > 64 ? 64 : (256 / NPAIR);   // threads per (j, j') pair
+    constexpr int TPP = (NT / NPAIR) > 64 ? 64 : (NT / NPAIR);   // threads per (j, j') pair
     if (tid < NPAIR * TPP) {
       const int pair = tid / TPP, sub = tid % TPP;
       const int j = pair / KP, jp = pair % KP;
@@ -246,9 +278,11 @@ __global__ __launch_bounds__(256, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyAr
   __syncthreads();
 
   // ---- 4. outputs: normalise, add the causal convolution -------------------------------
-  for (int idx = tid; idx < kk * CW; idx += 256) {
+  for (int idx = tid; idx < kk * CW; idx += NT) {
     const int j = idx / CW, c = idx % CW;
-    float num = sm.red[0][j][c] + sm.red[1][j][c] + sm.red[2][j][c] + sm.red[3][j][c];
+    float num = 0.f;
+#pragma unroll
+    for (int v = 0; v < NT / kWave; ++v) num += sm.red[v][j][c];
     for (int jp = 0; jp <= j; ++jp) num = fmaf(sm.amat[j][jp], sm.vv[jp][c], num);
     float u = 0.f;
     for (int t = 0; t < Kc; ++t) {
@@ -268,7 +302,7 @@ __global__ __launch_bounds__(256, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyAr
   }
   if (Kc > 1) {
     __syncthreads();   // every conv read of the old history is done
-    for (int c = tid; c < CW; c += 256) {
+    for (int c = tid; c < CW; c += NT) {
       for (int r = 0; r < Kc - 1; ++r) {
         const int sidx = n - (Kc - 1) + r;   // position in (history ++ accepted drafts)
         const int64_t dst = hist0 + (int64_t)r * DV + c0 + c;
@@ -279,8 +313,8 @@ __global__ __launch_bounds__(256, (KP <= 8 ? 4 : 2)) void verify_kernel(VerifyAr
   }
 }
 
-// z += sum of the accepted phi(k_j); used when a head's columns are split over
-// several workgroups (they all read the old z, so it cannot be updated by one of them).
+// z += sum of the accepted phi(k_j); used when several workgroups have a head's value columns
+// (they all read the old z, so it cannot be updated by one of them).
 template <typename Io, int D>
 __global__ __launch_bounds__(256) void verify_z_kernel(VerifyArgs a) {
   const int gid = blockIdx.x * 256 + threadIdx.x;
@@ -316,41 +350,63 @@ hipError_t launch_verify_z(const VerifyArgs& a, bool bf16, int d, hipStream_t st
   return hipGetLastError();
 }
 
-template <typename Io, int D, int CW>
+template <typename Io, int D, int CW, int KP, int NT>
+static hipError_t launch_nt(const VerifyArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL((verify_kernel<Io, D, CW, KP, NT>), dim3((unsigned)(a.B * a.H * (a.dv / CW))), dim3(NT), 0, st, a);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess || a.dv == CW ? e : launch_verify_z(a, sizeof(typename Io::elem) == 2, D, st);
+}
+
+// Threads per workgroup.  More threads ask for more of the state at once and shorten the chain of row passes, which
+// is all that counts while every workgroup has a compute unit of its own; beyond that, fewer threads let more workgroups
+// share one (and 8 drafts, 120 registers, fill it with 1024 threads).  Measured, us a call, 256 / 512 / 1024 threads, 128 x 128 state:
+//   1 draft    256 heads 14.3 / 11.5 / 11.4, 512 17.8 / 13.9 / 12.9, 576 19.5 / 16.1 / 15.1, 640 19.9 / 16.8 / 18.8, 768 21.2 / 19.4 / 21.1,
+//              1024 26.0 / 28.8 / 26.9
+//   4 drafts   256 heads 16.3 / 12.2 / 11.5, 320 18.6 / 14.4 / 16.1, 512 20.3 / 16.0 / 17.2, 640 22.5 / 23.6 / 23.8
+//   8 drafts   32 heads 15.3 / 11.4 / 11.8, 192 17.9 / 13.7 / 12.9, 256 21.8 / 16.3 / 14.9, 320 24.7 / 19.6 / 24.8, 512 26.4 / 21.3 / 26.8, 640 29.6 / 31.9 / 37.2
+//   16 drafts  4 heads 20.0 / 14.3, 320 30.6 / 29.1, 640 58.6 / 45.0, 1024 65.3 / 62.1 (1024 threads: registers)
+// 64 x 128 state, 256 / 512 threads: 8 drafts 128 heads 11.9 / 11.4, 384 14.7 / 13.3, 768 19.9 / 23.4; 16 drafts 384 18.5 / 23.4, 1024 38.2 / 45.2.
+// 64 x 64: 256 threads have a row each in four passes.
+static int pick_threads(int state, int kp, int blocks) {
+  if (state == 64 * 64) return 256;
+  if (state == 64 * 128) return blocks <= (kp == 16 ? 256 : 384) ? 512 : 256;
+  if (kp == 16) return 512;
+  if (kp == 1) return blocks <= 576 ? 1024 : blocks < 1024 ? 512 : 256;
+  if (kp == 8 && blocks <= 64) return 512;
+  return blocks <= 256 ? 1024 : blocks <= 512 ? 512 : 256;
+}
+
+template <typename Io, int D, int CW, int KP>
 static hipError_t launch_kp(const VerifyArgs& a, hipStream_t st) {
-  const dim3 grid((unsigned)(a.B * a.H * (a.dv / CW))), block(256);
-  if (a.kk <= 1) hipLaunchKernelGGL((verify_kernel<Io, D, CW, 1>), grid, block, 0, st, a);
-  else if (a.kk <= 4) hipLaunchKernelGGL((verify_kernel<Io, D, CW, 4>), grid, block, 0, st, a);
-  else if (a.kk <= 8) hipLaunchKernelGGL((verify_kernel<Io, D, CW, 8>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((verify_kernel<Io, D, CW, 16>), grid, block, 0, st, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (a.dv / CW > 1) {
-    const int total = a.B * a.H * D;
-    hipLaunchKernelGGL((verify_z_kernel<Io, D>), dim3((total + 255) / 256), block, 0, st, a);
-    e = hipGetLastError();
-  }
-  return e;
+  const int blocks = a.B * a.H * (a.dv / CW);
+  const int nt = pick_threads(D * CW, KP, blocks);
+  if constexpr (D * CW == 128 * 128 && KP < 16)
+    if (nt >= 1024) return launch_nt<Io, D, CW, KP, 1024>(a, st);
+  if constexpr (D * CW >= 64 * 128)
+    if (nt >= 512) return launch_nt<Io, D, CW, KP, 512>(a, st);
+  if constexpr (D * CW < 128 * 128 || KP < 16) return launch_nt<Io, D, CW, KP, 256>(a, st);
+  return hipErrorInvalidValue;                             // (not reached)
 }
 
+template <typename Io, int D, int CW>
+static hipError_t launch_cw(const VerifyArgs& a, hipStream_t st) {
+  if (a.kk <= 1) return launch_kp<Io, D, CW, 1>(a, st);
+  if (a.kk <= 4) return launch_kp<Io, D, CW, 4>(a, st);
+  if (a.kk <= 8) return launch_kp<Io, D, CW, 8>(a, st);
+  return launch_kp<Io, D, CW, 16>(a, st);
+}
+
+// whole heads where the value rows have up to 128 elements, slices of D columns otherwise
 template <typename Io, int D>
-static hipError_t launch_split(const VerifyArgs& a, int nsplit, hipStream_t st) {
-  if (nsplit <= 1) return launch_kp<Io, D, D>(a, st);
-  if (nsplit == 2) return launch_kp<Io, D, D / 2>(a, st);
-  return launch_kp<Io, D, D / 4>(a, st);
+static hipError_t launch_d(const VerifyArgs& a, hipStream_t st) {
+  if constexpr (D == 64)
+    if (a.dv == 128) return launch_cw<Io, D, 2 * D>(a, st);
+  return launch_cw<Io, D, D>(a, st);
 }
 
-// Columns of a head are split over 1, 2 or 4 workgroups so that small B*H still
-// puts enough workgroups on the 256 compute units.
-int verify_pick_split(int BH) {
-  if (BH >= 768) return 1;
-  if (BH >= 384) return 2;
-  return 4;
-}
-
-hipError_t launch_verify(const VerifyArgs& a, bool bf16, int d, int nsplit, hipStream_t st) {
-  if (bf16) return d == 128 ? launch_split<IoBf16, 128>(a, nsplit, st) : launch_split<IoBf16, 64>(a, nsplit, st);
-  return d == 128 ? launch_split<IoF32, 128>(a, nsplit, st) : launch_split<IoF32, 64>(a, nsplit, st);
+hipError_t launch_verify(const VerifyArgs& a, bool bf16, int d, hipStream_t st) {
+  if (bf16) return d == 128 ? launch_d<IoBf16, 128>(a, st) : launch_d<IoBf16, 64>(a, st);
+  return d == 128 ? launch_d<IoF32, 128>(a, st) : launch_d<IoF32, 64>(a, st);
 }
 
 }  // namespace linattn

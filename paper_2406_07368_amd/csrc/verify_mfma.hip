@@ -274,8 +274,8 @@ __global__ __launch_bounds__(D * 2, 4) void verify_mfma_kernel(VerifyArgs a) {
   }
 }
 
-bool verify_mfma_available(bool bf16, int d, int nsplit, int kk) {
-  return bf16 && nsplit == 1 && kk <= VmCfg<128>::KT && (d == 128 || d == 64);
+bool verify_mfma_available(bool bf16, int d, int blocks, int kk) {
+  return bf16 && blocks >= 768 && kk <= VmCfg<128>::KT && (d == 128 || d == 64);
 }
 
 hipError_t launch_verify_mfma(const VerifyArgs& a, int d, hipStream_t st) {

@@ -67,6 +67,23 @@ def test_verify_every_column_split(BH, expect_split):
     assert np.array_equal(got[3], workloads.round_to_io(want[3], io).astype(np.float64))
 
 
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+@pytest.mark.parametrize("B,H", [(1, 1), (5, 13), (1, 257), (1, 385), (27, 19), (1, 577)])
+@pytest.mark.parametrize("kk", [1, 3, 7, 15])
+def test_verify_every_workgroup_size(io, B, H, kk):
+    """One workgroup per head, its threads chosen by the number of heads and drafts: 256, 512 and 1024 threads on each
+    number of drafts a kernel is built for."""
+    d, Kc = 128, 4
+    q, k, v, w, S, z, hist = make_case(40 + kk + B * H, B, H, d, Kc, kk, io, prefix=4)
+    n_commit = (np.arange(B) % (kk + 1)).astype(np.int32) if B > 1 else np.array([kk], dtype=np.int32)
+    want = oracle.verify(q, k, v, w, S, z, hist, n_commit, eps=1e-3)
+    got = run_gpu(q, k, v, w, S, z, hist, io, n_commit, eps=1e-3)
+    check(got[0], want[0], TOL[io], "out")
+    check(got[1], want[1], 1e-5, "S")
+    check(got[2], want[2], 1e-5, "z")
+    assert np.array_equal(got[3], workloads.round_to_io(want[3], io).astype(np.float64)), "hist"
+
+
 # ---- the matrix-core kernel: bf16 drafts, B*H >= 768 (whole heads per workgroup) -------------------
 MB, MH = 24, 32
 
