@@ -4,7 +4,9 @@ Every call has the name and argument order of its declaration in ``include/linat
 Tensors are torch tensors on the GPU (torch is used for device memory and
 streams, nothing else); every arithmetic step runs inside the library's
 kernels.  If the library is missing or a call is refused, this module raises;
-there is no other code path.
+there is no other code path.  The tensor-level calls at the end go through
+``csrc/calls.cpp`` where their arguments are what they ordinarily are (it answers
+None otherwise): the same marshalling, without the interpreter's time.
 """
 from __future__ import annotations
 
@@ -16,6 +18,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblinattn.so")
 _lib = None
+_calls, _bound = None, None         # the native tensor-level calls, and the library they were given
 
 LINATTN_F32, LINATTN_BF16 = 0, 1
 LINATTN_PHI_ELU1, LINATTN_PHI_RELU = 0, 1
@@ -80,6 +83,30 @@ def load():
     lib.linattn_set_wait_limit.argtypes = [i32]
     _lib = lib
     return lib
+
+
+def _native():
+    """The native tensor-level calls, bound to the library that is loaded."""
+    global _calls, _bound
+    lib = load()
+    if _bound is not lib:
+        if _calls is None:
+            from . import build as _build
+            if not os.path.exists(_build.CALLS):
+                _build.build_calls()
+            from . import _calls as mod
+            _calls = mod
+        f = [lib.linattn_workspace_bytes, lib.linattn_prefill, lib.linattn_prefill_grouped, lib.linattn_backward_workspace_bytes,
+             lib.linattn_prefill_grouped_backward, lib.linattn_verify, lib.linattn_verify_grouped, lib.linattn_verify_tree, lib.linattn_decode]
+        _calls.bind(*[ctypes.cast(x, ctypes.c_void_p).value for x in f], torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _bound = lib
+    return _calls
+
+
+def _result(r, where: str):
+    if type(r) is int:
+        raise LinattnError(r, where)
+    return r
 
 
 def status_string(status: int) -> str:
@@ -208,6 +235,10 @@ def prefill(q, k, v, conv_w, state=None, chunk=64, eps=0.0, want_state=True, str
     with unit stride along the last axis (e.g. ``x.transpose(1, 2)`` of a token-major [B,L,H,d] tensor); q and k
     share their strides, and so does v when d_v = d; ``out`` gets v's shape and strides.  Returns out, (S, z, hist).
     grouped_alpha: None, or the weight of the grouped branch of the three-branch form (``linattn_prefill_grouped``)."""
+    if stream is None:
+        r = _native().prefill(q, k, v, conv_w, state, chunk, eps, want_state, phi, grouped_alpha)
+        if r is not None:
+            return _result(r, "linattn_prefill" if grouped_alpha is None else "linattn_prefill_grouped")
     B, H, L, d = q.shape
     d_v = v.shape[3]
     Kc = conv_w.shape[2]
@@ -249,6 +280,10 @@ def prefill_grouped_backward(q, k, v, conv_w, dout, alpha=1.0, eps=0.0, stream=N
     """Gradient of ``prefill_grouped`` for a sequence that starts from nothing: q, k, v, dout bf16 [B,H,L,d] CUDA
     tensors, dense or views that share their strides and are contiguous along d.  Returns dq, dk, dv (same layout)
     and the gradient of the conv weights (fp32 [H,d,Kc], summed over the batch; None if not wanted)."""
+    if stream is None:
+        r = _native().prefill_grouped_backward(q, k, v, conv_w, dout, alpha, eps, phi, group, want_dw)
+        if r is not None:
+            return _result(r, "linattn_prefill_grouped_backward")
     B, H, L, d = q.shape
     Kc = conv_w.shape[2]
     dense = all(t.is_contiguous() for t in (q, k, v, dout))
@@ -268,6 +303,10 @@ def prefill_grouped_backward(q, k, v, conv_w, dout, alpha=1.0, eps=0.0, stream=N
 
 def verify(q, k, v, conv_w, state, n_commit=None, eps=0.0, stream=None, phi="elu1"):
     """q, k: dense [B,H,kk,d]; v: dense [B,H,kk,d_v].  ``state`` = (S, z, hist) is updated in place.  Returns out."""
+    if stream is None:
+        r = _native().verify(q, k, v, conv_w, state, n_commit, eps, phi)
+        if r is not None:
+            return _result(r, "linattn_verify")
     B, H, kk, d = q.shape
     desc = make_desc(B, H, d, conv_w.shape[2], 64, q.dtype, eps, L=kk, phi=phi, d_v=v.shape[-1])
     out = torch.empty_like(v)
@@ -294,6 +333,10 @@ def grouped_state(B, H, d, conv_k, dtype=torch.bfloat16, device="cuda", prefill_
 
 def verify_grouped(q, k, v, conv_w, state, alpha=1.0, n_commit=None, eps=0.0, stream=None, phi="elu1"):
     """q, k, v: dense [B,H,kk,d].  ``state`` = (S, z, hist, kwin, vwin, fill) is updated in place.  Returns out."""
+    if stream is None:
+        r = _native().verify_grouped(q, k, v, conv_w, state, alpha, n_commit, eps, phi)
+        if r is not None:
+            return _result(r, "linattn_verify_grouped")
     B, H, kk, d = q.shape
     desc = make_desc(B, H, d, conv_w.shape[2], 64, q.dtype, eps, L=kk, phi=phi)
     out = torch.empty_like(q)
@@ -305,6 +348,10 @@ def verify_grouped(q, k, v, conv_w, state, alpha=1.0, n_commit=None, eps=0.0, st
 def verify_tree(q, k, v, parent, conv_w, state, accept=None, eps=0.0, stream=None, phi="elu1"):
     """q, k, v: dense [B,H,n,d], bf16 or fp32; parent: int32 [n] on the GPU.  ``state`` is updated in place along the
     root path of candidate ``accept[b]`` (int32 [B] on the GPU; None accepts nothing).  Returns out."""
+    if stream is None:
+        r = _native().verify_tree(q, k, v, parent, conv_w, state, accept, eps, phi)
+        if r is not None:
+            return _result(r, "linattn_verify_tree")
     B, H, n, d = q.shape
     desc = make_desc(B, H, d, conv_w.shape[2], 64, q.dtype, eps, L=n, phi=phi)
     out = torch.empty_like(q)
@@ -315,6 +362,10 @@ def verify_tree(q, k, v, parent, conv_w, state, accept=None, eps=0.0, stream=Non
 
 def decode(q, k, v, conv_w, state, eps=0.0, stream=None, phi="elu1"):
     """q, k: dense [B,H,d] (or [B,H,1,d]); v: dense [B,H,d_v].  ``state`` is updated in place.  Returns out."""
+    if stream is None:
+        r = _native().decode(q, k, v, conv_w, state, eps, phi)
+        if r is not None:
+            return _result(r, "linattn_decode")
     B, H, d = q.shape[0], q.shape[1], q.shape[-1]
     desc = make_desc(B, H, d, conv_w.shape[2], 64, q.dtype, eps, L=1, phi=phi, d_v=v.shape[-1])
     out = torch.empty_like(v)

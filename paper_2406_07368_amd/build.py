@@ -1,4 +1,4 @@
-"""Builds liblinattn.so (HIP, gfx950 only) next to this file.
+"""Builds liblinattn.so (HIP, gfx950 only) and the extension module of the tensor-level calls next to this file.
 
     python -m paper_2406_07368_amd.build
 
@@ -15,6 +15,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblinattn.so")
+CALLS = os.path.join(HERE, "_calls.so")
 OBJ = os.path.join(HERE, "_build")
 
 FLAGS = [
@@ -35,9 +36,23 @@ def _run(cmd, verbose):
     # the host pass does not know the device-only feature flag and says so; drop that line
     log = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + log)
+        raise RuntimeError(f"{cmd[0]} failed:\n" + log)
     if verbose and log.strip():
         print(log)
+
+
+def build_calls(verbose: bool = False) -> str:
+    """csrc/calls.cpp: host code on torch's C++ interface."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f"-isystem{p}" for p in (*include_paths(), sysconfig.get_paths()["include"])], os.path.join(CSRC, "calls.cpp"), "-o", CALLS,
+           *[f"-L{p}" for p in library_paths()], "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+    _run(cmd, verbose)
+    return CALLS
 
 
 def build(verbose: bool = False, extra=()) -> str:
@@ -53,7 +68,9 @@ def build(verbose: bool = False, extra=()) -> str:
         objs.append(obj)
         jobs.append(["hipcc", *compile_flags, *extra, "-c", src, "-o", obj])
     with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as pool:
+        calls = pool.submit(build_calls, verbose)
         list(pool.map(lambda cmd: _run(cmd, verbose), jobs))
+        calls.result()
     _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], verbose)
     return LIB
 
