@@ -404,20 +404,23 @@ linattn_status linattn_prefill_grouped_backward(const linattn_desc* desc, int32_
   // The conv's share of dv (the same taps met from the other side, dv[s] = sum_j w[j] dout[s + j]) is written first
   // and the conv-weight sums need nothing from the other kernels: both run on the side stream; the kernel that adds
   // the rest of dv waits for the first, the end of the call for the second.
+  // Small calls: all of it in the launches of the rows.
   hipError_t e = hipSuccess;
+  ConvLongArgs c{};
+  c.v = dout; c.conv_w = conv_w; c.out = dv;
+  c.B = a.B; c.H = a.H; c.L = L; c.Kc = a.Kc; c.sb = a.sb; c.sh = a.sh; c.st = a.st; c.m = 1; c.bwd = 1;
+  c.dw_v = v; c.dw_part = dconv_w ? a.dw_part : nullptr;
+  if (L > 0 && conv_rides(a, desc->d))
+    return launch_grouped_bwd_core(a, &c, desc->d, stream, nullptr) == hipSuccess ? LINATTN_OK : LINATTN_ERR_HIP;
   SideLane* lane = (L > 0) ? side_lane(stream) : nullptr;
   hipStream_t cs = lane ? lane->s : stream;
   if (lane) e = fork_side(lane, stream);
   if (e == hipSuccess && L > 0) {
-    ConvLongArgs c{};
-    c.v = dout; c.conv_w = conv_w; c.out = dv;
-    c.B = a.B; c.H = a.H; c.L = L; c.Kc = a.Kc; c.sb = a.sb; c.sh = a.sh; c.st = a.st; c.m = 1; c.bwd = 1;
-    c.dw_v = v; c.dw_part = dconv_w ? a.dw_part : nullptr;
     e = launch_conv_mfma(c, desc->d, cs);
     if (e == hipSuccess && lane) e = hipEventRecord(lane->mid, cs);
   }
   if (e == hipSuccess && dconv_w) e = launch_grouped_bwd_dw(a, desc->d, cs); // no tokens: the sums over nothing
-  if (e == hipSuccess) e = launch_grouped_bwd_core(a, desc->d, stream, lane ? lane->mid : nullptr);
+  if (e == hipSuccess) e = launch_grouped_bwd_core(a, nullptr, desc->d, stream, lane ? lane->mid : nullptr);
   if (lane) {                                              // joined whatever happened, so that nothing stays forked
     const hipError_t ej = join_side(lane, stream);
     if (e == hipSuccess) e = ej;

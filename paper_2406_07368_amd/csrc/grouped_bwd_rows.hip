@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "conv_mfma.h"
 #include "kernels.h"
 #include "mfma_util.h"
 
@@ -213,10 +214,29 @@ __device__ __forceinline__ void group_and_half(int bx, int ng, int first, int& g
 // Pass 1 over the key rows up to the queries: scores, running maximum and sum, and the running sum of e_i dp_i (so pbar
 // needs no pass of its own).  Pass 2, from the last rows (still in LDS) back: scores and dp again, dQ^T += K^T ds^T.  Then
 // the grouped branch with S_g in LDS.
-template <int D, int GT>
-__global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel(GroupedBwdArgs a) {
+//
+// CONV: the workgroups behind the first `ndq` are the conv's (its share of dv and the partial sums of the tap gradient).  A
+// small gradient call does not fill the chip, and as launches of their own on a side stream these cost more host time (events
+// to fork and join, 6 to 7 us each) than the whole call's work; see conv_rides.
+template <int D, int GT> struct RidingConv {
+  static constexpr int NW = RowsCfg<D, GT>::NW, CB = 4 * NW;   // four channels per wave
+  template <int KS> using Cfg = ConvCfg<KS, CM_BWD, CM_SUB, CB, NW>;
+};
+template <int D, int GT, bool CONV>
+__global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel(GroupedBwdArgs a, ConvLongArgs c, int ndq) {
   using G = RowsCfg<D, GT>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if constexpr (CONV) {
+    if ((int)blockIdx.x >= ndq) {                          // uniform
+      using R = RidingConv<D, GT>;
+      const int per = (c.L + CM_SUB - 1) / CM_SUB * (D / R::CB), e = blockIdx.x - ndq, bx = e % per, by = e / per;
+      uint32_t* smu = reinterpret_cast<uint32_t*>(smem);
+      if (c.Kc <= 17) conv_mfma_workgroup<D, 1, CM_BWD, CM_SUB, R::CB, R::NW>(c, bx, by, smu);
+      else if (c.Kc <= 49) conv_mfma_workgroup<D, 2, CM_BWD, CM_SUB, R::CB, R::NW>(c, bx, by, smu);
+      else conv_mfma_workgroup<D, 3, CM_BWD, CM_SUB, R::CB, R::NW>(c, bx, by, smu);
+      return;
+    }
+  }
   uint16_t* Kl = reinterpret_cast<uint16_t*>(smem);
   uint16_t* Vl = reinterpret_cast<uint16_t*>(smem + G::OFF_B);
   float* zl = reinterpret_cast<float*>(smem + G::OFF_Z);
@@ -227,8 +247,9 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
   int g, half;
-  group_and_half<G::NH>(blockIdx.x, a.ng, G::NH - 1, g, half);   // the longer one (later queries, more keys) first
-  const int bh = blockIdx.y, b = bh / a.H, h = bh % a.H;
+  const int per_head = G::NH * a.ng;
+  group_and_half<G::NH>(blockIdx.x % per_head, a.ng, G::NH - 1, g, half);   // the longer one (later queries, more keys) first
+  const int bh = blockIdx.x / per_head, b = bh / a.H, h = bh % a.H;
   const int tok0 = g * GT, q0 = half * G::RC;
   const int nt = (a.L - tok0) < GT ? (a.L - tok0) : GT;
   if (q0 >= nt) return;                                    // uniform: no queries in this run
@@ -487,10 +508,31 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
 }
 
 // ---- dk, dv ---------------------------------------------------------------------------------------------------------
+// Elements NT block .. NT block + NT - 1 of the tap gradient: the partial sums of the token blocks, 32 at a time and those
+// sums in turn, the order of the stages of grouped_bwd_dw_reduce_kernel.
+template <int NT>
+__device__ __forceinline__ void dw_sums(const GroupedBwdArgs& a, int d, int block) {
+  const int e = block * NT + threadIdx.x, per_head = d * a.Kc, n = a.B * a.nwb;
+  if (e >= a.H * per_head) return;
+  const float* p = a.dw_part + (size_t)(e / per_head) * n * per_head + e % per_head;
+  float sum = 0.f;
+  for (int i0 = 0; i0 < n; i0 += 32) {
+    float s = 0.f;
+#pragma unroll 8
+    for (int i = i0; i < (i0 + 32 < n ? i0 + 32 : n); ++i, p += per_head) s += *p;
+    sum += s;
+  }
+  a.dconv_w[e] = sum;
+}
+
 // SPLIT: dk and dv in workgroups of their own (see split_pays); otherwise both from one pass over the scores.
 template <int D, int GT, bool SPLIT>
 __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kernel(GroupedBwdArgs a) {
   using G = RowsCfg<D, GT>;
+  if ((int)blockIdx.y >= a.B * a.H) {                      // uniform: the sums of the tap gradient ride along
+    dw_sums<G::NT>(a, D, ((blockIdx.y - a.B * a.H) * gridDim.z + blockIdx.z) * gridDim.x + blockIdx.x);
+    return;
+  }
   const bool with_dv = !SPLIT || blockIdx.z != 0, with_dk = !SPLIT || blockIdx.z == 0;   // uniform
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint16_t* Ql = reinterpret_cast<uint16_t*>(smem);
@@ -744,30 +786,59 @@ template <int D>
 bool split_pays(int64_t wgs) { return wgs <= (D == 128 ? 256 : 128); }
 
 template <int D, int GT>
-hipError_t launch_rows(const GroupedBwdArgs& a, bool keys, hipStream_t st) {
+int riding_blocks(const GroupedBwdArgs& a) {
+  return (a.L + CM_SUB - 1) / CM_SUB * (D / RidingConv<D, GT>::CB) * a.B * a.H;
+}
+
+template <int D, int GT>
+hipError_t launch_rows(const GroupedBwdArgs& a, const ConvLongArgs* conv, bool keys, hipStream_t st) {
   using G = RowsCfg<D, GT>;
-  auto kq = grouped_bwd_dq_kernel<D, GT>;
-  auto kk = grouped_bwd_dkdv_kernel<D, GT, false>;
+  using R = RidingConv<D, GT>;
   hipError_t e;
-  if ((e = LINATTN_MAX_LDS_ONCE(kq, G::TOTAL)) != hipSuccess) return e;
-  if ((e = LINATTN_MAX_LDS_ONCE(kk, G::TOTAL)) != hipSuccess) return e;
-  const dim3 grid((unsigned)(G::NH * a.ng), (unsigned)(a.B * a.H));
-  if (!keys) {
-    hipLaunchKernelGGL(kq, grid, dim3(G::NT), G::TOTAL, st, a);
-  } else if (split_pays<D>((int64_t)G::NH * a.ng * a.B * a.H)) {
-    auto k2 = grouped_bwd_dkdv_kernel<D, GT, true>;
-    if ((e = LINATTN_MAX_LDS_ONCE(k2, G::TOTAL)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k2, dim3(grid.x, grid.y, 2), dim3(G::NT), G::TOTAL, st, a);
+  const int runs = G::NH * a.ng * a.B * a.H;
+  if (!keys && !conv) {
+    auto kq = grouped_bwd_dq_kernel<D, GT, false>;
+    if ((e = LINATTN_MAX_LDS_ONCE(kq, G::TOTAL)) != hipSuccess) return e;
+    hipLaunchKernelGGL(kq, dim3((unsigned)runs), dim3(G::NT), G::TOTAL, st, a, ConvLongArgs{}, runs);
+  } else if (!keys) {
+    constexpr int conv_bytes = 4 * (R::template Cfg<3>::TOTAL > R::template Cfg<2>::TOTAL ? R::template Cfg<3>::TOTAL : R::template Cfg<2>::TOTAL);
+    static_assert(conv_bytes <= G::TOTAL && R::template Cfg<1>::TOTAL * 4 <= G::TOTAL, "the conv's workgroups in the rows' LDS");
+    auto kq = grouped_bwd_dq_kernel<D, GT, true>;
+    if ((e = LINATTN_MAX_LDS_ONCE(kq, G::TOTAL)) != hipSuccess) return e;
+    hipLaunchKernelGGL(kq, dim3((unsigned)(runs + riding_blocks<D, GT>(a))), dim3(G::NT), G::TOTAL, st, a, *conv, runs);
   } else {
-    hipLaunchKernelGGL(kk, grid, dim3(G::NT), G::TOTAL, st, a);
+    const bool split = split_pays<D>(runs);
+    auto kk = grouped_bwd_dkdv_kernel<D, GT, false>;
+    auto k2 = grouped_bwd_dkdv_kernel<D, GT, true>;
+    if ((e = split ? LINATTN_MAX_LDS_ONCE(k2, G::TOTAL) : LINATTN_MAX_LDS_ONCE(kk, G::TOTAL)) != hipSuccess) return e;
+    dim3 grid((unsigned)(G::NH * a.ng), (unsigned)(a.B * a.H), split ? 2 : 1);
+    if (conv && a.dconv_w) {
+      const unsigned blocks = (unsigned)((a.H * D * a.Kc + G::NT - 1) / G::NT);
+      grid.y += (blocks + grid.x * grid.z - 1) / (grid.x * grid.z);
+    }
+    hipLaunchKernelGGL(split ? k2 : kk, grid, dim3(G::NT), G::TOTAL, st, a);
   }
   return hipGetLastError();
 }
 }  // namespace
 
-hipError_t launch_grouped_bwd_rows(const GroupedBwdArgs& a, int d, bool keys, hipStream_t st) {
-  if (d == 128) return a.group == 256 ? launch_rows<128, 256>(a, keys, st) : launch_rows<128, 64>(a, keys, st);
-  return a.group == 256 ? launch_rows<64, 256>(a, keys, st) : launch_rows<64, 64>(a, keys, st);
+hipError_t launch_grouped_bwd_rows(const GroupedBwdArgs& a, const ConvLongArgs* conv, int d, bool keys, hipStream_t st) {
+  if (d == 128) return a.group == 256 ? launch_rows<128, 256>(a, conv, keys, st) : launch_rows<128, 64>(a, conv, keys, st);
+  return a.group == 256 ? launch_rows<64, 256>(a, conv, keys, st) : launch_rows<64, 64>(a, conv, keys, st);
+}
+
+// The conv's workgroups in the dq launch and the sums of the tap gradient in the dk / dv launch, instead of launches of their
+// own on a side stream.  Calls that do not fill the chip gain: the events that fork and join the stream cost the host 40 us, more than
+// such a call's work, and in the dq launch the conv costs the GPU next to nothing.  Where the rows' workgroups fill the chip by themselves,
+// the conv in its own shape (four waves, more channels: memory lines shared) is the better one, more so against the two waves of groups of
+// 64.  us a gradient call, side stream / riding, by runs of queries: groups of 256, d = 128: 4 64.2 / 27.1, 64 79.7 / 68.7, 384 133.8 / 123.6,
+// 960 286 / 271, 1024 201 / 195, 2560 698 / 710; d = 64: 4 65.6 / 18.2, 256 92.5 / 83.2, 2560 296 / 281; groups of 64, d = 128: 64 73.7 / 53.0,
+// 512 129 / 123 and 128 / 127, 528 121 / 124, 768 139 / 151; d = 64: 64 72.6 / 29.8, 768 83.5 / 74.2, 1056 92.2 / 92.7, 1920 117 / 127.
+bool conv_rides(const GroupedBwdArgs& a, int d) {
+  if (conv_mfma_blocks(a.L, a.B * a.H, d) != (a.L + CM_SUB - 1) / CM_SUB) return false;   // (two tiles per workgroup: calls that fill the chip)
+  const int run = a.group < 128 ? a.group : 128;
+  const int64_t runs = (int64_t)((a.L + run - 1) / run) * a.B * a.H;
+  return runs <= (a.group == 256 ? (d == 128 ? 1024 : 2560) : (d == 128 ? 512 : 1024));
 }
 
 }  // namespace linattn

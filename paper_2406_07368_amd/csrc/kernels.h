@@ -225,9 +225,11 @@ hipError_t launch_conv_mfma(const ConvLongArgs& a, int d, hipStream_t st);
 // ... in two parts that need nothing from each other: everything but the conv-weight sums (dv is added to what it
 // holds: the conv's share is written first; `before_dkdv`, if not null, is waited for ahead of the kernel that does
 // so), and the conv-weight sums
-hipError_t launch_grouped_bwd_core(const GroupedBwdArgs& a, int d, hipStream_t st, hipEvent_t before_dkdv);
+// conv, if not null: the conv's share of dv and the conv-weight sums ride along in the launches of the rows
+hipError_t launch_grouped_bwd_core(const GroupedBwdArgs& a, const ConvLongArgs* conv, int d, hipStream_t st, hipEvent_t before_dkdv);
 // grouped_bwd_rows.hip: dq and the per-token scalars, or dk and dv (keys)
-hipError_t launch_grouped_bwd_rows(const GroupedBwdArgs& a, int d, bool keys, hipStream_t st);
+hipError_t launch_grouped_bwd_rows(const GroupedBwdArgs& a, const ConvLongArgs* conv, int d, bool keys, hipStream_t st);
+bool conv_rides(const GroupedBwdArgs& a, int d);
 hipError_t launch_grouped_bwd_dw(const GroupedBwdArgs& a, int d, hipStream_t st);
 
 // prefill_mfma.hip : launch plan of the bf16 prefill (segments, prefix sum over segment states)

@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void grouped_bwd_dw_reduce_kernel(const float*
 }
 
 template <int D, int GT>
-static hipError_t launch_bwd_core(const GroupedBwdArgs& a, hipStream_t st, hipEvent_t before_dkdv) {
+static hipError_t launch_bwd_core(const GroupedBwdArgs& a, const ConvLongArgs* conv, hipStream_t st, hipEvent_t before_dkdv) {
   using G = BwdCfg<D, GT>;
   const int BH = a.B * a.H;
   hipError_t e;
@@ -230,7 +230,7 @@ static hipError_t launch_bwd_core(const GroupedBwdArgs& a, hipStream_t st, hipEv
     f.ws = a.P; f.B = a.B; f.H = a.H; f.m = 1; f.nseg = a.ng;
     if ((e = launch_segment_scan(f, D, st)) != hipSuccess) return e;
   }
-  if ((e = launch_grouped_bwd_rows(a, D, false, st)) != hipSuccess) return e;
+  if ((e = launch_grouped_bwd_rows(a, conv, D, false, st)) != hipSuccess) return e;
   if (walk && a.ng > 1) {
     const size_t n = (size_t)BH * a.L;
     s.a = a.q; s.b = a.dout; s.w = a.stats + 3 * n; s.wz = a.stats + 4 * n; s.slots = a.Dg;
@@ -242,7 +242,7 @@ static hipError_t launch_bwd_core(const GroupedBwdArgs& a, hipStream_t st, hipEv
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (before_dkdv && (e = hipStreamWaitEvent(st, before_dkdv, 0)) != hipSuccess) return e;
-  return launch_grouped_bwd_rows(a, D, true, st);
+  return launch_grouped_bwd_rows(a, conv, D, true, st);
 }
 
 // The conv-weight sums over batch rows and token blocks (no tokens: zeros).
@@ -267,11 +267,11 @@ hipError_t launch_grouped_bwd_dw(const GroupedBwdArgs& a, int d, hipStream_t st)
   return hipSuccess;
 }
 
-// Everything but the conv-weight sums, in order.
-hipError_t launch_grouped_bwd_core(const GroupedBwdArgs& a, int d, hipStream_t st, hipEvent_t before_dkdv) {
+// Everything but the conv's share and the conv-weight sums, in order; conv: those as well, on the way.
+hipError_t launch_grouped_bwd_core(const GroupedBwdArgs& a, const ConvLongArgs* conv, int d, hipStream_t st, hipEvent_t before_dkdv) {
   if (a.L <= 0) return hipSuccess;
-  if (d == 128) return a.group == 256 ? launch_bwd_core<128, 256>(a, st, before_dkdv) : launch_bwd_core<128, 64>(a, st, before_dkdv);
-  return a.group == 256 ? launch_bwd_core<64, 256>(a, st, before_dkdv) : launch_bwd_core<64, 64>(a, st, before_dkdv);
+  if (d == 128) return a.group == 256 ? launch_bwd_core<128, 256>(a, conv, st, before_dkdv) : launch_bwd_core<128, 64>(a, conv, st, before_dkdv);
+  return a.group == 256 ? launch_bwd_core<64, 256>(a, conv, st, before_dkdv) : launch_bwd_core<64, 64>(a, conv, st, before_dkdv);
 }
 
 }  // namespace linattn

@@ -187,3 +187,16 @@ def test_gradient_with_dk_and_dv_together_or_apart(B, H, L, d, group):
     q, k, v, w, dout = case(9800 + H + d, B, H, L, d, 3, d ** -0.5)
     want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, alpha=0.9, eps=0.0)
     compare(run(q, k, v, w, dout, group, 0.9, 0.0), want, f"B={B} H={H} d={d} group={group} L={L}")
+
+
+@pytest.mark.parametrize("d,group", [(64, 64), (128, 64), (64, 256), (128, 256)])
+@pytest.mark.parametrize("B,H,L,Kc", [(2, 3, 300, 17), (1, 2, 257, 18), (3, 1, 255, 49), (2, 2, 513, 50), (17, 2, 513, 63), (1, 5, 2, 63),
+                                      (2, 65, 260, 9)])   # (two tokens, not one: dq of a single token is exactly
+                                                          # zero, which leaves no scale for a relative error)
+def test_gradient_with_the_conv_in_the_launches_of_the_rows(d, group, B, H, L, Kc):
+    """Small calls: the conv's workgroups behind those of dq (one, two and three contraction steps of the taps), the sums of the
+    tap gradient behind those of dk and dv (more than 32 partial sums: in stages); the last size is beyond the line for
+    groups of 64 at d = 128 and takes launches of its own."""
+    q, k, v, w, dout = case(9700 + L + Kc + d, B, H, L, d, Kc)
+    want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, eps=1e-3)
+    compare(run(q, k, v, w, dout, group, 1.0, 1e-3), want, f"d={d} group={group} B={B} H={H} L={L} Kc={Kc}")
