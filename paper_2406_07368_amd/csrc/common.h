@@ -21,7 +21,11 @@ constexpr int kWave = 64;
 // the embedding of the kernelised attention the paper builds on).
 __device__ __forceinline__ float phi_elu1(float x) { return x > 0.f ? x + 1.f : __expf(x); }
 // Either feature map; `relu` is uniform over a launch.
-__device__ __forceinline__ float phi_any(float x, int relu) { return relu ? fmaxf(x, 0.f) : phi_elu1(x); }
+// (both sides and a select: as a branch, every element of an unrolled loop sat in a block of its own)
+__device__ __forceinline__ float phi_any(float x, int relu) {
+  const float e = x > 0.f ? x + 1.f : __expf(x), m = fmaxf(x, 0.f);
+  return __builtin_unpredictable(relu != 0) ? m : e;
+}
 
 __device__ __forceinline__ float bf16_lo_to_f32(uint32_t packed) { return __uint_as_float(packed << 16); }
 __device__ __forceinline__ float bf16_hi_to_f32(uint32_t packed) { return __uint_as_float(packed & 0xffff0000u); }

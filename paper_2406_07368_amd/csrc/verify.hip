@@ -362,6 +362,7 @@ static hipError_t launch_nt(const VerifyArgs& a, hipStream_t st) {
 // share one (and 8 drafts, 120 registers, fill it with 1024 threads).  Measured, us a call, 256 / 512 / 1024 threads, 128 x 128 state:
 //   1 draft    256 heads 14.3 / 11.5 / 11.4, 512 17.8 / 13.9 / 12.9, 576 19.5 / 16.1 / 15.1, 640 19.9 / 16.8 / 18.8, 768 21.2 / 19.4 / 21.1,
 //              1024 26.0 / 28.8 / 26.9
+//   2 drafts   320 heads 10.0 (1024), 11.5 (512); 576 20.9 (256), 16.3 (1024); 640 20.9 (256), 17.4 (512)
 //   4 drafts   256 heads 16.3 / 12.2 / 11.5, 320 18.6 / 14.4 / 16.1, 512 20.3 / 16.0 / 17.2, 640 22.5 / 23.6 / 23.8
 //   8 drafts   32 heads 15.3 / 11.4 / 11.8, 192 17.9 / 13.7 / 12.9, 256 21.8 / 16.3 / 14.9, 320 24.7 / 19.6 / 24.8, 512 26.4 / 21.3 / 26.8, 640 29.6 / 31.9 / 37.2
 //   16 drafts  4 heads 20.0 / 14.3, 320 30.6 / 29.1, 640 58.6 / 45.0, 1024 65.3 / 62.1 (1024 threads: registers)
@@ -371,7 +372,7 @@ static int pick_threads(int state, int kp, int blocks) {
   if (state == 64 * 64) return 256;
   if (state == 64 * 128) return blocks <= (kp == 16 ? 256 : 384) ? 512 : 256;
   if (kp == 16) return 512;
-  if (kp == 1) return blocks <= 576 ? 1024 : blocks < 1024 ? 512 : 256;
+  if (kp <= 2) return blocks <= 576 ? 1024 : blocks < 1024 ? 512 : 256;
   if (kp == 8 && blocks <= 64) return 512;
   return blocks <= 256 ? 1024 : blocks <= 512 ? 512 : 256;
 }
@@ -391,6 +392,7 @@ static hipError_t launch_kp(const VerifyArgs& a, hipStream_t st) {
 template <typename Io, int D, int CW>
 static hipError_t launch_cw(const VerifyArgs& a, hipStream_t st) {
   if (a.kk <= 1) return launch_kp<Io, D, CW, 1>(a, st);
+  if (a.kk <= 2) return launch_kp<Io, D, CW, 2>(a, st);
   if (a.kk <= 4) return launch_kp<Io, D, CW, 4>(a, st);
   if (a.kk <= 8) return launch_kp<Io, D, CW, 8>(a, st);
   return launch_kp<Io, D, CW, 16>(a, st);

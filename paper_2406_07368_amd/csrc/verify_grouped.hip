@@ -21,6 +21,7 @@
 // workgroup owns the one it reads and advances.
 #include "common.h"
 #include "kernels.h"
+#include "mfma_util.h"
 
 namespace linattn {
 
@@ -421,15 +422,19 @@ __global__ __launch_bounds__(256, (sizeof(typename Io::elem) != 2 ? 2 : KP <= 8 
     }
     return;
   }
-  // The group is complete: its 64 rows of (window ++ drafts) enter S and z, S += phi(K)^T V on the fp32 matrix
-  // instructions (exact fp32 products, as everywhere in this kernel), the 32 x 32 tiles of S dealt out over the waves.
+  // The group is complete: its 64 rows of (window ++ drafts) enter S and z, S += phi(K)^T V on the matrix
+  // instructions (exact products, as everywhere in this kernel), the 32 x 32 tiles of S dealt out over the waves.
   // Only the heads whose group fills up come here, a few of a launch at a time, so it is their latency that counts:
   // every request -- rows and tiles -- leaves at once.  (Sixteen rows at a time with the state slice read, added to
   // and written back per sixteen rows on the vector ALUs took up to 70 us: a step of 1024 heads whose batch rows stand at
-  // different counts had almost always one of them to wait for: 46 us a step of 1024 heads at D = 128, now 22.)
+  // different counts had almost always one of them to wait for.  With the rows on fp32 instructions it still doubled a step: 32 heads of 128, us a
+  // step without / with a completed group 9.7 / 21.2, now 9.7 / 13.3; 1024 heads, counts at random, two drafts 31.5, now 22.8.)
   constexpr int TPW = D * D / (32 * 32) / 4;                        // tiles per wave: one column of tiles (D = 64: half of one)
   const int l32 = lane & 31, hi = lane >> 5;
-  const int cb = TPW == 1 ? (wv & 1) : wv, ib0 = TPW == 1 ? (wv >> 1) : 0;
+  constexpr bool BF = sizeof(typename Io::elem) == 2;
+  // bf16 rows: one row of tiles per wave (its features are mapped once); fp32 rows: one column of tiles
+  const int cb = TPW == 1 ? (wv & 1) : BF ? 0 : wv, ib0 = TPW == 1 ? (wv >> 1) : BF ? wv : 0;
+  constexpr int TSTEP = BF ? 32 * 4 : 32 * D * 4;                   // bytes from one tile of a wave to its next
   constexpr int CRT = GC / NPART;
   typename Io::raw8 ck[CRT], cv[CRT];
 #pragma unroll
@@ -443,12 +448,19 @@ __global__ __launch_bounds__(256, (sizeof(typename Io::elem) != 2 ? 2 : KP <= 8 
   // tile register r: feature 8(r/4) + 4hi + r%4, channel l32 (descriptor, lane offset and a constant: no address registers)
   const __amdgpu_buffer_rsrc_t Srs = __builtin_amdgcn_make_buffer_rsrc(a.S + (size_t)bh * D * D, 0, D * D * 4, 0x00020000);
   const int so = ((32 * ib0 + 4 * hi) * D + 32 * cb + l32) * 4;
+  auto request_tile = [&](f32x16& S, int i) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) S[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(Srs, so, TSTEP * i + (8 * (r >> 2) + (r & 3)) * (D * 4), 0));
+  };
+  auto store_tile = [&](const f32x16& S, int i) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(S[r]), Srs, so, TSTEP * i + (8 * (r >> 2) + (r & 3)) * (D * 4), 0);
+  };
+  // (bf16 rows: the tiles once the rows are out of their registers, in either branch below)
   f32x16 S[TPW];
+  if (!BF)
 #pragma unroll
-  for (int i = 0; i < TPW; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      S[i][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(Srs, so, (32 * i + 8 * (r >> 2) + (r & 3)) * (D * 4), 0));
+    for (int i = 0; i < TPW; ++i) request_tile(S[i], i);
   const bool z_mine = TPW > 1 || cb == 0;                           // D = 64: two waves see the same features
   const int z_f = 32 * (TPW > 1 ? wv : ib0) + l32;
   const float z_old = sm.zz[z_f];
@@ -457,6 +469,7 @@ __global__ __launch_bounds__(256, (sizeof(typename Io::elem) != 2 ? 2 : KP <= 8 
   // With more than eight drafts the registers allow two workgroups at most.
   constexpr int SR = VgStage<typename Io::elem, D, KP>::ROWS;
   float zsum = 0.f;
+  __shared__ int odd_rows[4];
 #pragma unroll
   for (int c = 0; c < GC / SR; ++c) {
     __syncthreads();                                                // outputs, history or the rows before are done with LDS
@@ -468,24 +481,86 @@ __global__ __launch_bounds__(256, (sizeof(typename Io::elem) != 2 ? 2 : KP <= 8 
         *reinterpret_cast<typename Io::raw8*>(&smem.st.v[r][8 * c8]) = cv[t];
       }
     }
-    __syncthreads();
-#pragma unroll 4
-    for (int j = 0; j < SR / 2; ++j) {                              // two rows per instruction, four apart (banks)
-      const int r = 8 * (j >> 2) + 4 * hi + (j & 3);
-      const float x = Io::load1(&smem.st.v[r][0], 32 * cb + l32);
+    // (0 times an infinity is a NaN, and a bf16 term may be 0 where its number is not: rows with an infinity or a NaN -- rare --
+    // take the fp32 instructions)
+    bool odd = false;
+    if constexpr (BF) {
+      typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+      u16x2 top = {0, 0};
 #pragma unroll
+      for (int t = 0; t < CRT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, ck[t][i] & 0x7fff7fffu));
+          top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, cv[t][i] & 0x7fff7fffu));
+        }
+      const int wave_odd = __any(top[0] >= 0x7f80 || top[1] >= 0x7f80);
+      if (lane == 0) odd_rows[wv] = wave_odd;
+    }
+    __syncthreads();
+    if constexpr (BF) odd = (odd_rows[0] | odd_rows[1] | odd_rows[2] | odd_rows[3]) != 0;
+    if (BF && !odd) {                                               // uniform
+#pragma unroll
+      for (int i = 0; i < TPW; ++i) request_tile(S[i], i);
+      // phi(K) as three bf16 terms, which is all 24 bits of it: exact products with the bf16 values, sums fp32, sixteen rows per
+      // instruction.  (Two rows per fp32 instruction: 128 of them, 64 cycles each, one after the other in every wave.)
+      const uint16_t *kl = reinterpret_cast<const uint16_t*>(&smem.st.k[0][0]), *vl = reinterpret_cast<const uint16_t*>(&smem.st.v[0][0]);
+      constexpr int RS = D + 16 / sizeof(typename Io::elem);
+#pragma unroll 1
+      for (int ks = 0; ks < GC / 16; ++ks) {
+        const u32x4 raw = __builtin_bit_cast(u32x4, tr_operand(kl, RS, 16 * ks, 32 * ib0, lane));
+        u32x4 t[3];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float x0 = phi_any(bf16_lo_to_f32(raw[i]), a.relu), x1 = phi_any(bf16_hi_to_f32(raw[i]), a.relu);
+          zsum += x0 + x1;
+#pragma unroll
+          for (int u = 0; u < 3; ++u) {
+            t[u][i] = pack_bf16x2(x0, x1);
+            x0 -= bf16_lo_to_f32(t[u][i]);
+            x1 -= bf16_hi_to_f32(t[u][i]);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < TPW; ++i) {
+          const bf16x8 vo = tr_operand(vl, RS, 16 * ks, 32 * (cb + i), lane);
+#pragma unroll
+          for (int u = 2; u >= 0; --u) S[i] = mfma(__builtin_bit_cast(bf16x8, t[u]), vo, S[i]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < TPW; ++i) store_tile(S[i], i);
+    } else if constexpr (BF) {
+#pragma unroll 1
       for (int i = 0; i < TPW; ++i) {
-        const float y = phi_any(Io::load1(&smem.st.k[r][0], 32 * (ib0 + i) + l32), a.relu);
-        S[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(y, x, S[i], 0, 0, 0);
-        if (ib0 + i == z_f / 32) zsum += y;                         // uniform
+        f32x16 T;
+        request_tile(T, i);
+#pragma unroll 1
+        for (int j = 0; j < SR / 2; ++j) {                          // two rows per instruction, four apart (banks)
+          const int r = 8 * (j >> 2) + 4 * hi + (j & 3);
+          const float y = phi_any(Io::load1(&smem.st.k[r][0], 32 * ib0 + l32), a.relu);
+          T = __builtin_amdgcn_mfma_f32_32x32x2f32(y, Io::load1(&smem.st.v[r][0], 32 * (cb + i) + l32), T, 0, 0, 0);
+          if (i == 0) zsum += y;
+        }
+        store_tile(T, i);
+      }
+    } else {
+#pragma unroll 4
+      for (int j = 0; j < SR / 2; ++j) {
+        const int r = 8 * (j >> 2) + 4 * hi + (j & 3);
+        const float x = Io::load1(&smem.st.v[r][0], 32 * cb + l32);
+#pragma unroll
+        for (int i = 0; i < TPW; ++i) {
+          const float y = phi_any(Io::load1(&smem.st.k[r][0], 32 * (ib0 + i) + l32), a.relu);
+          S[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(y, x, S[i], 0, 0, 0);
+          if (ib0 + i == z_f / 32) zsum += y;                       // uniform
+        }
       }
     }
   }
+  if (!BF)
 #pragma unroll
-  for (int i = 0; i < TPW; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(S[i][r]), Srs, so, (32 * i + 8 * (r >> 2) + (r & 3)) * (D * 4), 0);
+    for (int i = 0; i < TPW; ++i) store_tile(S[i], i);
   zsum = add_xor32(zsum);
   if (z_mine && hi == 0) a.z[(size_t)bh * D + z_f] = z_old + zsum;
   // the next group opens with the kept drafts beyond the completed one: drafts 64-n .. m-1 -> rows 0 ..
@@ -501,7 +576,9 @@ template <typename Io, int D>
 static hipError_t launch_kp(const VerifyGroupedArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)(a.B * a.H)), block(256);
   if (a.kk <= 1) hipLaunchKernelGGL((verify_grouped_kernel<Io, D, 1>), grid, block, 0, st, a);
+  else if (a.kk <= 2) hipLaunchKernelGGL((verify_grouped_kernel<Io, D, 2>), grid, block, 0, st, a);
   else if (a.kk <= 4) hipLaunchKernelGGL((verify_grouped_kernel<Io, D, 4>), grid, block, 0, st, a);
+  else if constexpr (sizeof(typename Io::elem) == 2) return hipErrorInvalidValue;   // (four bf16 drafts and more: the matrix-core kernel)
   else if (a.kk <= 8) hipLaunchKernelGGL((verify_grouped_kernel<Io, D, 8>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((verify_grouped_kernel<Io, D, 16>), grid, block, 0, st, a);
   return hipGetLastError();

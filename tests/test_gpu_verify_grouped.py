@@ -128,3 +128,44 @@ def test_whole_model_shape_one_token():
     check(host(out)[rows], want[0], TOL["bf16"], "out")
     check(host(gs[0])[rows], want[1], STATE_TOL, "S")
     assert gs[5].cpu().numpy()[rows, 0].tolist() == want[6].tolist()
+
+
+@pytest.mark.parametrize("d,kk", [(64, 1), (128, 1), (128, 2), (128, 3)])
+@pytest.mark.parametrize("phi", ["elu1", "relu"])
+def test_completion_against_64_bits_and_with_rows_that_are_not_finite(d, kk, phi):
+    """A group of bf16 rows fills up: S and z to the rounding of fp32 sums (64 products per element, exact; bound: 64 roundings of 2^-24
+    of the largest partial sum, measured below 1e-7 in the 2-norm).  Infinities and NaN in keys and values reach exactly the
+    elements that the sums themselves give them."""
+    B, H, Kc = 3, 2, 3
+    torch.manual_seed(d + kk)
+    w = torch.randn(H, d, Kc, device="cuda")
+    q, k, v = (torch.randn(B, H, kk, d, device="cuda").to(torch.bfloat16) for _ in range(3))
+    for bad in (False, True):
+        st = binding.grouped_state(B, H, d, Kc)
+        st[0].normal_(std=30.0)
+        st[1].uniform_(50.0, 90.0)
+        st[3].normal_()
+        st[4].normal_()
+        st[5].fill_(64 - kk)
+        if bad:
+            st[4][0, 0, 7, 3] = float("inf")
+            st[4][0, 1, 60, d - 1] = float("nan")
+            st[4][1, 0, 0, 0] = float("-inf")
+            st[3][1, 1, 9, 5] = float("inf")
+            st[3][2, 0, 11, 33] = float("nan")
+            st[3][2, 1, 12, 40] = float("-inf")
+        rk = torch.cat([st[3][:, :, :64 - kk], k], 2).double()
+        rv = torch.cat([st[4][:, :, :64 - kk], v], 2).double()
+        f = rk.clamp(min=0) if phi == "relu" else torch.where(rk > 0, rk + 1, rk.exp())
+        if phi == "relu":
+            f = torch.where(rk.isnan(), torch.zeros_like(f), f)     # the map max(x, 0) takes a NaN to 0
+        S = st[0].double() + (f[..., :, None] * rv[..., None, :]).sum(2)
+        z = st[1].double() + f.sum(2)
+        binding.verify_grouped(q, k, v, w, st, eps=1e-3, phi=phi)
+        torch.cuda.synchronize()
+        for got, want in ((st[0], S), (st[1], z)):
+            assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf())
+            ok = want.isfinite()
+            err = (got.double() - want)[ok].norm() / want[ok].norm()
+            assert err < 2e-7, float(err)
+        assert int(st[5].sum()) == 0
