@@ -147,7 +147,7 @@ linattn_status linattn_prefill(const linattn_desc *desc, int32_t L,
 /* linattn_prefill for callers that cannot allocate or pass device scratch (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): same arguments minus the workspace, same kernels, same
  * results bit for bit.  The scratch of a segmented prefill lives in a static device array inside the library,
- * linattn_noalloc_scratch_bytes() = 17 432 576 bytes, which every GPU the library runs on holds until the
+ * linattn_noalloc_scratch_bytes() = 18 087 936 bytes, which every GPU the library runs on holds until the
  * process ends; that is enough for every descriptor linattn_prefill accepts (LINATTN_ERR_WORKSPACE if a request
  * ever needed more).  The call allocates and frees nothing; its first use on a device asks the runtime once for the
  * array's address there (with that device current, which is also the device `hip_stream` must belong to).

@@ -20,11 +20,13 @@ constexpr int32_t kDefaultWaitSpins = 1 << 20;
 std::atomic<int32_t> g_wait_spins{kDefaultWaitSpins};
 
 // Scratch of linattn_prefill_noalloc: the workspace of a segmented prefill, held by every GPU the library runs
-// on until the process ends.  Sized for the largest workspace any descriptor can ask for: the launch plans put at most
-// 256 (b, h, segment) slots of d*d + d floats on the chip at d = 128 and 512, a quarter as large each, at d = 64, plus 8
-// staged history rows per head; only calls of at most 128 heads (256 at d = 64) are segmented, so rows of 4 bytes (fp32)
-// take no more than the 256 heads of 2-byte rows of 128 counted here.
-constexpr size_t kScratchBytes = 256 * (128 * 128 + 128) * sizeof(float) + 256 * HALO * 128 * sizeof(uint16_t);
+// on until the process ends.  Sized for the largest workspace any descriptor can ask for: slots of d*d + d floats and 8
+// staged history rows per head.  At d = 128 the launch plans put at most 256 (b, h, segment) slots on the chip, on at most
+// 128 heads; at d = 64 1024 (fp32 rows; bf16 512), a quarter as large each, on at most 512 heads.
+constexpr size_t scratch_bytes(size_t slots, size_t heads, size_t d) {
+  return slots * (d * d + d) * sizeof(float) + heads * HALO * d * sizeof(float);
+}
+constexpr size_t kScratchBytes = scratch_bytes(1024, 512, 64) > scratch_bytes(256, 128, 128) ? scratch_bytes(1024, 512, 64) : scratch_bytes(256, 128, 128);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 // In host code `scratch` is only a handle for the symbol: the array's device address is asked for once per device
