@@ -40,8 +40,8 @@ struct RowsCfg {
   static constexpr int REGION = ((ROWS > SREG ? (ROWS > STG ? ROWS : STG) : (SREG > STG ? SREG : STG)) + 15) / 16 * 16;
   static constexpr int OFF_B = RC * KS * 2;        // the second tensor's rows
   static constexpr int OFF_Z = REGION;             // [D] float
-  static constexpr int OFF_ST = OFF_Z + D * 4;     // [3][RC] float: per-token scalars
-  static constexpr int TOTAL = OFF_ST + 3 * RC * 4;
+  static constexpr int OFF_ST = OFF_Z + D * 4;     // [2][RC] float: per-token scalars
+  static constexpr int TOTAL = OFF_ST + 2 * RC * 4;
   static constexpr int PPT = RC * (D / 8) / NT;    // 16-byte pieces of RC rows per thread
   static constexpr int SLOT = D * D + D;
   static_assert(TOTAL <= 80 * 1024, "two workgroups per CU");
@@ -303,24 +303,27 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
   };
   using Both = std::integral_constant<int, 0>;
   using Second = std::integral_constant<int, 1>;
+  // which tile has its own queries among the 32 keys of a unit (keys later than the query do not exist for it)
+  using Whole = std::integral_constant<int, -1>;
+  using First = std::integral_constant<int, 0>;
 
   // ---- pass 1: largest logit, sum of the weights and sum of e_i dp_i per query, of the keys that this lane holds (the four
   // lanes of a query are merged behind the loop).  The maximum starts from the lowest finite number: a lane may have met
   // only keys that do not exist for its query.
   float mtop[2] = {-3.402823466e38f, -3.402823466e38f}, mass[2] = {0.f, 0.f}, racc[2] = {0.f, 0.f};
-  auto stats_unit = [&](auto n0, int kt, bool diag) __attribute__((always_inline)) {
-    constexpr int N0 = decltype(n0)::value;
+  auto stats_unit = [&](auto n0, int kt, auto diag) __attribute__((always_inline)) {
+    constexpr int N0 = decltype(n0)::value, DIAG = decltype(diag)::value;
     f32x4 sc[2][2], dp[2][2];
     scores(n0, kt, sc, dp);
 #pragma unroll
     for (int n = N0; n < 2; ++n) {
-      const int qi = diag ? 16 * tile[n] + l16 : G::RC;    // keys later than the query do not exist for it
+      const int qi = 16 * tile[n] + l16;
       float mnew = mtop[n];
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          sc[n][s][r] = 32 * kt + 16 * s + 4 * g4 + r <= qi ? sc[n][s][r] : -INFINITY;
+          if (n == DIAG) sc[n][s][r] = 32 * kt + 16 * s + 4 * g4 + r <= qi ? sc[n][s][r] : -INFINITY;
           mnew = fmaxf(mnew, sc[n][s][r]);
         }
       const float corr = __builtin_amdgcn_exp2f((mtop[n] - mnew) * to_log2);
@@ -339,14 +342,17 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
       mtop[n] = mnew;
     }
   };
-  // the units of one run of key rows: both tiles, then (on the diagonal) the later tile alone
+  // the units of one run of key rows: both tiles, then (on the diagonal) the later tile alone; every tile's last one is its own
   auto walk = [&](auto&& unit, bool diag) __attribute__((always_inline)) {
-    const int n0 = diag ? tile[0] / 2 + 1 : G::NW, n1 = diag ? tile[1] / 2 + 1 : G::NW;
+    const int d0 = diag ? tile[0] / 2 : G::NW, d1 = tile[1] / 2;   // d0 < d1
     int kt = 0;
 #pragma unroll 1
-    for (; kt < n0; ++kt) unit(Both{}, kt, diag);
+    for (; kt < d0; ++kt) unit(Both{}, kt, Whole{});
+    if (!diag) return;                                     // uniform
+    unit(Both{}, kt++, First{});
 #pragma unroll 1
-    for (; kt < n1; ++kt) unit(Second{}, kt, diag);
+    for (; kt < d1; ++kt) unit(Second{}, kt, Whole{});
+    unit(Second{}, kt, Second{});
   };
   rows.put(Kl, Vl, nt < G::RC ? nt : G::RC, tid);
   __syncthreads();
@@ -358,7 +364,7 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
     __syncthreads();
   }
   walk(stats_unit, true);
-  float mlog2[2], inv_mass[2], pbar[2];
+  float mlog2[2], pbar[2];                                 // p = exp2(x - mlog2)
 #pragma unroll
   for (int n = 0; n < 2; ++n) {
     float top = fmaxf(mtop[n], __shfl_xor(mtop[n], 16));
@@ -369,9 +375,8 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
     rc += __shfl_xor(rc, 16);
     ms += __shfl_xor(ms, 32);
     rc += __shfl_xor(rc, 32);
-    inv_mass[n] = 1.f / ms;                                // the token itself is always seen: the sum is at least 1
-    pbar[n] = rc * inv_mass[n];
-    mlog2[n] = top * to_log2;
+    pbar[n] = rc / ms;                                     // the token itself is always seen: the sum is at least 1
+    mlog2[n] = fmaf(top, to_log2, __builtin_amdgcn_logf(ms));
   }
 
   // ---- pass 2: ds = p (dp - pbar), dQ^T += K^T ds^T (the 1 / sqrt(d) once, behind the loop) ----------------------
@@ -381,21 +386,22 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
   for (int n = 0; n < 2; ++n)
 #pragma unroll
     for (int ft = 0; ft < G::CT; ++ft) dqa[n][ft] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto dq_unit = [&](auto n0, int kt, bool diag) __attribute__((always_inline)) {
-    constexpr int N0 = decltype(n0)::value;
+  auto dq_unit = [&](auto n0, int kt, auto diag) __attribute__((always_inline)) {
+    constexpr int N0 = decltype(n0)::value, DIAG = decltype(diag)::value;
     f32x4 sc[2][2], dp[2][2];
     scores(n0, kt, sc, dp);
     bf16x8 dh[2], dl[2];
 #pragma unroll
     for (int n = N0; n < 2; ++n) {
-      const int qi = diag ? 16 * tile[n] + l16 : G::RC;
+      const int qi = 16 * tile[n] + l16;
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           // (the mask as a select on the exponent, exp2(-inf) = 0: a branch per element would cut the loop into pieces)
-          const float arg = 32 * kt + 16 * s + 4 * g4 + r <= qi ? fmaf(sc[n][s][r], to_log2, -mlog2[n]) : -INFINITY;
-          sc[n][s][r] = __builtin_amdgcn_exp2f(arg) * inv_mass[n] * (dp[n][s][r] - pbar[n]);
+          float arg = fmaf(sc[n][s][r], to_log2, -mlog2[n]);
+          if (n == DIAG) arg = 32 * kt + 16 * s + 4 * g4 + r <= qi ? arg : -INFINITY;
+          sc[n][s][r] = __builtin_amdgcn_exp2f(arg) * (dp[n][s][r] - pbar[n]);
         }
       split44(sc[n][0], sc[n][1], dh[n], dl[n]);
     }
@@ -497,10 +503,9 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
     if (g4 == 0 && q < nq) {
       const size_t e = (size_t)bh * a.L + tok0 + q0 + q;
       a.stats[e] = mlog2[n];
-      a.stats[ntok + e] = inv_mass[n];
-      a.stats[2 * ntok + e] = pbar[n];
-      a.stats[3 * ntok + e] = fscale;
-      a.stats[4 * ntok + e] = dden;
+      a.stats[ntok + e] = pbar[n];
+      a.stats[2 * ntok + e] = fscale;
+      a.stats[3 * ntok + e] = dden;
     }
   }
   const HeldRows<D, GT> none{};
@@ -538,9 +543,8 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
   uint16_t* Ql = reinterpret_cast<uint16_t*>(smem);
   uint16_t* Dl = reinterpret_cast<uint16_t*>(smem + G::OFF_B);
   float* zl = reinterpret_cast<float*>(smem + G::OFF_Z);
-  float* ml = reinterpret_cast<float*>(smem + G::OFF_ST);  // largest logit (log2 units), 1 / sum, pbar per query
-  float* il = ml + G::RC;
-  float* pl = il + G::RC;
+  float* ml = reinterpret_cast<float*>(smem + G::OFF_ST);  // log2 of the sum of the weights, pbar per query
+  float* pl = ml + G::RC;
   uint16_t* Sl = Ql;                                       // D_g, once the token rows are done with
   float* Ol = reinterpret_cast<float*>(smem);
 
@@ -572,18 +576,16 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
   rows.fetch(gq + (int64_t)k0 * a.st, gdo + (int64_t)k0 * a.st, a.st, nk, tid);
   // the scalars of queries r0 .. r0 + RC - 1 (queries past the end weigh nothing)
   static_assert(G::RC <= G::NT, "one thread per query");
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f;
+  float s0 = 0.f, s1 = 0.f;
   auto fetch_scalars = [&](int r0, int nr) __attribute__((always_inline)) {
     const size_t e = e0 + r0 + (tid < nr ? tid : nr - 1);
     s0 = a.stats[e];
     s1 = a.stats[ntok + e];
-    s2 = a.stats[2 * ntok + e];
   };
   auto put_scalars = [&](int nr) __attribute__((always_inline)) {
     if (tid < G::RC) {
-      ml[tid] = tid < nr ? s0 : 0.f;
-      il[tid] = tid < nr ? s1 : 0.f;
-      pl[tid] = tid < nr ? s2 : 0.f;
+      ml[tid] = tid < nr ? s0 : INFINITY;
+      pl[tid] = tid < nr ? s1 : 0.f;
     }
   };
   fetch_scalars(k0, nk);
@@ -607,9 +609,10 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
     for (int ct = 0; ct < G::CT; ++ct) dkb[n][ct] = dva[n][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
   f32x4 (&dka)[2][G::CT] = SPLIT ? dva : dkb;              // (a workgroup with one of them has one set of accumulators)
 
-  // 32 queries against tiles 0 .. N1 - 1
-  auto unit = [&](auto n1, int qt, bool diag) __attribute__((always_inline)) {
-    constexpr int N1 = decltype(n1)::value;
+  // 32 queries against tiles 0 .. N1 - 1; DIAG: the tile that has its own tokens among them (queries earlier than the key do
+  // not see it)
+  auto unit = [&](auto n1, int qt, auto diag) __attribute__((always_inline)) {
+    constexpr int N1 = decltype(n1)::value, DIAG = decltype(diag)::value;
     f32x4 sc[2][2], dp[2][2];                              // [n][s][r]: query 32qt + 16s + 4 (lane / 16) + r, key lane % 16
     auto product = [&](const uint16_t* rl, const u32x4 (&op)[2][G::KSD], f32x4 (&x)[2][2]) __attribute__((always_inline)) {
 #pragma unroll
@@ -641,14 +644,14 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const int t0 = 32 * qt + 16 * s + 4 * g4;
-      const f32x4 mt = *reinterpret_cast<const f32x4*>(ml + t0), it = *reinterpret_cast<const f32x4*>(il + t0);
+      const f32x4 mt = *reinterpret_cast<const f32x4*>(ml + t0);
 #pragma unroll
       for (int n = 0; n < N1; ++n) {
-        const int ki = diag ? 16 * tile[n] + l16 : 0;
+        const int ki = 16 * tile[n] + l16;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const float x = fmaf(sc[n][s][r], to_log2, -mt[r]);
-          sc[n][s][r] = __builtin_amdgcn_exp2f(t0 + r >= ki ? x : -INFINITY) * it[r];
+          sc[n][s][r] = __builtin_amdgcn_exp2f(n != DIAG || t0 + r >= ki ? x : -INFINITY);
         }
       }
     }
@@ -668,14 +671,21 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
   };
   using One = std::integral_constant<int, 1>;
   using Both = std::integral_constant<int, 2>;
+  using Whole = std::integral_constant<int, -1>;
+  using First = std::integral_constant<int, 0>;
+  using Second = std::integral_constant<int, 1>;
   auto walk = [&](int nr, bool diag) __attribute__((always_inline)) {
-    const int nqt = (nr + 31) / 32;
-    int qt = diag ? tile[0] / 2 : 0;
-    const int from1 = diag ? (tile[1] / 2 < nqt ? tile[1] / 2 : nqt) : 0;
+    const int nqt = (nr + 31) / 32, d0 = tile[0] / 2, d1 = tile[1] / 2;   // d0 < d1
+    int qt = 0;
+    if (diag) {                                            // uniform
+      qt = d0;
+      if (qt < nqt) unit(One{}, qt++, First{});
 #pragma unroll 1
-    for (; qt < from1; ++qt) unit(One{}, qt, diag);
+      for (; qt < (d1 < nqt ? d1 : nqt); ++qt) unit(One{}, qt, Whole{});
+      if (d1 < nqt) unit(Both{}, qt++, Second{});
+    }
 #pragma unroll 1
-    for (; qt < nqt; ++qt) unit(Both{}, qt, diag);
+    for (; qt < nqt; ++qt) unit(Both{}, qt, Whole{});
   };
   put_scalars(nk);
   rows.put(Ql, Dl, nk, tid);
