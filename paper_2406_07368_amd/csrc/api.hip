@@ -214,7 +214,10 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
   if (no_ws || (plan.direct && in_place)) { plan.nseg = 1; plan.seg_len = L; plan.direct = false; }
 
   bool fold = false;
-  if (plan.mfma && !cont && !(grouped && desc->chunk == 256)) {
+  const int lead = plan.mfma && !cont && !(grouped && desc->chunk == 256) ? prefill_mfma_lead_segments(L, desc->B * desc->H * m) : 0;
+  if (lead > 0) {
+    plan.cut(L, 64, lead);                               // (needs no workspace)
+  } else if (plan.mfma && !cont && !(grouped && desc->chunk == 256)) {
     const int n = prefill_mfma_fold_segments(plan.nseg, L, desc->B * desc->H * m, desc->d);
     fold = n > 0;
     if (fold) plan.cut(L, desc->chunk, n);               // never more segments than the workspace was sized for
@@ -238,7 +241,7 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
   a.sh_v = m > 1 ? desc->stride_h_v : desc->stride_h;
   a.st_v = m > 1 ? desc->stride_t_v : desc->stride_t;
   a.nseg = plan.nseg; a.seg_len = plan.seg_len; a.direct = plan.direct; a.f32 = !plan.mfma;
-  a.alpha = alpha; a.fold = fold;
+  a.alpha = alpha; a.fold = lead > 0 ? 2 : fold;
   a.wait_spins = g_wait_spins.load(std::memory_order_relaxed);
   hipError_t e;
   const bool bf16 = desc->io_dtype == LINATTN_BF16;

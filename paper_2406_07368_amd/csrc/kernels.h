@@ -102,7 +102,8 @@ struct PrefillArgs {
   int f32;                  // fp32 rows (the history rows staged by the prefix sum are floats)
   int no_conv;              // the taps are taken as zero: a convolution with more than 8 taps runs as a pass of its own
   int group;                // three-branch form: tokens per group (64 or 256)
-  int fold;                 // bf16 rows: the full pass adds up the segments' increments itself
+  int fold;                 // bf16 rows: 1: the full pass adds up the segments' increments itself; 2: one launch, every
+                            // segment's workgroup walks the groups ahead of it as well
   // Value rows wider than key rows: d_v = m d.  The kernels then see B*H*m heads of d value channels each, head
   // (b, h, block) sharing q, k, z with its siblings and owning channels block*d .. block*d + d - 1 of v, out, hist,
   // conv_w and of the rows of S.  m = 1: nothing changes.
@@ -236,6 +237,7 @@ hipError_t launch_grouped_bwd_dw(const GroupedBwdArgs& a, int d, hipStream_t st)
 hipError_t launch_segment_scan(const PrefillArgs& a, int d, hipStream_t st);   // the prefix sum alone
 int prefill_mfma_pick_segments(int BH, int L, int chunk, int d);
 int prefill_mfma_fold_segments(int nseg, int L, int heads, int d);   // 0: the prefix sum is a launch of its own
+int prefill_mfma_lead_segments(int L, int heads);   // 0: not in one launch
 size_t prefill_mfma_workspace_bytes(int BH, int d, int nseg);
 hipError_t launch_prefill_mfma(const PrefillArgs& a, int d, int chunk, bool grouped, hipStream_t st);
 
@@ -248,5 +250,7 @@ hipError_t launch_prefill_grouped256(const PrefillArgs& a, int d, hipStream_t st
 // prefill_mfma_ws.hip : the matrix-core kernel, with front-end waves (HBM traffic, feature map, scores)
 // and state waves (everything that touches S and z) working side by side
 hipError_t launch_prefill_mfma_ws(const PrefillArgs& a, int d, bool state_only, bool grouped, hipStream_t st);
+// prefill_mfma_lead.hip : the same kernel for short new sequences in one launch (a.fold == 2)
+hipError_t launch_prefill_mfma_lead(const PrefillArgs& a, int d, bool grouped, hipStream_t st);
 
 }  // namespace linattn

@@ -1,6 +1,6 @@
 // Prefill of bf16 inputs (Sec. 4.1): the launch plan around the matrix-core kernel.
 //
-// The kernel itself (prefill_mfma_ws.hip) walks one (b, h) -- or one segment of its
+// The kernel itself (prefill_mfma_ws.h) walks one (b, h) -- or one segment of its
 // sequence -- group by group with the state in registers.  When B*H alone cannot fill
 // the chip the sequence axis is cut into segments: a first pass reduces each segment's
 // K, V to its state increment, a prefix sum over the segments (here) turns the
@@ -108,6 +108,20 @@ int prefill_mfma_fold_segments(int nseg, int L, int heads, int d) {
   return L <= 16 * 64 && (d == 64 || heads >= 12) ? 6 : 0;
 }
 
+// A short new sequence in one launch, a workgroup per group of 64: the one of group g walks the g groups before its own for their
+// state only, which takes half the time of a group with scores and outputs (1.6 us against 3.2 at d = 128), so the call is as long
+// as its last group's walk instead of a walk that computes everything.  Costs g times the reads of K and V, from the last-level cache, and a
+// compute unit per group.  Returns the number of segments (= groups), 0: not that way.
+// It pays while every group has a compute unit to itself, up to the length where the plan cuts the sequence (8 groups).  Measured, us a call,
+// one workgroup per head / this: d = 128, 16 heads: 2 groups 13.1 / 11.7, 3 16.1 / 13.2, 5 22.3 / 16.9, 6 25.4 / 18.8, 8 (in segments) 24.6 / 23.2, three-branch
+// form 26.6 / 28.5; 32 heads of 6 26.0 / 20.1, 64 of 4 20.3 / 18.3, 128 of 2 14.5 / 14.5, 64 of 5 23.1 / 26.8, 96 of 3 17.3 / 21.4; three-branch form 32 heads of
+// 6 31.8 / 24.1, 64 of 4 24.6 / 21.6.  d = 64: 16 heads of 6 22.1 / 16.4, 64 of 4 17.4 / 14.3, 128 of 2 12.1 / 11.0, 96 of 3 14.6 / 14.2, 96 of 4 17.6 / 19.1; three-branch
+// form 64 of 4 21.9 / 17.5, 96 of 3 17.7 / 21.0.
+int prefill_mfma_lead_segments(int L, int heads) {
+  const int groups = (L + 63) / 64;
+  return groups >= 2 && groups < 8 && (int64_t)groups * heads <= 256 ? groups : 0;
+}
+
 size_t prefill_mfma_workspace_bytes(int BH, int d, int nseg) {
   if (nseg <= 1) return 0;
   return (size_t)BH * nseg * ((size_t)d * d + d) * sizeof(float) + (size_t)BH * HALO * d * sizeof(uint16_t);
@@ -145,6 +159,7 @@ hipError_t launch_segment_scan(const PrefillArgs& a, int d, hipStream_t st) {
 }
 
 hipError_t launch_prefill_mfma(const PrefillArgs& a, int d, int chunk, bool grouped, hipStream_t st) {
+  if (a.fold == 2) return launch_prefill_mfma_lead(a, d, grouped, st);
   hipError_t e;
   if (a.nseg > 1) {
     if ((e = launch_prefill_mfma_ws(a, d, true, false, st)) != hipSuccess) return e;

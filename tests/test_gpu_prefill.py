@@ -463,3 +463,41 @@ def test_fp32_three_branch_rounds_no_more_than_short_chains_do(B, H, L, d, unit)
     want = oracle.prefill_grouped(q, k, v, w, 64)[0]
     err = float(np.linalg.norm(host(out).astype(np.float64) - want) / np.linalg.norm(want))
     assert err <= {64: (4.95e-8, 6.15e-8), 128: (5.0e-8, 6.7e-8)}[d][unit], err
+
+
+@pytest.mark.parametrize("form", ["tokens", "grouped"])
+@pytest.mark.parametrize("B,H,L,d,d_v,Kc,layout,phi", [
+    (1, 4, 65, 64, 64, 3, "bhld", "elu1"), (2, 16, 447, 128, 128, 5, "blhd", "elu1"), (1, 36, 448, 128, 128, 1, "bhld", "elu1"),
+    (1, 37, 448, 128, 128, 3, "bhld", "elu1"),                                            # 259 groups: one workgroup per head
+    (4, 32, 128, 128, 128, 8, "blhd", "relu"), (1, 3, 129, 64, 64, 63, "bhld", "elu1"), (1, 3, 449, 64, 64, 3, "bhld", "elu1"),   # 8 groups: segments
+    (3, 5, 300, 64, 128, 4, "blhd", "elu1"), (2, 8, 191, 64, 192, 2, "bhld", "relu"), (1, 2, 64, 64, 64, 3, "bhld", "elu1")])
+def test_short_sequences_with_a_workgroup_per_group(form, B, H, L, d, d_v, Kc, layout, phi):
+    """A new sequence of 2 to 7 groups: every group's workgroup forms the state before it.  The same sums in the same order as the
+    walk over a head, which a call with a state of zeros takes: the same bits, up to seven groups; and the oracle's numbers."""
+    if form == "grouped" and d_v != d:
+        pytest.skip("value rows as wide as key rows")
+    rng = np.random.default_rng(8800 + L + d + Kc)
+    q, k = (workloads.round_to_io(rng.standard_normal((B, H, L, d)), "bf16") for _ in range(2))
+    v = workloads.round_to_io(rng.standard_normal((B, H, L, d_v)), "bf16")
+    w = workloads.conv_weights(rng, H, d_v, Kc)
+    bf = torch.bfloat16
+
+    def put(x):
+        x = dev(x, bf)
+        return x.transpose(1, 2).contiguous().transpose(1, 2) if layout == "blhd" else x
+    qd, kd, vd, wd = put(q), put(k), put(v), dev(w)
+    zeros = (torch.zeros(B, H, d, d_v, device="cuda"), torch.zeros(B, H, d, device="cuda"), torch.zeros(B, H, Kc - 1, d_v, device="cuda", dtype=bf))
+    call = binding.prefill if form == "tokens" else binding.prefill_grouped
+    eps = 1e-3 if phi == "relu" else 0.0
+    out, st = call(qd, kd, vd, wd, eps=eps, phi=phi)
+    out0, st0 = call(qd, kd, vd, wd, state=zeros, eps=eps, phi=phi)
+    torch.cuda.synchronize()
+    if L <= 448:
+        for a, b in zip((out, *st), (out0, *st0)):
+            assert torch.equal(a, b)
+    if phi == "elu1":
+        if form == "tokens":
+            want = oracle.prefill_recurrent(q, k, v, w)
+        else:
+            want = oracle.prefill_grouped(q, k, v, w, 64)
+        compare((host(out), host(st[0]), host(st[1]), host(st[2])), want, "bf16", form)
