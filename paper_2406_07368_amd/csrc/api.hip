@@ -249,17 +249,16 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
     // Groups of 256 with a long conv: the conv pass writes out first and the full pass adds the rest to it (one
     // rounding of the sum, and the conv pass reads only V).  On the caller's stream: beside the first pass on the
     // side stream the call took 9 to 14 us longer -- the fork and the join cost more than the two short kernels
-    // they would overlap.
-    {
-      ConvLongArgs c{};
-      c.v = v; c.conv_w = conv_w; c.hist_in = hist_in; c.out = out; c.hist_out = hist_out;
-      c.B = desc->B; c.H = desc->H; c.L = L; c.Kc = desc->conv_k;
-      c.sb = a.sb_v; c.sh = a.sh_v; c.st = a.st_v; c.m = m; c.assign = 1;
-      e = launch_conv_long(c, true, desc->d, stream);
-    }
+    // they would overlap.  A conv that does not fill the chip goes into the launch of the prefix sum instead.
+    ConvLongArgs c{};
+    c.v = v; c.conv_w = conv_w; c.hist_in = hist_in; c.out = out; c.hist_out = hist_out;
+    c.B = desc->B; c.H = desc->H; c.L = L; c.Kc = desc->conv_k;
+    c.sb = a.sb_v; c.sh = a.sh_v; c.st = a.st_v; c.m = m; c.assign = 1;
+    const bool beside = a.nseg > 1 && conv_beside_scan(c, desc->d);
+    e = beside ? hipSuccess : launch_conv_long(c, true, desc->d, stream);
     if (e == hipSuccess && a.nseg > 1) {
       e = launch_prefill_mfma_ws(a, desc->d, true, false, stream);
-      if (e == hipSuccess) e = launch_segment_scan(a, desc->d, stream);
+      if (e == hipSuccess) e = beside ? launch_segment_scan_conv(a, c, desc->d, stream) : launch_segment_scan(a, desc->d, stream);
     }
     if (e == hipSuccess) e = launch_prefill_grouped256(a, desc->d, stream);
     return e == hipSuccess ? LINATTN_OK : LINATTN_ERR_HIP;

@@ -27,6 +27,7 @@
 #include "conv_mfma.h"
 #include "kernels.h"
 #include "mfma_util.h"
+#include "segment_scan.h"
 
 namespace linattn {
 
@@ -82,6 +83,53 @@ hipError_t launch_conv_mfma(const ConvLongArgs& a, int d, hipStream_t st) {
   if (a.bwd) return d == 128 ? launch_cm<128, CM_BWD>(a, st) : launch_cm<64, CM_BWD>(a, st);
   if (a.assign) return d == 128 ? launch_cm<128, CM_ASSIGN>(a, st) : launch_cm<64, CM_ASSIGN>(a, st);
   return d == 128 ? launch_cm<128, CM_ADD>(a, st) : launch_cm<64, CM_ADD>(a, st);
+}
+
+// The forward conv of a call in groups of 256 (out = conv, ahead of the kernel that adds the rest) in the launch of the prefix
+// sum over its segments: neither needs anything from the other.  Both are short, a launch apart they were two gaps on the stream
+// and two launches that leave most of the chip idle; the conv's workgroups are the longer ones and go first.  16 channels each
+// (see launch_cm), the tap count chosen at run time, so the workgroups of the prefix sum hold the conv's LDS too: nothing to
+// them, they use few registers and end early.
+template <int D>
+__global__ __launch_bounds__(64 * CM_NW) void segment_scan_conv_kernel(PrefillArgs p, ConvLongArgs c, int nconv) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t smu[];
+  constexpr int CB = 16;
+  static_assert(64 * CM_NW == 256, "the prefix sum's workgroups");
+  if ((int)blockIdx.x < nconv) {                           // uniform; the longer ones first
+    const int per = (c.L + CM_SUB - 1) / CM_SUB * (D / CB), bx = blockIdx.x % per, by = blockIdx.x / per;
+    if (c.Kc <= 17) conv_mfma_workgroup<D, 1, CM_ASSIGN, CM_SUB, CB, CM_NW>(c, bx, by, smu);
+    else if (c.Kc <= 49) conv_mfma_workgroup<D, 2, CM_ASSIGN, CM_SUB, CB, CM_NW>(c, bx, by, smu);
+    else conv_mfma_workgroup<D, 3, CM_ASSIGN, CM_SUB, CB, CM_NW>(c, bx, by, smu);
+    return;
+  }
+  constexpr int PER = (D * D + D + 255) / 256;
+  const int e = blockIdx.x - nconv;
+  segment_scan_workgroup<D>(p, e % PER, e / PER);
+}
+
+// Every conv of one tile a workgroup (with two tiles it lasts many times the prefix sum).  us a call, conv in a launch of its own /
+// beside the prefix sum: d = 128, 63 taps: 8 heads, 1000 tokens 45.1 / 43.4; 8 heads, 2000 tokens 48.7 / 45.6; 32 heads, 700 tokens
+// 54.6 / 50.2; 96 heads, 600 tokens (2304 workgroups) 90.4 / 85.1; d = 64: 8 heads, 1000 tokens 28.8 / 28.0; 4 heads, 8000 tokens
+// 34.4 / 31.1.  A history written over the one that is read wants a kernel of its own after the conv (conv_long.hip).
+bool conv_beside_scan(const ConvLongArgs& c, int d) {
+  return c.L > 0 && cm_tokens(c.L, c.B * c.H * c.m, d) == CM_SUB && !(c.hist_out && c.hist_out == c.hist_in);
+}
+
+template <int D>
+static hipError_t launch_scan_conv(const PrefillArgs& p, ConvLongArgs c, hipStream_t st) {
+  constexpr int b3 = ConvCfg<3, CM_ASSIGN, CM_SUB, 16, CM_NW>::TOTAL, b1 = ConvCfg<1, CM_ASSIGN, CM_SUB, 16, CM_NW>::TOTAL;
+  constexpr int bytes = 4 * (b3 > b1 ? b3 : b1);
+  static_assert(ConvCfg<2, CM_ASSIGN, CM_SUB, 16, CM_NW>::TOTAL * 4 <= bytes, "LDS");
+  auto kern = segment_scan_conv_kernel<D>;
+  hipError_t e = LINATTN_MAX_LDS_ONCE(kern, bytes);
+  if (e != hipSuccess) return e;
+  c.hist_fused = c.hist_out != nullptr;
+  const int heads = c.B * c.H * c.m, nconv = (c.L + CM_SUB - 1) / CM_SUB * (D / 16) * heads;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(nconv + (D * D + D + 255) / 256 * heads)), dim3(256), bytes, st, p, c, nconv);
+  return hipGetLastError();
+}
+hipError_t launch_segment_scan_conv(const PrefillArgs& p, const ConvLongArgs& c, int d, hipStream_t st) {
+  return d == 128 ? launch_scan_conv<128>(p, c, st) : launch_scan_conv<64>(p, c, st);
 }
 
 }  // namespace linattn

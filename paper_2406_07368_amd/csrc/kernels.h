@@ -220,6 +220,9 @@ hipError_t launch_conv_long(const ConvLongArgs& a, bool bf16, int d, hipStream_t
 
 // conv_mfma.hip : the same for bf16 rows on the matrix cores, and its gradients
 int conv_mfma_blocks(int L, int heads, int d);             // token blocks per sequence
+// ... the forward one (out = conv) in the launch of the prefix sum over the segments
+bool conv_beside_scan(const ConvLongArgs& c, int d);
+hipError_t launch_segment_scan_conv(const PrefillArgs& p, const ConvLongArgs& c, int d, hipStream_t st);
 hipError_t launch_conv_mfma(const ConvLongArgs& a, int d, hipStream_t st);
 
 // prefill_grouped_bwd.hip : gradient of the three-branch form (bf16 rows, groups of 64 or 256)

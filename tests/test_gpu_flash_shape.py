@@ -114,6 +114,34 @@ def test_three_branch_form_in_groups_of_256_launch_plans(B, H, L, d, Kc, with_st
     compare(run(q, k, v, w, state, "bf16", 256, 1e-3, alpha=1.0), want, "bf16", f"B{B} H{H} L{L} d{d}")
 
 
+@pytest.mark.parametrize("B,H,L,d,Kc,with_state", [(1, 1, 257, 64, 9, False), (1, 1, 257, 128, 17, True), (1, 3, 511, 64, 18, True),
+                                                   (2, 2, 513, 128, 49, True), (1, 4, 1000, 128, 50, False), (2, 5, 800, 64, 63, True),
+                                                   (6, 8, 1030, 128, 63, True), (1, 4, 2100, 128, 40, True)])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_long_conv_in_the_launch_of_the_prefix_sum(B, H, L, d, Kc, with_state, in_place):
+    """Groups of 256, several segments, a conv of one tile a workgroup: it runs beside the prefix sum (every number of contraction
+    steps, ragged last tiles, a history or none); with the history updated in place, and with two tiles a workgroup (48 heads of
+    1030 tokens), in a launch of its own.  Out is one rounding of the sum in either, and the two agree to the bit."""
+    if in_place and not with_state:
+        pytest.skip("no history to update")
+    q, k, v, w, state = small_case(7470 + L + Kc, B, H, L, d, Kc, "bf16", with_state)
+    args = {} if state is None else dict(S0=state[0], z0=state[1], hist0=state[2])
+    want = oracle.prefill_grouped(q, k, v, w, 256, alpha=1.0, eps=1e-3, **args)
+    got = run(q, k, v, w, state, "bf16", 256, 1e-3, alpha=1.0)
+    compare(got, want, "bf16", f"B{B} H{H} L{L} d{d} Kc{Kc}")
+    if in_place:
+        dt = torch.bfloat16
+        S, z, h = dev(state[0]), dev(state[1]), dev(state[2], dt)
+        desc = binding.make_desc(B, H, d, Kc, 256, dt, 1e-3, L=L)
+        nb = binding.linattn_workspace_bytes(desc, L)
+        ws = torch.empty(max(nb, 16), dtype=torch.uint8, device="cuda")
+        out = torch.empty(B, H, L, d, dtype=dt, device="cuda")
+        binding.linattn_prefill_grouped(desc, L, 1.0, dev(q, dt), dev(k, dt), dev(v, dt), dev(w), S, z, h, out, S, z, h, ws, nb)
+        torch.cuda.synchronize()
+        for a, b in zip(got, (out, S, z, h)):
+            assert np.array_equal(a, host(b))
+
+
 def test_three_branch_form_in_groups_of_256_details():
     """Nothing before the first group and eps = 0 (the linear branch is absent there, no division by zero reaches
     the output); the other feature map; token-major tensors; peaked softmax weights; no leak from later tokens."""
