@@ -249,6 +249,9 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a, int d, int chunk, bool grou
 int prefill_grouped256_pick_segments(int BH, int L);
 size_t prefill_grouped256_workspace_bytes(int BH, int d, int nseg);
 hipError_t launch_prefill_grouped256(const PrefillArgs& a, int d, hipStream_t st);
+// prefill_grouped256_split.hip : the same with several workgroups per group, where the groups are few
+int prefill_grouped256_parts(const PrefillArgs& a);        // 1: one workgroup per segment
+hipError_t launch_prefill_grouped256_split(const PrefillArgs& a, int d, int parts, hipStream_t st);
 
 // prefill_mfma_ws.hip : the matrix-core kernel, with front-end waves (HBM traffic, feature map, scores)
 // and state waves (everything that touches S and z) working side by side

@@ -142,6 +142,46 @@ def test_long_conv_in_the_launch_of_the_prefix_sum(B, H, L, d, Kc, with_state, i
             assert np.array_equal(a, host(b))
 
 
+@pytest.mark.parametrize("B,H,L,d,Kc,with_state", [(1, 1, 1, 128, 3, True), (1, 2, 31, 64, 63, False), (1, 2, 33, 128, 1, True),
+                                                   (1, 3, 65, 64, 8, True), (1, 5, 255, 128, 63, True), (1, 4, 256, 64, 4, True),
+                                                   (1, 3, 545, 128, 5, False), (1, 8, 1000, 64, 3, True), (1, 8, 1000, 128, 63, True),
+                                                   (2, 12, 600, 64, 63, True), (4, 8, 700, 128, 7, True), (1, 8, 4090, 64, 2, True),
+                                                   (16, 8, 130, 128, 3, True), (16, 8, 129, 64, 63, True)])
+@pytest.mark.parametrize("phi", ["elu1", "relu"])
+def test_groups_of_256_shared_by_workgroups(B, H, L, d, Kc, with_state, phi):
+    """Few groups: 8, 4 or 2 workgroups share one (queries), and the state after the last token is another's work.  Against the
+    oracle, token-major rows to the bit, and -- sequences of one group, whose state and history updated in place keep one
+    workgroup per group -- against the other kernel: S, z and the history to the bit, the outputs to two roundings."""
+    io, dt = "bf16", torch.bfloat16
+    q, k, v, w, state = small_case(7480 + L + Kc, B, H, L, d, Kc, io, with_state)
+    args = {} if state is None else dict(S0=state[0], z0=state[1], hist0=state[2])
+    with oracle.feature_map(phi):
+        want = oracle.prefill_grouped(q, k, v, w, 256, alpha=0.7, eps=0.05, **args)
+    st = None if state is None else (dev(state[0]), dev(state[1]), dev(state[2], dt))
+    out, new = binding.prefill(dev(q, dt), dev(k, dt), dev(v, dt), dev(w), st, 256, 0.05, phi=phi, grouped_alpha=0.7)
+    torch.cuda.synchronize()
+    got = [host(x) for x in (out, *new)]
+    compare(got, want, io, f"B{B} H{H} L{L} d{d} Kc{Kc} {phi}")
+    tq, tk, tv = (dev(np.ascontiguousarray(x.transpose(0, 2, 1, 3)), dt).transpose(1, 2) for x in (q, k, v))
+    out2, new2 = binding.prefill(tq, tk, tv, dev(w), st, 256, 0.05, phi=phi, grouped_alpha=0.7)
+    torch.cuda.synchronize()
+    for x, y in zip(got, (out2, *new2)):
+        assert np.array_equal(x, host(y))
+    if with_state and L <= 256 and phi == "elu1":
+        S, z, h = (x.clone() for x in st)
+        desc = binding.make_desc(B, H, d, Kc, 256, dt, 0.05, L=L)
+        nb = binding.linattn_workspace_bytes(desc, L)
+        ws = torch.empty(max(nb, 16), dtype=torch.uint8, device="cuda")
+        o = torch.empty(B, H, L, d, dtype=dt, device="cuda")
+        binding.linattn_prefill_grouped(desc, L, 0.7, dev(q, dt), dev(k, dt), dev(v, dt), dev(w), S, z, h, o, S, z, h, ws, nb)
+        torch.cuda.synchronize()
+        for x, y in zip(got[1:], (S, z, h)):
+            assert np.array_equal(x, host(y))
+        err = np.abs(got[0] - host(o))
+        # one rounding of the output either way, the weights' rounding (2 ** -9 of a value) taken at another tile's maximum
+        assert (err <= 2.0 ** -7 * (np.abs(host(o)) + np.abs(v).max())).all()
+
+
 def test_three_branch_form_in_groups_of_256_details():
     """Nothing before the first group and eps = 0 (the linear branch is absent there, no division by zero reaches
     the output); the other feature map; token-major tensors; peaked softmax weights; no leak from later tokens."""
