@@ -200,3 +200,18 @@ def test_gradient_with_the_conv_in_the_launches_of_the_rows(d, group, B, H, L, K
     q, k, v, w, dout = case(9700 + L + Kc + d, B, H, L, d, Kc)
     want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, eps=1e-3)
     compare(run(q, k, v, w, dout, group, 1.0, 1e-3), want, f"d={d} group={group} B={B} H={H} L={L} Kc={Kc}")
+
+
+@pytest.mark.parametrize("B,H,L,d,group", [(1, 16, 700, 128, 256), (1, 17, 700, 128, 256),    # one tile of the sums per workgroup, four
+                                           (1, 2, 1281, 128, 256), (1, 2, 1537, 128, 256),    # walks of six groups, seven apart
+                                           (2, 8, 448, 128, 64), (1, 3, 449, 128, 64),        # of seven, eight apart
+                                           (4, 16, 769, 64, 256), (5, 13, 769, 64, 256), (4, 16, 320, 64, 64), (5, 13, 257, 64, 64)])
+def test_gradient_with_one_tile_of_the_sums_per_workgroup(B, H, L, d, group):
+    """Either side of the choice (256 workgroups of one tile) and of the number of groups a walk takes; a second call gives the
+    same bits (the waves' shares of a tile are added in a fixed order)."""
+    q, k, v, w, dout = case(9900 + L + d + B, B, H, L, d, 3)
+    want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, alpha=0.9, eps=1e-3)
+    got = run(q, k, v, w, dout, group, 0.9, 1e-3)
+    compare(got, want, f"B={B} H={H} L={L} d={d} group={group}")
+    again = run(q, k, v, w, dout, group, 0.9, 1e-3)
+    assert all(np.array_equal(got[n], again[n]) for n in got)
