@@ -262,9 +262,10 @@ __global__ __launch_bounds__(512) void prefill_grouped256_split_kernel(PrefillAr
       top = fmaxf(top, acc[r]);
     }
     top = fmaxf(top, __shfl_xor(top, 32));
-    const float mnew = fmaxf(mtop, top);
-    const float corr = __builtin_amdgcn_exp2f((mtop - mnew) * to_log2);
-    const float shift = -mnew * to_log2;
+    // (a wave may have met only logits of -inf, another one the tile with the finite ones: weights of zero, not NaN)
+    const float mnew = fmaxf(mtop, top), from = mnew == -INFINITY ? 0.f : mnew;
+    const float corr = __builtin_amdgcn_exp2f((mtop - from) * to_log2);
+    const float shift = -from * to_log2;
     float rs = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {

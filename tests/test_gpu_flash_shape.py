@@ -182,6 +182,31 @@ def test_groups_of_256_shared_by_workgroups(B, H, L, d, Kc, with_state, phi):
         assert (err <= 2.0 ** -7 * (np.abs(host(o)) + np.abs(v).max())).all()
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [1, 40, 64, 100])        # workgroups per group: 8, 8, 8, 4; of 300 tokens 8, 4, 2, 1
+@pytest.mark.parametrize("L", [64, 300])
+def test_key_tiles_whose_logits_are_all_minus_infinity(d, heads, L):
+    """Keys of -inf against positive queries have no weight.  A wave that meets nothing but such a tile hands on zeros: against
+    160 or more heads, whose groups have one workgroup each and whose waves see the first tile before."""
+    dt = torch.bfloat16
+    g = torch.Generator().manual_seed(7491 + d)
+    q, k, v = (torch.randn((1, 1, L, d), generator=g) * d ** -0.5 for _ in range(3))
+    k[:, :, 32:64] = -float("inf")
+    w = torch.randn((1, d, 3), generator=g) * 0.3
+    def call(B):
+        a = [x.expand(B, 1, L, d).contiguous().to(dt).cuda() for x in (q.abs() + 0.01, k, v)]
+        out, (S, z, h) = binding.prefill_grouped(*a, w.cuda(), group=256)
+        torch.cuda.synchronize()
+        return [host(x)[:1] for x in (out, S, z, h)]
+    got, want = call(heads), call(320)
+    assert all(np.isfinite(x).all() for x in got)
+    for x, y in zip(got[1:], want[1:]):
+        # fp32 sums over L tokens, in the same order where there is one group
+        assert np.array_equal(x, y) if L <= 256 else np.abs(x - y).max() <= L * 2.0 ** -24 * np.abs(y).max()
+    # one rounding of the output either way, the weights' rounding (2 ** -9 of a value) taken at another tile's maximum
+    assert (np.abs(got[0] - want[0]) <= 2.0 ** -7 * (np.abs(want[0]) + v.abs().max().item())).all()
+
+
 def test_three_branch_form_in_groups_of_256_details():
     """Nothing before the first group and eps = 0 (the linear branch is absent there, no division by zero reaches
     the output); the other feature map; token-major tensors; peaked softmax weights; no leak from later tokens."""
