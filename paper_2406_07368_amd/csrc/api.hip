@@ -89,6 +89,9 @@ struct PrefillPlan {
   bool direct;              // fp32 rows: see F32Plan
   int nseg, seg_len;
   size_t ws_bytes;
+  int fine;                 // groups of 256: see PrefillArgs; where the workspace also has fine_bytes behind ws_bytes
+  size_t fine_bytes;
+  size_t all_bytes() const { return ws_bytes + fine_bytes; }
   void cut(int L, int chunk, int n) {       // n segments or fewer, on multiples of the group size
     const int chunks = (L + chunk - 1) / chunk;
     seg_len = (chunks + n - 1) / n * chunk;
@@ -120,6 +123,10 @@ PrefillPlan plan_prefill(const linattn_desc* d, int32_t L, bool grouped = false)
   }
   p.ws_bytes = g256 ? prefill_grouped256_workspace_bytes(heads, d->d, p.nseg)
                                   : prefill_mfma_workspace_bytes(heads, d->d, p.nseg);
+  if (g256) {
+    p.fine = prefill_grouped256_fine(heads, p.nseg, p.seg_len);
+    p.fine_bytes = prefill_grouped256_fine_bytes(heads, d->d, p.nseg, p.fine);
+  }
   return p;
 }
 
@@ -241,6 +248,10 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
   a.sh_v = m > 1 ? desc->stride_h_v : desc->stride_h;
   a.st_v = m > 1 ? desc->stride_t_v : desc->stride_t;
   a.nseg = plan.nseg; a.seg_len = plan.seg_len; a.direct = plan.direct; a.f32 = !plan.mfma;
+  if (plan.fine && workspace_bytes - plan.ws_bytes >= plan.fine_bytes) {   // (a workspace of ws_bytes was enough: above)
+    a.fine = plan.fine;
+    a.ws_fine = reinterpret_cast<float*>(static_cast<char*>(workspace) + plan.ws_bytes);
+  }
   a.alpha = alpha; a.fold = lead > 0 ? 2 : fold;
   a.wait_spins = g_wait_spins.load(std::memory_order_relaxed);
   hipError_t e;
@@ -257,7 +268,7 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
     const bool beside = a.nseg > 1 && conv_beside_scan(c, desc->d);
     e = beside ? hipSuccess : launch_conv_long(c, true, desc->d, stream);
     if (e == hipSuccess && a.nseg > 1) {
-      e = launch_prefill_mfma_ws(a, desc->d, true, false, stream);
+      e = launch_first_pass(a, desc->d, stream);
       if (e == hipSuccess) e = beside ? launch_segment_scan_conv(a, c, desc->d, stream) : launch_segment_scan(a, desc->d, stream);
     }
     if (e == hipSuccess) e = launch_prefill_grouped256(a, desc->d, stream);
@@ -305,7 +316,7 @@ size_t linattn_workspace_bytes(const linattn_desc* desc, int32_t L) {
   if (check_desc(desc, true, true, LINATTN_MAX_CONV_K_PREFILL) != LINATTN_OK || L < 0) return 0;
   // the descriptor does not say which prefill form will be called: enough for either
   const size_t a = plan_prefill(desc, L, false).ws_bytes;
-  const size_t b = (desc->chunk == 256 || desc->io_dtype == LINATTN_F32) && value_blocks(desc) == 1 ? plan_prefill(desc, L, true).ws_bytes : 0;
+  const size_t b = (desc->chunk == 256 || desc->io_dtype == LINATTN_F32) && value_blocks(desc) == 1 ? plan_prefill(desc, L, true).all_bytes() : 0;
   return a > b ? a : b;
 }
 

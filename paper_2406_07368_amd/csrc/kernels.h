@@ -104,6 +104,10 @@ struct PrefillArgs {
   int group;                // three-branch form: tokens per group (64 or 256)
   int fold;                 // bf16 rows: 1: the full pass adds up the segments' increments itself; 2: one launch, every
                             // segment's workgroup walks the groups ahead of it as well
+  // Groups of 256: the first pass takes every segment in 1 << fine parts (workgroups), whose increments it leaves in slots of
+  // their own; 0: whole segments, in the slots of ws.
+  float* ws_fine;           // [B*H][((nseg - 1) << fine) + 1][d*d + d], slot 0 unused
+  int fine;
   // Value rows wider than key rows: d_v = m d.  The kernels then see B*H*m heads of d value channels each, head
   // (b, h, block) sharing q, k, z with its siblings and owning channels block*d .. block*d + d - 1 of v, out, hist,
   // conv_w and of the rows of S.  m = 1: nothing changes.
@@ -248,6 +252,9 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a, int d, int chunk, bool grou
 // workspace slot per (b, h, segment) also without segments
 int prefill_grouped256_pick_segments(int BH, int L);
 size_t prefill_grouped256_workspace_bytes(int BH, int d, int nseg);
+int prefill_grouped256_fine(int BH, int nseg, int seg_len);        // log2 of the parts of a segment in the first pass
+size_t prefill_grouped256_fine_bytes(int BH, int d, int nseg, int fine);   // what that takes behind the workspace
+hipError_t launch_first_pass(const PrefillArgs& a, int d, hipStream_t st);
 hipError_t launch_prefill_grouped256(const PrefillArgs& a, int d, hipStream_t st);
 // prefill_grouped256_split.hip : the same with several workgroups per group, where the groups are few
 int prefill_grouped256_parts(const PrefillArgs& a);        // 1: one workgroup per segment

@@ -105,6 +105,31 @@ size_t prefill_grouped256_workspace_bytes(int BH, int d, int nseg) {
   return (size_t)BH * nseg * ((size_t)d * d + d) * sizeof(float) + (size_t)BH * HALO * d * sizeof(uint16_t);
 }
 
+// The first pass over segments of one group, where they are few: 2 or 4 workgroups share a segment's 256 tokens, as many as have a
+// compute unit each, and the prefix sum adds their increments up.  A workgroup's walk over four steps of 64 tokens was the
+// longest part of such a call's first half (10.9 of 31 us at 8 heads of 1000 tokens).  What it costs are more slots written and read, so never
+// more workgroups than compute units.  us a call of 63 taps as a graph, whole segments / parts: d = 128: 4 heads, 300 tokens 26.5 / 23.1, 8 heads: 1000
+// 30.0 / 29.1, 2000 37.2 / 35.7, 2200 (2 parts) 41.2 / 38.6, 4000 49.8 / 48.2, 16 heads, 1000 39.2 / 36.3, 40 heads, 700 49.1 / 46.6, 120 heads, 500
+// 73.4 / 71.7; d = 64: 8 heads: 1000 20.6 / 18.6, 4000 29.4 / 28.1, 60 heads, 700 36.0 / 33.7, 120 heads, 500 40.8 / 38.1; 5 taps, 4 heads, 600 17.1 / 14.6.
+int prefill_grouped256_fine(int BH, int nseg, int seg_len) {
+  if (nseg <= 1 || seg_len != 256) return 0;
+  const int64_t segs = (int64_t)BH * (nseg - 1);
+  return 4 * segs <= 256 ? 2 : 2 * segs <= 256 ? 1 : 0;
+}
+size_t prefill_grouped256_fine_bytes(int BH, int d, int nseg, int fine) {
+  return fine ? (size_t)BH * (((size_t)(nseg - 1) << fine) + 1) * ((size_t)d * d + d) * sizeof(float) : 0;
+}
+
+// The segments' increments into a.ws, or their parts' into a.ws_fine.
+hipError_t launch_first_pass(const PrefillArgs& a, int d, hipStream_t st) {
+  if (a.fine == 0) return launch_prefill_mfma_ws(a, d, true, false, st);
+  PrefillArgs f = a;
+  f.ws = a.ws_fine;
+  f.nseg = ((a.nseg - 1) << a.fine) + 1;
+  f.seg_len = a.seg_len >> a.fine;
+  return launch_prefill_mfma_ws(f, d, true, false, st);
+}
+
 // The group size only blocks the computation; the result does not depend on it (the in-group
 // part is the exact masked product).  A requested group of 128 tokens is walked as two steps of
 // 64: two 128-token row buffers do not fit in LDS, and larger groups only add in-group MFMA work
@@ -125,7 +150,7 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a, int d, int chunk, bool grou
   if (a.fold == 2) return launch_prefill_mfma_lead(a, d, grouped, st);
   hipError_t e;
   if (a.nseg > 1) {
-    if ((e = launch_prefill_mfma_ws(a, d, true, false, st)) != hipSuccess) return e;
+    if ((e = launch_first_pass(a, d, st)) != hipSuccess) return e;
     if (!a.fold && (e = launch_segment_scan(a, d, st)) != hipSuccess) return e;
   }
   if (grouped && chunk == 256) return launch_prefill_grouped256(a, d, st);

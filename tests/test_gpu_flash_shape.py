@@ -182,6 +182,37 @@ def test_groups_of_256_shared_by_workgroups(B, H, L, d, Kc, with_state, phi):
         assert (err <= 2.0 ** -7 * (np.abs(host(o)) + np.abs(v).max())).all()
 
 
+@pytest.mark.parametrize("B,H,L,d,Kc,with_state", [(1, 1, 257, 128, 3, True), (1, 3, 513, 64, 63, False), (1, 8, 1000, 128, 63, True),
+                                                   (4, 8, 768, 64, 4, True), (1, 22, 1030, 128, 63, True), (1, 2, 8200, 128, 5, True)])
+def test_parts_of_a_segment_in_the_first_pass(B, H, L, d, Kc, with_state):
+    """Groups of 256, few segments: 4 or 2 workgroups share one in the first pass, with slots of their own behind the rest of the
+    workspace.  A workspace without room for these is enough, with whole segments; and nothing is written behind either."""
+    dt = torch.bfloat16
+    q, k, v, w, state = small_case(7492 + L + Kc, B, H, L, d, Kc, "bf16", with_state)
+    args = {} if state is None else dict(S0=state[0], z0=state[1], hist0=state[2])
+    want = oracle.prefill_grouped(q, k, v, w, 256, alpha=0.7, eps=1e-3, **args)
+    desc = binding.make_desc(B, H, d, Kc, 256, dt, 1e-3, L=L)
+    full = binding.linattn_workspace_bytes(desc, L)
+    whole = B * H * (-(-L // 256) * (d * d + d) * 4 + 8 * d * 2)
+    assert full > whole
+    st = (None, None, None) if state is None else (dev(state[0]), dev(state[1]), dev(state[2], dt))
+    got = []
+    for nb in (full, whole):
+        ws = torch.full((nb + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        out = torch.empty(B, H, L, d, dtype=dt, device="cuda")
+        S, z = torch.empty(B, H, d, d, device="cuda"), torch.empty(B, H, d, device="cuda")
+        h = torch.empty(B, H, Kc - 1, d, dtype=dt, device="cuda")
+        binding.linattn_prefill_grouped(desc, L, 0.7, dev(q, dt), dev(k, dt), dev(v, dt), dev(w), *st, out, S, z, h, ws, nb)
+        torch.cuda.synchronize()
+        assert (ws[nb:] == 0xA5).all()
+        got.append([host(x) for x in (out, S, z, h)])
+        compare(got[-1], want, "bf16", f"B{B} H{H} L{L} d{d} Kc{Kc} workspace {nb}")
+    for x, y in zip(got[0][1:], got[1][1:]):               # fp32 sums over L tokens in another order
+        assert np.abs(x - y).max(initial=0) <= L * 2.0 ** -24 * np.abs(y).max(initial=0)
+    with pytest.raises(binding.LinattnError):
+        binding.linattn_prefill_grouped(desc, L, 0.7, dev(q, dt), dev(k, dt), dev(v, dt), dev(w), *st, out, S, z, h, ws, whole - 1)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("heads", [1, 40, 64, 100])        # workgroups per group: 8, 8, 8, 4; of 300 tokens 8, 4, 2, 1
 @pytest.mark.parametrize("L", [64, 300])
