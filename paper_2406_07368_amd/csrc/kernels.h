@@ -104,15 +104,15 @@ struct PrefillArgs {
   int group;                // three-branch form: tokens per group (64 or 256)
   int fold;                 // bf16 rows: 1: the full pass adds up the segments' increments itself; 2: one launch, every
                             // segment's workgroup walks the groups ahead of it as well
-  // Groups of 256: the first pass takes every segment in 1 << fine parts (workgroups), whose increments it leaves in slots of
-  // their own; 0: whole segments, in the slots of ws.
-  float* ws_fine;           // [B*H][((nseg - 1) << fine) + 1][d*d + d], slot 0 unused
-  int fine;
   // Value rows wider than key rows: d_v = m d.  The kernels then see B*H*m heads of d value channels each, head
   // (b, h, block) sharing q, k, z with its siblings and owning channels block*d .. block*d + d - 1 of v, out, hist,
   // conv_w and of the rows of S.  m = 1: nothing changes.
   int m;
   int64_t sb_v, sh_v, st_v; // element strides of v and out
+  // Groups of 256: the first pass takes every segment in 1 << fine parts (workgroups), whose increments it leaves in slots of
+  // their own; 0: whole segments, in the slots of ws.
+  float* ws_fine;           // [B*H][((nseg - 1) << fine) + 1][d*d + d], slot 0 unused
+  int fine;
 };
 
 // (b, h, value block) of a prefill workgroup and what follows from it
