@@ -23,22 +23,38 @@ __device__ __forceinline__ void segment_scan_workgroup(const PrefillArgs& a, int
     if (a.S_in) run = e < D * D ? a.S_in[(size_t)bh * D * hx.dvt + (size_t)(e / D) * hx.dvt + hx.blk * D + e % D]
                                 : a.z_in[(size_t)bh * D + (e - D * D)];
     ws_bh[e] = run;
-    const int n = ((a.nseg - 1) << a.fine) + 1, whole = (1 << a.fine) - 1;
-    const float* from = a.fine ? a.ws_fine + (size_t)hx.bhs * n * SLOT : ws_bh;
-    // sixteen segments at a time: all their increments are requested before the first is added (read, add and
+    // sixteen increments at a time: all of them are requested before the first is added (read, add and
     // write back one by one, every segment would pay a trip to memory of its own: the compiler may not move a
     // load across the store before it)
-    for (int g0 = 1; g0 < n; g0 += 16) {
-      float inc[16];
+    if (a.fine) {                                          // uniform: the parts' increments, in slots of their own
+      const int n = ((a.nseg - 1) << a.fine) + 1, whole = (1 << a.fine) - 1;
+      const float* from = a.ws_fine + (size_t)hx.bhs * n * SLOT;
+      for (int g0 = 1; g0 < n; g0 += 16) {
+        float inc[16];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int g = g0 + i < n ? g0 + i : n - 1;             // past the end: the last one again, not used
-        inc[i] = from[(size_t)g * SLOT + e];
+        for (int i = 0; i < 16; ++i) {
+          const int g = g0 + i < n ? g0 + i : n - 1;       // past the end: the last one again, not used
+          inc[i] = from[(size_t)g * SLOT + e];
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          run += inc[i];
+          if (g0 + i < n && ((g0 + i) & whole) == 0) ws_bh[(size_t)((g0 + i) >> a.fine) * SLOT + e] = run;
+        }
       }
+    } else {
+      for (int g0 = 1; g0 < a.nseg; g0 += 16) {
+        float inc[16];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        run += inc[i];
-        if (g0 + i < n && ((g0 + i) & whole) == 0) ws_bh[(size_t)((g0 + i) >> a.fine) * SLOT + e] = run;
+        for (int i = 0; i < 16; ++i) {
+          const int g = g0 + i < a.nseg ? g0 + i : a.nseg - 1;
+          inc[i] = ws_bh[(size_t)g * SLOT + e];
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          run += inc[i];
+          if (g0 + i < a.nseg) ws_bh[(size_t)(g0 + i) * SLOT + e] = run;
+        }
       }
     }
   }
