@@ -220,7 +220,7 @@ linattn_status linattn_prefill_grouped(const linattn_desc *desc, int32_t L, floa
  *   workspace    scratch device, >= linattn_backward_workspace_bytes(desc, L), 16-byte
  *                        aligned: the sums before every group and the gradients with
  *                        respect to them ((d*d+d) floats per group and head, twice),
- *                        four floats per token and head, and the partial conv-weight
+ *                        five floats per token and head, and the partial conv-weight
  *                        sums.  Contents on entry are ignored.
  * Arithmetic: bf16 operands on the matrix cores, fp32 accumulation; the conv's
  * share of dv is rounded to bf16 before the rest is added to it (a second rounding).

@@ -366,7 +366,7 @@ BackwardPlan plan_backward(const linattn_desc* d, int32_t L) {
   p.off_P = 0;
   p.off_D = round256(BH * (p.ng > 0 ? p.ng : 1) * slot * sizeof(float));
   p.off_stats = p.off_D + round256(BH * (p.ng > 0 ? p.ng : 1) * slot * sizeof(float));
-  p.off_dw = p.off_stats + round256(4 * BH * (size_t)(L > 0 ? L : 1) * sizeof(float));
+  p.off_dw = p.off_stats + round256(5 * BH * (size_t)(L > 0 ? L : 1) * sizeof(float));
   // partial conv-weight sums, and as much again for the stages of their reduction
   p.bytes = p.off_dw + 2 * round256(BH * (size_t)(p.nwb > 0 ? p.nwb : 1) * d->d * d->conv_k * sizeof(float));
   return p;

@@ -40,8 +40,8 @@ struct RowsCfg {
   static constexpr int REGION = ((ROWS > SREG ? (ROWS > STG ? ROWS : STG) : (SREG > STG ? SREG : STG)) + 15) / 16 * 16;
   static constexpr int OFF_B = RC * KS * 2;        // the second tensor's rows
   static constexpr int OFF_Z = REGION;             // [D] float
-  static constexpr int OFF_ST = OFF_Z + D * 4;     // [2][RC] float: per-token scalars
-  static constexpr int TOTAL = OFF_ST + 2 * RC * 4;
+  static constexpr int OFF_ST = OFF_Z + D * 4;     // [3][RC] float: per-token scalars
+  static constexpr int TOTAL = OFF_ST + 3 * RC * 4;
   static constexpr int PPT = RC * (D / 8) / NT;    // 16-byte pieces of RC rows per thread
   static constexpr int SLOT = D * D + D;
   static_assert(TOTAL <= 80 * 1024, "two workgroups per CU");
@@ -364,7 +364,10 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
     __syncthreads();
   }
   walk(stats_unit, true);
-  float mlog2[2], pbar[2];                                 // p = exp2(x - mlog2)
+  // p = exp2(x - mlog2) * inv_mass.  (The sum's logarithm as part of mlog2 saved a multiplication and a scalar and cost bits: mlog2
+  // is the size of the logits, and what its rounding takes off has to be what it took off in the sum, where it cancels.  Logits of
+  // 60 to 330: weights of 1 off by up to 5e-5, now 1e-7; a training step of B8 H8 L8192 d128 takes 0.2 % longer.)
+  float mlog2[2], inv_mass[2], pbar[2];
 #pragma unroll
   for (int n = 0; n < 2; ++n) {
     float top = fmaxf(mtop[n], __shfl_xor(mtop[n], 16));
@@ -375,8 +378,9 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
     rc += __shfl_xor(rc, 16);
     ms += __shfl_xor(ms, 32);
     rc += __shfl_xor(rc, 32);
-    pbar[n] = rc / ms;                                     // the token itself is always seen: the sum is at least 1
-    mlog2[n] = fmaf(top, to_log2, __builtin_amdgcn_logf(ms));
+    inv_mass[n] = 1.f / ms;                                // the token itself is always seen: the sum is at least 1
+    pbar[n] = rc * inv_mass[n];
+    mlog2[n] = top * to_log2;
   }
 
   // ---- pass 2: ds = p (dp - pbar), dQ^T += K^T ds^T (the 1 / sqrt(d) once, behind the loop) ----------------------
@@ -401,7 +405,7 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
           // (the mask as a select on the exponent, exp2(-inf) = 0: a branch per element would cut the loop into pieces)
           float arg = fmaf(sc[n][s][r], to_log2, -mlog2[n]);
           if (n == DIAG) arg = 32 * kt + 16 * s + 4 * g4 + r <= qi ? arg : -INFINITY;
-          sc[n][s][r] = __builtin_amdgcn_exp2f(arg) * (dp[n][s][r] - pbar[n]);
+          sc[n][s][r] = __builtin_amdgcn_exp2f(arg) * inv_mass[n] * (dp[n][s][r] - pbar[n]);
         }
       split44(sc[n][0], sc[n][1], dh[n], dl[n]);
     }
@@ -503,9 +507,10 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
     if (g4 == 0 && q < nq) {
       const size_t e = (size_t)bh * a.L + tok0 + q0 + q;
       a.stats[e] = mlog2[n];
-      a.stats[ntok + e] = pbar[n];
-      a.stats[2 * ntok + e] = fscale;
-      a.stats[3 * ntok + e] = dden;
+      a.stats[ntok + e] = inv_mass[n];
+      a.stats[2 * ntok + e] = pbar[n];
+      a.stats[3 * ntok + e] = fscale;
+      a.stats[4 * ntok + e] = dden;
     }
   }
   const HeldRows<D, GT> none{};
@@ -543,8 +548,9 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
   uint16_t* Ql = reinterpret_cast<uint16_t*>(smem);
   uint16_t* Dl = reinterpret_cast<uint16_t*>(smem + G::OFF_B);
   float* zl = reinterpret_cast<float*>(smem + G::OFF_Z);
-  float* ml = reinterpret_cast<float*>(smem + G::OFF_ST);  // log2 of the sum of the weights, pbar per query
-  float* pl = ml + G::RC;
+  float* ml = reinterpret_cast<float*>(smem + G::OFF_ST);  // largest logit (log2 units), 1 / sum, pbar per query
+  float* il = ml + G::RC;
+  float* pl = il + G::RC;
   uint16_t* Sl = Ql;                                       // D_g, once the token rows are done with
   float* Ol = reinterpret_cast<float*>(smem);
 
@@ -576,16 +582,18 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
   rows.fetch(gq + (int64_t)k0 * a.st, gdo + (int64_t)k0 * a.st, a.st, nk, tid);
   // the scalars of queries r0 .. r0 + RC - 1 (queries past the end weigh nothing)
   static_assert(G::RC <= G::NT, "one thread per query");
-  float s0 = 0.f, s1 = 0.f;
+  float s0 = 0.f, s1 = 0.f, s2 = 0.f;
   auto fetch_scalars = [&](int r0, int nr) __attribute__((always_inline)) {
     const size_t e = e0 + r0 + (tid < nr ? tid : nr - 1);
     s0 = a.stats[e];
     s1 = a.stats[ntok + e];
+    s2 = a.stats[2 * ntok + e];
   };
   auto put_scalars = [&](int nr) __attribute__((always_inline)) {
     if (tid < G::RC) {
-      ml[tid] = tid < nr ? s0 : INFINITY;
-      pl[tid] = tid < nr ? s1 : 0.f;
+      ml[tid] = tid < nr ? s0 : 0.f;
+      il[tid] = tid < nr ? s1 : 0.f;
+      pl[tid] = tid < nr ? s2 : 0.f;
     }
   };
   fetch_scalars(k0, nk);
@@ -644,14 +652,14 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const int t0 = 32 * qt + 16 * s + 4 * g4;
-      const f32x4 mt = *reinterpret_cast<const f32x4*>(ml + t0);
+      const f32x4 mt = *reinterpret_cast<const f32x4*>(ml + t0), it = *reinterpret_cast<const f32x4*>(il + t0);
 #pragma unroll
       for (int n = 0; n < N1; ++n) {
         const int ki = 16 * tile[n] + l16;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const float x = fmaf(sc[n][s][r], to_log2, -mt[r]);
-          sc[n][s][r] = __builtin_amdgcn_exp2f(n != DIAG || t0 + r >= ki ? x : -INFINITY);
+          sc[n][s][r] = __builtin_amdgcn_exp2f(n != DIAG || t0 + r >= ki ? x : -INFINITY) * it[r];
         }
       }
     }

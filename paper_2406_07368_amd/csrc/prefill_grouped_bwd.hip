@@ -100,7 +100,7 @@ __global__ __launch_bounds__(GT * 2) void grouped_bwd_gs_kernel(GroupedBwdArgs a
   float f3 = 0.f, d4 = 0.f;
   if (tid < GT && tid < nt) {
     if (SUMS) f3 = d4 = 1.f;
-    else { f3 = a.stats[2 * n + e0 + tid]; d4 = a.stats[3 * n + e0 + tid]; }
+    else { f3 = a.stats[3 * n + e0 + tid]; d4 = a.stats[4 * n + e0 + tid]; }
   }
   load_rows2<D, GT>(gq, gdo, a.st, tok0, nt, Ql, Dl, tid);
   if (tid < GT) { fs[tid] = f3; dd[tid] = d4; }
@@ -233,7 +233,7 @@ static hipError_t launch_bwd_core(const GroupedBwdArgs& a, const ConvLongArgs* c
   if ((e = launch_grouped_bwd_rows(a, conv, D, false, st)) != hipSuccess) return e;
   if (walk && a.ng > 1) {
     const size_t n = (size_t)BH * a.L;
-    s.a = a.q; s.b = a.dout; s.w = a.stats + 2 * n; s.wz = a.stats + 3 * n; s.slots = a.Dg;
+    s.a = a.q; s.b = a.dout; s.w = a.stats + 3 * n; s.wz = a.stats + 4 * n; s.slots = a.Dg;
     if ((e = launch_group_sums(s, D, GT, true, st)) != hipSuccess) return e;
   } else if (a.ng > 1) {
     hipLaunchKernelGGL(kg, dim3((unsigned)(a.ng - 1), (unsigned)BH), dim3(G::NT), G::TOTAL, st, a);

@@ -215,3 +215,31 @@ def test_gradient_with_one_tile_of_the_sums_per_workgroup(B, H, L, d, group):
     compare(got, want, f"B={B} H={H} L={L} d={d} group={group}")
     again = run(q, k, v, w, dout, group, 0.9, 1e-3)
     assert all(np.array_equal(got[n], again[n]) for n in got)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("group", [64, 256])
+def test_weights_of_large_logits_keep_their_bits(d, group):
+    """Logits of 60 to 330, one of them so far above a query's others that its weight is 1 to the last bit of 64.  Every key has two
+    such queries, of different length, with gradient rows of +-256 that cancel: dv = 256 (p1 - p2) r, zero but for the weights'
+    rounding.  Raw products are whole numbers (exact in fp32); a weight is one exponential, one sum, one reciprocal and one product:
+    four roundings of 2^-24, two weights, and as much again for the accumulation.  Rows rounded to bf16 would hide a wrong scale of
+    the weights everywhere else."""
+    rng = np.random.default_rng(9900 + d + group)
+    B, H, L, half = 2, 2, 2 * group, group // 2
+    q, k, dout = (np.zeros((B, H, L, d)) for _ in range(3))
+    v = workloads.round_to_io(rng.standard_normal((B, H, L, d)), "bf16")
+    w = np.zeros((H, d, 3), dtype=np.float32)
+    for g0 in range(0, L, group):
+        keys = rng.choice([-5.0, -4.0, -3.0, 3.0, 4.0, 5.0], (B, H, half, d))
+        k[:, :, g0:g0 + half] = keys
+        for i in range(0, half, 2):                        # tokens half + i and half + i + 1 look for key i
+            t = g0 + half + i
+            r = rng.choice([-1.0, 1.0], (B, H, d))
+            q[:, :, t], q[:, :, t + 1] = keys[:, :, i], keys[:, :, i] * (2.0 if i % 4 else 1.0) + np.sign(keys[:, :, i])
+            dout[:, :, t], dout[:, :, t + 1] = 256.0 * r, -256.0 * r
+    want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, alpha=0.0, eps=1.0)
+    assert np.abs(want["dv"]).max() < 1e-9
+    got = run(q, k, v, w, dout, group, 0.0, 1.0)
+    err = np.abs(got["dv"]).max()
+    assert err <= 256.0 * 16 * 2.0 ** -24, err
