@@ -432,7 +432,8 @@ static hipError_t launch_split_p(const PrefillArgs& a, int parts, hipStream_t st
 template <int D>
 static hipError_t launch_split_d(const PrefillArgs& a, int parts, hipStream_t st) {
   if (a.no_conv) return launch_split_p<D, 0>(a, parts, st);
-  return a.Kc <= 3 ? launch_split_p<D, 3>(a, parts, st) : launch_split_p<D, 8>(a, parts, st);
+  // (as many tap counts as prefill_grouped256.hip: a tap that does not exist weighs its row with 0, and 0 times an infinity is a NaN)
+  return a.Kc <= 3 ? launch_split_p<D, 3>(a, parts, st) : a.Kc <= 5 ? launch_split_p<D, 5>(a, parts, st) : launch_split_p<D, 8>(a, parts, st);
 }
 hipError_t launch_prefill_grouped256_split(const PrefillArgs& a, int d, int parts, hipStream_t st) {
   return d == 128 ? launch_split_d<128>(a, parts, st) : launch_split_d<64>(a, parts, st);

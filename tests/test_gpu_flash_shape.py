@@ -238,6 +238,29 @@ def test_key_tiles_whose_logits_are_all_minus_infinity(d, heads, L):
     assert (np.abs(got[0] - want[0]) <= 2.0 ** -7 * (np.abs(want[0]) + v.abs().max().item())).all()
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [1, 40, 100])            # workgroups per group of 300 tokens: 8, 4, 1 (of 64 heads 2)
+@pytest.mark.parametrize("Kc", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_values_that_are_not_finite_reach_the_same_outputs_with_a_group_shared(d, heads, Kc):
+    """An infinity or a NaN in the values, inside a group, at its end (the next group's first taps see it) and in its last rows:
+    infinities and NaN come out where the kernel of one workgroup per group has them, whose conv takes no row beyond its taps but for
+    those of a tap count it was not built for."""
+    dt, L = torch.bfloat16, 300
+    g = torch.Generator().manual_seed(7493 + d + Kc)
+    q, k, v = (torch.randn((3, 1, L, d), generator=g) * (d ** -0.5 if i < 2 else 1.0) for i in range(3))
+    v[0, :, 17, 3] = v[1, :, 254, d - 1] = v[2, :, 290, 8] = float("inf")
+    v[0, :, 200, 40], v[2, :, 100, 9] = float("nan"), -float("inf")
+    w = torch.randn((1, d, Kc), generator=g).abs() * 0.3 + 0.1
+    def call(B, one):
+        a = [x[one:one + 1].expand(B, 1, L, d).contiguous().to(dt).cuda() for x in (q, k, v)]
+        out, _ = binding.prefill_grouped(*a, w.cuda(), group=256)
+        torch.cuda.synchronize()
+        return host(out)[:1]
+    for one in range(3):
+        got, want = call(heads, one), call(320, one)
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+
+
 def test_three_branch_form_in_groups_of_256_details():
     """Nothing before the first group and eps = 0 (the linear branch is absent there, no division by zero reaches
     the output); the other feature map; token-major tensors; peaked softmax weights; no leak from later tokens."""
