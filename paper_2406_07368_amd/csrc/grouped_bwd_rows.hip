@@ -519,7 +519,7 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
 
 // ---- dk, dv ---------------------------------------------------------------------------------------------------------
 // Elements NT block .. NT block + NT - 1 of the tap gradient: the partial sums of the token blocks, 32 at a time and those
-// sums in turn, the order of the stages of grouped_bwd_dw_reduce_kernel.
+// sums in turn, the order of the stages of grouped_bwd_dw_reduce_kernel (two of them: dw_sums_ride).
 template <int NT>
 __device__ __forceinline__ void dw_sums(const GroupedBwdArgs& a, int d, int block) {
   const int e = block * NT + threadIdx.x, per_head = d * a.Kc, n = a.B * a.nwb;
@@ -527,9 +527,11 @@ __device__ __forceinline__ void dw_sums(const GroupedBwdArgs& a, int d, int bloc
   const float* p = a.dw_part + (size_t)(e / per_head) * n * per_head + e % per_head;
   float sum = 0.f;
   for (int i0 = 0; i0 < n; i0 += 32) {
-    float s = 0.f;
-#pragma unroll 8
-    for (int i = i0; i < (i0 + 32 < n ? i0 + 32 : n); ++i, p += per_head) s += *p;
+    float x[32], s = 0.f;                                  // every request before the first sum; past the end the last one again, not used
+#pragma unroll
+    for (int i = 0; i < 32; ++i) x[i] = p[(size_t)(i0 + i < n ? i0 + i : n - 1) * per_head];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) s = i0 + i < n ? s + x[i] : s;
     sum += s;
   }
   a.dconv_w[e] = sum;
@@ -830,7 +832,7 @@ hipError_t launch_rows(const GroupedBwdArgs& a, const ConvLongArgs* conv, bool k
     auto k2 = grouped_bwd_dkdv_kernel<D, GT, true>;
     if ((e = split ? LINATTN_MAX_LDS_ONCE(k2, G::TOTAL) : LINATTN_MAX_LDS_ONCE(kk, G::TOTAL)) != hipSuccess) return e;
     dim3 grid((unsigned)(G::NH * a.ng), (unsigned)(a.B * a.H), split ? 2 : 1);
-    if (conv && a.dconv_w) {
+    if (conv && a.dconv_w && dw_sums_ride(a)) {
       const unsigned blocks = (unsigned)((a.H * D * a.Kc + G::NT - 1) / G::NT);
       grid.y += (blocks + grid.x * grid.z - 1) / (grid.x * grid.z);
     }
@@ -852,6 +854,13 @@ hipError_t launch_grouped_bwd_rows(const GroupedBwdArgs& a, const ConvLongArgs* 
 // 64.  us a gradient call, side stream / riding, by runs of queries: groups of 256, d = 128: 4 64.2 / 27.1, 64 79.7 / 68.7, 384 133.8 / 123.6,
 // 960 286 / 271, 1024 201 / 195, 2560 698 / 710; d = 64: 4 65.6 / 18.2, 256 92.5 / 83.2, 2560 296 / 281; groups of 64, d = 128: 64 73.7 / 53.0,
 // 512 129 / 123 and 128 / 127, 528 121 / 124, 768 139 / 151; d = 64: 64 72.6 / 29.8, 768 83.5 / 74.2, 1056 92.2 / 92.7, 1920 117 / 127.
+// The sums over the partial sums are one chain per thread, 32 of them a step: beyond 384 it outlasts the rows, and launches that deal
+// the partial sums out over workgroups are the faster way.  us a gradient call as a graph, launches / riding, by partial sums (batch rows
+// times token blocks): d = 64: groups of 256: 256 43 / 39, 512 67 / 71, 1024 107 / 123, 2560 257 / 321; groups of 64: 384 61.7 / 58.4, 512
+// 39.2 / 43.2; d = 128, groups of 256: 400 157 / 151, 512 141 / 141, 800 199 / 200, 1024 246 / 257.  (Eight at a time, and riding at any
+// number: 2560 403.)
+bool dw_sums_ride(const GroupedBwdArgs& a) { return (int64_t)a.B * a.nwb <= 384; }
+
 bool conv_rides(const GroupedBwdArgs& a, int d) {
   if (conv_mfma_blocks(a.L, a.B * a.H, d) != (a.L + CM_SUB - 1) / CM_SUB) return false;   // (two tiles per workgroup: calls that fill the chip)
   const int run = a.group < 128 ? a.group : 128;

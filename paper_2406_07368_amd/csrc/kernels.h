@@ -238,6 +238,7 @@ hipError_t launch_grouped_bwd_core(const GroupedBwdArgs& a, const ConvLongArgs* 
 // grouped_bwd_rows.hip: dq and the per-token scalars, or dk and dv (keys)
 hipError_t launch_grouped_bwd_rows(const GroupedBwdArgs& a, const ConvLongArgs* conv, int d, bool keys, hipStream_t st);
 bool conv_rides(const GroupedBwdArgs& a, int d);
+bool dw_sums_ride(const GroupedBwdArgs& a);               // ... and the sums of the tap gradient, in the launch of dk and dv
 hipError_t launch_grouped_bwd_dw(const GroupedBwdArgs& a, int d, hipStream_t st);
 
 // prefill_mfma.hip : launch plan of the bf16 prefill (segments, prefix sum over segment states)

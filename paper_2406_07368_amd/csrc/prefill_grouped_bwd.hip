@@ -241,6 +241,7 @@ static hipError_t launch_bwd_core(const GroupedBwdArgs& a, const ConvLongArgs* c
     hipLaunchKernelGGL(grouped_bwd_suffix_kernel, dim3((unsigned)((G::SLOT + 255) / 256), (unsigned)BH), dim3(256), 0, st, a, (int)G::SLOT);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
+  if (conv && a.dconv_w && !dw_sums_ride(a) && (e = launch_grouped_bwd_dw(a, D, st)) != hipSuccess) return e;
   if (before_dkdv && (e = hipStreamWaitEvent(st, before_dkdv, 0)) != hipSuccess) return e;
   return launch_grouped_bwd_rows(a, conv, D, true, st);
 }

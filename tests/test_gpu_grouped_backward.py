@@ -243,3 +243,13 @@ def test_weights_of_large_logits_keep_their_bits(d, group):
     got = run(q, k, v, w, dout, group, 0.0, 1.0)
     err = np.abs(got["dv"]).max()
     assert err <= 256.0 * 16 * 2.0 ** -24, err
+
+
+@pytest.mark.parametrize("d,group", [(64, 256), (128, 64)])
+@pytest.mark.parametrize("B,Kc", [(31, 3), (33, 5), (384, 3), (385, 18), (1030, 3)])
+def test_sums_of_the_tap_gradient_over_many_batch_rows(d, group, B, Kc):
+    """Up to 384 partial sums in the launch of dk and dv, more in launches of their own: in one, two and three stages of 32.  (groups of
+    64 at d = 128 take the side stream beyond 512 heads: the same sums.)"""
+    q, k, v, w, dout = case(9950 + B + d, B, 1, 3, d, Kc)
+    want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, eps=1e-3)
+    compare(run(q, k, v, w, dout, group, 1.0, 1e-3), want, f"d={d} group={group} B={B} Kc={Kc}")
