@@ -848,24 +848,28 @@ hipError_t launch_grouped_bwd_rows(const GroupedBwdArgs& a, const ConvLongArgs* 
 }
 
 // The conv's workgroups in the dq launch and the sums of the tap gradient in the dk / dv launch, instead of launches of their
-// own on a side stream.  Calls that do not fill the chip gain: the events that fork and join the stream cost the host 40 us, more than
-// such a call's work, and in the dq launch the conv costs the GPU next to nothing.  Where the rows' workgroups fill the chip by themselves,
-// the conv in its own shape (four waves, more channels: memory lines shared) is the better one, more so against the two waves of groups of
-// 64.  us a gradient call, side stream / riding, by runs of queries: groups of 256, d = 128: 4 64.2 / 27.1, 64 79.7 / 68.7, 384 133.8 / 123.6,
-// 960 286 / 271, 1024 201 / 195, 2560 698 / 710; d = 64: 4 65.6 / 18.2, 256 92.5 / 83.2, 2560 296 / 281; groups of 64, d = 128: 64 73.7 / 53.0,
-// 512 129 / 123 and 128 / 127, 528 121 / 124, 768 139 / 151; d = 64: 64 72.6 / 29.8, 768 83.5 / 74.2, 1056 92.2 / 92.7, 1920 117 / 127.
-// The sums over the partial sums are one chain per thread, 32 of them a step: beyond 384 it outlasts the rows, and launches that deal
-// the partial sums out over workgroups are the faster way.  us a gradient call as a graph, launches / riding, by partial sums (batch rows
-// times token blocks): d = 64: groups of 256: 256 43 / 39, 512 67 / 71, 1024 107 / 123, 2560 257 / 321; groups of 64: 384 61.7 / 58.4, 512
-// 39.2 / 43.2; d = 128, groups of 256: 400 157 / 151, 512 141 / 141, 800 199 / 200, 1024 246 / 257.  (Eight at a time, and riding at any
-// number: 2560 403.)
-bool dw_sums_ride(const GroupedBwdArgs& a) { return (int64_t)a.B * a.nwb <= 384; }
-
+// own on a side stream.  Calls that do not fill the chip gain: the events that fork and join the stream cost the host 40 us, more
+// than such a call's work, and in the dq launch the conv costs the GPU next to nothing.  Where the rows' workgroups fill the chip by
+// themselves, the conv in its own shape (four waves, more channels: memory lines shared) is the better one, more so against the two
+// waves of groups of 64.  us a gradient call as a graph (in brackets: as plain calls, where the host's share differs), side stream /
+// riding, by runs of queries:
+//   groups of 256, d = 128: 64 57.8 / 45.4 (68 / 46), 512 138 / 136, 768 223 / 216 and 196 / 197, 1000 303 / 301, 1024 235 / 242
+//   and 274 / 270; d = 64: 64 30.1 / 20.9 (76 / 23), 1024 119 / 110, 2048 205 / 198, 2560 254 / 254 and 301 / 286
+//   groups of 64, d = 128: 128 68 / 61 (82 / 62), 256 63 / 60, 314 114 / 106, 320 81 / 81 and 85 / 88, 384 86 / 89, 448 95 / 104,
+//   512 98 / 106 and 118 / 124; d = 64: 256 49 / 40 (80 / 40), 768 60.7 / 56.0 and 71.9 / 72.1 (91 / 72), 896 77 / 80 and 65 / 63
+//   (89 / 80 and 90 / 63), 1000 102 / 106 (101 / 106), 1024 81 / 86 (92 / 87)
 bool conv_rides(const GroupedBwdArgs& a, int d) {
   if (conv_mfma_blocks(a.L, a.B * a.H, d) != (a.L + CM_SUB - 1) / CM_SUB) return false;   // (two tiles per workgroup: calls that fill the chip)
   const int run = a.group < 128 ? a.group : 128;
   const int64_t runs = (int64_t)((a.L + run - 1) / run) * a.B * a.H;
-  return runs <= (a.group == 256 ? (d == 128 ? 1024 : 2560) : (d == 128 ? 512 : 1024));
+  return runs <= (a.group == 256 ? (d == 128 ? 768 : 2560) : (d == 128 ? 320 : 896));
 }
+
+// The sums over the partial sums are one chain per thread, 32 of them a step: beyond 384 it outlasts the rows, and launches that
+// deal the partial sums out over workgroups are the faster way.  us a gradient call as a graph, launches / riding, by partial sums
+// (batch rows times token blocks): d = 64: groups of 256: 256 43 / 39, 512 67 / 71, 1024 107 / 123, 2560 257 / 321; groups of 64:
+// 384 61.7 / 58.4, 512 39.2 / 43.2; d = 128, groups of 256: 400 157 / 151, 512 141 / 141, 800 199 / 200.  (Eight at a time, and
+// riding at any number: 2560 403.)
+bool dw_sums_ride(const GroupedBwdArgs& a) { return (int64_t)a.B * a.nwb <= 384; }
 
 }  // namespace linattn
