@@ -124,7 +124,7 @@ PrefillPlan plan_prefill(const linattn_desc* d, int32_t L, bool grouped = false)
   p.ws_bytes = g256 ? prefill_grouped256_workspace_bytes(heads, d->d, p.nseg)
                                   : prefill_mfma_workspace_bytes(heads, d->d, p.nseg);
   if (g256) {
-    p.fine = prefill_grouped256_fine(heads, p.nseg, p.seg_len);
+    p.fine = prefill_grouped256_fine(heads, p.nseg, p.seg_len, d->d, d->conv_k);
     p.fine_bytes = prefill_grouped256_fine_bytes(heads, d->d, p.nseg, p.fine);
   }
   return p;

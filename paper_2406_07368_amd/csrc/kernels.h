@@ -253,7 +253,7 @@ hipError_t launch_prefill_mfma(const PrefillArgs& a, int d, int chunk, bool grou
 // workspace slot per (b, h, segment) also without segments
 int prefill_grouped256_pick_segments(int BH, int L);
 size_t prefill_grouped256_workspace_bytes(int BH, int d, int nseg);
-int prefill_grouped256_fine(int BH, int nseg, int seg_len);        // log2 of the parts of a segment in the first pass
+int prefill_grouped256_fine(int BH, int nseg, int seg_len, int d, int conv_k);   // log2 of the parts of a segment in the first pass
 size_t prefill_grouped256_fine_bytes(int BH, int d, int nseg, int fine);   // what that takes behind the workspace
 hipError_t launch_first_pass(const PrefillArgs& a, int d, hipStream_t st);
 hipError_t launch_prefill_grouped256(const PrefillArgs& a, int d, hipStream_t st);

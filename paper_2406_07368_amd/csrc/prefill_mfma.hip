@@ -105,16 +105,27 @@ size_t prefill_grouped256_workspace_bytes(int BH, int d, int nseg) {
   return (size_t)BH * nseg * ((size_t)d * d + d) * sizeof(float) + (size_t)BH * HALO * d * sizeof(uint16_t);
 }
 
-// The first pass over segments of one group, where they are few: 2 or 4 workgroups share a segment's 256 tokens, as many as have a
-// compute unit each, and the prefix sum adds their increments up.  A workgroup's walk over four steps of 64 tokens was the
-// longest part of such a call's first half (10.9 of 31 us at 8 heads of 1000 tokens).  What it costs are more slots written and read, so never
-// more workgroups than compute units.  us a call of 63 taps as a graph, whole segments / parts: d = 128: 4 heads, 300 tokens 26.5 / 23.1, 8 heads: 1000
-// 30.0 / 29.1, 2000 37.2 / 35.7, 2200 (2 parts) 41.2 / 38.6, 4000 49.8 / 48.2, 16 heads, 1000 39.2 / 36.3, 40 heads, 700 49.1 / 46.6, 120 heads, 500
-// 73.4 / 71.7; d = 64: 8 heads: 1000 20.6 / 18.6, 4000 29.4 / 28.1, 60 heads, 700 36.0 / 33.7, 120 heads, 500 40.8 / 38.1; 5 taps, 4 heads, 600 17.1 / 14.6.
-int prefill_grouped256_fine(int BH, int nseg, int seg_len) {
+// The first pass over segments of one group, where they are few: 2 or 4 workgroups share a segment's 256 tokens, while each has
+// a compute unit, and the prefix sum adds their increments up.  A workgroup's walk over four steps of 64 tokens was the longest
+// part of such a call's first half (10.9 of 31 us at 8 heads of 1000 tokens).  What it costs are more slots written and read: a
+// longer chain in the prefix sum where a head has many segments (at most 48 slots in four parts, 64 in two), and more of its
+// traffic where the heads are many: sequences of two groups on more than 96 heads keep whole segments -- at d = 128 on more than 64,
+// without a long conv beside the prefix sum --, but for long taps at d = 64, whose conv lasts longer than the prefix sum either way.
+// us a call as a graph, whole segments / two parts / four:
+//   63 taps, d = 128: 4 heads, 300 tokens 26.5 / - / 23.1; 8 heads, 1000 30.0 / - / 29.1, 2000 38.2 / 35.6 / 36.1, 3000 43.2 / 40.4; 4 heads, 3000
+//   34.6 / 32.6 / 32.5; 1 head, 8000 37.6 / 36.0 / 39.0, 12000 35.2 / 33.4 / 37.5, 16000 37.5 / 37.8 / 44.1; two groups: 65 heads 55.7 / 53.0, 90
+//   57.1 / 56.4, 110 65.5 / 66.8, 128 71.0 / 75.4; d = 64: 8 heads, 2000 23.1 / 21.4 / 21.3; 1 head, 4000 20.0 / 17.9 / 17.3, 16000 24.0 / 25.8 / 32.2;
+//   128 heads, two groups 42.3 / 39.4
+//   5 taps, d = 128: 8 heads, 2000 36.4 / 35.3 / 37.2; 1 head, 8000 36.3 / 36.0 / 39.5; 64 heads, three groups 53.9 / 53.3; two groups: 64 heads
+//   47.2 / - / 46.9, 65 52.5 / 54.6, 128 61.0 / 63.6; d = 64: 1 head, 16000 22.1 / 23.9 / 30.8; two groups: 80 heads 28.8 / 28.6, 128 31.6 / 31.9
+int prefill_grouped256_fine(int BH, int nseg, int seg_len, int d, int conv_k) {
   if (nseg <= 1 || seg_len != 256) return 0;
   const int64_t segs = (int64_t)BH * (nseg - 1);
-  return 4 * segs <= 256 ? 2 : 2 * segs <= 256 ? 1 : 0;
+  if (4 * segs <= 256 && 4 * (nseg - 1) <= 48) return 2;
+  if (2 * segs > 256 || 2 * (nseg - 1) > 64) return 0;
+  const bool long_conv = conv_k > 8;
+  if (nseg == 2 && (d == 128 ? !long_conv || segs > 96 : !long_conv && segs > 96)) return 0;
+  return 1;
 }
 size_t prefill_grouped256_fine_bytes(int BH, int d, int nseg, int fine) {
   return fine ? (size_t)BH * (((size_t)(nseg - 1) << fine) + 1) * ((size_t)d * d + d) * sizeof(float) : 0;

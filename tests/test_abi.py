@@ -250,3 +250,16 @@ def test_no_plan_asks_for_more_than_the_static_scratch(dtype, d):
                 desc = binding.make_desc(1, heads, d, 3, 64, io, L=L, d_v=m * d)
                 most = max(most, binding.linattn_workspace_bytes(desc, L))
     assert 0 < most <= binding.linattn_noalloc_scratch_bytes()
+
+
+@pytest.mark.parametrize("H,L,d,Kc,parts", [
+    (8, 1000, 128, 63, 4), (64, 500, 128, 3, 4), (4, 3300, 64, 3, 4), (4, 3400, 64, 3, 2), (1, 8448, 128, 63, 2), (1, 8449, 128, 63, 1),
+    (1, 16000, 64, 5, 1), (65, 500, 128, 3, 1), (60, 700, 128, 3, 2), (96, 500, 128, 63, 2), (97, 500, 128, 63, 1), (96, 500, 64, 3, 2),
+    (97, 500, 64, 3, 1), (128, 500, 64, 63, 2)])
+def test_parts_of_a_segment_in_the_workspace(H, L, d, Kc, parts):
+    """Groups of 256: the slots of the first pass's parts, where the plan has them -- not where the prefix sum over them would take
+    longer than the parts save: long chains, many heads of two groups."""
+    nseg = min(-(-L // 256), 256 // H, 64)
+    slot = (d * d + d) * 4
+    want = H * (nseg * slot + 8 * d * 2) + (H * ((nseg - 1) * parts + 1) * slot if parts > 1 else 0)
+    assert binding.linattn_workspace_bytes(binding.make_desc(1, H, d, Kc, 256, L=L), L) == want
