@@ -367,7 +367,7 @@ static hipError_t launch_nt(const VerifyArgs& a, hipStream_t st) {
 //   8 drafts   32 heads 15.3 / 11.4 / 11.8, 192 17.9 / 13.7 / 12.9, 256 21.8 / 16.3 / 14.9, 320 24.7 / 19.6 / 24.8, 512 26.4 / 21.3 / 26.8, 640 29.6 / 31.9 / 37.2
 //   16 drafts  4 heads 20.0 / 14.3, 320 30.6 / 29.1, 640 58.6 / 45.0, 1024 65.3 / 62.1 (1024 threads: registers)
 // 64 x 128 state, 256 / 512 threads: 8 drafts 128 heads 11.9 / 11.4, 384 14.7 / 13.3, 768 19.9 / 23.4; 16 drafts 384 18.5 / 23.4, 1024 38.2 / 45.2.
-// 64 x 64: 256 threads have a row each in four passes.
+// 64 x 64: 256 threads have a row each in four passes.  Slices of 128 x 64 (launch_d) as 64 x 128.
 static int pick_threads(int state, int kp, int blocks) {
   if (state == 64 * 64) return 256;
   if (state == 64 * 128) return blocks <= (kp == 16 ? 256 : 384) ? 512 : 256;
@@ -398,11 +398,27 @@ static hipError_t launch_cw(const VerifyArgs& a, hipStream_t st) {
   return launch_kp<Io, D, CW, 16>(a, st);
 }
 
-// whole heads where the value rows have up to 128 elements, slices of D columns otherwise
+// Whole heads where the value rows have up to 128 elements, slices otherwise, z in a launch of its own: of D columns, but at D =
+// 128 of 64 while the chip has room for all of them (up to 384, of 512 threads), and of 64 or 32 where blocks of 128 would leave a
+// second round to a few workgroups.  Measured, us a call as a graph, d_v = 256 and 1024, by blocks of 128 columns, slices of 32 /
+// 64 / 128:
+//   1 draft    64 blocks 8.0 / 7.8 / 8.1, 192 9.2 / 9.1 / 9.1, 256 9.8 / 10.2 / 9.9, 288 11.7 / 12.4 / 13.0, 384 14.4 / 14.3 / 13.0
+//   2 drafts   64 8.7 / 8.4 / 8.7, 192 10.1 / 9.9 / 9.9, 288 12.0 / 13.0 / 13.6, 384 15.2 / 15.2 / 15.2
+//   4 drafts   64 9.2 / 9.4 / 10.9, 128 10.4 / 10.1 / 11.6, 192 11.3 / 11.7 / 11.6, 256 12.9 / 11.5 / 12.1, 320 14.3 / 13.7 / 16.1
+//   8 drafts   64 12.5 / 12.2 / 13.7, 128 14.3 / 12.9 / 15.0, 192 15.8 / 15.2 / 15.5, 256 18.3 / 15.6 / 16.3, 320 24.0 / 18.6 / 19.5
+//   16 drafts  64 14.2 / 14.4 / 17.2, 128 17.6 / 14.9 / 17.6, 192 25.2 / 19.6 / 17.8, 320 36 / 30 / 31
+// d = 64 (d_v = 256 on): slices of 64 columns as before the whole heads: 64 blocks, 1, 8 and 16 drafts 7.3, 11.3, 13.3.
 template <typename Io, int D>
 static hipError_t launch_d(const VerifyArgs& a, hipStream_t st) {
   if constexpr (D == 64)
     if (a.dv == 128) return launch_cw<Io, D, 2 * D>(a, st);
+  if constexpr (D == 128)
+    if (a.dv > D) {
+      const int blocks = a.B * a.H * (a.dv / D);
+      const bool odd_round = blocks > 256 && blocks < 384;
+      if (odd_round && a.kk <= 2) return a.kk == 1 ? launch_nt<Io, D, D / 4, 1, 256>(a, st) : launch_nt<Io, D, D / 4, 2, 256>(a, st);
+      if (odd_round || blocks <= (a.kk > 8 ? 128 : 192)) return launch_cw<Io, D, D / 2>(a, st);
+    }
   return launch_cw<Io, D, D>(a, st);
 }
 

@@ -122,6 +122,29 @@ def test_verify_and_decode_with_wide_values(io, B, H, d, m, kk, Kc):
     check(host(st1[1]), want1[2], STATE_TOL, "decode z")
 
 
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+@pytest.mark.parametrize("kk", [1, 2, 4, 7, 13])
+@pytest.mark.parametrize("H,m", [(3, 2), (64, 2), (65, 2), (96, 2), (97, 2), (43, 6), (144, 2), (12, 16), (13, 16), (191, 2), (192, 2)])
+def test_verify_with_wide_values_in_slices(io, kk, H, m):
+    """d = 128: blocks of 128 columns in slices of 64 (up to 192 of them, 128 for more than eight drafts; between 257 and 383), 32 (there, for
+    one and two drafts) or as they are."""
+    d, Kc = 128, 3
+    rng = np.random.default_rng(8300 + H + m + kk)
+    q, k, v, w, state = wide_case(8300 + H + m + kk, 1, H, kk, d, m, Kc, io, True, scale=0.7)
+    S0, z0, h0 = state
+    z0 = z0 + 20.0
+    n = np.array([kk // 2 + 1], dtype=np.int32)
+    want = oracle.verify(q, k, v, w, S0, z0, h0, n, eps=1e-3)
+    dt = IO[io]
+    st = (dev(S0), dev(z0), dev(h0, dt))
+    out = binding.verify(dev(q, dt), dev(k, dt), dev(v, dt), dev(w), st, torch.from_numpy(n).cuda(), 1e-3)
+    torch.cuda.synchronize()
+    check(host(out), want[0], TOL[io], "out")
+    check(host(st[0]), want[1], 1e-5, "S")
+    check(host(st[1]), want[2], 1e-5, "z")
+    assert np.array_equal(host(st[2]), workloads.round_to_io(want[3], io).astype(np.float64)), "hist"
+
+
 def test_wide_values_workloads_every_head():
     """B8 H32 L4096 d_k 64 d_v 128 bf16 at full size (the launch the bench times), then the verify workload:
     B32 H32, state from a 2048-token prefix, 8 drafts; every head against the oracle."""
