@@ -575,7 +575,7 @@ def main():
     if args.only == "all" and not args.length:
         # next row of the scope (not part of the step): value rows wider than key rows, d_k 64 / d_v 128 on the
         # LLaMA layer shape -- prefill (two value blocks per head on the matrix-core kernel, q and k read by both)
-        # and an 8-draft verify step (streaming kernel: column slices of the 64 x 128 state)
+        # and an 8-draft verify step (the matrix-core kernel, two blocks of 64 x 64 per head)
         wide = {}
         wl = workloads.CONFIGS["wide_values_prefill"]
         gs = torch.Generator(device=dev).manual_seed(wl.seed)

@@ -13,13 +13,13 @@
 // convolution over (history ++ drafts <= j).
 //
 // What bounds it: with few heads the one launch and its chain of request, products,
-// reduction (6 us of GPU time, behind a host call of about 11); with many the state's
+// reduction (5.2 us as a graph for one draft, as long as a plain call's host part); with many the state's
 // traffic.  Few heads get more threads each (pick_threads), so that the whole state
 // is requested at once.  Splitting a head's columns over four workgroups instead put as
 // many requests under way, but then all of them read the old z and a second launch had
-// to advance it, and every slice repeated the drafts' feature maps and scores.  us a call,
-// slices / whole heads: B1 H32 d128 one draft 14.7 / 11.6, eight 14.6 / 11.4; B8 H32 d128 eight 19.8 /
-// 14.9; B8 H32 d64 sixteen 26.8 / 12.7.
+// to advance it, and every slice repeated the drafts' feature maps and scores.  us a call
+// as a graph, slices / whole heads: B1 H32 d128 one draft 8.1 / 5.5, eight 12.6 / 10.9; B8 H32 d128 eight 18.2 /
+// 14.6; 200 heads of 64, sixteen 26.4 / 10.9.
 #include "common.h"
 #include "kernels.h"
 
@@ -359,21 +359,26 @@ static hipError_t launch_nt(const VerifyArgs& a, hipStream_t st) {
 
 // Threads per workgroup.  More threads ask for more of the state at once and shorten the chain of row passes, which
 // is all that counts while every workgroup has a compute unit of its own; beyond that, fewer threads let more workgroups
-// share one (and 8 drafts, 120 registers, fill it with 1024 threads).  Measured, us a call, 256 / 512 / 1024 threads, 128 x 128 state:
-//   1 draft    256 heads 14.3 / 11.5 / 11.4, 512 17.8 / 13.9 / 12.9, 576 19.5 / 16.1 / 15.1, 640 19.9 / 16.8 / 18.8, 768 21.2 / 19.4 / 21.1,
-//              1024 26.0 / 28.8 / 26.9
-//   2 drafts   320 heads 10.0 (1024), 11.5 (512); 576 20.9 (256), 16.3 (1024); 640 20.9 (256), 17.4 (512)
-//   4 drafts   256 heads 16.3 / 12.2 / 11.5, 320 18.6 / 14.4 / 16.1, 512 20.3 / 16.0 / 17.2, 640 22.5 / 23.6 / 23.8
-//   8 drafts   32 heads 15.3 / 11.4 / 11.8, 192 17.9 / 13.7 / 12.9, 256 21.8 / 16.3 / 14.9, 320 24.7 / 19.6 / 24.8, 512 26.4 / 21.3 / 26.8, 640 29.6 / 31.9 / 37.2
-//   16 drafts  4 heads 20.0 / 14.3, 320 30.6 / 29.1, 640 58.6 / 45.0, 1024 65.3 / 62.1 (1024 threads: registers)
-// 64 x 128 state, 256 / 512 threads: 8 drafts 128 heads 11.9 / 11.4, 384 14.7 / 13.3, 768 19.9 / 23.4; 16 drafts 384 18.5 / 23.4, 1024 38.2 / 45.2.
-// 64 x 64: 256 threads have a row each in four passes.  Slices of 128 x 64 (launch_d) as 64 x 128.
+// share one (and 8 drafts, 120 registers, fill it with 1024 threads).  Measured, us a call as a graph (a plain call takes the
+// host about 5), 256 / 512 / 1024 threads, 128 x 128 state:
+//   1 draft    4 heads 7.3 / 5.9 / 5.2, 256 13.0 / 9.8 / 7.6, 512 17.5 / 13.5 / 12.9, 576 19.2 / 16.2 / 15.4, 640 19.5 / 16.7 / 17.8,
+//              767 20.6 / 18.6 / 20.4; fp32 rows 900 23.9 / 24.4 / 24.7, 1024 26.1 / 28.2 / 26.6
+//   2 drafts   4 heads 8.2 / 6.5 / 5.7, 256 15.1 / 10.7 / 8.2, 512 18.5 / 14.1 / 13.7, 576 20.3 / 16.5 / 16.9, 640 20.8 / 17.1 / 19.5;
+//              fp32 rows 900 24.7 / 25.1 / 25.8, 1024 27.2 / 28.0 / 28.7
+//   4 drafts   4 heads 9.3 / 7.5 / 7.8, 64 9.9 / 8.1 / 8.5, 128 13.1 / 9.8 / 9.2, 256 15.9 / 11.7 / 9.9, 320 18.4 / 14.1 / 16.5,
+//              512 19.9 / 15.6 / 17.2, 576 21.8 / 21.1 / 23.6, 640 22.2 / 22.9 / 23.8
+//   8 drafts   4 heads 14.6 / 10.6 / 11.2, 64 15.9 / 11.8 / 12.0, 128 15.4 / 11.7 / 12.1, 192 16.7 / 13.1 / 12.9, 256 21.4 / 15.9 / 14.6,
+//              320 22.7 / 18.3 / 23.2, 512 26.5 / 21.5 / 27.2, 576 28.9 / 30.4 / 36.3
+//   16 drafts  one kernel, of 512 threads (1024 have too few registers): 4 heads 14.2, 256 17.3, 767 46; fp32 rows 1024 61
+// 64 x 128 state, 256 / 512 threads: 1 draft 32 heads 6.0 / 5.2, 384 7.6 / 7.1; 8 drafts 32 11.2 / 8.9, 256 11.9 / 9.8, 384 12.9 / 12.8,
+// 767 19.4 / 22.3; 16 drafts 256 15.6 / 12.7, 288 17.2 / 22.6, 1024 37.8 / 45.2.  Slices of 128 x 64 (launch_d) likewise.
+// 64 x 64: 256 threads have a row each in four passes.
 static int pick_threads(int state, int kp, int blocks) {
   if (state == 64 * 64) return 256;
   if (state == 64 * 128) return blocks <= (kp == 16 ? 256 : 384) ? 512 : 256;
   if (kp == 16) return 512;
   if (kp <= 2) return blocks <= 576 ? 1024 : blocks < 1024 ? 512 : 256;
-  if (kp == 8 && blocks <= 64) return 512;
+  if (blocks <= (kp == 8 ? 128 : 64)) return 512;
   return blocks <= 256 ? 1024 : blocks <= 512 ? 512 : 256;
 }
 
@@ -385,7 +390,8 @@ static hipError_t launch_kp(const VerifyArgs& a, hipStream_t st) {
     if (nt >= 1024) return launch_nt<Io, D, CW, KP, 1024>(a, st);
   if constexpr (D * CW >= 64 * 128)
     if (nt >= 512) return launch_nt<Io, D, CW, KP, 512>(a, st);
-  if constexpr (D * CW < 128 * 128 || KP < 16) return launch_nt<Io, D, CW, KP, 256>(a, st);
+  // (768 blocks of bf16 rows and more are verify_mfma.hip's: one and two drafts of them never come here)
+  if constexpr (D * CW < 128 * 128 || (KP < 16 && (KP > 2 || sizeof(typename Io::elem) == 4))) return launch_nt<Io, D, CW, KP, 256>(a, st);
   return hipErrorInvalidValue;                             // (not reached)
 }
 
