@@ -50,37 +50,36 @@ def test_verify_matches_oracle_small(io, d, kk, Kc):
     assert np.array_equal(got[3], workloads.round_to_io(want[3], io).astype(np.float64)), "hist"
 
 
-@pytest.mark.parametrize("BH,expect_split", [((24, 32), 1), ((16, 32), 2), ((2, 32), 4)])
-def test_verify_every_column_split(BH, expect_split):
-    """B*H decides over how many workgroups a head's columns are spread; all variants must agree with the oracle."""
-    B, H = BH
+@pytest.mark.parametrize("B,H", [(24, 32), (16, 32), (2, 32)])
+def test_verify_on_both_sides_of_the_matrix_core_line(B, H):
+    """768 heads of bf16 drafts and more take the matrix-core kernel, fewer the streaming one; both must agree with the oracle."""
     d, Kc, kk, io = 64, 3, 4, "bf16"
     q, k, v, w, S, z, hist = make_case(7, B, H, d, Kc, kk, io, prefix=8)
     n_commit = (np.arange(B) % (kk + 1)).astype(np.int32)
     want = oracle.verify(q, k, v, w, S, z, hist, n_commit)
     got = run_gpu(q, k, v, w, S, z, hist, io, n_commit)
     check(got[0], want[0], TOL[io], "out")
-    # whole heads of bf16 drafts take the matrix-core kernel (phi(k) as two bf16 terms), the others the
-    # column-split kernel (fp32 products): the same state either way
+    # the matrix-core kernel takes phi(k) as two bf16 terms, the streaming kernel fp32 products: the same state either way
     check(got[1], want[1], STATE_TOL, "S")
     check(got[2], want[2], STATE_TOL, "z")
     assert np.array_equal(got[3], workloads.round_to_io(want[3], io).astype(np.float64))
 
 
 @pytest.mark.parametrize("io", ["bf16", "f32"])
-@pytest.mark.parametrize("B,H", [(1, 1), (5, 13), (1, 257), (1, 385), (27, 19), (1, 577)])
-@pytest.mark.parametrize("kk", [1, 3, 7, 15])
+@pytest.mark.parametrize("B,H", [(1, 1), (1, 64), (5, 13), (1, 129), (1, 257), (1, 385), (27, 19), (1, 577), (1, 1025)])
+@pytest.mark.parametrize("kk", [1, 2, 3, 7, 15])
 def test_verify_every_workgroup_size(io, B, H, kk):
     """One workgroup per head, its threads chosen by the number of heads and drafts: 256, 512 and 1024 threads on each
-    number of drafts a kernel is built for."""
+    number of drafts a kernel is built for (one and two drafts on 256 threads: fp32 only, from 1024 heads on; 1025 heads of bf16 drafts are
+    the matrix-core kernel's)."""
     d, Kc = 128, 4
     q, k, v, w, S, z, hist = make_case(40 + kk + B * H, B, H, d, Kc, kk, io, prefix=4)
     n_commit = (np.arange(B) % (kk + 1)).astype(np.int32) if B > 1 else np.array([kk], dtype=np.int32)
     want = oracle.verify(q, k, v, w, S, z, hist, n_commit, eps=1e-3)
     got = run_gpu(q, k, v, w, S, z, hist, io, n_commit, eps=1e-3)
     check(got[0], want[0], TOL[io], "out")
-    check(got[1], want[1], 1e-5, "S")
-    check(got[2], want[2], 1e-5, "z")
+    check(got[1], want[1], STATE_TOL if io == "bf16" and B * H >= 768 else 1e-5, "S")
+    check(got[2], want[2], STATE_TOL if io == "bf16" and B * H >= 768 else 1e-5, "z")
     assert np.array_equal(got[3], workloads.round_to_io(want[3], io).astype(np.float64)), "hist"
 
 
@@ -133,7 +132,7 @@ def test_matrix_core_verify_equals_sequential_decode_and_leaks_nothing():
 
 
 def test_fp32_drafts_on_whole_heads_keep_the_exact_update():
-    """fp32 drafts never take the matrix-core kernel: B*H >= 768 runs the streaming kernel unsplit (fp32 products)."""
+    """fp32 drafts never take the matrix-core kernel: B*H >= 768 runs the streaming kernel (fp32 products)."""
     B, H, d, Kc, kk, io = MB, MH, 64, 3, 5, "f32"
     q, k, v, w, S, z, hist = make_case(19, B, H, d, Kc, kk, io, prefix=8)
     n_commit = (np.arange(B) % (kk + 1)).astype(np.int32)

@@ -124,11 +124,12 @@ def test_verify_and_decode_with_wide_values(io, B, H, d, m, kk, Kc):
 
 @pytest.mark.parametrize("io", ["bf16", "f32"])
 @pytest.mark.parametrize("kk", [1, 2, 4, 7, 13])
-@pytest.mark.parametrize("H,m", [(3, 2), (64, 2), (65, 2), (96, 2), (97, 2), (43, 6), (144, 2), (12, 16), (13, 16), (191, 2), (192, 2)])
-def test_verify_with_wide_values_in_slices(io, kk, H, m):
+@pytest.mark.parametrize("H,d,m", [(3, 128, 2), (64, 128, 2), (65, 128, 2), (96, 128, 2), (97, 128, 2), (43, 128, 6), (144, 128, 2), (12, 128, 16),
+                                   (13, 128, 16), (191, 128, 2), (192, 128, 2), (256, 64, 2), (257, 64, 2), (383, 64, 2), (385, 64, 2), (40, 64, 5)])
+def test_verify_with_wide_values_in_slices(io, kk, H, d, m):
     """d = 128: blocks of 128 columns in slices of 64 (up to 192 of them, 128 for more than eight drafts; between 257 and 383), 32 (there, for
-    one and two drafts) or as they are."""
-    d, Kc = 128, 3
+    one and two drafts) or as they are.  d = 64: a state of 64 x 128 is one workgroup's, of 256 or 512 threads; wider ones in slices of 64."""
+    Kc = 3
     rng = np.random.default_rng(8300 + H + m + kk)
     q, k, v, w, state = wide_case(8300 + H + m + kk, 1, H, kk, d, m, Kc, io, True, scale=0.7)
     S0, z0, h0 = state
@@ -140,8 +141,9 @@ def test_verify_with_wide_values_in_slices(io, kk, H, m):
     out = binding.verify(dev(q, dt), dev(k, dt), dev(v, dt), dev(w), st, torch.from_numpy(n).cuda(), 1e-3)
     torch.cuda.synchronize()
     check(host(out), want[0], TOL[io], "out")
-    check(host(st[0]), want[1], 1e-5, "S")
-    check(host(st[1]), want[2], 1e-5, "z")
+    mfma = io == "bf16" and H * m >= 768                   # phi(k) as two bf16 terms
+    check(host(st[0]), want[1], STATE_TOL if mfma else 1e-5, "S")
+    check(host(st[1]), want[2], STATE_TOL if mfma else 1e-5, "z")
     assert np.array_equal(host(st[2]), workloads.round_to_io(want[3], io).astype(np.float64)), "hist"
 
 
