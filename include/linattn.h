@@ -187,7 +187,7 @@ size_t linattn_noalloc_scratch_bytes(void);
  * fp32 rows in exact fp32 products: groups of 64 on the fp32 matrix instructions,
  * groups of 256 on the vector ALUs.  For fp32 rows (here and in linattn_prefill) a
  * missing or short workspace is no error: the sequence is then not split over
- * workgroups. */
+ * workgroups (rows of 64: split into half as many parts where it has room for these). */
 linattn_status linattn_prefill_grouped(const linattn_desc *desc, int32_t L, float alpha,
                                        const void *q, const void *k, const void *v,
                                        const float *conv_w,

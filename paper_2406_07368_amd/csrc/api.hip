@@ -103,7 +103,7 @@ struct PrefillPlan {
 // matrix instructions (exact fp32 products), bf16 inputs to the bf16 one; when B*H alone
 // cannot fill the 256 compute units the sequence axis is cut into segments whose start
 // states come from a first pass over K, V and a scan.
-PrefillPlan plan_prefill(const linattn_desc* d, int32_t L, bool grouped = false) {
+PrefillPlan plan_prefill(const linattn_desc* d, int32_t L, bool grouped = false, int f32_per_cu = 4) {
   PrefillPlan p{};
   p.mfma = d->io_dtype == LINATTN_BF16;
   const bool g256 = p.mfma && grouped && d->chunk == 256;   // three-branch form in groups of 256: its own full pass
@@ -112,7 +112,7 @@ PrefillPlan plan_prefill(const linattn_desc* d, int32_t L, bool grouped = false)
   const int heads = d->B * d->H * value_blocks(d);      // what the kernels see as heads: one per value block
   if (!p.mfma) {
     if (L <= 0 || (grouped && d->chunk == 256)) return p;   // (groups of 256: one workgroup per head)
-    const F32Plan f = prefill_f32_plan(heads, L, d->d, grouped);
+    const F32Plan f = prefill_f32_plan(heads, L, d->d, grouped, f32_per_cu);
     p.nseg = f.nseg; p.seg_len = f.seg_len; p.direct = f.direct;
     p.ws_bytes = prefill_f32_workspace_bytes(heads, d->d, f);
     return p;
@@ -213,7 +213,9 @@ linattn_status prefill_any(const linattn_desc* desc, int32_t L, bool grouped, fl
       (double)desc->stride_b_v * desc->B + (double)desc->stride_h_v * desc->H + (double)desc->stride_t_v * L > 9.0e18)
     return LINATTN_ERR_SHAPE;
   PrefillPlan plan = plan_prefill(desc, L, grouped);
-  const bool no_ws = plan.ws_bytes > 0 && (!workspace || workspace_bytes < plan.ws_bytes);
+  auto short_ws = [&] { return plan.ws_bytes > 0 && (!workspace || workspace_bytes < plan.ws_bytes); };
+  if (short_ws() && !plan.mfma) plan = plan_prefill(desc, L, grouped, 2);      // (at d = 64 half of the segments)
+  const bool no_ws = short_ws();
   if (no_ws && plan.mfma) return LINATTN_ERR_WORKSPACE;
   // fp32 rows: a workspace buys segments, nothing else; and in the quadratic kernel every workgroup reads
   // the incoming state, so none of the outputs may be it

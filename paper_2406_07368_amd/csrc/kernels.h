@@ -209,7 +209,8 @@ struct F32Plan {
   int nseg, seg_len;        // workgroups along the sequence axis, tokens of each
   bool direct;              // the quadratic kernel: one launch, no workspace
 };
-F32Plan prefill_f32_plan(int heads, int L, int d, bool grouped);
+// per_cu: most workgroups per compute unit, 4 or 2 (a workspace that has room for half of the segments)
+F32Plan prefill_f32_plan(int heads, int L, int d, bool grouped, int per_cu);
 size_t prefill_f32_workspace_bytes(int heads, int d, const F32Plan& p);
 hipError_t launch_prefill_f32(const PrefillArgs& a, int d, bool grouped, hipStream_t st);
 

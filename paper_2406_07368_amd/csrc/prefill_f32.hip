@@ -789,7 +789,7 @@ static bool prefill_f32_direct_pays(int heads, int tiles, int d, bool grouped) {
 
 // Segments per (b, h, value block), or the quadratic kernel.  Steps of 32 tokens (groups of 64 in the three-branch form)
 // are the unit.
-F32Plan prefill_f32_plan(int heads, int L, int d, bool grouped) {
+F32Plan prefill_f32_plan(int heads, int L, int d, bool grouped, int per_cu) {
   F32Plan p{1, L > 0 ? L : 1, false};
   const int tiles = (L + FT - 1) / FT;
   if (prefill_f32_direct_pays(heads, tiles, d, grouped)) {
@@ -803,7 +803,7 @@ F32Plan prefill_f32_plan(int heads, int L, int d, bool grouped) {
   // 49 / 40, 320 heads L = 700 194 / 125, 16 heads L = 16000 200 / 126), but not for sequences of fewer than 8 steps on 256
   // heads or more (512 heads, 130 tokens: 49 / 59; 256 heads, 200 tokens 52 / 53).  d = 128: one (two: 32 heads L = 1400 86 / 83, 64 heads L = 500 64 / 66, 160 heads L = 300, which 256 leaves
   // whole, 87 / 101).  Three-branch form: the registers and LDS of two and one.
-  int want = (d == 64 ? (grouped ? 512 : 1024) : 256) / heads;
+  int want = (d == 64 ? (grouped || per_cu <= 2 ? 512 : 1024) : 256) / heads;
   if (!grouped && heads >= 256 && units < 8) want = 512 / heads;
   const int most = units / 2 < 64 ? units / 2 : 64;
   if (want > most) want = most;

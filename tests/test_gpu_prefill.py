@@ -501,3 +501,32 @@ def test_short_sequences_with_a_workgroup_per_group(form, B, H, L, d, d_v, Kc, l
         else:
             want = oracle.prefill_grouped(q, k, v, w, 64)
         compare((host(out), host(st[0]), host(st[1]), host(st[2])), want, "bf16", form)
+
+
+@pytest.mark.parametrize("H,L,Kc,with_state", [(12, 3000, 3, False), (24, 2500, 1, True), (128, 300, 5, True), (255, 300, 8, False)])
+def test_fp32_rows_of_64_with_a_workspace_for_half_of_the_segments(H, L, Kc, with_state):
+    """The plan asks for up to 1024 segments.  A workspace for the segments of a plan of up to 512 buys these, not none: it is written, to its
+    end at most, and the results are the oracle's.  A shorter one is left alone."""
+    d = 64
+    rng = np.random.default_rng(8900 + L)
+    q, k, v = (rng.standard_normal((1, H, L, d)).astype(np.float32) * 0.5 for _ in range(3))
+    w = workloads.conv_weights(rng, H, d, Kc)
+    state = (rng.standard_normal((1, H, d, d)).astype(np.float32), np.abs(rng.standard_normal((1, H, d))).astype(np.float32) + 50.0,
+             rng.standard_normal((1, H, Kc - 1, d)).astype(np.float32)) if with_state else (None, None, None)
+    want = oracle.prefill_recurrent(q, k, v, w, *(state if with_state else ()))
+    desc = binding.make_desc(1, H, d, Kc, 64, torch.float32, L=L)
+    units = -(-L // 32)
+    per = -(-units // min(512 // H, units // 2, 64))
+    half = H * (-(-units // per) * (d * d + d) + 8 * d) * 4
+    full = binding.linattn_workspace_bytes(desc, L)
+    assert half < full
+    st = [None if x is None else dev(x) for x in state]
+    qd, kd, vd, wd = dev(q), dev(k), dev(v), dev(w)
+    for nb, used in ((full, True), (half, True), (half - 16, False)):
+        ws = torch.full((full + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        out, S, z = torch.empty(1, H, L, d, device="cuda"), torch.empty(1, H, d, d, device="cuda"), torch.empty(1, H, d, device="cuda")
+        h = torch.empty(1, H, Kc - 1, d, device="cuda")
+        binding.linattn_prefill(desc, L, qd, kd, vd, wd, *st, out, S, z, h, ws, nb)
+        torch.cuda.synchronize()
+        assert bool((ws[:nb] != 0xA5).any()) == used and bool((ws[nb:] == 0xA5).all())
+        compare((host(out), host(S), host(z), host(h)), want, "f32", f"workspace of {nb}")
