@@ -530,3 +530,36 @@ def test_fp32_rows_of_64_with_a_workspace_for_half_of_the_segments(H, L, Kc, wit
         torch.cuda.synchronize()
         assert bool((ws[:nb] != 0xA5).any()) == used and bool((ws[nb:] == 0xA5).all())
         compare((host(out), host(S), host(z), host(h)), want, "f32", f"workspace of {nb}")
+
+
+@pytest.mark.parametrize("B,H,L,Kc,in_place", [
+    (1, 257, 256, 3, True), (2, 150, 289, 1, False), (1, 512, 257, 3, True), (1, 512, 130, 5, False), (1, 513, 300, 3, False),     # three segments, two, whole heads
+    (1, 255, 200, 3, True), (1, 170, 450, 8, False), (1, 16, 4100, 3, True), (1, 2, 4200, 5, False)])                              # ... five; up to 64
+def test_fp32_rows_of_64_in_up_to_1024_segments(B, H, L, Kc, in_place):
+    """Four workgroups per compute unit: against the oracle, from a state that is updated in place, and with the static scratch to the
+    bit."""
+    d = 64
+    rng = np.random.default_rng(8950 + H + L)
+    q, k, v = (rng.standard_normal((B, H, L, d)).astype(np.float32) * 0.5 for _ in range(3))
+    w = workloads.conv_weights(rng, H, d, Kc)
+    S0 = rng.standard_normal((B, H, d, d)).astype(np.float32)
+    z0 = np.abs(rng.standard_normal((B, H, d))).astype(np.float32) + 50.0
+    h0 = rng.standard_normal((B, H, Kc - 1, d)).astype(np.float32)
+    want = oracle.prefill_recurrent(q, k, v, w, S0, z0, h0)
+    desc = binding.make_desc(B, H, d, Kc, 64, torch.float32, L=L)
+    a = [dev(x) for x in (q, k, v, w)]
+    got = []
+    for noalloc in (False, True):
+        st = [dev(x) for x in (S0, z0, h0)]
+        new = st if in_place else [torch.empty_like(x) for x in st]
+        out = torch.empty(B, H, L, d, device="cuda")
+        if noalloc:
+            binding.linattn_prefill_noalloc(desc, L, *a, *st, out, *new)
+        else:
+            nb = binding.linattn_workspace_bytes(desc, L)
+            binding.linattn_prefill(desc, L, *a, *st, out, *new, torch.empty(max(nb, 16), dtype=torch.uint8, device="cuda"), nb)
+        torch.cuda.synchronize()
+        got.append([host(x) for x in (out, *new)])
+        compare(got[-1], want, "f32", f"B{B} H{H} L{L}")
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)
