@@ -42,16 +42,24 @@ def _run(cmd, verbose):
 
 
 def build_calls(verbose: bool = False) -> str:
-    """csrc/calls.cpp: host code on torch's C++ interface."""
+    """csrc/calls.cpp: host code on torch's C++ interface.  Compiled under another name and put in place whole: several
+    processes may start at once, and one that finds the file loads it."""
     import sysconfig
+    import threading
 
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
 
+    tmp = f"{CALLS}.{os.getpid()}.{threading.get_ident()}"
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           *[f"-isystem{p}" for p in (*include_paths(), sysconfig.get_paths()["include"])], os.path.join(CSRC, "calls.cpp"), "-o", CALLS,
+           *[f"-isystem{p}" for p in (*include_paths(), sysconfig.get_paths()["include"])], os.path.join(CSRC, "calls.cpp"), "-o", tmp,
            *[f"-L{p}" for p in library_paths()], "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
-    _run(cmd, verbose)
+    try:
+        _run(cmd, verbose)
+        os.replace(tmp, CALLS)
+    finally:
+        if os.path.exists(tmp):
+            os.remove(tmp)
     return CALLS
 
 
