@@ -6,12 +6,14 @@ streams, nothing else); every arithmetic step runs inside the library's
 kernels.  If the library is missing or a call is refused, this module raises;
 there is no other code path.  The tensor-level calls at the end go through
 ``csrc/calls.cpp`` where their arguments are what they ordinarily are (it answers
-None otherwise): the same marshalling, without the interpreter's time.
+None otherwise): the same marshalling, without the interpreter's time.  Where that module
+cannot be built or loaded they are marshalled here, and a warning says so once.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -85,17 +87,32 @@ def load():
     return lib
 
 
+class _NoCalls:
+    """In the place of the native calls where they cannot be had: every call takes the general path."""
+
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+def _load_calls():
+    try:
+        from . import build as _build
+        if not os.path.exists(_build.CALLS):
+            _build.build_calls()
+        from . import _calls as mod
+        return mod
+    except (ImportError, OSError, RuntimeError) as e:     # no compiler, another torch, a folder that is read-only
+        warnings.warn(f"the native tensor-level calls are not available ({e}); the calls go through ctypes", RuntimeWarning)
+        return _NoCalls()
+
+
 def _native():
     """The native tensor-level calls, bound to the library that is loaded."""
     global _calls, _bound
     lib = load()
     if _bound is not lib:
         if _calls is None:
-            from . import build as _build
-            if not os.path.exists(_build.CALLS):
-                _build.build_calls()
-            from . import _calls as mod
-            _calls = mod
+            _calls = _load_calls()
         f = [lib.linattn_workspace_bytes, lib.linattn_prefill, lib.linattn_prefill_grouped, lib.linattn_backward_workspace_bytes,
              lib.linattn_prefill_grouped_backward, lib.linattn_verify, lib.linattn_verify_grouped, lib.linattn_verify_tree, lib.linattn_decode]
         _calls.bind(*[ctypes.cast(x, ctypes.c_void_p).value for x in f], torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
