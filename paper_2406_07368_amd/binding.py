@@ -97,7 +97,7 @@ class _NoCalls:
 def _load_calls():
     try:
         from . import build as _build
-        if not os.path.exists(_build.CALLS):
+        if not _build.calls_current():
             _build.build_calls()
         from . import _calls as mod
         return mod

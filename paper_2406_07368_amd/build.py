@@ -7,6 +7,7 @@ switched off for all device code.
 """
 from __future__ import annotations
 
+import contextlib
 import glob
 import os
 import subprocess
@@ -16,6 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblinattn.so")
 CALLS = os.path.join(HERE, "_calls.so")
+CALLS_KEY = os.path.join(HERE, "_calls.key")    # what CALLS was built from and for
 OBJ = os.path.join(HERE, "_build")
 
 FLAGS = [
@@ -41,6 +43,28 @@ def _run(cmd, verbose):
         print(log)
 
 
+def calls_key() -> str:
+    """The sources of the extension module and the torch and Python it is built for."""
+    import hashlib
+
+    import torch
+
+    h = hashlib.sha256(f"{torch.__version__} {torch.version.git_version} {sys.implementation.cache_tag}".encode())
+    for path in (os.path.join(CSRC, "calls.cpp"), os.path.join(os.path.dirname(HERE), "include", "linattn.h")):
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
+
+
+def calls_current() -> bool:
+    """Whether the extension module that lies there is the one that build_calls would make."""
+    try:
+        with open(CALLS_KEY) as f:
+            return f.read() == calls_key() and os.path.exists(CALLS)
+    except FileNotFoundError:
+        return False
+
+
 def build_calls(verbose: bool = False) -> str:
     """csrc/calls.cpp: host code on torch's C++ interface.  Compiled under another name and put in place whole: several
     processes may start at once, and one that finds the file loads it."""
@@ -54,9 +78,15 @@ def build_calls(verbose: bool = False) -> str:
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            *[f"-isystem{p}" for p in (*include_paths(), sysconfig.get_paths()["include"])], os.path.join(CSRC, "calls.cpp"), "-o", tmp,
            *[f"-L{p}" for p in library_paths()], "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+    key = calls_key()
     try:
         _run(cmd, verbose)
+        with contextlib.suppress(FileNotFoundError):
+            os.remove(CALLS_KEY)                   # (at no time a key beside a module that is not its own)
         os.replace(tmp, CALLS)
+        with open(tmp, "w") as f:
+            f.write(key)
+        os.replace(tmp, CALLS_KEY)
     finally:
         if os.path.exists(tmp):
             os.remove(tmp)

@@ -12,6 +12,7 @@ from paper_2406_07368_amd import binding, build
 @pytest.fixture
 def place(tmp_path, monkeypatch):
     monkeypatch.setattr(build, "CALLS", str(tmp_path / "_calls.so"))
+    monkeypatch.setattr(build, "CALLS_KEY", str(tmp_path / "_calls.key"))
     return tmp_path
 
 
@@ -54,6 +55,7 @@ def test_calls_without_the_module_take_the_general_path(place, monkeypatch, miss
         monkeypatch.setattr(build, "_run", run)
     else:
         (place / "_calls.so").write_bytes(b"not a module")
+        (place / "_calls.key").write_text(build.calls_key())
         monkeypatch.setitem(sys.modules, "paper_2406_07368_amd._calls", None)        # "from . import _calls" raises ImportError
         monkeypatch.delattr("paper_2406_07368_amd._calls", raising=False)
     monkeypatch.setattr(binding, "_calls", None)
@@ -70,3 +72,26 @@ def test_calls_without_the_module_take_the_general_path(place, monkeypatch, miss
     with warnings.catch_warnings():
         warnings.simplefilter("error")
         call()
+
+
+def test_a_module_of_other_sources_or_another_torch_is_built_again(place, monkeypatch):
+    def run(cmd, verbose):
+        with open(cmd[cmd.index("-o") + 1], "wb") as f:
+            f.write(b"module")
+    monkeypatch.setattr(build, "_run", run)
+    (place / "_calls.so").write_bytes(b"of unknown origin")
+    assert not build.calls_current()
+    build.build_calls()
+    assert build.calls_current() and sorted(os.listdir(place)) == ["_calls.key", "_calls.so"]
+    with monkeypatch.context() as m:
+        m.setattr(torch, "__version__", "0.0")
+        assert not build.calls_current()
+    with monkeypatch.context() as m:
+        (place / "csrc").mkdir()
+        with open(os.path.join(build.CSRC, "calls.cpp")) as f:
+            (place / "csrc" / "calls.cpp").write_text(f.read() + "// another line\n")
+        m.setattr(build, "CSRC", str(place / "csrc"))
+        assert not build.calls_current()
+    assert build.calls_current()
+    os.remove(place / "_calls.so")
+    assert not build.calls_current()
