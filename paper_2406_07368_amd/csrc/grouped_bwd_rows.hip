@@ -303,9 +303,12 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
   };
   using Both = std::integral_constant<int, 0>;
   using Second = std::integral_constant<int, 1>;
-  // which tile has its own queries among the 32 keys of a unit (keys later than the query do not exist for it)
+  // which tile has its own queries among the 32 keys of a unit (keys later than the query do not exist for it).  Groups of 64 are
+  // two units, each some tile's own: the select in both tiles and one body for either unit is the faster way (us a gradient call, B4 H4 L15958
+  // d128 787 / 777, B16 H8 L1000 356 / 351).
   using Whole = std::integral_constant<int, -1>;
   using First = std::integral_constant<int, 0>;
+  using Each = std::integral_constant<int, 2>;
 
   // ---- pass 1: largest logit, sum of the weights and sum of e_i dp_i per query, of the keys that this lane holds (the four
   // lanes of a query are merged behind the loop).  The maximum starts from the lowest finite number: a lane may have met
@@ -323,7 +326,7 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
       for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          if (n == DIAG) sc[n][s][r] = 32 * kt + 16 * s + 4 * g4 + r <= qi ? sc[n][s][r] : -INFINITY;
+          if (DIAG == 2 || n == DIAG) sc[n][s][r] = 32 * kt + 16 * s + 4 * g4 + r <= qi ? sc[n][s][r] : -INFINITY;
           mnew = fmaxf(mnew, sc[n][s][r]);
         }
       const float corr = __builtin_amdgcn_exp2f((mtop[n] - mnew) * to_log2);
@@ -344,8 +347,15 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
   };
   // the units of one run of key rows: both tiles, then (on the diagonal) the later tile alone; every tile's last one is its own
   auto walk = [&](auto&& unit, bool diag) __attribute__((always_inline)) {
-    const int d0 = diag ? tile[0] / 2 : G::NW, d1 = tile[1] / 2;   // d0 < d1
     int kt = 0;
+    if constexpr (G::NH == 1) {                            // (the one run of a group is its own)
+#pragma unroll 1
+      for (; kt <= tile[0] / 2; ++kt) unit(Both{}, kt, Each{});
+#pragma unroll 1
+      for (; kt <= tile[1] / 2; ++kt) unit(Second{}, kt, Each{});
+      return;
+    }
+    const int d0 = diag ? tile[0] / 2 : G::NW, d1 = tile[1] / 2;   // d0 < d1
 #pragma unroll 1
     for (; kt < d0; ++kt) unit(Both{}, kt, Whole{});
     if (!diag) return;                                     // uniform
@@ -404,7 +414,7 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dq_kernel
         for (int r = 0; r < 4; ++r) {
           // (the mask as a select on the exponent, exp2(-inf) = 0: a branch per element would cut the loop into pieces)
           float arg = fmaf(sc[n][s][r], to_log2, -mlog2[n]);
-          if (n == DIAG) arg = 32 * kt + 16 * s + 4 * g4 + r <= qi ? arg : -INFINITY;
+          if (DIAG == 2 || n == DIAG) arg = 32 * kt + 16 * s + 4 * g4 + r <= qi ? arg : -INFINITY;
           sc[n][s][r] = __builtin_amdgcn_exp2f(arg) * inv_mass[n] * (dp[n][s][r] - pbar[n]);
         }
       split44(sc[n][0], sc[n][1], dh[n], dl[n]);
@@ -661,7 +671,7 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const float x = fmaf(sc[n][s][r], to_log2, -mt[r]);
-          sc[n][s][r] = __builtin_amdgcn_exp2f(n != DIAG || t0 + r >= ki ? x : -INFINITY) * it[r];
+          sc[n][s][r] = __builtin_amdgcn_exp2f((DIAG != 2 && n != DIAG) || t0 + r >= ki ? x : -INFINITY) * it[r];
         }
       }
     }
@@ -684,9 +694,17 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
   using Whole = std::integral_constant<int, -1>;
   using First = std::integral_constant<int, 0>;
   using Second = std::integral_constant<int, 1>;
+  using Each = std::integral_constant<int, 2>;             // (groups of 64: as in the dq kernel)
   auto walk = [&](int nr, bool diag) __attribute__((always_inline)) {
     const int nqt = (nr + 31) / 32, d0 = tile[0] / 2, d1 = tile[1] / 2;   // d0 < d1
     int qt = 0;
+    if constexpr (G::NH == 1) {
+#pragma unroll 1
+      for (qt = d0; qt < (d1 < nqt ? d1 : nqt); ++qt) unit(One{}, qt, Each{});
+#pragma unroll 1
+      for (; qt < nqt; ++qt) unit(Both{}, qt, Each{});
+      return;
+    }
     if (diag) {                                            // uniform
       qt = d0;
       if (qt < nqt) unit(One{}, qt++, First{});
