@@ -876,10 +876,14 @@ hipError_t launch_grouped_bwd_rows(const GroupedBwdArgs& a, const ConvLongArgs* 
 //   groups of 64, d = 128: 128 68 / 61 (82 / 62), 256 63 / 60, 314 114 / 106, 320 81 / 81 and 85 / 88, 384 86 / 89, 448 95 / 104,
 //   512 98 / 106 and 118 / 124; d = 64: 256 49 / 40 (80 / 40), 768 60.7 / 56.0 and 71.9 / 72.1 (91 / 72), 896 77 / 80 and 65 / 63
 //   (89 / 80 and 90 / 63), 1000 102 / 106 (101 / 106), 1024 81 / 86 (92 / 87)
+// A workgroup of the conv takes a tile of 256 tokens, whatever the sequence has of them: in groups of 64 at d = 128, where 16 of them
+// (two waves, eight channels each) go to a head's tile, many short sequences are the conv's call, not the rows': 64 tokens, 128
+// heads 47.3 / 43.1, 160 49.5 / 50.1, 240 58 / 68, 320 72 / 88.
 bool conv_rides(const GroupedBwdArgs& a, int d) {
   if (conv_mfma_blocks(a.L, a.B * a.H, d) != (a.L + CM_SUB - 1) / CM_SUB) return false;   // (two tiles per workgroup: calls that fill the chip)
   const int run = a.group < 128 ? a.group : 128;
-  const int64_t runs = (int64_t)((a.L + run - 1) / run) * a.B * a.H;
+  const int64_t heads = (int64_t)a.B * a.H, runs = (a.L + run - 1) / run * heads;
+  if (a.group == 64 && d == 128 && (a.L + CM_SUB - 1) / CM_SUB * heads > 160) return false;
   return runs <= (a.group == 256 ? (d == 128 ? 768 : 2560) : (d == 128 ? 320 : 896));
 }
 

@@ -253,3 +253,12 @@ def test_sums_of_the_tap_gradient_over_many_batch_rows(d, group, B, Kc):
     q, k, v, w, dout = case(9950 + B + d, B, 1, 3, d, Kc)
     want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, eps=1e-3)
     compare(run(q, k, v, w, dout, group, 1.0, 1e-3), want, f"d={d} group={group} B={B} Kc={Kc}")
+
+
+@pytest.mark.parametrize("d,group", [(128, 64), (64, 64)])
+@pytest.mark.parametrize("B,H,L", [(20, 8, 40), (23, 7, 40), (1, 81, 257)])
+def test_gradient_of_many_short_sequences(d, group, B, H, L):
+    """160 tiles of the conv ride at d = 128, 161 and 162 have launches of their own; at d = 64 all of these ride."""
+    q, k, v, w, dout = case(9970 + L + H, B, H, L, d, 5)
+    want = oracle.prefill_grouped_backward(q, k, v, w, dout, group, eps=1e-3)
+    compare(run(q, k, v, w, dout, group, 1.0, 1e-3), want, f"d={d} group={group} B={B} H={H} L={L}")
