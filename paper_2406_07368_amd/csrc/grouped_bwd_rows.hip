@@ -817,9 +817,11 @@ __global__ __launch_bounds__((RowsCfg<D, GT>::NT), 2) void grouped_bwd_dkdv_kern
 namespace {
 // dk and dv in workgroups of their own: twice the workgroups, each with half of the products and none of the other half's
 // accumulators, but the scores computed twice.  Pays while all of them fit the chip at once (two to a CU) and the extra ones
-// take CUs that would stand idle.  Measured, us a gradient call, together / apart: D = 128, groups of 64: 64 workgroups 92 / 83,
-// 128 95 / 86, 256 106 / 99, 320 101 / 98, 512 138 / 140; groups of 256: 64 112 / 98, 256 133 / 124, 512 173 / 181.  D = 64, where
-// a workgroup is short: 16 67 / 65, 64 84 / 81, 128 89 / 89, 256 71 / 73, 512 105 / 109.
+// take CUs that would stand idle.  Measured, us a gradient call as a graph, together / apart, by workgroups: D = 128, groups of 64: 64
+// 61.5 / 53.1, 128 65.9 / 57.6, 256 83.6 / 79.2, 320 102.0 / 100.3 and 77.4 / 76.1, 400 95.8 / 96.6; groups of 256: 64 79.0 / 66.2, 128 94.0 /
+// 86.3, 256 109 / 101, 320 80.5 / 79.3, 384 64.7 / 63.4, 512 76.5 / 78.5.  D = 64, where a workgroup is short: groups of 64: 64 29.6 /
+// 28.3, 128 35.7 / 35.8, 256 40.2 / 40.2; groups of 256: 32 36.4 / 34.6, 64 47.3 / 45.6, 96 52.5 / 53.2, 128 51.2 / 52.2, 256 25.2 / 25.7: up to 64
+// it pays, from there to the line neither way is ahead by more than 2 %.
 template <int D>
 bool split_pays(int64_t wgs) { return wgs <= (D == 128 ? 256 : 128); }
 
