@@ -1,11 +1,13 @@
 // The tensor-level calls of binding.py in native code: allocate the outputs, fill the descriptor, call the library on the
 // current stream.  What bounds a small call is its host part, and most of that was interpreter time: building the
-// descriptor, asking for the stream, a pointer per argument through ctypes.  Host us a call, through ctypes / here: decode of 32 heads
-// 12.0 / 4.7, fp32 prefill in one launch 17.8 / 7.3, bf16 prefill in two 23.1 / 10.7; the whole call where the GPU is the faster side: decode 12.0 / 5.3,
-// three-branch step of 4 heads 12.0 / 7.7, B1 H4 L256 fp32 prefill 17.9 / 13.4.
+// descriptor, asking for the stream, a pointer per argument through ctypes.  Host us a call, through ctypes / here: decode of 32
+// heads 12.0 / 4.7, fp32 prefill in one launch 17.8 / 7.3, bf16 prefill in two 23.1 / 10.7; the whole call where the GPU is the
+// faster side: decode 12.0 / 5.3, three-branch step of 4 heads 12.0 / 7.7, B1 H4 L256 fp32 prefill 17.9 / 13.4.
 //
-// Only what a program ordinarily passes is served: plain GPU tensors of the expected rank, fp32 or bf16, no explicit
-// stream.  For anything else a call returns None and binding.py takes its general path, which also raises the errors.
+// Only what a program ordinarily passes is served: tensors that are plain torch.Tensor objects, q on the GPU in fp32 or bf16
+// and of the expected rank, no explicit stream, no torch mode.  For anything else a call returns None and binding.py takes its
+// general path, which also raises the errors.  Like there, devices and types of the other tensors are the caller's business: they
+// are handed on as the pointers they are.
 // The library's functions are handed over as addresses (bind), so that there is one place that loads it.
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>

@@ -5,10 +5,11 @@
 //
 // One workgroup walks one (b, h) for 32 features (D = 64: all 64) in four 32 x 32 tiles of the sums (lane = channel,
 // registers = features), a wave each (groups of 256: two, see below), in accumulator registers from the first group to the
-// last -- or, where the heads are few, one tile with all waves sharing a step's tokens (one_tile) --; at the start of every group they go to the group's slot as they are.  Rows come 128 tokens at a time (64 in groups of
-// 64), requested two steps ahead into registers; on their way into one of two LDS buffers the left rows get the feature map and their weight and are
-// split into two bf16 terms (hi = bf16(x), lo = bf16(x - hi)): once per element, where making the operand as it is read
-// would repeat it in every wave.  Both operands are then transpose reads; the vector part is summed in fp32 by the
+// last; at the start of every group they go to the group's slot as they are.  Where the heads are few, a workgroup has one tile
+// and all its waves share a step's tokens (one_tile).  Rows come 128 tokens at a time (64 in groups of 64), requested two steps
+// ahead into registers; on their way into one of two LDS buffers the left rows get the feature map and their weight and are split
+// into two bf16 terms (hi = bf16(x), lo = bf16(x - hi)): once per element, where making the operand as it is read would repeat it
+// in every wave.  Both operands are then transpose reads; the vector part is summed in fp32 by the
 // threads that map the rows.
 // What bounds it: the traffic, every row once from memory (the four workgroups of a head are neighbours on one chiplet and
 // share the right rows through its L2: FETCH_SIZE counts them once) and one slot per group written and never read back by a

@@ -798,11 +798,12 @@ F32Plan prefill_f32_plan(int heads, int L, int d, bool grouped, int per_cu) {
   }
   const int unit = grouped ? FGROUP : FT;
   const int units = (L + unit - 1) / unit;
-  // As many workgroups as keep the chip busy.  Token form at d = 64: four per compute unit (two waves each and 38 KB of LDS; with two, half of
-  // the matrix units' time went by: us a call, 512 / 1024 workgroups: 12 heads L = 9164 96 / 79, 24 heads L = 4180 95 / 69, 128 heads L = 300
-  // 49 / 40, 320 heads L = 700 194 / 125, 16 heads L = 16000 200 / 126), but not for sequences of fewer than 8 steps on 256
-  // heads or more (512 heads, 130 tokens: 49 / 59; 256 heads, 200 tokens 52 / 53).  d = 128: one (two: 32 heads L = 1400 86 / 83, 64 heads L = 500 64 / 66, 160 heads L = 300, which 256 leaves
-  // whole, 87 / 101).  Three-branch form: the registers and LDS of two and one.
+  // As many workgroups as keep the chip busy.  Token form at d = 64: four per compute unit (two waves each and 38 KB of LDS; with
+  // two, half of the matrix units' time went by: us a call, 512 / 1024 workgroups: 12 heads L = 9164 96 / 79, 24 heads L = 4180
+  // 95 / 69, 128 heads L = 300 49 / 40, 320 heads L = 700 194 / 125, 16 heads L = 16000 200 / 126), but not for sequences of fewer
+  // than 8 steps on 256 heads or more (512 heads, 130 tokens: 49 / 59; 256 heads, 200 tokens 52 / 53).  d = 128: one (two: 32 heads
+  // L = 1400 86 / 83, 64 heads L = 500 64 / 66, 160 heads L = 300, which 256 leaves whole, 87 / 101).  Three-branch form: the
+  // registers and LDS of two and one.
   int want = (d == 64 ? (grouped || per_cu <= 2 ? 512 : 1024) : 256) / heads;
   if (!grouped && heads >= 256 && units < 8) want = 512 / heads;
   const int most = units / 2 < 64 ? units / 2 : 64;

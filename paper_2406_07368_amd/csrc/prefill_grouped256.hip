@@ -530,8 +530,9 @@ static hipError_t launch_g256(const PrefillArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The full pass of the three-branch form in groups of 256 tokens; few groups go to prefill_grouped256_split.hip.  a.ws holds one slot per (b, h, segment) -- with
-// segments, filled by the first pass and the prefix sum; without, initialised here -- and the staged history rows.
+// The full pass of the three-branch form in groups of 256 tokens; few groups go to prefill_grouped256_split.hip.  a.ws holds one
+// slot per (b, h, segment) -- with segments, filled by the first pass and the prefix sum; without, initialised here -- and the
+// staged history rows.
 hipError_t launch_prefill_grouped256(const PrefillArgs& a, int d, hipStream_t st) {
   if (const int parts = prefill_grouped256_parts(a); parts > 1) return launch_prefill_grouped256_split(a, d, parts, st);
   if (d == 128) {

@@ -73,13 +73,16 @@ int prefill_mfma_fold_segments(int nseg, int L, int heads, int d) {
 
 // A short new sequence in one launch, a workgroup per group of 64: the one of group g walks the g groups before its own for their
 // state only, which takes half the time of a group with scores and outputs (1.6 us against 3.2 at d = 128), so the call is as long
-// as its last group's walk instead of a walk that computes everything.  Costs g times the reads of K and V, from the last-level cache, and a
-// compute unit per group.  Returns the number of segments (= groups), 0: not that way.
-// It pays while every group has a compute unit to itself, up to the length where the plan cuts the sequence (8 groups).  Measured, us a call,
-// one workgroup per head / this: d = 128, 16 heads: 2 groups 13.1 / 11.7, 3 16.1 / 13.2, 5 22.3 / 16.9, 6 25.4 / 18.8, 8 (in segments) 24.6 / 23.2, three-branch
-// form 26.6 / 28.5; 32 heads of 6 26.0 / 20.1, 64 of 4 20.3 / 18.3, 128 of 2 14.5 / 14.5, 64 of 5 23.1 / 26.8, 96 of 3 17.3 / 21.4; three-branch form 32 heads of
-// 6 31.8 / 24.1, 64 of 4 24.6 / 21.6.  d = 64: 16 heads of 6 22.1 / 16.4, 64 of 4 17.4 / 14.3, 128 of 2 12.1 / 11.0, 96 of 3 14.6 / 14.2, 96 of 4 17.6 / 19.1; three-branch
-// form 64 of 4 21.9 / 17.5, 96 of 3 17.7 / 21.0.
+// as its last group's walk instead of a walk that computes everything.  Costs g times the reads of the rows, from the last-level
+// cache, and a compute unit per group.  (The front end fetches and maps Q of the groups before its own as well, which nobody
+// reads.)  Returns the number of segments (= groups), 0: not that way.
+// It pays while every group has a compute unit to itself, up to the length where the plan cuts the sequence (8 groups).  Measured,
+// us a call, one workgroup per head / this:
+//   d = 128: 16 heads: 2 groups 13.1 / 11.7, 3 16.1 / 13.2, 5 22.3 / 16.9, 6 25.4 / 18.8, 8 (in segments) 24.6 / 23.2, three-branch form
+//   26.6 / 28.5; 32 heads of 6 26.0 / 20.1, 64 of 4 20.3 / 18.3, 128 of 2 14.5 / 14.5, 64 of 5 23.1 / 26.8, 96 of 3 17.3 / 21.4;
+//   three-branch form 32 heads of 6 31.8 / 24.1, 64 of 4 24.6 / 21.6
+//   d = 64: 16 heads of 6 22.1 / 16.4, 64 of 4 17.4 / 14.3, 128 of 2 12.1 / 11.0, 96 of 3 14.6 / 14.2, 96 of 4 17.6 / 19.1; three-branch
+//   form 64 of 4 21.9 / 17.5, 96 of 3 17.7 / 21.0
 int prefill_mfma_lead_segments(int L, int heads) {
   const int groups = (L + 63) / 64;
   return groups >= 2 && groups < 8 && (int64_t)groups * heads <= 256 ? groups : 0;
@@ -112,8 +115,8 @@ size_t prefill_grouped256_workspace_bytes(int BH, int d, int nseg) {
 // traffic where the heads are many: sequences of two groups on more than 96 heads keep whole segments -- at d = 128 on more than 64,
 // without a long conv beside the prefix sum --, but for long taps at d = 64, whose conv lasts longer than the prefix sum either way.
 // us a call as a graph, whole segments / two parts / four:
-//   63 taps, d = 128: 4 heads, 300 tokens 26.5 / - / 23.1; 8 heads, 1000 30.0 / - / 29.1, 2000 38.2 / 35.6 / 36.1, 3000 43.2 / 40.4; 4 heads, 3000
-//   34.6 / 32.6 / 32.5; 1 head, 8000 37.6 / 36.0 / 39.0, 12000 35.2 / 33.4 / 37.5, 16000 37.5 / 37.8 / 44.1; two groups: 65 heads 55.7 / 53.0, 90
+//   63 taps, d = 128: 4 heads, 300 tokens 26.5 / - / 23.1; 8 heads, 1000 30.0 / - / 29.1, 2000 38.2 / 35.6 / 36.1, 3000 43.2 / 40.4; 4
+//   heads, 3000 34.6 / 32.6 / 32.5; 1 head, 8000 37.6 / 36.0 / 39.0, 12000 35.2 / 33.4 / 37.5, 16000 37.5 / 37.8 / 44.1; two groups: 65 heads 55.7 / 53.0, 90
 //   57.1 / 56.4, 110 65.5 / 66.8, 128 71.0 / 75.4; d = 64: 8 heads, 2000 23.1 / 21.4 / 21.3; 1 head, 4000 20.0 / 17.9 / 17.3, 16000 24.0 / 25.8 / 32.2;
 //   128 heads, two groups 42.3 / 39.4
 //   5 taps, d = 128: 8 heads, 2000 36.4 / 35.3 / 37.2; 1 head, 8000 36.3 / 36.0 / 39.5; 64 heads, three groups 53.9 / 53.3; two groups: 64 heads

@@ -93,8 +93,8 @@ struct WsCfg {
 // increment (S, z) only: no Q, no scores, no output.
 //
 // LEAD: a short new sequence in one launch, every segment by a workgroup that forms the state before it by itself: it walks
-// the groups from the sequence's start, the ones ahead of its segment for their state only (no scores, no outputs).  See
-// prefill_mfma_lead_segments.
+// the groups from the sequence's start, the ones ahead of its segment for their state only (no scores, no outputs; the front end
+// takes their Q along, in the three-branch form their raw rows too).  See prefill_mfma_lead_segments.
 template <int D, int C, int KCM, bool STATE_ONLY, bool GROUPED = false, bool LEAD = false>
 __global__ __launch_bounds__(D * 4) void prefill_mfma_ws_kernel(PrefillArgs a) {
   static_assert(!(STATE_ONLY && (GROUPED || LEAD)), "the first pass: no outputs, in either form");

@@ -8,8 +8,9 @@
 namespace linattn {
 
 // Prefix sum over the segments of one (b, h): slot 0 <- incoming state, slot g <- slot g-1 +
-// increment of segment g-1 (or the increments of its 1 << fine parts, one after the other).  Also stages the incoming history so that the second pass never
-// reads hist_in (which hist_out may alias).  One thread per state element walks the segments.
+// increment of segment g-1 (or the increments of its 1 << fine parts, one after the other).  Also
+// stages the incoming history so that the second pass never reads hist_in (which hist_out may
+// alias).  One thread per state element walks the segments.
 // Workgroup (bx, by) of dim3(ceil((D * D + D) / 256), B H m), 256 threads.
 template <int D>
 __device__ __forceinline__ void segment_scan_workgroup(const PrefillArgs& a, int bx, int by) {
