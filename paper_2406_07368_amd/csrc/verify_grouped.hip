@@ -481,20 +481,24 @@ __global__ __launch_bounds__(256, (sizeof(typename Io::elem) != 2 ? 2 : KP <= 8 
         *reinterpret_cast<typename Io::raw8*>(&smem.st.v[r][8 * c8]) = cv[t];
       }
     }
-    // (0 times an infinity is a NaN, and a bf16 term may be 0 where its number is not: rows with an infinity or a NaN -- rare --
-    // take the fp32 instructions)
+    // (0 times an infinity is a NaN, and a bf16 term may be 0 where its number is not: rows with an infinity or a NaN take the fp32
+    // instructions.  So do keys of -104 to -70, whose exponentials are so small that their second and third terms are no normal
+    // numbers: S of keys of -87 to -84 was off by 2e-4 with them, by 3e-6 -- the exponential -- without.  Both rare.)
     bool odd = false;
     if constexpr (BF) {
       typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-      u16x2 top = {0, 0};
+      u16x2 top = {0, 0}, low = {0xffff, 0xffff};
+      constexpr uint16_t small = 0xc28c, smallest = 0xc2d0;         // -70, -104
 #pragma unroll
       for (int t = 0; t < CRT; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, ck[t][i] & 0x7fff7fffu));
           top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, cv[t][i] & 0x7fff7fffu));
+          low = __builtin_elementwise_min(low, __builtin_bit_cast(u16x2, ck[t][i]) - u16x2{small, small});
         }
-      const int wave_odd = __any(top[0] >= 0x7f80 || top[1] >= 0x7f80);
+      const bool tiny = !a.relu && (low[0] <= smallest - small || low[1] <= smallest - small);
+      const int wave_odd = __any(top[0] >= 0x7f80 || top[1] >= 0x7f80 || tiny);
       if (lane == 0) odd_rows[wv] = wave_odd;
     }
     __syncthreads();

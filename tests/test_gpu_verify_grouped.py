@@ -169,3 +169,30 @@ def test_completion_against_64_bits_and_with_rows_that_are_not_finite(d, kk, phi
             err = (got.double() - want)[ok].norm() / want[ok].norm()
             assert err < 2e-7, float(err)
         assert int(st[5].sum()) == 0
+
+
+@pytest.mark.parametrize("d,kk", [(64, 1), (128, 2)])
+@pytest.mark.parametrize("low,high", [(-87.0, -84.0), (-78.0, -69.0), (-104.0, -88.0), (-70.0, -60.0)])
+def test_completion_with_features_near_the_end_of_the_range(d, kk, low, high):
+    """Keys whose exponentials are 1e-26 to 1e-46: what S gets of a group of them is off by what the exponential's argument is rounded to
+    (|k| roundings of 2^-24), the products' sums (64) and features below the smallest normal number, not by the bf16 terms they are
+    multiplied as."""
+    B, H, Kc = 2, 3, 3
+    torch.manual_seed(d + kk)
+    w = torch.randn(H, d, Kc, device="cuda")
+    q, v = (torch.randn(B, H, kk, d, device="cuda").to(torch.bfloat16) for _ in range(2))
+    st = binding.grouped_state(B, H, d, Kc)
+    keys = (torch.rand(B, H, 64, d, device="cuda") * (high - low) + low).to(torch.bfloat16)
+    k = keys[:, :, 64 - kk:].contiguous()
+    st[3].copy_(keys)
+    st[4].normal_()
+    st[5].fill_(64 - kk)
+    rv = torch.cat([st[4][:, :, :64 - kk], v], 2).double()
+    f = keys.double().exp()
+    S = (f[..., :, None] * rv[..., None, :]).sum(2)
+    most = (f[..., :, None] * rv.abs()[..., None, :]).sum(2)        # of the same sums without cancellation
+    binding.verify_grouped(q, k, v, w, st, eps=1e-3)
+    torch.cuda.synchronize()
+    err = (st[0].double() - S).abs()
+    lost = (torch.where(f < 1.01 * 2.0 ** -126, f, 0.0)[..., :, None] * rv.abs()[..., None, :]).sum(2)
+    assert (err <= (-low + 64) * 2.0 ** -24 * most + lost + 64 * 2.0 ** -148).all(), float((err / most.clamp(min=1e-300)).max())
