@@ -362,9 +362,9 @@ static hipError_t launch_nt(const VerifyArgs& a, hipStream_t st) {
 // share one (and 8 drafts, 120 registers, fill it with 1024 threads).  Measured, us a call as a graph (a plain call takes the
 // host about 5), 256 / 512 / 1024 threads, 128 x 128 state:
 //   1 draft    4 heads 7.3 / 5.9 / 5.2, 256 13.0 / 9.8 / 7.6, 512 17.5 / 13.5 / 12.9, 576 19.2 / 16.2 / 15.4, 640 19.5 / 16.7 / 17.8,
-//              767 20.6 / 18.6 / 20.4; fp32 rows 900 23.9 / 24.4 / 24.7, 1024 26.1 / 28.2 / 26.6
+//              767 20.6 / 18.6 / 20.4; fp32 rows 832 22.4 / 22.5, 900 23.9 / 24.7, 1000 25.7 / 27.7, 1024 26.1 / 28.2
 //   2 drafts   4 heads 8.2 / 6.5 / 5.7, 256 15.1 / 10.7 / 8.2, 512 18.5 / 14.1 / 13.7, 576 20.3 / 16.5 / 16.9, 640 20.8 / 17.1 / 19.5;
-//              fp32 rows 900 24.7 / 25.1 / 25.8, 1024 27.2 / 28.0 / 28.7
+//              fp32 rows 832 23.9 / 23.8, 900 24.5 / 25.1, 1000 27.0 / 27.6, 1024 27.2 / 28.0
 //   4 drafts   4 heads 9.3 / 7.5 / 7.8, 64 9.9 / 8.1 / 8.5, 128 13.1 / 9.8 / 9.2, 256 15.9 / 11.7 / 9.9, 320 18.4 / 14.1 / 16.5,
 //              512 19.9 / 15.6 / 17.2, 576 21.8 / 21.1 / 23.6, 640 22.2 / 22.9 / 23.8
 //   8 drafts   4 heads 14.6 / 10.6 / 11.2, 64 15.9 / 11.8 / 12.0, 128 15.4 / 11.7 / 12.1, 192 16.7 / 13.1 / 12.9, 256 21.4 / 15.9 / 14.6,
@@ -377,7 +377,7 @@ static int pick_threads(int state, int kp, int blocks) {
   if (state == 64 * 64) return 256;
   if (state == 64 * 128) return blocks <= (kp == 16 ? 256 : 384) ? 512 : 256;
   if (kp == 16) return 512;
-  if (kp <= 2) return blocks <= 576 ? 1024 : blocks < 1024 ? 512 : 256;
+  if (kp <= 2) return blocks <= 576 ? 1024 : blocks < 832 ? 512 : 256;
   if (blocks <= (kp == 8 ? 128 : 64)) return 512;
   return blocks <= 256 ? 1024 : blocks <= 512 ? 512 : 256;
 }

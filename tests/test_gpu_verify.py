@@ -70,7 +70,7 @@ def test_verify_on_both_sides_of_the_matrix_core_line(B, H):
 @pytest.mark.parametrize("kk", [1, 2, 3, 7, 15])
 def test_verify_every_workgroup_size(io, B, H, kk):
     """One workgroup per head, its threads chosen by the number of heads and drafts: 256, 512 and 1024 threads on each
-    number of drafts a kernel is built for (one and two drafts on 256 threads: fp32 only, from 1024 heads on; 1025 heads of bf16 drafts are
+    number of drafts a kernel is built for (one and two drafts on 256 threads: fp32 only, from 832 heads on; 1025 heads of bf16 drafts are
     the matrix-core kernel's)."""
     d, Kc = 128, 4
     q, k, v, w, S, z, hist = make_case(40 + kk + B * H, B, H, d, Kc, kk, io, prefix=4)
