@@ -805,7 +805,7 @@ F32Plan prefill_f32_plan(int heads, int L, int d, bool grouped, int per_cu) {
   // L = 1400 86 / 83, 64 heads L = 500 64 / 66, 160 heads L = 300, which 256 leaves whole, 87 / 101).  Three-branch form: the
   // registers and LDS of two and one.
   int want = (d == 64 ? (grouped || per_cu <= 2 ? 512 : 1024) : 256) / heads;
-  if (!grouped && heads >= 256 && units < 8) want = 512 / heads;
+  if (d == 64 && !grouped && heads >= 256 && units < 8) want = 512 / heads;
   const int most = units / 2 < 64 ? units / 2 : 64;
   if (want > most) want = most;
   if (want < 2) return p;

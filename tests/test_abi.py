@@ -250,6 +250,11 @@ def test_no_plan_asks_for_more_than_the_static_scratch(dtype, d):
                 desc = binding.make_desc(1, heads, d, 3, 64, io, L=L, d_v=m * d)
                 most = max(most, binding.linattn_workspace_bytes(desc, L))
     assert 0 < most <= binding.linattn_noalloc_scratch_bytes()
+    for heads in (1, 12, 127, 128, 129, 255, 256, 257, 300, 511, 512, 513):          # every number of steps of the shortest sequences
+        for L in range(1, 1100, 16):
+            desc = binding.make_desc(1, heads, d, 3, 64, io, L=L)
+            most = max(most, binding.linattn_workspace_bytes(desc, L))
+    assert most <= binding.linattn_noalloc_scratch_bytes()
 
 
 @pytest.mark.parametrize("H,L,d,Kc,parts", [
