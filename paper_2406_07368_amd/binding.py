@@ -52,7 +52,7 @@ def load():
         return _lib
     if not os.path.exists(LIB_PATH):
         from . import build as _build
-        _build.build()
+        _build.build(calls=False)
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
     dp = ctypes.POINTER(Desc)

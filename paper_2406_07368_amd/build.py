@@ -93,8 +93,9 @@ def build_calls(verbose: bool = False) -> str:
     return CALLS
 
 
-def build(verbose: bool = False, extra=()) -> str:
-    """Every source to an object file of its own (in parallel; no device code crosses a file), then one link."""
+def build(verbose: bool = False, extra=(), calls: bool = True) -> str:
+    """Every source to an object file of its own (in parallel; no device code crosses a file), then one link.  calls: the
+    extension module too; where that fails the library is in place all the same."""
     from concurrent.futures import ThreadPoolExecutor
 
     os.makedirs(OBJ, exist_ok=True)
@@ -106,10 +107,11 @@ def build(verbose: bool = False, extra=()) -> str:
         objs.append(obj)
         jobs.append(["hipcc", *compile_flags, *extra, "-c", src, "-o", obj])
     with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as pool:
-        calls = pool.submit(build_calls, verbose)
+        module = pool.submit(build_calls, verbose) if calls else None
         list(pool.map(lambda cmd: _run(cmd, verbose), jobs))
-        calls.result()
-    _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], verbose)
+        _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], verbose)
+        if module:
+            module.result()
     return LIB
 
 

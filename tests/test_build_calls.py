@@ -95,3 +95,20 @@ def test_a_module_of_other_sources_or_another_torch_is_built_again(place, monkey
     assert build.calls_current()
     os.remove(place / "_calls.so")
     assert not build.calls_current()
+
+
+def test_the_library_does_not_wait_for_the_module(place, monkeypatch):
+    """No compiler for the module: an explicit build says so, with the library in place; what loads the library asks for nothing else."""
+    def run(cmd, verbose):
+        if cmd[0] == "g++":
+            raise FileNotFoundError("g++")
+        with open(cmd[cmd.index("-o") + 1], "wb") as f:
+            f.write(b"object")
+    monkeypatch.setattr(build, "_run", run)
+    monkeypatch.setattr(build, "LIB", str(place / "liblinattn.so"))
+    monkeypatch.setattr(build, "OBJ", str(place / "_build"))
+    with pytest.raises(FileNotFoundError):
+        build.build()
+    assert (place / "liblinattn.so").exists()
+    os.remove(place / "liblinattn.so")
+    assert build.build(calls=False) == str(place / "liblinattn.so") and (place / "liblinattn.so").exists()
